@@ -17,14 +17,15 @@ BUILD = os.path.join(PKG, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # (source, object name, extra flags): the step kernels compile once per
-# workgroup size so the three builds run in parallel.
+# workgroup size and kind of kernel so that the builds run in parallel.
 SOURCES = [
     ("analysis.cpp", "analysis", []),
     ("api.cpp", "api", []),
     ("aux.hip", "aux", []),
-    ("step.hip", "step64", ["-DEMT_BS=64"]),
-    ("step.hip", "step256", ["-DEMT_BS=256"]),
-    ("step.hip", "step512", ["-DEMT_BS=512"]),
+    *(("step.hip", f"step{bs}{part}", [f"-DEMT_BS={bs}", f"-DEMT_PART_{part.upper()}"])
+      for bs in (512, 256, 64) for part in ("fwd", "ext", "adj", "pipe")),
+    ("closed.cpp", "closed_plan", []),
+    ("closed.hip", "closed", []),
     ("split.hip", "split", []),
     ("scratch.hip", "scratch", []),
     ("steady.hip", "steady", []),
@@ -58,7 +59,7 @@ def _compile(spec) -> str:
 
 
 def build(verbose: bool = False) -> str:
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=max(4, min(len(SOURCES), os.cpu_count() or 4))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = OUT + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]

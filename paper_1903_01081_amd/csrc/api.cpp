@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <map>
 #include <memory>
 #include <cstdlib>
 #include <cstring>
@@ -12,6 +13,7 @@
 #include <vector>
 
 #include "analysis.h"
+#include "closed.h"
 #include "comp.h"
 #include "comp_plan.h"
 #include "device.h"
@@ -58,8 +60,10 @@ struct emt_ctx {
   emt::DevCtx dc{};
   int n_items = 0;
   int32_t *d_order = nullptr;
-  int32_t *d_pairs = nullptr;
-  int n_pairs = 0;
+  // (item, topology) pairs factorised by LDL^T (level passes, split and
+  // compensation components) and by the closed form
+  int32_t *d_pairs = nullptr, *d_closed = nullptr;
+  int n_pairs = 0, n_closed = 0, closed_values = 0, closed_tail = 0, ldl_tail = 0;
   emt::CompanionArgs ca{};
   int32_t *d_bscen = nullptr, *d_bitem = nullptr, *d_blocal = nullptr;
   int64_t nbr_total = 0, nodes_total = 0;
@@ -134,15 +138,35 @@ struct emt_ctx {
 
 namespace {
 
-// Largest dense tail whose inverse fits the lanes of one workgroup: 16
-// entries per lane up to 256 lanes (d <= 4 sqrt(lanes)), 32 with 512 lanes.
+// Largest dense tail of the level passes and of the dense solver at a block
+// size (what dense_tail is capped by).
 int tail_max(int bs) { return bs >= 512 ? 128 : (bs >= 256 ? 64 : 32); }
 
-int tpr_of(int d, int bs) {
-  int t = 16;
-  while (t > 1 && d * t > bs) t >>= 1;
-  return t;
+// Largest dense tail of the closed form: the kernels' largest capacities.
+int closed_tail_max(int bs) { return bs >= 512 ? 192 : (bs >= 256 ? 128 : 64); }
+
+// Capacity (KernelShape::dt) that holds a tail of d nodes; 0 = none.
+int tail_capacity(int bs, int d) {
+  for (int cap : {32, 64, 128, 192})
+    if (cap >= d && cap >= (bs == 64 ? 32 : 64) && cap <= closed_tail_max(bs)) return cap;
+  return 0;
 }
+
+// The closed form's values (1, 0, N, Q) that its numeric kernel holds in LDS.
+constexpr int64_t kClosedValues = 15000;
+
+// Rough cycles of one solve. Closed form: three phases, the tail's
+// multiply-adds, LDS reads and 16-lane sums, and 36 LDS cycles per quad of N
+// (twice) and Q. Level passes: about 700 cycles each.
+double closed_cost(const emt::ClosedSize &z, int d, int n, int bs) {
+  const double waves = bs / 64.0, simd = std::max(1.0, waves / 4.0);
+  const double rows = d > 0 ? (d * 16 + bs - 1) / bs : 0, q = (d + 31) / 32;
+  const double tail = d > 0 ? 250 + simd * rows * (8 * q + 56) + 8 * q * waves : 0;
+  const double entries = 2.0 * z.nn + z.q + (d < n ? d : 0);
+  const double rounds = entries / (4.0 * bs);
+  return tail + (d < n ? 300 : 0) + (d > 0 && d < n ? 300 : 0) + entries / 256.0 * 36 + 40 * rounds;
+}
+double levels_cost(const emt::SweepPlan &P) { return 700.0 * (P.nfpass() + P.nbpass()) + (P.d > 0 ? 600 : 0); }
 
 }  // namespace
 
@@ -210,11 +234,6 @@ static void fill_branch_params(emt_ctx &c, const emt_net *nets, std::vector<int3
     }
   }
   c.scen_br_off.push_back((int64_t)br_ids.size());
-}
-
-static emt::LdsShape shape_of(const emt::Item &it, const emt::Symbolic &S, const emt::SweepPlan &P, bool dyn) {
-  return emt::LdsShape{it.n, P.d, P.ns, it.n_br, it.n_src, P.nsv(), (int)P.fdesc.size(), (int)P.bdesc.size(),
-                       it.nptr[it.n], (int)it.rec_node.size(), S.levels_f(), dyn};
 }
 
 // log2 of the lanes that share one row in a sweep pass: enough lanes that
@@ -755,9 +774,27 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       if (b >= 0 && (nets[it.scen].kind[b] == EMT_DIODE || nets[it.scen].kind[b] == EMT_CSWITCH))
         sym_diode[it.sym] = item_diode[q] = 1;
   }
+  // Entries of G in each symbolic pattern (those of its first item: items
+  // share a pattern only with the same edges).
+  std::vector<std::vector<int>> gpos(A.syms.size());
+  for (const Item &it : A.items) {
+    std::vector<int> &g = gpos[it.sym];
+    if (!g.empty()) continue;
+    for (int p : it.gpos)
+      if (p >= 0) g.push_back(p);
+    g.insert(g.end(), it.mpos.begin(), it.mpos.end());
+  }
+  // Closed form or level passes. The closed form where its row programs are
+  // estimated cheaper than the level passes (a tail that cuts the rest into
+  // small clusters; a pass costs about 700 cycles whatever it holds, a quad
+  // of a row program about 10 per wave). Level passes stay for solver
+  // SPARSE, for items refactorised inside the loop and for factors whose
+  // closed form would be too dense.
+  std::vector<char> closed(A.syms.size(), 0);
   for (size_t q = 0; q < A.syms.size(); ++q) {
     const int n = A.syms[q].n;
     int d;
+    bool may = false;
     if (sym_split[q] || sym_diode[q]) {
       d = 0;  // factor values only; the split kernels use the explicit inverse
     } else if (solver == EMT_SOLVER_SPARSE || solver == EMT_SOLVER_COMPENSATION) {
@@ -767,37 +804,133 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
         throw Error{EMT_EINVAL, "the dense solver holds components of at most " + std::to_string(c.ks.dmax) +
                                     " nodes at this block size; a component has " + std::to_string(n)};
       d = n;
+      may = true;
     } else {
       d = forced_tail >= 0 ? std::min({forced_tail, n, c.ks.dmax}) : choose_tail(A.syms[q], c.ks.dmax);
+      may = true;
     }
     plans[q] = plan_sweeps(A.syms[q], d);
+    if (!may || 2 * (n + 1) > 65535) continue;
+    const bool fixed = solver == EMT_SOLVER_DENSE || forced_tail >= 0;
+    const std::vector<ClosedSize> z = closed_sizes(A.syms[q], fixed ? d : closed_tail_max(bs));
+    double best = levels_cost(plans[q]);
+    int best_d = -1;
+    for (int e = fixed ? d : 0; e < (int)z.size(); ++e) {
+      if (2 + z[e].q + z[e].nn > kClosedValues) continue;
+      const double cost = closed_cost(z[e], e, n, bs);
+      if (cost < best) {
+        best = cost;
+        best_d = e;
+      }
+    }
+    if (best_d < 0) continue;
+    closed[q] = 1;
+    if (best_d != d) plans[q] = plan_sweeps(A.syms[q], best_d);
   }
-  auto item_lds = [&](const Item &it, bool adj) {
-    return lds_bytes(shape_of(it, A.syms[it.sym], plans[it.sym], item_diode[&it - &A.items[0]]), true, adj);
+  std::vector<ClosedPlan> cplans(A.syms.size());
+  auto plan_closed_of = [&](size_t q) {
+    if (closed[q]) cplans[q] = plan_closed(A.syms[q], gpos[q], plans[q].d, bs);
   };
+  for (size_t q = 0; q < A.syms.size(); ++q) plan_closed_of(q);
+  // Row programs of the injection sums, forward and with the adjoint's
+  // seeds; items with the same node CSR share them. Not for the split and
+  // compensation components, whose kernels sum by the CSR.
+  std::vector<RowProgram> gprogs;
+  std::vector<int> prog_f(NI, -1), prog_a(NI, -1);
+  std::map<std::vector<int>, int> prog_ids;
+  auto plan_gathers = [&]() {
+    gprogs.clear();
+    prog_ids.clear();
+    if (comp) return;
+    for (int q = 0; q < NI; ++q) {
+      const Item &it = A.items[q];
+      if (c.is_split[q]) continue;
+      std::vector<RowSum> rows(it.n);
+      std::vector<int> key = it.nptr;
+      key.insert(key.end(), it.nent.begin(), it.nent.end());
+      key.push_back(it.n_br);
+      for (int r = 0; r < it.n; ++r) {
+        rows[r].row = r;
+        for (int e = it.nptr[r]; e < it.nptr[r + 1]; ++e) rows[r].e.push_back({it.nent[e], 0});
+      }
+      auto program = [&](const std::vector<int> &k) {
+        auto f = prog_ids.emplace(k, (int)gprogs.size());
+        if (f.second) gprogs.push_back(schedule_rows(rows, bs, it.n_br << 1, 0));
+        return f.first->second;
+      };
+      prog_f[q] = program(key);
+      if (K <= 0) continue;
+      // seed q of the adjoint is the q-th recorded node in node order
+      std::vector<int> nodes = it.rec_node;
+      std::sort(nodes.begin(), nodes.end());
+      if (((int64_t)it.n_br + 1 + (int64_t)nodes.size()) * 2 > 65535)
+        throw Error{EMT_EINVAL, "a connected component has too many branches and recorded nodes for the adjoint"};
+      for (size_t e = 0; e < nodes.size(); ++e) {
+        rows[nodes[e]].e.push_back({(it.n_br + 1 + (int)e) << 1, 0});
+        key.push_back(nodes[e]);
+      }
+      key.push_back(-1);
+      prog_a[q] = program(key);
+    }
+  };
+  plan_gathers();
+  auto step_shape = [&](int q, bool adj) {
+    const Item &it = A.items[q];
+    const SweepPlan &P = plans[it.sym];
+    const ClosedPlan &C = cplans[it.sym];
+    StepShape z{};
+    z.n = it.n;
+    z.d = P.d;
+    z.ns = P.ns;
+    z.nbr = it.n_br;
+    z.nsrc = it.n_src;
+    z.nrec = (int)it.rec_node.size();
+    z.closed = closed[it.sym];
+    z.nfpass = P.nfpass();
+    z.nbpass = P.nbpass();
+    z.nsv = closed[it.sym] ? 256 * (C.fwd.quads + C.bwd.quads) : P.nsv();
+    z.nfdesc = (int)P.fdesc.size();
+    z.nbdesc = (int)P.bdesc.size();
+    const int g = adj ? prog_a[q] : prog_f[q];
+    if (g >= 0) {
+      z.gb = gprogs[g].batches;
+      z.gq = gprogs[g].quads;
+    }
+    z.fb = C.fwd.batches;
+    z.fq = C.fwd.quads;
+    z.bb = C.bwd.batches;
+    z.bq = C.bwd.quads;
+    z.nlev = item_diode[q] ? A.syms[it.sym].levels_f() : 0;
+    z.nent = item_diode[q] ? it.nptr[it.n] : 0;
+    z.bs = bs;
+    return z;
+  };
+  auto item_lds = [&](int q, bool adj) { return (size_t)step_lds(step_shape(q, adj), true, adj).total; };
   if (solver == EMT_SOLVER_AUTO) {
-    for (const Item &it : A.items) {
-      if (c.is_split[&it - &A.items[0]]) continue;
+    for (int q = 0; q < NI; ++q) {
+      if (c.is_split[q]) continue;
+      const Item &it = A.items[q];
       SweepPlan &P = plans[it.sym];
-      if (!sym_diode[it.sym] && item_lds(it, false) > (size_t)max_lds && P.d < std::min(c.ks.dmax, it.n))
+      if (!sym_diode[it.sym] && !closed[it.sym] && item_lds(q, false) > (size_t)max_lds &&
+          P.d < std::min(c.ks.dmax, it.n))
         P = plan_sweeps(A.syms[it.sym], std::min(c.ks.dmax, it.n));
     }
   }
   size_t f_sm = 0, a_sm = 0, f_gl = 0, a_gl = 0;
-  int wpt = 1;
+  int max_d = 0;
   auto lds_figures = [&]() {
     f_sm = a_sm = f_gl = a_gl = 0;
-    wpt = 1;
-    for (const Item &it : A.items) {
-      if (c.is_split[&it - &A.items[0]]) continue;
-      const LdsShape sh = shape_of(it, A.syms[it.sym], plans[it.sym], item_diode[&it - &A.items[0]]);
-      f_sm = std::max(f_sm, lds_bytes(sh, true, false));
-      a_sm = std::max(a_sm, lds_bytes(sh, true, true));
-      f_gl = std::max(f_gl, lds_bytes(sh, false, false));
-      a_gl = std::max(a_gl, lds_bytes(sh, false, true));
-      const int d = plans[it.sym].d;
-      if (d > 0) wpt = std::max(wpt, (d + tpr_of(d, bs) - 1) / tpr_of(d, bs));
-      if (plans[it.sym].nsv() > 65535) throw Error{EMT_EINVAL, "a connected component's factor is too large"};
+    max_d = 0;
+    for (int q = 0; q < NI; ++q) {
+      if (c.is_split[q] || comp) continue;
+      const Item &it = A.items[q];
+      f_sm = std::max(f_sm, (size_t)step_lds(step_shape(q, false), true, false).total);
+      f_gl = std::max(f_gl, (size_t)step_lds(step_shape(q, false), false, false).total);
+      a_sm = std::max(a_sm, (size_t)step_lds(step_shape(q, K > 0), true, true).total);
+      a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, K > 0), false, true).total);
+      max_d = std::max(max_d, plans[it.sym].d);
+      if (!closed[it.sym] && plans[it.sym].nsv() > 65535)
+        throw Error{EMT_EINVAL, "a connected component's factor is too large"};
     }
     c.sm_fwd = f_sm <= (size_t)max_lds && !sim.sweep_from_global;
     c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global;
@@ -813,6 +946,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       bpt = bg;
       c.ks.bpt = bpt;
       pad_items();
+      plan_gathers();
       lds_figures();
     }
     c.bpt_global = bpt;
@@ -821,8 +955,10 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   for (const Item &it : A.items)
     if (!c.is_split[&it - &A.items[0]] && it.n_br != bs * c.ks.bpt)
       throw Error{EMT_EDEVICE, "internal: an item's branch padding differs from the step kernels' slots"};
-  c.ks.wpt = wpt <= 4 ? 4 : (wpt <= 16 ? 16 : 32);
-  if (wpt > 32 || (wpt > 16 && bs < 512)) throw Error{EMT_EINVAL, "internal: dense tail too large for the block size"};
+  if (!comp) {
+    c.ks.dt = tail_capacity(bs, max_d);
+    if (c.ks.dt == 0) throw Error{EMT_EINVAL, "internal: dense tail too large for the block size"};
+  }
   c.ks.lds_fwd = c.sm_fwd ? f_sm : f_gl;
   c.ks.lds_adj = c.sm_adj ? a_sm : a_gl;
   if (f_gl > (size_t)max_lds) throw Error{EMT_EINVAL, "a connected component needs more LDS than a workgroup has"};
@@ -858,6 +994,21 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     for (int x : v) symh.push_back((uint16_t)x);
     return off;
   };
+  auto put_prog = [&](const RowProgram &p) {
+    RowProg d{};
+    if (p.quads > 65535) throw Error{EMT_EINVAL, "a connected component's row sums are too large"};
+    d.nb = p.batches;
+    d.nq = p.quads;
+    d.meta = put(p.meta);
+    while (symh.size() % 4) symh.push_back(0);  // codes are read four at a time
+    d.code = (int64_t)symh.size();
+    symh.insert(symh.end(), p.code.begin(), p.code.end());
+    d.row = (int64_t)symh.size();
+    symh.insert(symh.end(), p.row.begin(), p.row.end());
+    return d;
+  };
+  std::vector<RowProg> gdesc;
+  for (const RowProgram &p : gprogs) gdesc.push_back(put_prog(p));
   int max_tail = 0;
   auto passes = [&](const std::vector<int> &ptr, const std::vector<int> &maxcnt) {
     std::vector<int> v;
@@ -878,6 +1029,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     d.ns = P.ns;
     d.nnz = (int32_t)S.nnz();
     d.nsv = P.nsv();
+    d.closed = closed[q];
     d.nfpass = P.nfpass();
     d.nbpass = P.nbpass();
     d.nlev = S.levels_f();
@@ -930,6 +1082,37 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       d.rent = put(rent);
       d.rpair = put(rpair);
     }
+    if (closed[q]) {
+      const ClosedPlan &C = cplans[q];
+      d.fwd = put_prog(C.fwd);
+      d.bwd = put_prog(C.bwd);
+      d.nsv = 256 * (C.fwd.quads + C.bwd.quads);
+      std::vector<int> vsrc = C.fwd.src;
+      vsrc.insert(vsrc.end(), C.bwd.src.begin(), C.bwd.src.end());
+      d.vsrc = put(vsrc);
+      d.ncl = (int32_t)C.cluster.size() / 2;
+      d.n_n = C.n_n;
+      d.n_q = C.n_q;
+      d.ngrp = (int32_t)C.n_ptr.size() - 1;
+      d.nq_off = (int32_t)C.q_off.size() / 2;
+      d.ns_off = (int32_t)C.s_off.size() / 2;
+      d.ns_key = (int32_t)C.s_key.size();
+      d.cluster = put(C.cluster);
+      d.q_diag = put(C.q_diag);
+      d.q_off = put(C.q_off);
+      d.n_ptr = put(C.n_ptr);
+      d.n_adj = put(C.n_adj);
+      d.n_grp = put(C.n_grp);
+      d.n_col = put(C.n_col);
+      d.s_off = put(C.s_off);
+      d.s_key = put(C.s_key);
+      d.s_ptr = put(C.s_ptr);
+      d.s_term = put(C.s_term);
+      c.closed_values = std::max(c.closed_values, 2 + C.n_n + C.n_q);
+      c.closed_tail = std::max(c.closed_tail, P.d);
+    } else {
+      c.ldl_tail = std::max(c.ldl_tail, P.d);
+    }
     d.fdesc = (int64_t)symd.size();
     symd.insert(symd.end(), P.fdesc.begin(), P.fdesc.end());
     d.bdesc = (int64_t)symd.size();
@@ -957,7 +1140,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   std::vector<int64_t> ca_coef, ca_br;
   std::vector<int32_t> ca_nbr, ca_prefix;
   int64_t work = 0;
-  std::vector<int32_t> pairs;
+  std::vector<int32_t> pairs, closed_pairs;
   c.dense_items = 0;
   for (int q = 0; q < NI; ++q) {
     const Item &it = A.items[q];
@@ -984,6 +1167,8 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     d.w = w_off;
     d.rec = (int64_t)rnode.size();
     d.topo = scen_topo_off[it.scen];
+    if (prog_f[q] >= 0) d.gf = gdesc[prog_f[q]];
+    if (prog_a[q] >= 0) d.ga = gdesc[prog_a[q]];
     d.ck = ck_off;
     d.seg = seg_off;
     d.n_diodes = 0;
@@ -1036,14 +1221,15 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     coef_off += (int64_t)sc.n_topo * it.n_br;
     fac_off += (int64_t)sc.n_topo * S.nnz();
     dfac_off += (int64_t)sc.n_topo * it.n;
-    sv_off += (int64_t)sc.n_topo * P.nsv();
+    sv_off += (int64_t)sc.n_topo * sdesc[it.sym].nsv;
+    sv_off += sv_off & 1;  // the closed form's values are read in pairs
     w_off += (int64_t)sc.n_topo * P.d * P.d;
     ck_off += n_ck * it.n_br;
     seg_off += (c.adj_pipe ? 2 : 1) * seg_rows * it.n_br;
     node_off += it.n;
     for (int t = 0; t < sc.n_topo; ++t) {
-      pairs.push_back(q);
-      pairs.push_back(t);
+      (closed[it.sym] ? closed_pairs : pairs).push_back(q);
+      (closed[it.sym] ? closed_pairs : pairs).push_back(t);
     }
     ca_coef.push_back(d.coef);
     ca_br.push_back(d.br);
@@ -1075,6 +1261,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   if (work > INT32_MAX) throw Error{EMT_EINVAL, "too many branch-topology pairs"};
   c.n_items = NI;
   c.n_pairs = (int)pairs.size() / 2;
+  c.n_closed = (int)closed_pairs.size() / 2;
   c.nbr_total = (int64_t)bk.size();
   c.nodes_total = node_off;
 
@@ -1234,6 +1421,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.rec_stride = A.rec_stride;
   c.d_order = c.upload(order);
   c.d_pairs = c.upload(pairs);
+  c.d_closed = c.upload(closed_pairs);
   c.ca.coef_base = c.upload(ca_coef);
   c.ca.br_base = c.upload(ca_br);
   c.ca.nbr_of = c.upload(ca_nbr);
@@ -1262,7 +1450,9 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   // statistics
   c.sweep_levels = 0;
   for (const Item &it : A.items)
-    c.sweep_levels = std::max(c.sweep_levels, plans[it.sym].nfpass() + plans[it.sym].nbpass() + (plans[it.sym].d > 0 ? 1 : 0));
+    c.sweep_levels = std::max(
+        c.sweep_levels, closed[it.sym] ? (plans[it.sym].ns > 0 ? (plans[it.sym].d > 0 ? 3 : 1) : 1)
+                                       : plans[it.sym].nfpass() + plans[it.sym].nbpass() + (plans[it.sym].d > 0 ? 1 : 0));
 }
 
 static hipError_t launch_comp_step(emt_ctx &c, int64_t n0, int64_t ns, double *rec, hipStream_t st) {
@@ -1277,6 +1467,13 @@ static void launch_comp_factor(emt_ctx &c, hipStream_t st) {
   if (!c.comp) return;
   hip_check(emt::launch_fill_i32(c.dc.flags + 5, 2, 0, st), "clear flags");
   hip_check(emt::launch_comp_factor(c.dc, c.cc, st), "compensation factor");
+}
+
+// The components' factors: LDL^T (level passes, split and compensation
+// components) or the closed form.
+static void launch_factors(emt_ctx &c, hipStream_t st) {
+  hip_check(emt::launch_factor(c.dc, c.d_pairs, c.n_pairs, c.ldl_tail, st), "factor");
+  hip_check(emt::launch_closed(c.dc, c.d_closed, c.n_closed, c.closed_values, c.closed_tail, st), "closed form");
 }
 
 // Status words of a factorisation (after its work has finished).
@@ -1304,9 +1501,15 @@ static hipError_t launch_forward(emt_ctx &c, int64_t n0, int64_t ns, double *rec
   ks.sm = c.sm_fwd;
   if (!ks.sm) ks.bpt = c.bpt_global;
   switch (ks.bs) {
-    case 64: return emt::launch_forward_bs64(c.dc, ks, c.d_order, c.n_fwd, n0, ns, rec, st);
-    case 256: return emt::launch_forward_bs256(c.dc, ks, c.d_order, c.n_fwd, n0, ns, rec, st);
-    default: return emt::launch_forward_bs512(c.dc, ks, c.d_order, c.n_fwd, n0, ns, rec, st);
+    case 64:
+      return (ks.ext ? emt::launch_forward_ext_bs64 : emt::launch_forward_bs64)(c.dc, ks, c.d_order, c.n_fwd, n0, ns,
+                                                                               rec, st);
+    case 256:
+      return (ks.ext ? emt::launch_forward_ext_bs256 : emt::launch_forward_bs256)(c.dc, ks, c.d_order, c.n_fwd, n0,
+                                                                                 ns, rec, st);
+    default:
+      return (ks.ext ? emt::launch_forward_ext_bs512 : emt::launch_forward_bs512)(c.dc, ks, c.d_order, c.n_fwd, n0,
+                                                                                 ns, rec, st);
   }
 }
 
@@ -1500,7 +1703,7 @@ emt_status emt_factor(emt_ctx *ctx, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     hip_check(emt::launch_fill_i32(ctx->dc.flags, 1, 0, st), "clear flags");
     arm_split_flag(*ctx, st);
-    hip_check(emt::launch_factor(ctx->dc, ctx->d_pairs, ctx->n_pairs, ctx->max_tail, st), "factor");
+    launch_factors(*ctx, st);
     if (ctx->n_tiles > 0)
       hip_check(emt::launch_inverse(ctx->dc, ctx->sc, ctx->d_inv_jobs, ctx->n_inv_jobs, ctx->inverse_lds, st),
                 "inverse");
@@ -1519,7 +1722,7 @@ emt_status emt_factor_async(emt_ctx *ctx, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     hip_check(emt::launch_fill_i32(ctx->dc.flags, 1, 0, st), "clear flags");
     arm_split_flag(*ctx, st);
-    hip_check(emt::launch_factor(ctx->dc, ctx->d_pairs, ctx->n_pairs, ctx->max_tail, st), "factor");
+    launch_factors(*ctx, st);
     if (ctx->n_tiles > 0)
       hip_check(emt::launch_inverse(ctx->dc, ctx->sc, ctx->d_inv_jobs, ctx->n_inv_jobs, ctx->inverse_lds, st),
                 "inverse");

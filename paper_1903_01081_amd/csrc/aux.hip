@@ -5,6 +5,7 @@
 
 #include <cstdint>
 
+#include "assemble.h"
 #include "device.h"
 #include "launch.h"
 #include "trig.h"
@@ -133,37 +134,9 @@ __global__ __launch_bounds__(BS) void k_factor(DevCtx c, const int32_t *pairs) {
   const int32_t *colrow = c.symi + sd.colrow, *colpos = c.symi + sd.colpos;
   const int32_t *flevptr = c.symi + sd.flevptr, *flevrows = c.symi + sd.flevrows;
   const int32_t *fentptr = c.symi + sd.fentptr, *fent = c.symi + sd.fent;
-  const int32_t *nptr = c.nptr + it.nptr;
-  const uint16_t *nent = c.nent + it.nent;
-  const double *g = c.cg + it.coef + (int64_t)t * it.n_br;
-  const int32_t *bk = c.bk + it.br, *bm = c.bm + it.br, *gpos = c.bgpos + it.br;
   double *Lr = c.lfull + it.fac + (int64_t)t * sd.nnz;
   double *D = c.dpiv + it.dfac + (int64_t)t * n;
-  for (int r = threadIdx.x; r < n; r += BS) {
-    for (int q = rowptr[r]; q < rowptr[r + 1]; ++q) Lr[q] = 0.0;
-    double d = 0.0;
-    for (int e = nptr[r]; e < nptr[r + 1]; ++e) {
-      const int ent = nent[e];
-      const int b = ent >> 1;
-      const double gv = g[b];
-      d = d + gv;
-      const int other = (ent & 1) ? bk[b] : bm[b];
-      if (other >= 0 && other < r) Lr[gpos[b]] = Lr[gpos[b]] - gv;
-    }
-    D[r] = d;
-    if (it.n_groups > 0) {
-      // mutual conductances of coupled groups: +g_o between like terminals
-      // of two members, -g_o between a k and an m terminal
-      const int32_t *mp = c.mptr + it.mptr;
-      const int32_t *me = c.ment + it.ment;
-      const double *go = c.cgo + it.coef + (int64_t)t * it.n_br;
-      for (int e = mp[r]; e < mp[r + 1]; ++e) {
-        const int pos = me[2 * e], code = me[2 * e + 1];
-        const double v = go[code >> 1];
-        Lr[pos] = (code & 1) ? Lr[pos] - v : Lr[pos] + v;
-      }
-    }
-  }
+  assemble_g<BS>(c, it, sd, t, Lr, D);
   __syncthreads();
   for (int l = 0; l < sd.nlev; ++l) {
     for (int p = flevptr[l] + threadIdx.x; p < flevptr[l + 1]; p += BS) {
@@ -369,19 +342,6 @@ __global__ void k_grad(DevCtx c, const int32_t *lptr, const int64_t *lent, const
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
-
-size_t lds_bytes(const LdsShape &s, bool sm, bool adjoint) {
-  auto arr = [](size_t cnt, size_t size) { return (cnt * size + 15) & ~(size_t)15; };
-  size_t b = arr(s.d + 1, 8) + arr(s.n + 1, 8) + arr(s.nbr, 8) + arr(adjoint ? s.n : 0, 8) + arr(adjoint ? 1 : 0, 4);
-  if (sm) {
-    b += arr(s.nsv, 8) + arr(s.ns, 8) + arr(s.nfdesc, 8) + arr(s.nbdesc, 8) + arr(s.n + 1, 4) +
-         arr(adjoint ? s.n + 1 : 0, 4) + 3 * arr(s.nsv, 2) + arr(s.nent, 2) + 2 * arr(s.nrec, 2);
-    // the factorisation's own structure for the refactorisations inside the
-    // loop: row pointers, level pointers (rows, entries) and level rows
-    if (s.dyn) b += arr(s.n + 1, 4) + 2 * arr(s.nlev + 1, 4) + arr(s.n, 2);
-  }
-  return b;
-}
 
 static unsigned blocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 

@@ -24,12 +24,19 @@ constexpr uint32_t kTermGround = 0x7FFF;  // mask of one packed terminal
 constexpr int kMaxItemNodes = 0x7FFF;
 enum : uint32_t { GAMMA_PLUS_G = 0, GAMMA_MINUS_G = 1, GAMMA_ZERO = 2, GAMMA_PASS = 3 };
 
+// A set of row sums as the step kernels run it (closed.h): offsets of its
+// batch table in DevCtx::symi and of its codes and row ids in DevCtx::symh.
+struct RowProg {
+  int32_t nb, nq;           // batches, quads
+  int64_t meta, code, row;  // int32 [waves + 1 + nb]; uint16 [nq][64][4]; uint16 [nb][64]
+};
+
 // Symbolic factor and sweep plan (shared by isomorphic items). Offsets index
 // DevCtx::symi (int32) or DevCtx::symh (uint16).
 struct SymDesc {
   int32_t n, d, ns, nnz;        // nodes, dense-tail size, leading size, nonzeros of L
   int32_t nsv, nfpass, nbpass, nlev;  // sweep entries, sweep passes, factor levels
-  int32_t nfdesc, nbdesc, nlevb, pad1;  // row descriptors of the passes; backward levels
+  int32_t nfdesc, nbdesc, nlevb, closed;  // row descriptors of the passes; backward levels; closed-form solve
   // int32 (symi): full factor structure for the numeric factorisation
   int64_t rowptr, rowcol, colptr, colrow, colpos, flevptr, flevrows, fentptr, fent;
   // int32 (symi): backward levels over all n rows (explicit inverse)
@@ -46,6 +53,13 @@ struct SymDesc {
   // update pairs, nnz+1 of them; the pairs (qi | qj << 16), the CSR
   // positions of L_ik and L_jk for every column k < j common to rows i and j
   int64_t rent, rpair;
+  // closed-form solve (closed != 0; then nsv counts the values of the row
+  // programs, 256 per quad, forward then backward): the programs, and for
+  // the numeric kernel the plan's lists (closed.h) in symi
+  RowProg fwd, bwd;
+  int32_t ncl, n_n, n_q, ngrp, nq_off, ns_off, ns_key, padc;
+  int64_t cluster, q_diag, q_off, n_ptr, n_adj, n_grp, n_col, s_off, s_key, s_ptr, s_term;
+  int64_t vsrc;  // [nsv] value index of every program value
 };
 
 struct ItemDesc {
@@ -54,6 +68,7 @@ struct ItemDesc {
   int64_t coef;  // coefficient arrays [n_topo][n_br] (g, beta, in-service)
   int64_t nptr;  // node CSR pointers [n+1] (int32); also recorded-node pointers rptr
   int64_t nent;  // node CSR entries (uint16: local branch << 1 | end-is-m)
+  RowProg gf, ga;  // injection sums per node, forward and adjoint (codes: J entry << 1 | negative)
   int64_t node;  // per-node state [n]
   int64_t fac;   // full L values [n_topo][nnz] (factorisation work)
   int64_t dfac;  // pivots D and 1/D [n_topo][n]
@@ -72,6 +87,72 @@ struct ItemDesc {
   int64_t dyn;     // items with diodes: the factor refreshed inside the time loop, in DevCtx::dyn:
                    // current conductances [n_br], L [nnz], D [n], sweep values [nsv], 1/D [n]
 };
+
+// LDS of a step kernel's workgroup: byte offsets of its arrays (each 16-byte
+// aligned) and their total, the same on the host and on the device.
+struct StepShape {
+  int n, d, ns, nbr, nsrc, nrec, closed, nfpass, nbpass, nsv, nfdesc, nbdesc;
+  int gb, gq, fb, fq, bb, bq;  // batches and quads of the gather, forward and backward programs
+  int nlev, nent;              // factor levels and node-CSR entries of an item refactorised inside the loop, else 0
+  int bs;
+};
+struct StepLds {
+  uint32_t cD, xr, J, flag, emf, pass, sv, dinv, fdesc, bdesc, fcol, brow, bpos, gmeta, gcode, grow, fmeta, fcode,
+      frow, bmeta, bcode, brw, rnode, rcolumn, rf_rowptr, rf_flev, rf_fent, rf_rows, rf_nptr, rf_nent, total;
+};
+inline
+#ifdef __HIPCC__
+    __host__ __device__
+#endif
+        StepLds step_lds(const StepShape &s, bool sm, bool adjoint) {
+  StepLds o{};
+  uint32_t at = 0;
+  auto take = [&at](int cnt, int size) {
+    const uint32_t r = at;
+    at += ((uint32_t)cnt * (uint32_t)size + 15u) & ~15u;
+    return r;
+  };
+  const int waves = s.bs / 64;
+  o.cD = take((s.d + 31) / 32 * 32, 8);               // the tail's right-hand side, zero past d
+  o.xr = take((s.closed ? 2 : 1) * (s.n + 1), 8);     // right-hand side (closed form), then the solution
+  o.J = take(s.nbr + 1 + (adjoint ? s.nrec : 0), 8);  // branch injections, a zero, the adjoint's seeds
+  o.flag = take(adjoint ? 1 : 0, 4);
+  o.emf = take(s.nsrc > 0 ? s.bs : 0, 8);
+  if (!s.closed) o.pass = take(2 * (s.nfpass + s.nbpass + 2), 4);
+  if (sm) {
+    o.gmeta = take(waves + 1 + s.gb, 4);
+    o.gcode = take(s.gq * 256, 2);
+    o.grow = take(s.gb * 64, 2);
+    o.sv = take(s.nsv, 8);
+    if (s.closed) {
+      o.fmeta = take(waves + 1 + s.fb, 4);
+      o.fcode = take(s.fq * 256, 2);
+      o.frow = take(s.fb * 64, 2);
+      o.bmeta = take(waves + 1 + s.bb, 4);
+      o.bcode = take(s.bq * 256, 2);
+      o.brw = take(s.bb * 64, 2);
+    } else {
+      o.dinv = take(s.ns, 8);
+      o.fdesc = take(s.nfdesc, 8);
+      o.bdesc = take(s.nbdesc, 8);
+      o.fcol = take(s.nsv, 2);
+      o.brow = take(s.nsv, 2);
+      o.bpos = take(s.nsv, 2);
+    }
+    o.rnode = take(s.nrec, 2);
+    o.rcolumn = take(s.nrec, 2);
+    if (s.nlev > 0) {
+      o.rf_rowptr = take(s.n + 1, 4);
+      o.rf_flev = take(s.nlev + 1, 4);
+      o.rf_fent = take(s.nlev + 1, 4);
+      o.rf_rows = take(s.n, 2);
+      o.rf_nptr = take(s.n + 1, 4);
+      o.rf_nent = take(s.nent, 2);
+    }
+  }
+  o.total = at;
+  return o;
+}
 
 // One coupled three-phase group: its members' local branches and terminals
 // (a grounded terminal is the item's zero node slot n) and the sign of its

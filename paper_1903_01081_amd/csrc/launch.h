@@ -12,18 +12,11 @@
 
 namespace emt {
 
-// Sizes that decide an item's LDS footprint in the step kernels.
-struct LdsShape {
-  int n, d, ns, nbr, nsrc, nsv, nfdesc, nbdesc, nent, nrec;
-  int nlev = 0;      // factor levels
-  bool dyn = false;  // refactorised inside the loop (diodes, controlled switches)
-};
-
 // Launch shape of the step kernels, chosen once per context.
 struct KernelShape {
   int bs = 256;    // threads per workgroup (64, 256 or 512)
   int bpt = 1;     // branches per lane (1, 2, 4, 6, 8, 12, 16)
-  int wpt = 4;     // tail-inverse entries per lane (4, 16 or 32)
+  int dt = 64;     // dense-tail capacity of the kernel, nodes (64 lanes: 32, 64; 256: 64, 128; 512: 64, 128, 192)
   bool sm = true;  // index arrays and factors staged in LDS
   size_t lds_fwd = 0, lds_adj = 0;
   int dmax = 0;    // largest dense tail this block size supports
@@ -36,14 +29,19 @@ struct CompanionArgs {
   int total, n_items;
 };
 
-size_t lds_bytes(const LdsShape &s, bool sm, bool adjoint);
-
 hipError_t launch_forward_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
                                double *, hipStream_t);
 hipError_t launch_forward_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
                                 double *, hipStream_t);
 hipError_t launch_forward_bs512(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
                                 double *, hipStream_t);
+// the same for batches with lines, coupled groups or diodes
+hipError_t launch_forward_ext_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
+                                   double *, hipStream_t);
+hipError_t launch_forward_ext_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
+                                    double *, hipStream_t);
+hipError_t launch_forward_ext_bs512(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
+                                    double *, hipStream_t);
 hipError_t launch_adjoint_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, const double *,
                                hipStream_t);
 hipError_t launch_adjoint_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, const double *,
@@ -64,6 +62,11 @@ hipError_t adjoint_pipe_blocks_per_cu_bs256(const KernelShape &, int *);
 hipError_t adjoint_pipe_blocks_per_cu_bs512(const KernelShape &, int *);
 
 hipError_t launch_factor(const DevCtx &c, const int32_t *pairs, int n_pairs, int max_tail, hipStream_t st);
+// Numeric closed form (closed.hip) of the (item, topology) pairs given;
+// values: LDS doubles of the largest plan (2 + N + Q entries), max_tail its
+// largest tail.
+hipError_t launch_closed(const DevCtx &c, const int32_t *pairs, int n_pairs, int values, int max_tail,
+                         hipStream_t st);
 hipError_t launch_companions(const DevCtx &c, const CompanionArgs &a, hipStream_t st);
 hipError_t launch_set_params(const DevCtx &c, const double *theta, int P, const int32_t *bscen,
                              int64_t nbr_total, hipStream_t st);

@@ -102,32 +102,40 @@ struct Lds {
   __device__ __forceinline__ T &operator[](int i) const { return reinterpret_cast<T *>(emt_lds + off)[i]; }
 };
 
+// A row program (closed.h) as a wave runs it: its batches b0 .. b1 - 1, the
+// first one's batch word, quad of codes and row id held in registers, the
+// rest in LDS (SM) or global memory.
+template <bool SM>
+struct Rows {
+  int b0, b1;
+  uint32_t m0;
+  uint64_t c0;
+  int r0;
+  Ref<int32_t, SM> word;
+  Ref<uint64_t, SM> code;
+  Ref<uint16_t, SM> row;
+};
+
 // Per-workgroup view of an item: sizes, LDS arrays, and the sweep data in
 // LDS (SM = true) or global memory.
 template <bool SM>
 struct View {
-  int n, d, ns, nbr, nsrc, nsv, nrec, tpr, wlen;  // nbr: padded to whole lane slots
-  int nfpass, nbpass;
-  const int32_t *fpass, *bpass;  // (first descriptor, log2 lanes) pairs, global
+  int n, d, ns, nbr, nsrc, nsv, nrec;  // nbr: padded to whole lane slots
+  int closed, nfpass, nbpass, fvals;   // fvals: values of the forward program
+  Rows<SM> gather, fwd, bwd;
+  Lds<int32_t> pass;  // level passes: (first descriptor, log2 lanes) pairs, forward then backward
   Ref<uint64_t, SM> fdesc, bdesc;
-  Ref<uint16_t, SM> fcol, brow, bpos, nent, rnode, rcolumn;
-  Ref<int32_t, SM> nptr, rptr;
-  Lds<double> x, J, cD, dv, sv_s, dinv_s;  // x has n+1 entries, x[n] = 0
-  Lds<int32_t> flag;                       // adjoint: a word for broadcasts
+  Ref<uint16_t, SM> fcol, brow, bpos, rnode, rcolumn;
+  Lds<double> r, x, J, cD, sv_s, dinv_s, emf;  // x has n+1 entries, x[n] = 0; r: where the gather writes
+  Lds<int32_t> flag;                           // adjoint: a word for broadcasts
   Ref<double, SM> sv, dinv;
-  // SM, items refactorised inside the loop: the factorisation's row
-  // pointers, level pointers (rows, entries) and level rows
+  // items refactorised inside the loop: node CSR, and under SM the
+  // factorisation's row pointers, level pointers (rows, entries), level rows
+  Ref<int32_t, SM> nptr;
+  Ref<uint16_t, SM> nent;
   Lds<int32_t> rf_rowptr, rf_flev, rf_fent_ptr;
   Lds<uint16_t> rf_rows;
 };
-
-// Tail rows are split into tpr lanes of contiguous columns: tpr = the
-// largest power of two (<= 16, within one DPP row) with d * tpr <= block size.
-__device__ __forceinline__ int tail_tpr(int d, int bs) {
-  int t = 16;
-  while (t > 1 && d * t > bs) t >>= 1;
-  return t;
-}
 
 template <int BS, class T>
 __device__ __forceinline__ void copy_to(uint32_t off, const T *src, int cnt) {
@@ -142,11 +150,44 @@ __device__ __forceinline__ void copy_to_u16(uint32_t off, const int32_t *src, in
   for (int q = threadIdx.x; q < cnt; q += BS) dst[q] = (uint16_t)src[q];
 }
 
-// LDS layout (byte offsets from emt_lds, each array 16-byte aligned):
-// cD, x, J, [dv], then under SM sv, dinv, fdesc, bdesc, nptr, [rptr],
-// fcol, brow, bpos, nent, rnode, rcolumn, and for an item with diodes or
-// controlled switches rf_rowptr, rf_flev, rf_fent_ptr, rf_rows.
-// Must match lds_bytes() on the host.
+template <int BS, bool SM>
+__device__ __forceinline__ void load_rows(const DevCtx &c, const RowProg &p, uint32_t ometa, uint32_t ocode,
+                                          uint32_t orow, Rows<SM> &v) {
+  const int32_t *meta = c.symi + p.meta;
+  const uint64_t *code = reinterpret_cast<const uint64_t *>(c.symh + p.code);
+  const uint16_t *row = c.symh + p.row;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+  constexpr int W = BS / 64;
+  v.b0 = v.b1 = 0;
+  v.m0 = 0;
+  v.c0 = 0;
+  v.r0 = 0xFFFF;
+  if (p.nb > 0) {
+    v.b0 = __builtin_amdgcn_readfirstlane(meta[w]);
+    v.b1 = __builtin_amdgcn_readfirstlane(meta[w + 1]);
+    if (v.b0 < v.b1) {
+      v.m0 = (uint32_t)__builtin_amdgcn_readfirstlane(meta[W + 1 + v.b0]);
+      v.c0 = code[(int)(v.m0 & 0xFFFF) * 64 + lane];
+      v.r0 = row[v.b0 * 64 + lane];
+    }
+  }
+  if constexpr (SM) {
+    v.word.off = ometa + 4 * (W + 1);
+    v.code.off = ocode;
+    v.row.off = orow;
+    if (p.nb > 0) {
+      copy_to<BS>(ometa, meta, W + 1 + p.nb);
+      copy_to<BS>(ocode, code, p.nq * 64);
+      copy_to<BS>(orow, row, p.nb * 64);
+    }
+  } else {
+    v.word.p = meta + W + 1;
+    v.code.p = code;
+    v.row.p = row;
+  }
+}
+
+// The LDS layout is step_lds() (device.h), which the host sizes launches by.
 template <int BS, bool SM>
 __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint) {
   const SymDesc sd = c.syms[it.sym];
@@ -158,132 +199,220 @@ __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint)
   v.nsrc = it.n_src;
   v.nsv = sd.nsv;
   v.nrec = it.n_rec;
-  v.tpr = tail_tpr(sd.d, BS);
-  v.wlen = (sd.d + v.tpr - 1) / v.tpr;
+  v.closed = sd.closed;
   v.nfpass = sd.nfpass;
   v.nbpass = sd.nbpass;
-  v.fpass = c.symi + sd.fpass;
-  v.bpass = c.symi + sd.bpass;
-  const uint64_t *g_fdesc = c.symd + sd.fdesc, *g_bdesc = c.symd + sd.bdesc;
-  const uint16_t *g_fcol = c.symh + sd.fcol, *g_brow = c.symh + sd.brow, *g_bpos = c.symh + sd.bpos;
-  const int32_t *g_nptr = c.nptr + it.nptr, *g_rptr = c.rptr + it.nptr;
-  const uint16_t *g_nent = c.nent + it.nent, *g_rnode = c.rnode + it.rec, *g_rcolumn = c.rcolumn + it.rec;
-  const int nent_cnt = g_nptr[v.n];
-
-  uint32_t off = 0;
-  auto take = [&off](int cnt, int size) {
-    const uint32_t o = off;
-    off += ((uint32_t)cnt * (uint32_t)size + 15u) & ~15u;
-    return o;
-  };
-  v.cD.off = take(v.d + 1, 8);
-  v.x.off = take(v.n + 1, 8);
-  v.J.off = take(v.nbr, 8);
-  v.dv.off = take(adjoint ? v.n : 0, 8);
-  v.flag.off = take(adjoint ? 1 : 0, 4);
+  v.fvals = sd.fwd.nq * 256;
+  const int32_t *g_nptr = c.nptr + it.nptr;
+  const bool dyn = it.n_diodes > 0;
+  const int ne = dyn ? g_nptr[v.n] : 0;
+  const RowProg gp = adjoint ? it.ga : it.gf;
+  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  sd.closed,
+                     sd.nfpass,  sd.nbpass, sd.nsv,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
+                     sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, BS};
+  const StepLds o = step_lds(sh, SM, adjoint);
+  v.cD.off = o.cD;
+  // closed form: the gather writes r (the tail's right-hand side where the
+  // whole component is the tail), the solution goes to x; level passes work
+  // in place on x
+  v.x.off = o.xr + (v.closed ? (uint32_t)(v.n + 1) * 8u : 0u);
+  v.r.off = v.closed && v.ns == 0 ? o.cD : o.xr;
+  v.J.off = o.J;
+  v.flag.off = o.flag;
+  v.emf.off = o.emf;
+  for (int q = threadIdx.x; q < (v.d + 31) / 32 * 32; q += BS) v.cD[q] = 0.0;
   if (threadIdx.x == 0) {
-    v.cD[v.d] = 0.0;  // spare slot read by the last pair of the tail product
-    v.x[v.n] = 0.0;   // the ground: every grounded terminal points here
+    v.x[v.n] = 0.0;  // the ground: every grounded terminal points here
+    v.J[v.nbr] = 0.0;
+    reinterpret_cast<double *>(emt_lds + o.xr)[v.n] = 0.0;
+  }
+  load_rows<BS, SM>(c, gp, o.gmeta, o.gcode, o.grow, v.gather);
+  if (v.closed) {
+    load_rows<BS, SM>(c, sd.fwd, o.fmeta, o.fcode, o.frow, v.fwd);
+    load_rows<BS, SM>(c, sd.bwd, o.bmeta, o.bcode, o.brw, v.bwd);
+  } else {
+    v.pass.off = o.pass;
+    const int nf = 2 * (v.nfpass + 1), nb = 2 * (v.nbpass + 1);
+    copy_to<BS>(o.pass, c.symi + sd.fpass, nf);
+    copy_to<BS>(o.pass + 4 * nf, c.symi + sd.bpass, nb);
   }
   if constexpr (SM) {
-    v.sv_s.off = take(v.nsv, 8);
-    v.dinv_s.off = take(v.ns, 8);
-    v.fdesc.off = take(sd.nfdesc, 8);
-    v.bdesc.off = take(sd.nbdesc, 8);
-    v.nptr.off = take(v.n + 1, 4);
-    v.rptr.off = take(adjoint ? v.n + 1 : 0, 4);
-    v.fcol.off = take(v.nsv, 2);
-    v.brow.off = take(v.nsv, 2);
-    v.bpos.off = take(v.nsv, 2);
-    v.nent.off = take(nent_cnt, 2);
-    v.rnode.off = take(v.nrec, 2);
-    v.rcolumn.off = take(v.nrec, 2);
-    copy_to<BS>(v.fdesc.off, g_fdesc, sd.nfdesc);
-    copy_to<BS>(v.bdesc.off, g_bdesc, sd.nbdesc);
-    copy_to<BS>(v.nptr.off, g_nptr, v.n + 1);
-    if (adjoint) copy_to<BS>(v.rptr.off, g_rptr, v.n + 1);
-    copy_to<BS>(v.fcol.off, g_fcol, v.nsv);
-    copy_to<BS>(v.brow.off, g_brow, v.nsv);
-    copy_to<BS>(v.bpos.off, g_bpos, v.nsv);
-    copy_to<BS>(v.nent.off, g_nent, nent_cnt);
-    copy_to<BS>(v.rnode.off, g_rnode, v.nrec);
-    copy_to<BS>(v.rcolumn.off, g_rcolumn, v.nrec);
-    if (it.n_diodes > 0) {
-      v.rf_rowptr.off = take(v.n + 1, 4);
-      v.rf_flev.off = take(sd.nlev + 1, 4);
-      v.rf_fent_ptr.off = take(sd.nlev + 1, 4);
-      v.rf_rows.off = take(v.n, 2);
-      copy_to<BS>(v.rf_rowptr.off, c.symi + sd.rowptr, v.n + 1);
-      copy_to<BS>(v.rf_flev.off, c.symi + sd.flevptr, sd.nlev + 1);
-      copy_to<BS>(v.rf_fent_ptr.off, c.symi + sd.fentptr, sd.nlev + 1);
-      copy_to_u16<BS>(v.rf_rows.off, c.symi + sd.flevrows, v.n);
+    v.sv_s.off = v.sv.off = o.sv;
+    v.rnode.off = o.rnode;
+    v.rcolumn.off = o.rcolumn;
+    copy_to<BS>(o.rnode, c.rnode + it.rec, v.nrec);
+    copy_to<BS>(o.rcolumn, c.rcolumn + it.rec, v.nrec);
+    if (!v.closed) {
+      v.dinv_s.off = v.dinv.off = o.dinv;
+      v.fdesc.off = o.fdesc;
+      v.bdesc.off = o.bdesc;
+      v.fcol.off = o.fcol;
+      v.brow.off = o.brow;
+      v.bpos.off = o.bpos;
+      copy_to<BS>(o.fdesc, c.symd + sd.fdesc, sd.nfdesc);
+      copy_to<BS>(o.bdesc, c.symd + sd.bdesc, sd.nbdesc);
+      copy_to<BS>(o.fcol, c.symh + sd.fcol, v.nsv);
+      copy_to<BS>(o.brow, c.symh + sd.brow, v.nsv);
+      copy_to<BS>(o.bpos, c.symh + sd.bpos, v.nsv);
     }
-    v.sv.off = v.sv_s.off;
-    v.dinv.off = v.dinv_s.off;
+    if (dyn) {
+      v.nptr.off = o.rf_nptr;
+      v.nent.off = o.rf_nent;
+      copy_to<BS>(o.rf_nptr, g_nptr, v.n + 1);
+      copy_to<BS>(o.rf_nent, c.nent + it.nent, ne);
+      v.rf_rowptr.off = o.rf_rowptr;
+      v.rf_flev.off = o.rf_flev;
+      v.rf_fent_ptr.off = o.rf_fent;
+      v.rf_rows.off = o.rf_rows;
+      copy_to<BS>(o.rf_rowptr, c.symi + sd.rowptr, v.n + 1);
+      copy_to<BS>(o.rf_flev, c.symi + sd.flevptr, sd.nlev + 1);
+      copy_to<BS>(o.rf_fent, c.symi + sd.fentptr, sd.nlev + 1);
+      copy_to_u16<BS>(o.rf_rows, c.symi + sd.flevrows, v.n);
+    }
   } else {
-    v.fdesc.p = g_fdesc;
-    v.bdesc.p = g_bdesc;
-    v.fcol.p = g_fcol;
-    v.brow.p = g_brow;
-    v.bpos.p = g_bpos;
     v.nptr.p = g_nptr;
-    v.rptr.p = g_rptr;
-    v.nent.p = g_nent;
-    v.rnode.p = g_rnode;
-    v.rcolumn.p = g_rcolumn;
+    v.nent.p = c.nent + it.nent;
+    v.fdesc.p = c.symd + sd.fdesc;
+    v.bdesc.p = c.symd + sd.bdesc;
+    v.fcol.p = c.symh + sd.fcol;
+    v.brow.p = c.symh + sd.brow;
+    v.bpos.p = c.symh + sd.bpos;
+    v.rnode.p = c.rnode + it.rec;
+    v.rcolumn.p = c.rcolumn + it.rec;
   }
   return v;
 }
 
-// Factor values and the tail inverse of topology t (sweep values and 1/D in
-// LDS under SM; the lane's contiguous share of its tail row of W in VGPRs).
-template <int BS, int WPT, bool SM>
+// The tail inverse W in VGPRs: a row of W is shared by the 16 lanes of a DPP
+// row, lane j holding the column pairs 32 q + 2 j (so that one read of c is
+// 256 contiguous bytes for the 16 lanes, without bank conflicts); each group
+// of 16 lanes holds the rows g, g + BS/16, ... With one row per lane group
+// and contiguous columns a step read c d/4 times as often: a wave's LDS
+// reads return 64 x 16 B each even where the lanes read the same address, and
+// those reads, not the multiply-adds, set the tail's time.
+template <int BS, int DT>
+struct Tail {
+  static constexpr int G = BS / 16;          // groups of 16 lanes
+  static constexpr int R = (DT + G - 1) / G;  // rows per group
+  static constexpr int Q = (DT + 31) / 32;    // column pairs per lane
+  double w[2 * R * Q];
+};
+
+// The lane's share of the d x d row-major W.
+template <int BS, int DT>
+__device__ __forceinline__ void load_tail(const double *W, int d, Tail<BS, DT> &T) {
+  constexpr int G = Tail<BS, DT>::G, R = Tail<BS, DT>::R, Q = Tail<BS, DT>::Q;
+  const int tid = lane_id();
+  const int g = tid >> 4, j = tid & 15;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int row = g + k * G;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int col = 32 * q + 2 * j;
+      T.w[2 * (k * Q + q)] = row < d && col < d ? W[row * d + col] : 0.0;
+      T.w[2 * (k * Q + q) + 1] = row < d && col + 1 < d ? W[row * d + col + 1] : 0.0;
+    }
+  }
+}
+
+// In-place Gauss-Jordan inverse of the symmetric positive definite d x d
+// matrix held in T's layout (zero past d): pivot p's row and column go
+// through `line` (LDS, tail_lines() doubles), one barrier per pivot. Returns
+// the number of non-positive or non-finite pivots (the same in every lane).
+// Entries of the pivot's row and column take the general update a - c r / p
+// with (a, c) = (0, -1) and (a, r) = (0, 1).
+template <int BS, int DT>
+constexpr int tail_lines() {
+  return 2 * (Tail<BS, DT>::Q * 32 + Tail<BS, DT>::R * Tail<BS, DT>::G);
+}
+template <int BS, int DT>
+__device__ __forceinline__ int invert_tail(Tail<BS, DT> &T, int d, double *line) {
+  constexpr int G = Tail<BS, DT>::G, R = Tail<BS, DT>::R, Q = Tail<BS, DT>::Q;
+  static_assert(32 % G == 0, "a group's pivots share a column pair block");
+  constexpr int kBuf = Q * 32 + R * G;
+  const int tid = (int)threadIdx.x;
+  const int g = tid >> 4, j = tid & 15;
+  int bad = 0;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    constexpr int kStep = 2;
+    const int qk = k * G / 32;
+    for (int r0 = 0; r0 < G && k * G + r0 < d; r0 += kStep) {
+#pragma unroll
+      for (int b = 0; b < kStep; ++b) {
+        const int r = r0 + b, p = k * G + r;
+        if (p >= d) break;
+        double *prow = line + b * kBuf, *pcol = prow + Q * 32;
+        const bool in_row = g == r, in_col = j == ((p & 31) >> 1);
+        if (in_row) {
+#pragma unroll
+          for (int q = 0; q < Q; ++q)
+            reinterpret_cast<double2 *>(prow)[16 * q + j] =
+                make_double2(T.w[2 * (k * Q + q)], T.w[2 * (k * Q + q) + 1]);
+        }
+        if (in_col) {
+#pragma unroll
+          for (int i = 0; i < R; ++i) pcol[g + i * G] = T.w[2 * (i * Q + qk) + b];
+        }
+        lds_barrier();
+        const double piv = prow[p];
+        const bool ok = piv > 0.0 && piv < INFINITY;
+        bad += ok ? 0 : 1;
+        const double inv = ok ? 1.0 / piv : 0.0;
+        double rx[Q], ry[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const double2 rr = reinterpret_cast<const double2 *>(prow)[16 * q + j];
+          rx[q] = rr.x * inv;
+          ry[q] = rr.y * inv;
+        }
+        if (in_col) {
+          if (b == 0)
+            rx[qk] = inv;
+          else
+            ry[qk] = inv;
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          double cc = pcol[g + i * G];
+          const bool here = i == k && in_row;
+          if (here) cc = -1.0;
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            double wx = T.w[2 * (i * Q + q)], wy = T.w[2 * (i * Q + q) + 1];
+            if (here) wx = wy = 0.0;
+            if (q == qk && in_col) {
+              if (b == 0)
+                wx = 0.0;
+              else
+                wy = 0.0;
+            }
+            T.w[2 * (i * Q + q)] = __builtin_fma(-cc, rx[q], wx);
+            T.w[2 * (i * Q + q) + 1] = __builtin_fma(-cc, ry[q], wy);
+          }
+        }
+      }
+    }
+  }
+  return bad;
+}
+
+// Factor values and the tail inverse of topology t (values and 1/D in LDS
+// under SM, the lane's share of W in VGPRs).
+template <int BS, int DT, bool SM>
 __device__ __forceinline__ void select_factor(const DevCtx &c, const ItemDesc &it, View<SM> &v, int t,
-                                              double (&w)[WPT]) {
+                                              Tail<BS, DT> &T) {
   const double *sv = c.svals + it.sv + (int64_t)t * v.nsv;
   const double *di = c.dinv + it.dfac + (int64_t)t * v.n;
   if constexpr (SM) {
     copy_to<BS>(v.sv_s.off, sv, v.nsv);
-    copy_to<BS>(v.dinv_s.off, di, v.ns);
+    if (!v.closed) copy_to<BS>(v.dinv_s.off, di, v.ns);
   } else {
     v.sv.p = sv;
     v.dinv.p = di;
   }
-  const double *W = c.wtail + it.w + (int64_t)t * v.d * v.d;
-  const int tid = lane_id();
-  const int row = tid / v.tpr, col0 = (tid % v.tpr) * v.wlen;
-#pragma unroll
-  for (int q = 0; q < WPT; ++q) {
-    const int col = col0 + q;
-    w[q] = (row < v.d && q < v.wlen && col < v.d) ? W[row * v.d + col] : 0.0;
-  }
-}
-
-// Gather: x_r = sum of the signed branch injections at node r (+ dv_r in the
-// adjoint), for every node; loads run four entries ahead of the in-order sum.
-template <int BS, bool ADJ, bool SM>
-__device__ __forceinline__ void gather_all(const View<SM> &v) {
-  for (int r = lane_id(); r < v.n; r += BS) {
-    double acc = 0.0;
-    int e = v.nptr[r];
-    const int e1 = v.nptr[r + 1];
-    for (; e + 4 <= e1; e += 4) {
-      const int n0 = v.nent[e], n1 = v.nent[e + 1], n2 = v.nent[e + 2], n3 = v.nent[e + 3];
-      const double j0 = v.J[n0 >> 1], j1 = v.J[n1 >> 1], j2 = v.J[n2 >> 1], j3 = v.J[n3 >> 1];
-      acc = (n0 & 1) ? acc - j0 : acc + j0;
-      acc = (n1 & 1) ? acc - j1 : acc + j1;
-      acc = (n2 & 1) ? acc - j2 : acc + j2;
-      acc = (n3 & 1) ? acc - j3 : acc + j3;
-    }
-    for (; e < e1; ++e) {
-      const int ent = v.nent[e];
-      const double jv = v.J[ent >> 1];
-      acc = (ent & 1) ? acc - jv : acc + jv;
-    }
-    if (ADJ) acc = acc + v.dv[r];
-    v.x[r] = acc;
-  }
-  lds_barrier();
+  load_tail<BS, DT>(c.wtail + it.w + (int64_t)t * v.d * v.d, v.d, T);
 }
 
 // DPP row_shr:K of a double: lane i receives lane i-K of its 16-lane row
@@ -317,6 +446,85 @@ __device__ __forceinline__ double group_sum(double s, int lg, int sub) {
     if (sub >= 8) s = s + t;
   }
   return s;
+}
+
+// Two doubles at entry 2 i of a value array.
+template <bool SM>
+__device__ __forceinline__ double2 pair_at(const Ref<double, SM> &a, int i) {
+  if constexpr (SM)
+    return reinterpret_cast<const double2 *>(emt_lds + a.off)[i];
+  else
+    return reinterpret_cast<const double2 *>(a.p)[i];
+}
+
+// Runs a row program: per batch a lane adds up its quads' terms (quad(q,
+// codes, acc) for the codes of quad q), the lanes of a row meet in the DPP
+// scan, and the row's last lane hands the sum to out(row, sum). The rows of
+// all batches are independent; the caller places the barriers.
+// What bounds a step here is the chain of dependent LDS reads: code, operand,
+// sum. The first quad's codes sit in registers, four operands are in flight
+// at a time, and the batch word comes from a scalar register. (Row pointers,
+// column and operand read one after another, with the level passes' table in
+// global memory, took 2.3 us a step on 9-node components and 5.5 us on
+// 100-node ones.)
+template <bool SM, class F, class O>
+__device__ __forceinline__ void run_rows(const Rows<SM> &p, F &&quad, O &&out) {
+  const int lane = (int)threadIdx.x & 63;
+  for (int b = p.b0; b < p.b1; ++b) {
+    const bool first = b == p.b0;
+    const uint32_t m = first ? p.m0 : (uint32_t)__builtin_amdgcn_readfirstlane(p.word[b]);
+    const int q0 = (int)(m & 0xFFFF), nq = (int)((m >> 16) & 0xFF), lg = (int)(m >> 24);
+    const int row = first ? p.r0 : (int)p.row[b * 64 + lane];
+    double acc = 0.0;
+    quad(q0, first ? p.c0 : p.code[q0 * 64 + lane], acc);
+    for (int q = q0 + 1; q < q0 + nq; ++q) quad(q, p.code[q * 64 + lane], acc);
+    acc = group_sum(acc, lg, lane & ((1 << lg) - 1));
+    if (row != 0xFFFF) out(row, acc);
+  }
+}
+
+// Gather: r_i = sum of the signed branch injections at node i (with the
+// adjoint's program also the seeds of the node's recorded columns).
+template <bool SM>
+__device__ __forceinline__ void gather_all(const View<SM> &v) {
+  const char *J = emt_lds + v.J.off;
+  run_rows<SM>(
+      v.gather,
+      [&](int, uint64_t c, double &acc) {
+        const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
+        const uint32_t e[4] = {lo & 0xFFFF, lo >> 16, hi & 0xFFFF, hi >> 16};
+        double j[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j[k] = *reinterpret_cast<const double *>(J + ((e[k] & 0xFFFE) << 2));
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          acc = acc + __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, j[k]) ^ ((uint64_t)(e[k] & 1) << 63));
+      },
+      [&](int row, double s) { v.r[row] = s; });
+  lds_barrier();
+}
+
+// Row sums of the closed form: sum of value * (right-hand side or solution).
+template <bool SM, class O>
+__device__ __forceinline__ void value_rows(const View<SM> &v, const Rows<SM> &p, int val0, O &&out) {
+  const int lane = (int)threadIdx.x & 63;
+  const char *xr = emt_lds + (v.x.off - (uint32_t)(v.n + 1) * 8u);
+  run_rows<SM>(
+      p,
+      [&](int q, uint64_t c, double &acc) {
+        const int i = (val0 >> 1) + q * 128 + lane;
+        const double2 a0 = pair_at<SM>(v.sv, i), a1 = pair_at<SM>(v.sv, i + 64);
+        const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
+        const double x0 = *reinterpret_cast<const double *>(xr + ((lo & 0xFFFF) << 3));
+        const double x1 = *reinterpret_cast<const double *>(xr + ((lo >> 16) << 3));
+        const double x2 = *reinterpret_cast<const double *>(xr + ((hi & 0xFFFF) << 3));
+        const double x3 = *reinterpret_cast<const double *>(xr + ((hi >> 16) << 3));
+        acc = __builtin_fma(a0.x, x0, acc);
+        acc = __builtin_fma(a0.y, x1, acc);
+        acc = __builtin_fma(a1.x, x2, acc);
+        acc = __builtin_fma(a1.y, x3, acc);
+      },
+      out);
 }
 
 // One forward pass: for each row descriptor (r, q0, cnt) the row's lanes
@@ -377,52 +585,66 @@ __device__ __forceinline__ void backward_pass(const View<SM> &v, int p0, int p1,
   lds_barrier();
 }
 
-// x_D = W c: each tail row is shared by tpr adjacent lanes of one wave, lane
-// k owning the contiguous columns [k*wlen, (k+1)*wlen).
-template <int BS, int WPT, bool SM>
-__device__ __forceinline__ void tail_solve(const View<SM> &v, const double (&w)[WPT]) {
+// x_D = W c (the layout is Tail's).
+template <int BS, int DT, bool SM>
+__device__ __forceinline__ void tail_solve(const View<SM> &v, const Tail<BS, DT> &T) {
+  constexpr int G = Tail<BS, DT>::G, R = Tail<BS, DT>::R, Q = Tail<BS, DT>::Q;
   const int tid = lane_id();
-  const int row = tid / v.tpr, col0 = (tid % v.tpr) * v.wlen;
-  const double *cD = reinterpret_cast<const double *>(emt_lds + v.cD.off);
-  double s = 0.0;
-  if (row < v.d) {
-    if ((v.wlen & 1) == 0) {
-      // pairs: both columns of a pair are < d or both >= d up to the spare
-      // slot of cD, whose product with a zero W entry is zero
+  const int g = tid >> 4, j = tid & 15;
+  const double2 *c = reinterpret_cast<const double2 *>(emt_lds + v.cD.off);
+  double acc[R];
 #pragma unroll
-      for (int q = 0; q < WPT; q += 2) {
-        if (q < v.wlen && col0 + q < v.d) {
-          const double2 cc = *reinterpret_cast<const double2 *>(cD + col0 + q);
-          s = s + w[q] * cc.x;
-          s = s + w[q + 1] * cc.y;
-        }
-      }
-    } else {
+  for (int k = 0; k < R; ++k) acc[k] = 0.0;
 #pragma unroll
-      for (int q = 0; q < WPT; ++q)
-        if (q < v.wlen && col0 + q < v.d) s = s + w[q] * cD[col0 + q];
+  for (int q = 0; q < Q; ++q) {
+    if (q > 0 && 32 * q >= v.d) break;
+    const double2 cc = c[16 * q + j];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      acc[k] = __builtin_fma(T.w[2 * (k * Q + q)], cc.x, acc[k]);
+      acc[k] = __builtin_fma(T.w[2 * (k * Q + q) + 1], cc.y, acc[k]);
     }
   }
-  int lg = 0;
-  while ((1 << lg) < v.tpr) ++lg;
-  const int sub = tid % v.tpr;
-  s = group_sum(s, lg, sub);
-  if (row < v.d && sub == v.tpr - 1) v.x[v.ns + row] = s;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    if (k > 0 && k * G >= v.d) break;
+    const double s = group_sum(acc[k], 4, j);
+    const int row = g + k * G;
+    if (j == 15 && row < v.d) v.x[v.ns + row] = s;
+  }
   lds_barrier();
 }
 
-// The solve after the gather: forward passes, tail, backward passes.
-template <int BS, int WPT, bool SM>
-__device__ __forceinline__ void solve_after_gather(const View<SM> &v, const double (&w)[WPT]) {
+// The solve after the gather: closed form (c = r_D + N r_S, x_D = W c,
+// x_S = Q r_S + N^T x_D; a component that is all tail gathers straight into
+// c), or the level passes around the tail.
+template <int BS, int DT, bool SM>
+__device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail<BS, DT> &T) {
+  if (v.closed) {
+    if (v.d > 0) {
+      if (v.ns > 0) {
+        value_rows<SM>(v, v.fwd, 0, [&](int row, double s) { v.cD[row] = s; });
+        lds_barrier();
+      }
+      tail_solve<BS, DT, SM>(v, T);
+    }
+    if (v.ns > 0) {
+      value_rows<SM>(v, v.bwd, v.fvals, [&](int row, double s) { v.x[row] = s; });
+      lds_barrier();
+    }
+    return;
+  }
+  auto pass = [&](int i) { return __builtin_amdgcn_readfirstlane(v.pass[i]); };
   for (int k = 0; k < v.nfpass; ++k) {
-    const int p0 = v.fpass[2 * k], lg = v.fpass[2 * k + 1], p1 = v.fpass[2 * k + 2];
+    const int p0 = pass(2 * k), lg = pass(2 * k + 1), p1 = pass(2 * k + 2);
     // the last forward pass of an item with a dense tail is the tail rows'
     const bool tail_rows = v.d > 0 && k == v.nfpass - 1;
     forward_pass<BS, SM>(v, p0, p1, lg, tail_rows ? v.cD.off : v.x.off, tail_rows ? v.ns : 0);
   }
-  if (v.d > 0) tail_solve<BS, WPT, SM>(v, w);
+  if (v.d > 0) tail_solve<BS, DT, SM>(v, T);
+  const int o = 2 * (v.nfpass + 1);
   for (int k = 0; k < v.nbpass; ++k) {
-    const int p0 = v.bpass[2 * k], lg = v.bpass[2 * k + 1], p1 = v.bpass[2 * k + 2];
+    const int p0 = pass(o + 2 * k), lg = pass(o + 2 * k + 1), p1 = pass(o + 2 * k + 2);
     backward_pass<BS, SM>(v, p0, p1, lg);
   }
 }
@@ -436,21 +658,41 @@ template <int BPT>
 struct Lane {
   double g[BPT], be[BPT], h0;
   uint32_t pk[BPT];
-  // the source of slot 0 (sources are numbered first and fit in one slot):
-  // EMF parameters and the EMF of the current step
-  double sE, sw, sph, e0;
+  // EMF of the current step of slot 0 (sources are numbered first and fit in
+  // one slot; 0 elsewhere)
+  double e0;
+  // EMF table: the EMFs of `eper` steps at a time, one per lane (this lane's
+  // source and step offset ek, -1: none), from step ebase on in View::emf.
+  // A cosine is a chain of about 25 dependent FP64 operations; evaluated by
+  // the source lanes each step it stood in the branch update's way.
+  double sE, sw, sph;
+  int ek, eper;
+  int64_t ebase;
 };
 
 template <int BS, int BPT>
 __device__ __forceinline__ void load_lane(const DevCtx &c, const ItemDesc &it, Lane<BPT> &L) {
 #pragma unroll
   for (int j = 0; j < BPT; ++j) L.pk[j] = c.bpack[it.br + threadIdx.x + j * BS];
-  const int b0 = threadIdx.x;
-  const bool src = b0 < it.n_src;
-  L.sE = src ? c.bE[it.br + b0] : 0.0;
-  L.sw = src ? c.bw[it.br + b0] : 0.0;
-  L.sph = src ? c.bph[it.br + b0] : 0.0;
+  L.eper = it.n_src > 0 ? BS / it.n_src : 0;
+  const int k = it.n_src > 0 ? (int)threadIdx.x / it.n_src : 0;
+  const bool src = it.n_src > 0 && k < L.eper;
+  const int64_t b = it.br + (src ? (int)threadIdx.x - k * it.n_src : 0);
+  L.ek = src ? k : -1;
+  L.sE = src ? c.bE[b] : 0.0;
+  L.sw = src ? c.bw[b] : 0.0;
+  L.sph = src ? c.bph[b] : 0.0;
   L.e0 = 0.0;
+  L.ebase = 0;
+}
+
+// Makes the EMF table hold step n (a barrier must follow before it is read,
+// and one lie between its last reader and this call).
+template <int BPT, bool SM>
+__device__ __forceinline__ void emf_cover(const DevCtx &c, const View<SM> &v, Lane<BPT> &L, int64_t n, bool fresh) {
+  if (L.eper == 0 || (!fresh && n < L.ebase + L.eper)) return;
+  L.ebase = n;
+  if (L.ek >= 0) v.emf[(int)threadIdx.x] = L.sE * emf_cos(L.sw * ((double)(n + L.ek) * c.dt) + L.sph);
 }
 
 template <int BS, int BPT>
@@ -482,9 +724,9 @@ __device__ __forceinline__ void history_from_state(const double *si, const doubl
 }
 
 // EMF of step n for the lane's slot-0 branch (0 if it is not a source).
-template <int BPT>
-__device__ __forceinline__ double slot0_emf(const DevCtx &c, const Lane<BPT> &L, int tid, int nsrc, int64_t n) {
-  return tid < nsrc ? L.sE * emf_cos(L.sw * ((double)n * c.dt) + L.sph) : 0.0;
+template <int BPT, bool SM>
+__device__ __forceinline__ double slot0_emf(const View<SM> &v, const Lane<BPT> &L, int tid, int64_t n) {
+  return tid < v.nsrc ? v.emf[(int)(n - L.ebase) * v.nsrc + tid] : 0.0;
 }
 
 // Slot 0's injection of step n: J = g e - h (the other slots' injections
@@ -492,7 +734,9 @@ __device__ __forceinline__ double slot0_emf(const DevCtx &c, const Lane<BPT> &L,
 template <int BS, int BPT, bool SM>
 __device__ __forceinline__ void inject(const DevCtx &c, const View<SM> &v, Lane<BPT> &L, int64_t n) {
   const int tid = lane_id();
-  L.e0 = slot0_emf<BPT>(c, L, tid, v.nsrc, n);
+  emf_cover<BPT, SM>(c, v, L, n, true);
+  lds_barrier();
+  L.e0 = slot0_emf<BPT, SM>(v, L, tid, n);
   v.J[tid] = L.g[0] * L.e0 - L.h0;
 }
 
@@ -505,7 +749,7 @@ __device__ __forceinline__ void update_inject(const DevCtx &c, const View<SM> &v
                                               double *st_u, double *st2_i, double *st2_u, bool switch_next,
                                               int64_t next_coef, bool inj, int64_t n) {
   const int tid = lane_id();
-  const double e_next = inj ? slot0_emf<BPT>(c, L, tid, v.nsrc, n + 1) : 0.0;
+  const double e_next = inj ? slot0_emf<BPT, SM>(v, L, tid, n + 1) : 0.0;
 #pragma unroll
   for (int j = 0; j < BPT; ++j) {
     const int b = tid + j * BS;
@@ -911,7 +1155,7 @@ __device__ void refactor_dynamic(const DevCtx &c, const ItemDesc &it, View<SM> &
 // ---------------------------------------------------------------------------
 // EXT: the batch has distributed-parameter lines, coupled groups or diodes
 // (the variant without them carries none of their code or registers).
-template <int BS, int BPT, int WPT, bool SM, bool EXT>
+template <int BS, int BPT, int DT, bool SM, bool EXT>
 __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, int64_t n0, int64_t nsteps,
                                                 double *rec) {
   const ItemDesc it = c.items[order[blockIdx.x]];
@@ -920,7 +1164,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   int t = topo_of(topo, it.n_topo, n0 + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
   Lane<BPT> L;
-  double w[WPT];
+  Tail<BS, DT> w;
   load_lane<BS, BPT>(c, it, L);
   load_coefs<BS, BPT>(c, it, t, L.g, L.be);
   const bool diodes = EXT && it.n_diodes > 0;  // diodes or controlled switches
@@ -938,10 +1182,10 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   if (diodes) {
     // no dense tail: w stays zero
 #pragma unroll
-    for (int q = 0; q < WPT; ++q) w[q] = 0.0;
+    for (double &e : w.w) e = 0.0;
     refactor_dynamic<BS, BPT, SM>(c, it, v, L);
   } else {
-    select_factor<BS, WPT, SM>(c, it, v, t, w);
+    select_factor<BS, DT, SM>(c, it, v, t, w);
   }
   inject<BS, BPT, SM>(c, v, L, n0 + 1);
   lds_barrier();
@@ -953,20 +1197,36 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   }
   const int R = c.rec_stride;
   const int64_t n_end = n0 + nsteps;
+  // the lane's first recorded node and its column
+  const int tid0 = (int)threadIdx.x;
+  const bool rec0 = rec && tid0 < v.nrec;
+  const int rn0 = rec0 ? v.rnode[tid0] : 0;
+  double *row = rec ? rec + (int64_t)it.scen * nsteps * R : nullptr;
+  double *at0 = rec0 ? row + v.rcolumn[tid0] : nullptr;
+  // steps to the next checkpoint (a 64-bit remainder each step costs more
+  // than the whole branch update)
+  int64_t to_ck = c.K > 0 ? c.K - n0 % c.K : kNever;
+  int64_t ck_at = c.K > 0 ? it.ck + (n0 / c.K + 1) * (int64_t)v.nbr : 0;
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
-    gather_all<BS, false, SM>(v);
-    solve_after_gather<BS, WPT, SM>(v, w);
+    emf_cover<BPT, SM>(c, v, L, n + 1, false);
+    gather_all<SM>(v);
+    solve_after_gather<BS, DT, SM>(v, w);
+    if (rec0) {
+      *at0 = v.x[rn0];
+      at0 += R;
+    }
     if (rec) {
-      double *row = rec + ((int64_t)it.scen * nsteps + (n - n0 - 1)) * R;
-      for (int q = lane_id(); q < v.nrec; q += BS) row[v.rcolumn[q]] = v.x[v.rnode[q]];
+      for (int q = tid0 + BS; q < v.nrec; q += BS) row[v.rcolumn[q]] = v.x[v.rnode[q]];
+      row += R;
     }
     const bool sw = (n + 1 == next);
     const uint32_t fl = diodes ? diode_flips<BS, BPT, SM>(c, it, v, L, dmask, cmask, n) : 0u;
     double *ck_i = nullptr, *ck_u = nullptr, *st_i = nullptr, *st_u = nullptr;
-    if (c.K > 0 && n % c.K == 0) {
-      const int64_t o = it.ck + (n / c.K) * (int64_t)v.nbr;
-      ck_i = c.ck_i + o;
-      ck_u = c.ck_u + o;
+    if (--to_ck == 0) {
+      ck_i = c.ck_i + ck_at;
+      ck_u = c.ck_u + ck_at;
+      to_ck = c.K;
+      ck_at += v.nbr;
     }
     if (n == n_end) {
       st_i = c.si + it.br;
@@ -990,7 +1250,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     if (sw) {
       ++t;
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
-      if (!diodes) select_factor<BS, WPT, SM>(c, it, v, t, w);
+      if (!diodes) select_factor<BS, DT, SM>(c, it, v, t, w);
     }
     lds_barrier();
   }
@@ -1027,7 +1287,7 @@ __device__ __forceinline__ void with_next_coefs(const DevCtx &c, const ItemDesc 
 template <int BS, int BPT, bool SM>
 __device__ __forceinline__ void adjoint_seed(const DevCtx &c, const ItemDesc &it, const View<SM> &v,
                                              const Lane<BPT> &L, int t, int t_nx, const double (&hb_nx)[BPT],
-                                             const double *dJ, int64_t n) {
+                                             double seed0, const double *dJ, int64_t n) {
   const int tid = lane_id();
   with_next_coefs<BS, BPT>(c, it, L, t, t_nx, [&](int j, double g_nx, double be_nx) {
     const int b = tid + j * BS;
@@ -1035,21 +1295,28 @@ __device__ __forceinline__ void adjoint_seed(const DevCtx &c, const ItemDesc &it
     const double ga_nx = gamma_of(L.pk[j], g_nx);
     v.J[b] = (L.g[j] != 0.0) ? ga_nx * hb_nx[j] + L.g[j] * ibar : 0.0;
   });
-  const double *drow = dJ + ((int64_t)it.scen * c.T + (n - 1)) * c.rec_stride;
-  for (int r = tid; r < v.n; r += BS) {
-    double acc = 0.0;
-    const int e1 = v.rptr[r + 1];
-    for (int e = v.rptr[r]; e < e1; ++e) acc = acc + drow[v.rcolumn[e]];
-    v.dv[r] = acc;
+  // the recorded columns' cotangents, which the gather adds at their nodes
+  if (tid < v.nrec) v.J[v.nbr + 1 + tid] = seed0;
+  if (v.nrec > BS) {
+    const double *drow = dJ + ((int64_t)it.scen * c.T + (n - 1)) * c.rec_stride;
+    for (int q = tid + BS; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = drow[v.rcolumn[q]];
   }
+}
+
+// The cotangent of step n in the lane's first recorded column.
+template <bool SM>
+__device__ __forceinline__ double load_seed(const DevCtx &c, const ItemDesc &it, const View<SM> &v, const double *dJ,
+                                            int64_t n) {
+  const int tid = (int)threadIdx.x;
+  return tid < v.nrec ? dJ[((int64_t)it.scen * c.T + (n - 1)) * c.rec_stride + v.rcolumn[tid]] : 0.0;
 }
 
 // Recomputes steps lo+1..hi of segment s from its checkpoint into a
 // segment buffer (row 0 = the checkpoint, row n-lo = step n). Afterwards L's
 // coefficients and the factors are those of step hi.
-template <int BS, int BPT, int WPT, bool SM>
+template <int BS, int BPT, int DT, bool SM>
 __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v,
-                                                  Lane<BPT> &L, double (&w)[WPT], int64_t s, double *seg_i,
+                                                  Lane<BPT> &L, Tail<BS, DT> &w, int64_t s, double *seg_i,
                                                   double *seg_u) {
   const int64_t *topo = c.topo + it.topo;
   const int nbr = v.nbr;
@@ -1061,16 +1328,19 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
     seg_i[b] = c.ck_i[cko + b];
     seg_u[b] = c.ck_u[cko + b];
   }
+  // the gather's seeds are zero in the forward steps
+  for (int q = threadIdx.x; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = 0.0;
   int t = topo_of(topo, it.n_topo, lo + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
   load_coefs<BS, BPT>(c, it, t, L.g, L.be);
   history_from_state<BS, BPT, SM>(c.ck_i + cko, c.ck_u + cko, L, v);
-  select_factor<BS, WPT, SM>(c, it, v, t, w);
+  select_factor<BS, DT, SM>(c, it, v, t, w);
   inject<BS, BPT, SM>(c, v, L, lo + 1);
   lds_barrier();
   for (int64_t n = lo + 1; n <= hi; ++n) {
-    gather_all<BS, false, SM>(v);
-    solve_after_gather<BS, WPT, SM>(v, w);
+    emf_cover<BPT, SM>(c, v, L, n + 1, false);
+    gather_all<SM>(v);
+    solve_after_gather<BS, DT, SM>(v, w);
     const int64_t o = (n - lo) * (int64_t)nbr;
     const bool sw = (n + 1 == next) && n < hi;
     update_inject<BS, BPT, SM>(c, v, L, seg_i + o, seg_u + o, nullptr, nullptr, sw,
@@ -1078,7 +1348,7 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
     if (sw) {
       ++t;
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
-      select_factor<BS, WPT, SM>(c, it, v, t, w);
+      select_factor<BS, DT, SM>(c, it, v, t, w);
     }
     lds_barrier();
   }
@@ -1088,9 +1358,9 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
 // coefficients and the factors are those of step hi (topology t) and hb_nx
 // holds hbar of step hi+1 (0 past the horizon); on exit hb_nx holds hbar of
 // step lo+1, and the gradient accumulators have taken the segment's terms.
-template <int BS, int BPT, int WPT, bool SM>
+template <int BS, int BPT, int DT, bool SM>
 __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v,
-                                                Lane<BPT> &L, double (&w)[WPT], int64_t s, int t,
+                                                Lane<BPT> &L, Tail<BS, DT> &w, int64_t s, int t,
                                                 const double *seg_i, const double *seg_u, double (&hb_nx)[BPT],
                                                 double (&gb)[BPT], double (&bb)[BPT], double (&cb)[BPT],
                                                 const double *dJ) {
@@ -1101,23 +1371,36 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
   // the coefficients of step hi+1 are those of topology t_nx (unused at
   // hi = T, where hbar = 0)
   int t_nx = hi < T ? topo_of(topo, it.n_topo, hi + 1) : t;
-  adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, dJ, hi);
+  adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, load_seed<SM>(c, it, v, dJ, hi), dJ, hi);
   lds_barrier();
+  // the state of step n in the lane's slots, carried from one step (where it
+  // was the earlier one) to the next
+  double un[BPT];
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) un[j] = seg_u[(hi - lo) * (int64_t)nbr + threadIdx.x + j * BS];
   for (int64_t n = hi; n >= lo + 1; --n) {
-    gather_all<BS, true, SM>(v);
-    solve_after_gather<BS, WPT, SM>(v, w);
-    const int64_t on = (n - lo) * (int64_t)nbr, op = (n - 1 - lo) * (int64_t)nbr;
-    const int tid = lane_id();
+    // global reads of this step's update and the next step's seeds, issued
+    // ahead of the solve
+    const int64_t op = (n - 1 - lo) * (int64_t)nbr + threadIdx.x;
+    double ip[BPT], up[BPT];
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) {
+      ip[j] = seg_i[op + j * BS];
+      up[j] = seg_u[op + j * BS];
+    }
+    const double seed0 = n - 1 >= lo + 1 ? load_seed<SM>(c, it, v, dJ, n - 1) : 0.0;
+    gather_all<SM>(v);
+    solve_after_gather<BS, DT, SM>(v, w);
     with_next_coefs<BS, BPT>(c, it, L, t, t_nx, [&](int j, double g_nx, double be_nx) {
       (void)g_nx;
-      const int b = tid + j * BS;
       const uint32_t pk = L.pk[j];
       const double wk = v.x[pk & kTermGround], wm = v.x[(pk >> 15) & kTermGround];
       const double ibar = be_nx * hb_nx[j];
       const double hb = (L.g[j] != 0.0) ? ibar - (wk - wm) : 0.0;
-      gb[j] = gb[j] + hb * seg_u[on + b];
-      bb[j] = bb[j] + hb * seg_i[op + b];
-      cb[j] = cb[j] + hb * seg_u[op + b];
+      gb[j] = gb[j] + hb * un[j];
+      bb[j] = bb[j] + hb * ip[j];
+      cb[j] = cb[j] + hb * up[j];
+      un[j] = up[j];
       hb_nx[j] = hb;
     });
     // step n's coefficients become the next-step ones of step n-1
@@ -1127,9 +1410,9 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
       if (tp != t) {
         t = tp;
         load_coefs<BS, BPT>(c, it, t, L.g, L.be);
-        select_factor<BS, WPT, SM>(c, it, v, t, w);
+        select_factor<BS, DT, SM>(c, it, v, t, w);
       }
-      adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, dJ, n - 1);
+      adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, seed0, dJ, n - 1);
     }
     lds_barrier();
   }
@@ -1152,7 +1435,7 @@ __device__ __forceinline__ void store_branch_adjoints(const DevCtx &c, const Ite
 // is held to two waves per SIMD (two workgroups per compute unit), so a
 // batch of many components runs in fewer rounds than at the one wave per
 // SIMD that its largest branch-slot counts would otherwise take.
-template <int BS, int BPT, int WPT, bool SM>
+template <int BS, int BPT, int DT, bool SM>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 ? 2 : 1))) void k_adjoint(
     DevCtx c, const int32_t *order, const double *dJ) {
   const ItemDesc it = c.items[order[blockIdx.x]];
@@ -1160,17 +1443,17 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 ? 
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   double *seg_i = c.seg_i + it.seg, *seg_u = c.seg_u + it.seg;
   Lane<BPT> L;
-  double w[WPT];
+  Tail<BS, DT> w;
   load_lane<BS, BPT>(c, it, L);
   // per slot: hbar of step n+1 and the three gradient accumulators
   double hb_nx[BPT], gb[BPT], bb[BPT], cb[BPT];
 #pragma unroll
   for (int j = 0; j < BPT; ++j) hb_nx[j] = gb[j] = bb[j] = cb[j] = 0.0;
   for (int64_t s = nseg - 1; s >= 0; --s) {
-    recompute_segment<BS, BPT, WPT, SM>(c, it, v, L, w, s, seg_i, seg_u);
+    recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, seg_i, seg_u);
     const int64_t hi = (s * c.K + c.K < c.T) ? s * c.K + c.K : c.T;
     const int t = topo_of(c.topo + it.topo, it.n_topo, hi);
-    reverse_segment<BS, BPT, WPT, SM>(c, it, v, L, w, s, t, seg_i, seg_u, hb_nx, gb, bb, cb, dJ);
+    reverse_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, t, seg_i, seg_u, hb_nx, gb, bb, cb, dJ);
   }
   store_branch_adjoints<BS, BPT>(c, it, gb, bb, cb);
 }
@@ -1219,7 +1502,7 @@ __device__ __forceinline__ void publish_flag(int32_t *flag, int32_t value) {
 // recompute of segment s-1 overlaps the reversal of segment s. Per item,
 // pipe[2q] counts recomputed segments and pipe[2q+1] reversed ones; the
 // recompute of the k-th segment waits until the (k-2)-th is reversed.
-template <int BS, int BPT, int WPT, bool SM>
+template <int BS, int BPT, int DT, bool SM>
 __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *order, int n_items,
                                                      const double *dJ, int32_t *pipe) {
   const bool recompute = (int)blockIdx.x >= n_items;
@@ -1230,13 +1513,13 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
   const int64_t seg_len = ((c.K < c.T ? c.K : c.T) + 1) * (int64_t)v.nbr;
   int32_t *ready = pipe + 2 * q, *done = pipe + 2 * q + 1;
   Lane<BPT> L;
-  double w[WPT];
+  Tail<BS, DT> w;
   load_lane<BS, BPT>(c, it, L);
   if (recompute) {
     for (int64_t k = 0; k < nseg; ++k) {
       if (k >= 2 && !wait_flag(done, (int32_t)(k - 1), c.flags + 2, v.flag)) return;
       const int64_t o = it.seg + (k & 1) * seg_len;
-      recompute_segment<BS, BPT, WPT, SM>(c, it, v, L, w, nseg - 1 - k, c.seg_i + o, c.seg_u + o);
+      recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, nseg - 1 - k, c.seg_i + o, c.seg_u + o);
       publish_flag(ready, (int32_t)(k + 1));
     }
     return;
@@ -1250,10 +1533,10 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
     const int64_t hi = (s * c.K + c.K < c.T) ? s * c.K + c.K : c.T;
     const int t = topo_of(c.topo + it.topo, it.n_topo, hi);
     load_coefs<BS, BPT>(c, it, t, L.g, L.be);
-    select_factor<BS, WPT, SM>(c, it, v, t, w);
+    select_factor<BS, DT, SM>(c, it, v, t, w);
     lds_barrier();
     const int64_t o = it.seg + (k & 1) * seg_len;
-    reverse_segment<BS, BPT, WPT, SM>(c, it, v, L, w, s, t, c.seg_i + o, c.seg_u + o, hb_nx, gb, bb, cb, dJ);
+    reverse_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, t, c.seg_i + o, c.seg_u + o, hb_nx, gb, bb, cb, dJ);
     publish_flag(done, (int32_t)(k + 1));
   }
   store_branch_adjoints<BS, BPT>(c, it, gb, bb, cb);

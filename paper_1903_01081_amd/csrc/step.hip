@@ -1,5 +1,7 @@
 // Instantiations of the step kernels for one workgroup size (EMT_BS, set by
-// the build: 64, 256 or 512), so the three sizes compile in parallel.
+// the build: 64, 256 or 512) and one kind of kernel (EMT_PART_*: FWD, EXT =
+// the forward kernel with lines, groups, diodes; ADJ; PIPE), so that they
+// compile in parallel.
 #include <hip/hip_runtime.h>
 
 #include "launch.h"
@@ -13,10 +15,11 @@ namespace emt {
 
 namespace {
 
-template <int BPT, int WPT, bool SM, bool EXT>
+#if defined(EMT_PART_FWD) || defined(EMT_PART_EXT)
+template <int BPT, int DT, bool SM, bool EXT>
 hipError_t fwd(const DevCtx &c, const int32_t *order, int n_items, int64_t n0, int64_t ns, double *rec,
                size_t lds, hipStream_t st) {
-  auto k = step::k_forward<EMT_BS, BPT, WPT, SM, EXT>;
+  auto k = step::k_forward<EMT_BS, BPT, DT, SM, EXT>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -24,10 +27,11 @@ hipError_t fwd(const DevCtx &c, const int32_t *order, int n_items, int64_t n0, i
   return hipGetLastError();
 }
 
-template <int BPT, int WPT, bool SM>
+#elif defined(EMT_PART_ADJ)
+template <int BPT, int DT, bool SM>
 hipError_t adj(const DevCtx &c, const int32_t *order, int n_items, const double *dJ, size_t lds,
                hipStream_t st) {
-  auto k = step::k_adjoint<EMT_BS, BPT, WPT, SM>;
+  auto k = step::k_adjoint<EMT_BS, BPT, DT, SM>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -35,10 +39,11 @@ hipError_t adj(const DevCtx &c, const int32_t *order, int n_items, const double 
   return hipGetLastError();
 }
 
-template <int BPT, int WPT, bool SM>
+#else
+template <int BPT, int DT, bool SM>
 hipError_t adj_pipe(const DevCtx &c, const int32_t *order, int n_items, const double *dJ, int32_t *pipe,
                     size_t lds, hipStream_t st) {
-  auto k = step::k_adjoint_pipe<EMT_BS, BPT, WPT, SM>;
+  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -52,67 +57,87 @@ hipError_t adj_pipe(const DevCtx &c, const int32_t *order, int n_items, const do
                                     (unsigned)lds, st);
 }
 
-template <int BPT, int WPT, bool SM>
+template <int BPT, int DT, bool SM>
 hipError_t adj_pipe_occupancy(size_t lds, int *blocks) {
-  auto k = step::k_adjoint_pipe<EMT_BS, BPT, WPT, SM>;
+  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, reinterpret_cast<const void *>(k), EMT_BS, lds);
 }
+#endif
 
 }  // namespace
 
 #define EMT_CAT2(a, b) a##b
 #define EMT_CAT(a, b) EMT_CAT2(a, b)
 
-// Branches per lane x tail-inverse entries per lane: LDS-staged variants for
-// every size, global-memory fallbacks for the larger ones.
-#define EMT_SHAPES_W(X, W) \
-  X(1, W, true) X(2, W, true) X(4, W, true) X(6, W, true) X(8, W, true) X(12, W, true) X(16, W, true) \
-  X(4, W, false) X(8, W, false) X(16, W, false)
+// Branches per lane x dense-tail capacity (KernelShape::dt): LDS-staged
+// variants for every count, global-memory fallbacks for the larger ones.
+#define EMT_SHAPES_W(X, D) \
+  X(1, D, true) X(2, D, true) X(4, D, true) X(6, D, true) X(8, D, true) X(12, D, true) X(16, D, true) \
+  X(4, D, false) X(8, D, false) X(16, D, false)
 #if EMT_BS >= 512
-#define EMT_SHAPES(X) EMT_SHAPES_W(X, 4) EMT_SHAPES_W(X, 16) EMT_SHAPES_W(X, 32)
+#define EMT_SHAPES(X) EMT_SHAPES_W(X, 64) EMT_SHAPES_W(X, 128) EMT_SHAPES_W(X, 192)
+#elif EMT_BS >= 256
+#define EMT_SHAPES(X) EMT_SHAPES_W(X, 64) EMT_SHAPES_W(X, 128)
 #else
-#define EMT_SHAPES(X) EMT_SHAPES_W(X, 4) EMT_SHAPES_W(X, 16)
+#define EMT_SHAPES(X) EMT_SHAPES_W(X, 32) EMT_SHAPES_W(X, 64)
 #endif
 
-hipError_t EMT_CAT(launch_forward_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order,
-                                              int n_items, int64_t n0, int64_t ns, double *rec,
-                                              hipStream_t st) {
-#define EMT_CASE(BPT, WPT, SM)                                                                      \
-  if (ks.bpt == BPT && ks.wpt == WPT && ks.sm == SM)                                                \
-    return ks.ext ? fwd<BPT, WPT, SM, true>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st)          \
-                  : fwd<BPT, WPT, SM, false>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st);
+#ifdef EMT_PART_FWD
+hipError_t EMT_CAT(launch_forward_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order, int n_items,
+                               int64_t n0, int64_t ns, double *rec, hipStream_t st) {
+#define EMT_CASE(BPT, DT, SM)                      \
+  if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) \
+    return fwd<BPT, DT, SM, false>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st);
   EMT_SHAPES(EMT_CASE)
 #undef EMT_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
+#ifdef EMT_PART_EXT
+hipError_t EMT_CAT(launch_forward_ext_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order, int n_items,
+                               int64_t n0, int64_t ns, double *rec, hipStream_t st) {
+#define EMT_CASE(BPT, DT, SM)                      \
+  if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) \
+    return fwd<BPT, DT, SM, true>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st);
+  EMT_SHAPES(EMT_CASE)
+#undef EMT_CASE
+  return hipErrorInvalidValue;
+}
+#endif
+
+#ifdef EMT_PART_ADJ
 hipError_t EMT_CAT(launch_adjoint_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order,
                                               int n_items, const double *dJ, hipStream_t st) {
-#define EMT_CASE(BPT, WPT, SM) \
-  if (ks.bpt == BPT && ks.wpt == WPT && ks.sm == SM) return adj<BPT, WPT, SM>(c, order, n_items, dJ, ks.lds_adj, st);
+#define EMT_CASE(BPT, DT, SM) \
+  if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj<BPT, DT, SM>(c, order, n_items, dJ, ks.lds_adj, st);
   EMT_SHAPES(EMT_CASE)
 #undef EMT_CASE
   return hipErrorInvalidValue;
 }
 
+#endif
+
+#ifdef EMT_PART_PIPE
 hipError_t EMT_CAT(launch_adjoint_pipe_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order,
                                                    int n_items, const double *dJ, int32_t *pipe, hipStream_t st) {
-#define EMT_CASE(BPT, WPT, SM) \
-  if (ks.bpt == BPT && ks.wpt == WPT && ks.sm == SM) return adj_pipe<BPT, WPT, SM>(c, order, n_items, dJ, pipe, ks.lds_adj, st);
+#define EMT_CASE(BPT, DT, SM) \
+  if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj_pipe<BPT, DT, SM>(c, order, n_items, dJ, pipe, ks.lds_adj, st);
   EMT_SHAPES(EMT_CASE)
 #undef EMT_CASE
   return hipErrorInvalidValue;
 }
 
 hipError_t EMT_CAT(adjoint_pipe_blocks_per_cu_bs, EMT_BS)(const KernelShape &ks, int *blocks) {
-#define EMT_CASE(BPT, WPT, SM) \
-  if (ks.bpt == BPT && ks.wpt == WPT && ks.sm == SM) return adj_pipe_occupancy<BPT, WPT, SM>(ks.lds_adj, blocks);
+#define EMT_CASE(BPT, DT, SM) \
+  if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj_pipe_occupancy<BPT, DT, SM>(ks.lds_adj, blocks);
   EMT_SHAPES(EMT_CASE)
 #undef EMT_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
 }  // namespace emt
