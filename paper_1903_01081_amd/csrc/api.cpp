@@ -157,14 +157,17 @@ constexpr int64_t kClosedValues = 15000;
 
 // Rough cycles of one solve. Closed form: three phases, the tail's
 // multiply-adds, LDS reads and 16-lane sums, and 36 LDS cycles per quad of N
-// (twice) and Q. Level passes: about 700 cycles each.
-double closed_cost(const emt::ClosedSize &z, int d, int n, int bs) {
+// (twice) and Q; where its values overflow the LDS (`room` bytes left by the
+// component's other arrays) they come from L2, at about 64 B a cycle and the
+// latency of two such phases. Level passes: about 700 cycles each.
+double closed_cost(const emt::ClosedSize &z, int d, int n, int bs, double room) {
   const double waves = bs / 64.0, simd = std::max(1.0, waves / 4.0);
   const double rows = d > 0 ? (d * 16 + bs - 1) / bs : 0, q = (d + 31) / 32;
-  const double tail = d > 0 ? 250 + simd * rows * (8 * q + 56) + 8 * q * waves : 0;
+  const double tail = d > 0 ? 250 + simd * rows * (8 * q + 35) + 8 * q * waves : 0;
   const double entries = 2.0 * z.nn + z.q + (d < n ? d : 0);
-  const double rounds = entries / (4.0 * bs);
-  return tail + (d < n ? 300 : 0) + (d > 0 && d < n ? 300 : 0) + entries / 256.0 * 36 + 40 * rounds;
+  const double rounds = entries / (4.0 * bs), bytes = 12.5 * entries;
+  return tail + (d < n ? 300 : 0) + (d > 0 && d < n ? 300 : 0) + entries / 256.0 * 36 + 40 * rounds +
+         (bytes > room ? 1500 + bytes / 64 : 0);
 }
 double levels_cost(const emt::SweepPlan &P) { return 700.0 * (P.nfpass() + P.nbpass()) + (P.d > 0 ? 600 : 0); }
 
@@ -791,6 +794,9 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   // SPARSE, for items refactorised inside the loop and for factors whose
   // closed form would be too dense.
   std::vector<char> closed(A.syms.size(), 0);
+  std::vector<double> sym_lds(A.syms.size(), 0.0);  // injections and their sums' codes
+  for (const Item &it : A.items)
+    sym_lds[it.sym] = std::max(sym_lds[it.sym], 8.0 * it.n_br + 3.0 * it.nptr[it.n] + 4.0 * (double)it.rec_node.size());
   for (size_t q = 0; q < A.syms.size(); ++q) {
     const int n = A.syms[q].n;
     int d;
@@ -814,10 +820,11 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     const bool fixed = solver == EMT_SOLVER_DENSE || forced_tail >= 0;
     const std::vector<ClosedSize> z = closed_sizes(A.syms[q], fixed ? d : closed_tail_max(bs));
     double best = levels_cost(plans[q]);
+    const double room = max_lds - sym_lds[q] - 16.0 * (n + 1) - 8.0 * bs;
     int best_d = -1;
     for (int e = fixed ? d : 0; e < (int)z.size(); ++e) {
       if (2 + z[e].q + z[e].nn > kClosedValues) continue;
-      const double cost = closed_cost(z[e], e, n, bs);
+      const double cost = closed_cost(z[e], e, n, bs, room);
       if (cost < best) {
         best = cost;
         best_d = e;
@@ -827,6 +834,8 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     closed[q] = 1;
     if (best_d != d) plans[q] = plan_sweeps(A.syms[q], best_d);
   }
+  for (const Item &it : A.items)
+    if (!c.is_split[&it - &A.items[0]] && !closed[it.sym]) c.ks.ext = true;
   std::vector<ClosedPlan> cplans(A.syms.size());
   auto plan_closed_of = [&](size_t q) {
     if (closed[q]) cplans[q] = plan_closed(A.syms[q], gpos[q], plans[q].d, bs);

@@ -20,7 +20,7 @@ struct KernelShape {
   bool sm = true;  // index arrays and factors staged in LDS
   size_t lds_fwd = 0, lds_adj = 0;
   int dmax = 0;    // largest dense tail this block size supports
-  bool ext = false;  // the batch has distributed-parameter lines, coupled groups or diodes
+  bool ext = false;  // the batch has distributed-parameter lines, coupled groups, diodes or level passes
 };
 
 struct CompanionArgs {
@@ -35,7 +35,7 @@ hipError_t launch_forward_bs256(const DevCtx &, const KernelShape &, const int32
                                 double *, hipStream_t);
 hipError_t launch_forward_bs512(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
                                 double *, hipStream_t);
-// the same for batches with lines, coupled groups or diodes
+// the same for batches with lines, coupled groups, diodes or level passes
 hipError_t launch_forward_ext_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
                                    double *, hipStream_t);
 hipError_t launch_forward_ext_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,

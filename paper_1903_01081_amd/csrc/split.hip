@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kSplitBS) void k_split(DevCtx c, SplitCtx s, int64_
           acc = (ent & 1) ? acc - jv : acc + jv;
         }
       }
-      acc = group_sum(acc, 4, sub);
+      acc = group_sum(acc, 4);
       if (node < tl.cnt && sub == 15) rhs[node] = acc;
     }
     lds_barrier();
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kSplitBS) void k_split(DevCtx c, SplitCtx s, int64_
           const int q = sub + (k << lq_lg);
           acc = acc + (q < P ? __builtin_bit_cast(double, pv[k]) : 0.0);
         }
-        acc = group_sum(acc, lq_lg, sub);
+        acc = group_sum(acc, lq_lg);
         if (sub == (1 << lq_lg) - 1) x[slot] = acc;
       }
       if (quit) {

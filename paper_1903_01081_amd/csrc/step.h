@@ -47,6 +47,12 @@ __device__ __forceinline__ double gamma_of(uint32_t pk, double g) {
   return c == GAMMA_PLUS_G ? g : (c == GAMMA_MINUS_G ? -g : 0.0);
 }
 
+// gamma u from g u (gamma = g, -g or 0).
+__device__ __forceinline__ double gamma_times(uint32_t pk, double gu) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, gu) ^ ((uint64_t)((pk << 1) & 0x80000000u) << 32);
+  return (pk >> 31) ? 0.0 : __builtin_bit_cast(double, b);
+}
+
 __device__ __forceinline__ double source_emf(const DevCtx &c, int64_t gb, int64_t n) {
   const double t = (double)n * c.dt;
   return c.bE[gb] * emf_cos(c.bw[gb] * t + c.bph[gb]);
@@ -75,6 +81,27 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Waits here for a value read from global memory. For the reads inside the
+// time loop that only a switching step makes: left alone, the compiler waits
+// for them at their first use in the loop, which every step passes, and as
+// vector memory operations complete in order each step would wait there for
+// the stores of the recorded voltages (about half of a 9-node component's
+// step).
+__device__ __forceinline__ void settle(double &x) { asm volatile("" : "+v"(x)); }
+
+// The same for a workgroup of BS lanes. One wave's LDS accesses complete in
+// the order they were issued, so a single-wave workgroup needs no wait at
+// all, only that the compiler keeps the order.
+template <int BS>
+__device__ __forceinline__ void step_barrier() {
+  if constexpr (BS == 64) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    lds_barrier();
+  }
 }
 
 // Dynamic LDS of the step kernels (addressed with 32-bit offsets so that
@@ -188,7 +215,9 @@ __device__ __forceinline__ void load_rows(const DevCtx &c, const RowProg &p, uin
 }
 
 // The LDS layout is step_lds() (device.h), which the host sizes launches by.
-template <int BS, bool SM>
+// LEV: the batch may hold components solved by level passes (the kernels
+// without them carry none of their scalars: those of both together spill).
+template <int BS, bool SM, bool LEV>
 __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint) {
   const SymDesc sd = c.syms[it.sym];
   View<SM> v;
@@ -199,7 +228,7 @@ __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint)
   v.nsrc = it.n_src;
   v.nsv = sd.nsv;
   v.nrec = it.n_rec;
-  v.closed = sd.closed;
+  v.closed = LEV ? sd.closed : 1;
   v.nfpass = sd.nfpass;
   v.nbpass = sd.nbpass;
   v.fvals = sd.fwd.nq * 256;
@@ -207,7 +236,7 @@ __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint)
   const bool dyn = it.n_diodes > 0;
   const int ne = dyn ? g_nptr[v.n] : 0;
   const RowProg gp = adjoint ? it.ga : it.gf;
-  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  sd.closed,
+  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  v.closed,
                      sd.nfpass,  sd.nbpass, sd.nsv,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
                      sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, BS};
   const StepLds o = step_lds(sh, SM, adjoint);
@@ -355,7 +384,7 @@ __device__ __forceinline__ int invert_tail(Tail<BS, DT> &T, int d, double *line)
 #pragma unroll
           for (int i = 0; i < R; ++i) pcol[g + i * G] = T.w[2 * (i * Q + qk) + b];
         }
-        lds_barrier();
+        step_barrier<BS>();
         const double piv = prow[p];
         const bool ok = piv > 0.0 && piv < INFINITY;
         bad += ok ? 0 : 1;
@@ -413,6 +442,7 @@ __device__ __forceinline__ void select_factor(const DevCtx &c, const ItemDesc &i
     v.dinv.p = di;
   }
   load_tail<BS, DT>(c.wtail + it.w + (int64_t)t * v.d * v.d, v.d, T);
+  for (double &w : T.w) settle(w);
 }
 
 // DPP row_shr:K of a double: lane i receives lane i-K of its 16-lane row
@@ -425,26 +455,40 @@ __device__ __forceinline__ double dpp_row_shr(double v) {
   return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// Sum over an aligned group of 2^lg <= 16 lanes (sub = lane index in the
-// group) by an inclusive scan of row shifts: the group's last lane ends
-// with the sum, always added in the same order.
-__device__ __forceinline__ double group_sum(double s, int lg, int sub) {
-  if (lg >= 1) {
-    const double t = dpp_row_shr<1>(s);
-    if (sub >= 1) s = s + t;
-  }
-  if (lg >= 2) {
-    const double t = dpp_row_shr<2>(s);
-    if (sub >= 2) s = s + t;
-  }
-  if (lg >= 3) {
-    const double t = dpp_row_shr<4>(s);
-    if (sub >= 4) s = s + t;
-  }
-  if (lg >= 4) {
-    const double t = dpp_row_shr<8>(s);
-    if (sub >= 8) s = s + t;
-  }
+// A double through a DPP control (quad_perm, row_ror) that reads within the
+// lane's 16-lane row.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffu), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// Sums of four values over the 16 lanes of a DPP row: on return a lane holds
+// the sum of v[lane & 3]. Two halving exchanges leave one value per lane
+// pair and quad, which two rotations complete: 33 instructions where four
+// separate scans take 48, and the tail's sums are most of its instructions.
+__device__ __forceinline__ double sum16x4(double v0, double v1, double v2, double v3, bool b0, bool b1) {
+  const double k0 = b0 ? v1 : v0, s0 = b0 ? v0 : v1;  // even lanes keep rows 0 and 2, odd ones 1 and 3
+  const double k1 = b0 ? v3 : v2, s1 = b0 ? v2 : v3;
+  const double p0 = k0 + dpp_move<kDppXor1>(s0), p1 = k1 + dpp_move<kDppXor1>(s1);
+  const double k = b1 ? p1 : p0, s = b1 ? p0 : p1;
+  double a = k + dpp_move<kDppXor2>(s);
+  a = a + dpp_move<kDppRor4>(a);
+  return a + dpp_move<kDppRor8>(a);
+}
+
+// Sum over an aligned group of 2^lg <= 16 lanes by a scan of row shifts: the
+// group's last lane ends with the sum, always added in the same order (the
+// partial sums that reach it are its own group's; other lanes may pick up a
+// neighbour group's, which nothing reads).
+__device__ __forceinline__ double group_sum(double s, int lg) {
+  if (lg >= 1) s = s + dpp_row_shr<1>(s);
+  if (lg >= 2) s = s + dpp_row_shr<2>(s);
+  if (lg >= 3) s = s + dpp_row_shr<4>(s);
+  if (lg >= 4) s = s + dpp_row_shr<8>(s);
   return s;
 }
 
@@ -478,14 +522,14 @@ __device__ __forceinline__ void run_rows(const Rows<SM> &p, F &&quad, O &&out) {
     double acc = 0.0;
     quad(q0, first ? p.c0 : p.code[q0 * 64 + lane], acc);
     for (int q = q0 + 1; q < q0 + nq; ++q) quad(q, p.code[q * 64 + lane], acc);
-    acc = group_sum(acc, lg, lane & ((1 << lg) - 1));
+    acc = group_sum(acc, lg);
     if (row != 0xFFFF) out(row, acc);
   }
 }
 
 // Gather: r_i = sum of the signed branch injections at node i (with the
 // adjoint's program also the seeds of the node's recorded columns).
-template <bool SM>
+template <int BS, bool SM>
 __device__ __forceinline__ void gather_all(const View<SM> &v) {
   const char *J = emt_lds + v.J.off;
   run_rows<SM>(
@@ -501,7 +545,7 @@ __device__ __forceinline__ void gather_all(const View<SM> &v) {
           acc = acc + __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, j[k]) ^ ((uint64_t)(e[k] & 1) << 63));
       },
       [&](int row, double s) { v.r[row] = s; });
-  lds_barrier();
+  step_barrier<BS>();
 }
 
 // Row sums of the closed form: sum of value * (right-hand side or solution).
@@ -551,10 +595,10 @@ __device__ __forceinline__ void forward_pass(const View<SM> &v, int p0, int p1, 
       s = s + a1 * x1;
     }
     if (q < q1) s = s + v.sv[q] * v.x[v.fcol[q]];
-    s = group_sum(s, lg, sub);
+    s = group_sum(s, lg);
     if (sub == G - 1) reinterpret_cast<double *>(emt_lds + out_off)[r - shift] = xr - s;
   }
-  lds_barrier();
+  step_barrier<BS>();
 }
 
 // One backward pass: x_r = x_r / D_r - sum over the row's column entries of
@@ -579,10 +623,10 @@ __device__ __forceinline__ void backward_pass(const View<SM> &v, int p0, int p1,
       s = s + a1 * x1;
     }
     if (q < q1) s = s + v.sv[v.bpos[q]] * v.x[v.brow[q]];
-    s = group_sum(s, lg, sub);
+    s = group_sum(s, lg);
     if (sub == G - 1) v.x[r] = xr - s;
   }
-  lds_barrier();
+  step_barrier<BS>();
 }
 
 // x_D = W c (the layout is Tail's).
@@ -592,45 +636,48 @@ __device__ __forceinline__ void tail_solve(const View<SM> &v, const Tail<BS, DT>
   const int tid = lane_id();
   const int g = tid >> 4, j = tid & 15;
   const double2 *c = reinterpret_cast<const double2 *>(emt_lds + v.cD.off);
-  double acc[R];
+  const bool b0 = j & 1, b1 = j & 2;
+  double2 cc[Q];
 #pragma unroll
-  for (int k = 0; k < R; ++k) acc[k] = 0.0;
+  for (int q = 0; q < Q; ++q) cc[q] = c[16 * q + j];
+  // rows in fours
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    if (q > 0 && 32 * q >= v.d) break;
-    const double2 cc = c[16 * q + j];
+  for (int k0 = 0; k0 < R; k0 += 4) {
+    if (k0 > 0 && k0 * G >= v.d) break;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-      acc[k] = __builtin_fma(T.w[2 * (k * Q + q)], cc.x, acc[k]);
-      acc[k] = __builtin_fma(T.w[2 * (k * Q + q) + 1], cc.y, acc[k]);
+    for (int q = 0; q < Q; ++q) {
+      if (q > 0 && 32 * q >= v.d) break;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (k0 + k >= R) continue;
+        acc[k] = __builtin_fma(T.w[2 * ((k0 + k) * Q + q)], cc[q].x, acc[k]);
+        acc[k] = __builtin_fma(T.w[2 * ((k0 + k) * Q + q) + 1], cc[q].y, acc[k]);
+      }
     }
+    const double sum = sum16x4(acc[0], acc[1], acc[2], acc[3], b0, b1);
+    const int row = g + (k0 + j) * G;
+    if (j < 4 && row < v.d) v.x[v.ns + row] = sum;
   }
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    if (k > 0 && k * G >= v.d) break;
-    const double s = group_sum(acc[k], 4, j);
-    const int row = g + k * G;
-    if (j == 15 && row < v.d) v.x[v.ns + row] = s;
-  }
-  lds_barrier();
+  step_barrier<BS>();
 }
 
 // The solve after the gather: closed form (c = r_D + N r_S, x_D = W c,
 // x_S = Q r_S + N^T x_D; a component that is all tail gathers straight into
 // c), or the level passes around the tail.
-template <int BS, int DT, bool SM>
+template <int BS, int DT, bool SM, bool LEV>
 __device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail<BS, DT> &T) {
-  if (v.closed) {
+  if (!LEV || v.closed) {
     if (v.d > 0) {
       if (v.ns > 0) {
         value_rows<SM>(v, v.fwd, 0, [&](int row, double s) { v.cD[row] = s; });
-        lds_barrier();
+        step_barrier<BS>();
       }
       tail_solve<BS, DT, SM>(v, T);
     }
     if (v.ns > 0) {
       value_rows<SM>(v, v.bwd, v.fvals, [&](int row, double s) { v.x[row] = s; });
-      lds_barrier();
+      step_barrier<BS>();
     }
     return;
   }
@@ -661,20 +708,19 @@ struct Lane {
   // EMF of the current step of slot 0 (sources are numbered first and fit in
   // one slot; 0 elsewhere)
   double e0;
-  // EMF table: the EMFs of `eper` steps at a time, one per lane (this lane's
-  // source and step offset ek, -1: none), from step ebase on in View::emf.
+  // EMF table (View::emf): the EMFs of `eper` steps at a time, one per lane
+  // (this lane's source, and step offset ek, -1: none).
   // A cosine is a chain of about 25 dependent FP64 operations; evaluated by
   // the source lanes each step it stood in the branch update's way.
   double sE, sw, sph;
-  int ek, eper;
-  int64_t ebase;
+  int ek, eper, enext;  // enext: the next step's place in the table
 };
 
 template <int BS, int BPT>
 __device__ __forceinline__ void load_lane(const DevCtx &c, const ItemDesc &it, Lane<BPT> &L) {
 #pragma unroll
   for (int j = 0; j < BPT; ++j) L.pk[j] = c.bpack[it.br + threadIdx.x + j * BS];
-  L.eper = it.n_src > 0 ? BS / it.n_src : 0;
+  L.eper = it.n_src > 0 ? __builtin_amdgcn_readfirstlane(BS / it.n_src) : 0;
   const int k = it.n_src > 0 ? (int)threadIdx.x / it.n_src : 0;
   const bool src = it.n_src > 0 && k < L.eper;
   const int64_t b = it.br + (src ? (int)threadIdx.x - k * it.n_src : 0);
@@ -683,15 +729,17 @@ __device__ __forceinline__ void load_lane(const DevCtx &c, const ItemDesc &it, L
   L.sw = src ? c.bw[b] : 0.0;
   L.sph = src ? c.bph[b] : 0.0;
   L.e0 = 0.0;
-  L.ebase = 0;
+  L.enext = 0;
 }
 
-// Makes the EMF table hold step n (a barrier must follow before it is read,
+// Moves the EMF table's place on to step n, filling the table from there
+// when it is used up or `fresh` (a barrier must follow before it is read,
 // and one lie between its last reader and this call).
 template <int BPT, bool SM>
-__device__ __forceinline__ void emf_cover(const DevCtx &c, const View<SM> &v, Lane<BPT> &L, int64_t n, bool fresh) {
-  if (L.eper == 0 || (!fresh && n < L.ebase + L.eper)) return;
-  L.ebase = n;
+__device__ __forceinline__ void emf_advance(const DevCtx &c, const View<SM> &v, Lane<BPT> &L, int64_t n, bool fresh) {
+  if (L.eper == 0) return;
+  if (!fresh && ++L.enext < L.eper) return;
+  L.enext = 0;
   if (L.ek >= 0) v.emf[(int)threadIdx.x] = L.sE * emf_cos(L.sw * ((double)(n + L.ek) * c.dt) + L.sph);
 }
 
@@ -703,6 +751,11 @@ __device__ __forceinline__ void load_coefs(const DevCtx &c, const ItemDesc &it, 
   for (int j = 0; j < BPT; ++j) {
     g[j] = c.cg[base + threadIdx.x + j * BS];
     be[j] = c.cb[base + threadIdx.x + j * BS];
+  }
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) {
+    settle(g[j]);
+    settle(be[j]);
   }
 }
 
@@ -723,10 +776,11 @@ __device__ __forceinline__ void history_from_state(const double *si, const doubl
   }
 }
 
-// EMF of step n for the lane's slot-0 branch (0 if it is not a source).
+// EMF at the table's place for the lane's slot-0 branch (0 if it is not a
+// source).
 template <int BPT, bool SM>
-__device__ __forceinline__ double slot0_emf(const View<SM> &v, const Lane<BPT> &L, int tid, int64_t n) {
-  return tid < v.nsrc ? v.emf[(int)(n - L.ebase) * v.nsrc + tid] : 0.0;
+__device__ __forceinline__ double slot0_emf(const View<SM> &v, const Lane<BPT> &L, int tid) {
+  return tid < v.nsrc ? v.emf[L.enext * v.nsrc + tid] : 0.0;
 }
 
 // Slot 0's injection of step n: J = g e - h (the other slots' injections
@@ -734,9 +788,9 @@ __device__ __forceinline__ double slot0_emf(const View<SM> &v, const Lane<BPT> &
 template <int BS, int BPT, bool SM>
 __device__ __forceinline__ void inject(const DevCtx &c, const View<SM> &v, Lane<BPT> &L, int64_t n) {
   const int tid = lane_id();
-  emf_cover<BPT, SM>(c, v, L, n, true);
-  lds_barrier();
-  L.e0 = slot0_emf<BPT, SM>(v, L, tid, n);
+  emf_advance<BPT, SM>(c, v, L, n, true);
+  step_barrier<BS>();
+  L.e0 = slot0_emf<BPT, SM>(v, L, tid);
   v.J[tid] = L.g[0] * L.e0 - L.h0;
 }
 
@@ -749,7 +803,7 @@ __device__ __forceinline__ void update_inject(const DevCtx &c, const View<SM> &v
                                               double *st_u, double *st2_i, double *st2_u, bool switch_next,
                                               int64_t next_coef, bool inj, int64_t n) {
   const int tid = lane_id();
-  const double e_next = inj ? slot0_emf<BPT, SM>(v, L, tid, n + 1) : 0.0;
+  const double e_next = inj ? slot0_emf<BPT, SM>(v, L, tid) : 0.0;
 #pragma unroll
   for (int j = 0; j < BPT; ++j) {
     const int b = tid + j * BS;
@@ -760,10 +814,13 @@ __device__ __forceinline__ void update_inject(const DevCtx &c, const View<SM> &v
     // such branches; the kernels of other batches carry none of this)
     const bool line = PASS && (pk >> 30) == GAMMA_PASS;
     const double vk = v.x[pk & kTermGround], vm = v.x[(pk >> 15) & kTermGround];
-    const double e = j == 0 ? L.e0 : 0.0;
     const double h = (j == 0 && !line) ? L.h0 : -v.J[b];
-    const double u = (L.g[j] != 0.0) ? (vk - vm) - e : 0.0;
-    const double i = L.g[j] * u + h;
+    double u = j == 0 ? (vk - vm) - L.e0 : vk - vm;
+    // u of a branch out of service is 0; its coefficients are 0 too, so only
+    // a stored state or a change of coefficients sees it
+    if ((st_i || st2_i || switch_next) && L.g[j] == 0.0) u = 0.0;
+    const double gu = L.g[j] * u;
+    const double i = gu + h;
     if (st_i && !line) {
       st_i[b] = i;
       st_u[b] = u;
@@ -775,8 +832,11 @@ __device__ __forceinline__ void update_inject(const DevCtx &c, const View<SM> &v
     if (switch_next) {
       L.g[j] = c.cg[next_coef + b];
       L.be[j] = c.cb[next_coef + b];
+      settle(L.g[j]);
+      settle(L.be[j]);
     }
-    const double hn = L.be[j] * i + gamma_of(pk, L.g[j]) * u;
+    const double gam = switch_next ? gamma_of(pk, L.g[j]) * u : gamma_times(pk, gu);
+    const double hn = L.be[j] * i + gam;
     if (j == 0) {
       L.h0 = hn;
       if (inj && !line) v.J[b] = L.g[j] * e_next - hn;
@@ -1016,7 +1076,7 @@ __device__ __forceinline__ void ldl_levels(int nlev, const RP &rowptr, const LV 
           const double ljk = Lr[q];
           acc = acc + ljk * ljk * D[rowcol[q]];
         }
-        acc = group_sum(acc, lg, sub);
+        acc = group_sum(acc, lg);
         if (sub == g - 1) {
           const double d = D[j] - acc;
           D[j] = d;
@@ -1051,7 +1111,7 @@ __device__ __forceinline__ void ldl_levels(int nlev, const RP &rowptr, const LV 
           r += PC * g;
           if (r < r1) load_pairs(pr, rpair, r, r1, g);
         }
-        acc = group_sum(acc, lg, sub);
+        acc = group_sum(acc, lg);
         if (sub == g - 1) Lr[pos] = (Lr[pos] - acc) / D[rowcol[pos]];
       }
     }
@@ -1135,7 +1195,7 @@ __device__ void refactor_dynamic(const DevCtx &c, const ItemDesc &it, View<SM> &
     (void)sv;
     (void)di;
     for (int r = threadIdx.x; r < n; r += BS) D[r] = 1.0 / D[r];
-    lds_barrier();
+    step_barrier<BS>();
   } else {
     const int32_t *rowcol = c.symi + sd.rowcol;
     const int32_t *flevptr = c.symi + sd.flevptr, *flevrows = c.symi + sd.flevrows;
@@ -1153,13 +1213,14 @@ __device__ void refactor_dynamic(const DevCtx &c, const ItemDesc &it, View<SM> &
 // ---------------------------------------------------------------------------
 // Forward loop: steps n0+1 .. n0+nsteps for every item.
 // ---------------------------------------------------------------------------
-// EXT: the batch has distributed-parameter lines, coupled groups or diodes
-// (the variant without them carries none of their code or registers).
+// EXT: the batch has distributed-parameter lines, coupled groups, diodes or
+// components solved by level passes (the variant without them carries none
+// of their code or registers).
 template <int BS, int BPT, int DT, bool SM, bool EXT>
 __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, int64_t n0, int64_t nsteps,
                                                 double *rec) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM>(c, it, false);
+  View<SM> v = make_view<BS, SM, EXT>(c, it, false);
   const int64_t *topo = c.topo + it.topo;
   int t = topo_of(topo, it.n_topo, n0 + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
@@ -1188,12 +1249,12 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     select_factor<BS, DT, SM>(c, it, v, t, w);
   }
   inject<BS, BPT, SM>(c, v, L, n0 + 1);
-  lds_barrier();
+  step_barrier<BS>();
   const bool lines = EXT && it.n_lines > 0, groups = EXT && it.n_groups > 0;
   if (lines || groups) {
     if (lines) line_pass<BS, SM>(c, it, v, n0 + 1, false, nullptr, nullptr);
     if (groups) group_pass<BS, SM>(c, it, v, true, true, nullptr, nullptr);
-    lds_barrier();
+    step_barrier<BS>();
   }
   const int R = c.rec_stride;
   const int64_t n_end = n0 + nsteps;
@@ -1208,14 +1269,12 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   int64_t to_ck = c.K > 0 ? c.K - n0 % c.K : kNever;
   int64_t ck_at = c.K > 0 ? it.ck + (n0 / c.K + 1) * (int64_t)v.nbr : 0;
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
-    emf_cover<BPT, SM>(c, v, L, n + 1, false);
-    gather_all<SM>(v);
-    solve_after_gather<BS, DT, SM>(v, w);
-    if (rec0) {
-      *at0 = v.x[rn0];
-      at0 += R;
-    }
-    if (rec) {
+    emf_advance<BPT, SM>(c, v, L, n + 1, false);
+    gather_all<BS, SM>(v);
+    solve_after_gather<BS, DT, SM, EXT>(v, w);
+    // read here, stored after the update so that its own reads go ahead
+    const double rv0 = rec0 ? v.x[rn0] : 0.0;
+    if (v.nrec > BS && rec) {
       for (int q = tid0 + BS; q < v.nrec; q += BS) row[v.rcolumn[q]] = v.x[v.rnode[q]];
       row += R;
     }
@@ -1234,8 +1293,12 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     }
     update_inject<BS, BPT, SM, EXT>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
                                n < n_end, n);
+    if (rec0) {
+      *at0 = rv0;
+      at0 += R;
+    }
     if (lines || groups) {
-      lds_barrier();
+      step_barrier<BS>();
       if (lines) line_pass<BS, SM>(c, it, v, n, true, st_i, st_u);
       if (groups) group_pass<BS, SM>(c, it, v, false, n < n_end, st_i, st_u);
     }
@@ -1252,7 +1315,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
       if (!diodes) select_factor<BS, DT, SM>(c, it, v, t, w);
     }
-    lds_barrier();
+    step_barrier<BS>();
   }
   for (int q = threadIdx.x; q < v.n; q += BS) c.sv_state[it.node + q] = v.x[q];
 }
@@ -1336,11 +1399,11 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
   history_from_state<BS, BPT, SM>(c.ck_i + cko, c.ck_u + cko, L, v);
   select_factor<BS, DT, SM>(c, it, v, t, w);
   inject<BS, BPT, SM>(c, v, L, lo + 1);
-  lds_barrier();
+  step_barrier<BS>();
   for (int64_t n = lo + 1; n <= hi; ++n) {
-    emf_cover<BPT, SM>(c, v, L, n + 1, false);
-    gather_all<SM>(v);
-    solve_after_gather<BS, DT, SM>(v, w);
+    emf_advance<BPT, SM>(c, v, L, n + 1, false);
+    gather_all<BS, SM>(v);
+    solve_after_gather<BS, DT, SM, true>(v, w);
     const int64_t o = (n - lo) * (int64_t)nbr;
     const bool sw = (n + 1 == next) && n < hi;
     update_inject<BS, BPT, SM>(c, v, L, seg_i + o, seg_u + o, nullptr, nullptr, sw,
@@ -1350,7 +1413,7 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
       select_factor<BS, DT, SM>(c, it, v, t, w);
     }
-    lds_barrier();
+    step_barrier<BS>();
   }
 }
 
@@ -1372,7 +1435,7 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
   // hi = T, where hbar = 0)
   int t_nx = hi < T ? topo_of(topo, it.n_topo, hi + 1) : t;
   adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, load_seed<SM>(c, it, v, dJ, hi), dJ, hi);
-  lds_barrier();
+  step_barrier<BS>();
   // the state of step n in the lane's slots, carried from one step (where it
   // was the earlier one) to the next
   double un[BPT];
@@ -1389,8 +1452,8 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
       up[j] = seg_u[op + j * BS];
     }
     const double seed0 = n - 1 >= lo + 1 ? load_seed<SM>(c, it, v, dJ, n - 1) : 0.0;
-    gather_all<SM>(v);
-    solve_after_gather<BS, DT, SM>(v, w);
+    gather_all<BS, SM>(v);
+    solve_after_gather<BS, DT, SM, true>(v, w);
     with_next_coefs<BS, BPT>(c, it, L, t, t_nx, [&](int j, double g_nx, double be_nx) {
       (void)g_nx;
       const uint32_t pk = L.pk[j];
@@ -1414,7 +1477,7 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
       }
       adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, seed0, dJ, n - 1);
     }
-    lds_barrier();
+    step_barrier<BS>();
   }
 }
 
@@ -1439,7 +1502,7 @@ template <int BS, int BPT, int DT, bool SM>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 ? 2 : 1))) void k_adjoint(
     DevCtx c, const int32_t *order, const double *dJ) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM>(c, it, true);
+  View<SM> v = make_view<BS, SM, true>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   double *seg_i = c.seg_i + it.seg, *seg_u = c.seg_u + it.seg;
   Lane<BPT> L;
@@ -1508,7 +1571,7 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
   const bool recompute = (int)blockIdx.x >= n_items;
   const int q = order[recompute ? blockIdx.x - n_items : blockIdx.x];
   const ItemDesc it = c.items[q];
-  View<SM> v = make_view<BS, SM>(c, it, true);
+  View<SM> v = make_view<BS, SM, true>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   const int64_t seg_len = ((c.K < c.T ? c.K : c.T) + 1) * (int64_t)v.nbr;
   int32_t *ready = pipe + 2 * q, *done = pipe + 2 * q + 1;
@@ -1534,7 +1597,7 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
     const int t = topo_of(c.topo + it.topo, it.n_topo, hi);
     load_coefs<BS, BPT>(c, it, t, L.g, L.be);
     select_factor<BS, DT, SM>(c, it, v, t, w);
-    lds_barrier();
+    step_barrier<BS>();
     const int64_t o = it.seg + (k & 1) * seg_len;
     reverse_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, t, c.seg_i + o, c.seg_u + o, hb_nx, gb, bb, cb, dJ);
     publish_flag(done, (int32_t)(k + 1));
