@@ -157,9 +157,9 @@ constexpr int64_t kClosedValues = 15000;
 
 // Rough cycles of one solve. Closed form: three phases, the tail's
 // multiply-adds, LDS reads and 16-lane sums, and 36 LDS cycles per quad of N
-// (twice) and Q; where its values overflow the LDS (`room` bytes left by the
-// component's other arrays) they come from L2, at about 64 B a cycle and the
-// latency of two such phases. Level passes: about 700 cycles each.
+// (twice) and Q; the values that overflow the LDS (`room` bytes left by the
+// component's other arrays) come from L2, at about 32 B a cycle and some
+// latency. Level passes: about 700 cycles each.
 double closed_cost(const emt::ClosedSize &z, int d, int n, int bs, double room) {
   const double waves = bs / 64.0, simd = std::max(1.0, waves / 4.0);
   const double rows = d > 0 ? (d * 16 + bs - 1) / bs : 0, q = (d + 31) / 32;
@@ -167,7 +167,7 @@ double closed_cost(const emt::ClosedSize &z, int d, int n, int bs, double room) 
   const double entries = 2.0 * z.nn + z.q + (d < n ? d : 0);
   const double rounds = entries / (4.0 * bs), bytes = 12.5 * entries;
   return tail + (d < n ? 300 : 0) + (d > 0 && d < n ? 300 : 0) + entries / 256.0 * 36 + 40 * rounds +
-         (bytes > room ? 1500 + bytes / 64 : 0);
+         (bytes > room ? 300 + (bytes - std::max(0.0, room)) / 32 : 0);
 }
 double levels_cost(const emt::SweepPlan &P) { return 700.0 * (P.nfpass() + P.nbpass()) + (P.d > 0 ? 600 : 0); }
 
@@ -733,12 +733,6 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
                                 " branches; the step kernel holds at most " + std::to_string(16 * bs)};
   c.ks.bs = bs;
   c.ks.bpt = bpt;
-  c.ks.ext = false;
-  for (const Item &it : A.items) {
-    if (!it.line_bk.empty() || !it.grp_b.empty()) c.ks.ext = true;
-    for (int b : it.br)
-      if (b >= 0 && (nets[it.scen].kind[b] == EMT_DIODE || nets[it.scen].kind[b] == EMT_CSWITCH)) c.ks.ext = true;
-  }
   c.ks.dmax = tail_max(bs);
   // Pad every item's branch list to whole lane slots with inert branches, so
   // the step kernels need no per-slot bounds (each runs exactly bs * bpt
@@ -834,8 +828,18 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     closed[q] = 1;
     if (best_d != d) plans[q] = plan_sweeps(A.syms[q], best_d);
   }
-  for (const Item &it : A.items)
-    if (!c.is_split[&it - &A.items[0]] && !closed[it.sym]) c.ks.ext = true;
+  // the forward kernel's kind
+  bool any_line = false, any_group = false, any_full = false;
+  for (const Item &it : A.items) {
+    if (c.is_split[&it - &A.items[0]]) continue;
+    any_line = any_line || !it.line_bk.empty();
+    any_group = any_group || !it.grp_b.empty();
+    any_full = any_full || !closed[it.sym];
+  }
+  c.ks.kind = any_full || (any_line && any_group) ? STEP_FULL
+              : any_line                          ? STEP_LINES
+              : any_group                         ? STEP_GROUPS
+                                                  : STEP_PLAIN;
   std::vector<ClosedPlan> cplans(A.syms.size());
   auto plan_closed_of = [&](size_t q) {
     if (closed[q]) cplans[q] = plan_closed(A.syms[q], gpos[q], plans[q].d, bs);
@@ -883,6 +887,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     }
   };
   plan_gathers();
+  int sv_cap = INT32_MAX / 512 * 256;
   auto step_shape = [&](int q, bool adj) {
     const Item &it = A.items[q];
     const SweepPlan &P = plans[it.sym];
@@ -897,7 +902,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     z.closed = closed[it.sym];
     z.nfpass = P.nfpass();
     z.nbpass = P.nbpass();
-    z.nsv = closed[it.sym] ? 256 * (C.fwd.quads + C.bwd.quads) : P.nsv();
+    z.nsv = closed[it.sym] ? std::min(sv_cap, 256 * (C.fwd.quads + C.bwd.quads)) : P.nsv();
     z.nfdesc = (int)P.fdesc.size();
     z.nbdesc = (int)P.bdesc.size();
     const int g = adj ? prog_a[q] : prog_f[q];
@@ -945,6 +950,25 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global;
   };
   lds_figures();
+  if (!comp && !sim.sweep_from_global && (f_sm > (size_t)max_lds || (K > 0 && a_sm > (size_t)max_lds))) {
+    // Closed-form values that overflow the LDS: stage as many as every item
+    // of the batch has room for, the others stay in L2.
+    int64_t cap = INT32_MAX / 512 * 256;
+    for (int q = 0; q < NI; ++q) {
+      if (c.is_split[q]) continue;
+      for (bool adj : {false, true}) {
+        if (adj && K <= 0) continue;
+        StepShape z = step_shape(q, adj);
+        if (!closed[A.items[q].sym]) continue;
+        z.nsv = 0;
+        cap = std::min(cap, ((int64_t)max_lds - (int64_t)step_lds(z, true, adj).total) / 8);
+      }
+    }
+    if (cap >= 0) {
+      sv_cap = (int)(cap / 256 * 256);
+      lds_figures();
+    }
+  }
   if (!comp && (!c.sm_fwd || !c.sm_adj)) {
     // The global-memory variants exist for 4, 8 and 16 branches per lane and
     // run every one of those slots: items padded for fewer (1, 2, 6, 12)
@@ -1209,22 +1233,39 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     }
     d.n_lines = (int32_t)it.line_bk.size();
     d.lines = (int64_t)line_tab.size();
-    for (size_t l = 0; l < it.line_bk.size(); ++l) {
-      const int b = it.br[it.line_bk[l]];
-      LineDesc ld{};
-      ld.bk = it.line_bk[l];
-      ld.bm = it.line_bm[l];
-      ld.nk = it.line_nk[l];
-      ld.nm = it.line_nm[l];
-      ld.d0 = it.line_d0[l];
-      int32_t len = 1;  // ring length: a power of two holding steps n - D0 - 1 .. n
-      while (len < ld.d0 + 2) len *= 2;
-      ld.mask = len - 1;
-      ld.ring = ring_off;
-      ring_off += 2 * (int64_t)len;
-      line_tab.push_back(ld);
-      line_gf.push_back(1.0 / nets[it.scen].R[b]);
-      line_gf.push_back(it.line_f[l]);
+    // lines by their delay, so that neighbouring lanes carry lines of
+    // neighbouring delays and ring lengths
+    std::vector<size_t> by_delay(it.line_bk.size());
+    std::iota(by_delay.begin(), by_delay.end(), 0);
+    std::stable_sort(by_delay.begin(), by_delay.end(),
+                     [&](size_t x, size_t y) { return it.line_d0[x] < it.line_d0[y]; });
+    auto ring_slots = [](int d0) {  // steps n - D0 - 1 .. n
+      int32_t len = 1;
+      while (len < d0 + 2) len *= 2;
+      return len;
+    };
+    for (size_t e = 0; e < by_delay.size();) {
+      const int32_t len = ring_slots(it.line_d0[by_delay[e]]);
+      size_t e1 = e;
+      while (e1 < by_delay.size() && ring_slots(it.line_d0[by_delay[e1]]) == len) ++e1;
+      for (size_t f = e; f < e1; ++f) {
+        const size_t l = by_delay[f];
+        const int b = it.br[it.line_bk[l]];
+        LineDesc ld{};
+        ld.bk = it.line_bk[l];
+        ld.bm = it.line_bm[l];
+        ld.nk = it.line_nk[l];
+        ld.nm = it.line_nm[l];
+        ld.d0 = it.line_d0[l];
+        ld.mask = len - 1;
+        ld.stride = (int32_t)(e1 - e);
+        ld.ring = ring_off + 2 * (int64_t)(f - e);
+        line_tab.push_back(ld);
+        line_gf.push_back(1.0 / nets[it.scen].R[b]);
+        line_gf.push_back(it.line_f[l]);
+      }
+      ring_off += 2 * (int64_t)len * (int64_t)(e1 - e);
+      e = e1;
     }
     c.items[q] = d;
     coef_off += (int64_t)sc.n_topo * it.n_br;
@@ -1428,6 +1469,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.T = T;
   dc.K = K;
   dc.rec_stride = A.rec_stride;
+  dc.sv_cap = sv_cap;
   c.d_order = c.upload(order);
   c.d_pairs = c.upload(pairs);
   c.d_closed = c.upload(closed_pairs);
@@ -1509,17 +1551,15 @@ static hipError_t launch_forward(emt_ctx &c, int64_t n0, int64_t ns, double *rec
   emt::KernelShape ks = c.ks;
   ks.sm = c.sm_fwd;
   if (!ks.sm) ks.bpt = c.bpt_global;
-  switch (ks.bs) {
-    case 64:
-      return (ks.ext ? emt::launch_forward_ext_bs64 : emt::launch_forward_bs64)(c.dc, ks, c.d_order, c.n_fwd, n0, ns,
-                                                                               rec, st);
-    case 256:
-      return (ks.ext ? emt::launch_forward_ext_bs256 : emt::launch_forward_bs256)(c.dc, ks, c.d_order, c.n_fwd, n0,
-                                                                                 ns, rec, st);
-    default:
-      return (ks.ext ? emt::launch_forward_ext_bs512 : emt::launch_forward_bs512)(c.dc, ks, c.d_order, c.n_fwd, n0,
-                                                                                 ns, rec, st);
-  }
+  using Launch = hipError_t (*)(const emt::DevCtx &, const emt::KernelShape &, const int32_t *, int, int64_t, int64_t,
+                                double *, hipStream_t);
+  static const Launch table[3][4] = {
+      {emt::launch_forward<64, 0>, emt::launch_forward<64, 1>, emt::launch_forward<64, 2>, emt::launch_forward<64, 3>},
+      {emt::launch_forward<256, 0>, emt::launch_forward<256, 1>, emt::launch_forward<256, 2>,
+       emt::launch_forward<256, 3>},
+      {emt::launch_forward<512, 0>, emt::launch_forward<512, 1>, emt::launch_forward<512, 2>,
+       emt::launch_forward<512, 3>}};
+  return table[ks.bs == 64 ? 0 : (ks.bs == 256 ? 1 : 2)][ks.kind](c.dc, ks, c.d_order, c.n_fwd, n0, ns, rec, st);
 }
 
 // The split components' launch: both exchange buffers hold values whose

@@ -154,6 +154,15 @@ inline
   return o;
 }
 
+// What the components of a batch need besides the closed-form solve: a
+// forward kernel exists per kind.
+enum StepKind : int {
+  STEP_PLAIN = 0,   // nothing
+  STEP_LINES = 1,   // distributed-parameter lines
+  STEP_GROUPS = 2,  // coupled three-phase groups
+  STEP_FULL = 3,    // both, or level passes, diodes, controlled switches
+};
+
 // One coupled three-phase group: its members' local branches and terminals
 // (a grounded terminal is the item's zero node slot n) and the sign of its
 // Gamma (+1: R-L, Gamma = G; -1: C, Gamma = -G).
@@ -162,11 +171,13 @@ struct GroupDesc {
 };
 
 // One distributed-parameter line: its two local branches (k end, m end),
-// their local nodes, the integer part D0 of tau / dt and the offset of its
-// two wave rings (k end, then m end) in DevCtx::ring. Each ring holds
-// mask + 1 doubles, a power of two >= D0 + 2; step n's wave sits at n & mask.
+// their local nodes, the integer part D0 of tau / dt and its ring of waves.
+// A ring has mask + 1 slots, a power of two >= D0 + 2; the entry of step n
+// (the waves leaving the k and the m end, 16 bytes) sits in slot n & mask.
+// The rings of an item's lines of one length are interleaved: slot s of a
+// line is at ring + 2 stride s doubles in DevCtx::ring, stride lines apart.
 struct LineDesc {
-  int32_t bk, bm, nk, nm, d0, mask;
+  int32_t bk, bm, nk, nm, d0, mask, stride, pad;
   int64_t ring;
 };
 
@@ -255,6 +266,7 @@ struct DevCtx {
   int64_t T;
   int32_t K;
   int32_t rec_stride;
+  int32_t sv_cap;  // closed-form values per item staged in LDS at most (a multiple of 256)
   // distributed-parameter lines (ItemDesc::lines + q): descriptor, (1/Z,
   // fractional delay f) pairs, and the wave rings
   const LineDesc *line_tab;

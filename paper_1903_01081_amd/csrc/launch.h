@@ -20,7 +20,7 @@ struct KernelShape {
   bool sm = true;  // index arrays and factors staged in LDS
   size_t lds_fwd = 0, lds_adj = 0;
   int dmax = 0;    // largest dense tail this block size supports
-  bool ext = false;  // the batch has distributed-parameter lines, coupled groups, diodes or level passes
+  int kind = 0;    // StepKind
 };
 
 struct CompanionArgs {
@@ -29,19 +29,11 @@ struct CompanionArgs {
   int total, n_items;
 };
 
-hipError_t launch_forward_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
-                               double *, hipStream_t);
-hipError_t launch_forward_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
-                                double *, hipStream_t);
-hipError_t launch_forward_bs512(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
-                                double *, hipStream_t);
-// the same for batches with lines, coupled groups, diodes or level passes
-hipError_t launch_forward_ext_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
-                                   double *, hipStream_t);
-hipError_t launch_forward_ext_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
-                                    double *, hipStream_t);
-hipError_t launch_forward_ext_bs512(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t,
-                                    double *, hipStream_t);
+// Forward kernel of one workgroup size and StepKind (instantiated for 64, 256
+// and 512 lanes and every kind).
+template <int BS, int KIND>
+hipError_t launch_forward(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t, double *,
+                          hipStream_t);
 hipError_t launch_adjoint_bs64(const DevCtx &, const KernelShape &, const int32_t *, int, const double *,
                                hipStream_t);
 hipError_t launch_adjoint_bs256(const DevCtx &, const KernelShape &, const int32_t *, int, const double *,

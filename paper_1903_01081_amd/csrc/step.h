@@ -156,6 +156,8 @@ struct View {
   Lds<double> r, x, J, cD, sv_s, dinv_s, emf;  // x has n+1 entries, x[n] = 0; r: where the gather writes
   Lds<int32_t> flag;                           // adjoint: a word for broadcasts
   Ref<double, SM> sv, dinv;
+  int lim;           // pairs of closed-form values staged in LDS (the rest: svg)
+  const double *svg;  // the topology's closed-form values in global memory
   // items refactorised inside the loop: node CSR, and under SM the
   // factorisation's row pointers, level pointers (rows, entries), level rows
   Ref<int32_t, SM> nptr;
@@ -236,8 +238,11 @@ __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint)
   const bool dyn = it.n_diodes > 0;
   const int ne = dyn ? g_nptr[v.n] : 0;
   const RowProg gp = adjoint ? it.ga : it.gf;
+  // the closed form's values beyond what the LDS has room for stay in L2
+  const int nstage = v.closed && sd.nsv > c.sv_cap ? c.sv_cap : sd.nsv;
+  v.lim = SM ? nstage / 2 : 0;
   const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  v.closed,
-                     sd.nfpass,  sd.nbpass, sd.nsv,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
+                     sd.nfpass,  sd.nbpass, nstage,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
                      sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, BS};
   const StepLds o = step_lds(sh, SM, adjoint);
   v.cD.off = o.cD;
@@ -434,8 +439,9 @@ __device__ __forceinline__ void select_factor(const DevCtx &c, const ItemDesc &i
                                               Tail<BS, DT> &T) {
   const double *sv = c.svals + it.sv + (int64_t)t * v.nsv;
   const double *di = c.dinv + it.dfac + (int64_t)t * v.n;
+  v.svg = sv;
   if constexpr (SM) {
-    copy_to<BS>(v.sv_s.off, sv, v.nsv);
+    copy_to<BS>(v.sv_s.off, sv, v.closed ? 2 * v.lim : v.nsv);
     if (!v.closed) copy_to<BS>(v.dinv_s.off, di, v.ns);
   } else {
     v.sv.p = sv;
@@ -492,15 +498,6 @@ __device__ __forceinline__ double group_sum(double s, int lg) {
   return s;
 }
 
-// Two doubles at entry 2 i of a value array.
-template <bool SM>
-__device__ __forceinline__ double2 pair_at(const Ref<double, SM> &a, int i) {
-  if constexpr (SM)
-    return reinterpret_cast<const double2 *>(emt_lds + a.off)[i];
-  else
-    return reinterpret_cast<const double2 *>(a.p)[i];
-}
-
 // Runs a row program: per batch a lane adds up its quads' terms (quad(q,
 // codes, acc) for the codes of quad q), the lanes of a row meet in the DPP
 // scan, and the row's last lane hands the sum to out(row, sum). The rows of
@@ -513,17 +510,20 @@ __device__ __forceinline__ double2 pair_at(const Ref<double, SM> &a, int i) {
 // 100-node ones.)
 template <bool SM, class F, class O>
 __device__ __forceinline__ void run_rows(const Rows<SM> &p, F &&quad, O &&out) {
+  if (p.b0 >= p.b1) return;
   const int lane = (int)threadIdx.x & 63;
-  for (int b = p.b0; b < p.b1; ++b) {
-    const bool first = b == p.b0;
-    const uint32_t m = first ? p.m0 : (uint32_t)__builtin_amdgcn_readfirstlane(p.word[b]);
-    const int q0 = (int)(m & 0xFFFF), nq = (int)((m >> 16) & 0xFF), lg = (int)(m >> 24);
-    const int row = first ? p.r0 : (int)p.row[b * 64 + lane];
+  auto batch = [&](uint32_t m, uint64_t c, int row) {
+    const int q0 = (int)(m & 0xFFFF), q1 = q0 + (int)((m >> 16) & 0xFF), lg = (int)(m >> 24);
     double acc = 0.0;
-    quad(q0, first ? p.c0 : p.code[q0 * 64 + lane], acc);
-    for (int q = q0 + 1; q < q0 + nq; ++q) quad(q, p.code[q * 64 + lane], acc);
-    acc = group_sum(acc, lg);
+    quad(q0, c, acc);
+    for (int q = q0 + 1; q < q1; ++q) quad(q, p.code[q * 64 + lane], acc);
+    if (lg > 0) acc = group_sum(acc, lg);
     if (row != 0xFFFF) out(row, acc);
+  };
+  batch(p.m0, p.c0, p.r0);
+  for (int b = p.b0 + 1; b < p.b1; ++b) {
+    const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane(p.word[b]);
+    batch(m, p.code[(int)(m & 0xFFFF) * 64 + lane], (int)p.row[b * 64 + lane]);
   }
 }
 
@@ -557,7 +557,16 @@ __device__ __forceinline__ void value_rows(const View<SM> &v, const Rows<SM> &p,
       p,
       [&](int q, uint64_t c, double &acc) {
         const int i = (val0 >> 1) + q * 128 + lane;
-        const double2 a0 = pair_at<SM>(v.sv, i), a1 = pair_at<SM>(v.sv, i + 64);
+        double2 a0, a1;
+        if (SM && (val0 >> 1) + q * 128 < v.lim) {
+          const double2 *a = reinterpret_cast<const double2 *>(emt_lds + v.sv_s.off);
+          a0 = a[i];
+          a1 = a[i + 64];
+        } else {
+          const double2 *a = reinterpret_cast<const double2 *>(v.svg);
+          a0 = a[i];
+          a1 = a[i + 64];
+        }
         const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
         const double x0 = *reinterpret_cast<const double *>(xr + ((lo & 0xFFFF) << 3));
         const double x1 = *reinterpret_cast<const double *>(xr + ((lo >> 16) << 3));
@@ -794,6 +803,39 @@ __device__ __forceinline__ void inject(const DevCtx &c, const View<SM> &v, Lane<
   v.J[tid] = L.g[0] * L.e0 - L.h0;
 }
 
+// Branch phase of a step after which no coefficients change and which is
+// not the launch's last: the same arithmetic as update_inject below without
+// its cases (each a branch that every step would take). STORE: (i, u) of
+// every slot go to st_i, st_u.
+template <int BS, int BPT, bool SM, bool STORE, bool PASS = false>
+__device__ __forceinline__ void update_plain(const View<SM> &v, Lane<BPT> &L, double *st_i, double *st_u) {
+  const int tid = lane_id();
+  const double e_next = slot0_emf<BPT, SM>(v, L, tid);
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) {
+    const int b = tid + j * BS;
+    const uint32_t pk = L.pk[j];
+    const double vk = v.x[pk & kTermGround], vm = v.x[(pk >> 15) & kTermGround];
+    const bool pass = PASS && (pk >> 30) == GAMMA_PASS;
+    const double h = (j == 0 && !pass) ? L.h0 : -v.J[b];
+    const double u = j == 0 ? (vk - vm) - L.e0 : vk - vm;
+    const double gu = L.g[j] * u;
+    const double i = gu + h;
+    if constexpr (STORE) {
+      st_i[b] = i;
+      st_u[b] = L.g[j] == 0.0 ? 0.0 : u;
+    }
+    const double hn = L.be[j] * i + gamma_times(pk, gu);
+    if (j == 0) {
+      L.h0 = hn;
+      if (!pass) v.J[b] = L.g[j] * e_next - hn;
+    } else if (!pass) {
+      v.J[b] = -hn;
+    }
+  }
+  L.e0 = e_next;
+}
+
 // Branch phase after the solve of step n: u, i of step n with the current
 // coefficients; optional stores of (i, u) to up to two places (null = none);
 // if step n+1 starts a new topology its coefficients are loaded; the history
@@ -851,35 +893,141 @@ __device__ __forceinline__ void update_inject(const DevCtx &c, const View<SM> &v
 // equivalent to ground (1/Z) whose history current is the wave that left the
 // other end tau = (D0 + f) dt earlier: h_k(n) = -[(1 - f) w_m(n - D0) +
 // f w_m(n - D0 - 1)], w = g v + i, i = g v + h, w = 0 up to step 0 (the line
-// starts at rest). With advance set, the waves of step n are formed from the
-// solution (v.x) and the ends' injections J = -h of step n, stored, and the
-// injections of step n + 1 written; otherwise only those of step n.
-template <int BS, bool SM>
-__device__ __forceinline__ void line_pass(const DevCtx &c, const ItemDesc &it, const View<SM> &v, int64_t n,
-                                          bool advance, double *st_i, double *st_u) {
-  for (int q = lane_id(); q < it.n_lines; q += BS) {
-    const LineDesc ld = c.line_tab[it.lines + q];
-    const double g = c.line_gf[2 * (it.lines + q)], f = c.line_gf[2 * (it.lines + q) + 1];
-    double *rk = c.ring + ld.ring, *rm = rk + (ld.mask + 1);
-    int64_t m = n;
-    if (advance) {
-      const double vk = v.x[ld.nk], vm = v.x[ld.nm];
-      const double ik = g * vk - v.J[ld.bk], im = g * vm - v.J[ld.bm];
-      rk[n & ld.mask] = g * vk + ik;
-      rm[n & ld.mask] = g * vm + im;
-      if (st_i) {  // each end's current into the line and its voltage
-        st_i[ld.bk] = ik;
-        st_u[ld.bk] = vk;
-        st_i[ld.bm] = im;
-        st_u[ld.bm] = vm;
-      }
-      m = n + 1;
-    }
-    const int64_t j0 = m - ld.d0, j1 = j0 - 1;
-    const double k0 = j0 > 0 ? rk[j0 & ld.mask] : 0.0, k1 = j1 > 0 ? rk[j1 & ld.mask] : 0.0;
-    const double m0 = j0 > 0 ? rm[j0 & ld.mask] : 0.0, m1 = j1 > 0 ? rm[j1 & ld.mask] : 0.0;
-    v.J[ld.bk] = (1.0 - f) * m0 + f * m1;
-    v.J[ld.bm] = (1.0 - f) * k0 + f * k1;
+// starts at rest).
+// The two ends' waves of a step are one 16-byte entry of the line's ring;
+// the rings of all lines of one length are interleaved by step (device.h,
+// LineDesc), so that neighbouring lanes, whose lines have neighbouring
+// delays, read and write neighbouring entries. A lane keeps its first
+// kLineRegs lines' descriptors in registers, carries the entry of step
+// n - D0 over to the next step, where it is the one of n - D0 - 1, and reads
+// the entry of n + 1 - D0 ahead of the solve (of D0 = 1 lines it is the one
+// just formed). With a ring per end, descriptors read every step and four
+// ring reads after the branch update, this pass was two dependent trips to
+// L2 and 64 memory requests per wave and access: 3 of the 7.7 us of a step
+// with 1350 lines.
+constexpr int kLineRegs = 3, kGroupRegs = 2;
+
+struct LineLane {
+  uint32_t br, nd;  // local branches and nodes, k end | m end << 16
+  int d0, mask, stride;
+  double g, f;
+  double2 *ring;  // the line's entry of slot 0
+  double2 prev, ahead;
+};
+
+__device__ __forceinline__ double2 *ring_at(const LineLane &l, int64_t n) {
+  return l.ring + (int64_t)((int)n & l.mask) * l.stride;
+}
+__device__ __forceinline__ double2 ring_read(const LineLane &l, int64_t n) {
+  return n > 0 ? *ring_at(l, n) : make_double2(0.0, 0.0);
+}
+
+__device__ __forceinline__ void line_load(const DevCtx &c, const ItemDesc &it, int q, LineLane &l) {
+  const LineDesc d = c.line_tab[it.lines + q];
+  l.br = (uint32_t)d.bk | ((uint32_t)d.bm << 16);
+  l.nd = (uint32_t)d.nk | ((uint32_t)d.nm << 16);
+  l.d0 = d.d0;
+  l.mask = d.mask;
+  l.stride = d.stride;
+  l.g = c.line_gf[2 * (it.lines + q)];
+  l.f = c.line_gf[2 * (it.lines + q) + 1];
+  l.ring = reinterpret_cast<double2 *>(c.ring + d.ring);
+}
+
+// The ends' injections of a step from the entries of n - D0 (now) and
+// n - D0 - 1 (before).
+template <bool SM>
+__device__ __forceinline__ void line_inject(const View<SM> &v, const LineLane &l, double2 now, double2 before) {
+  v.J[(int)(l.br & 0xFFFF)] = (1.0 - l.f) * now.y + l.f * before.y;
+  v.J[(int)(l.br >> 16)] = (1.0 - l.f) * now.x + l.f * before.x;
+}
+
+// A line's injections of step n at the start of a launch.
+template <bool SM>
+__device__ __forceinline__ void line_start(const View<SM> &v, LineLane &l, int64_t n) {
+  const double2 now = ring_read(l, n - l.d0);
+  line_inject<SM>(v, l, now, ring_read(l, n - l.d0 - 1));
+  l.prev = now;
+}
+
+// A line after the solve of step n: the waves of step n stored, the ends'
+// state of step n (when st_i is set), the injections of step n + 1.
+template <bool SM>
+__device__ __forceinline__ void line_step(const View<SM> &v, LineLane &l, int64_t n, double *st_i, double *st_u) {
+  const double vk = v.x[(int)(l.nd & 0xFFFF)], vm = v.x[(int)(l.nd >> 16)];
+  const double ik = l.g * vk - v.J[(int)(l.br & 0xFFFF)], im = l.g * vm - v.J[(int)(l.br >> 16)];
+  const double2 w = make_double2(l.g * vk + ik, l.g * vm + im);
+  *ring_at(l, n) = w;
+  if (st_i) {  // each end's current into the line and its voltage
+    st_i[(int)(l.br & 0xFFFF)] = ik;
+    st_u[(int)(l.br & 0xFFFF)] = vk;
+    st_i[(int)(l.br >> 16)] = im;
+    st_u[(int)(l.br >> 16)] = vm;
+  }
+  const double2 now = l.d0 == 1 ? w : l.ahead;
+  line_inject<SM>(v, l, now, l.prev);
+  l.prev = now;
+}
+
+// A lane's lines: the first NL in registers, any more through memory.
+template <int NL>
+struct Lines {
+  LineLane l[NL > 0 ? NL : 1];
+};
+
+template <int BS, int NL, bool SM>
+__device__ __forceinline__ void lines_start(const DevCtx &c, const ItemDesc &it, const View<SM> &v, Lines<NL> &R,
+                                            int64_t n) {
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    const int q = (int)threadIdx.x + k * BS;
+    if (q >= it.n_lines) break;
+    line_load(c, it, q, R.l[k]);
+    line_start<SM>(v, R.l[k], n);
+  }
+  for (int q = (int)threadIdx.x + NL * BS; q < it.n_lines; q += BS) {
+    LineLane l;
+    line_load(c, it, q, l);
+    line_start<SM>(v, l, n);
+  }
+}
+
+// Reads ahead of the solve of step n.
+template <int BS, int NL>
+__device__ __forceinline__ void lines_ahead(const ItemDesc &it, Lines<NL> &R, int64_t n) {
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    if ((int)threadIdx.x + k * BS >= it.n_lines) break;
+    R.l[k].ahead = R.l[k].d0 > 1 ? ring_read(R.l[k], n + 1 - R.l[k].d0) : make_double2(0.0, 0.0);
+  }
+}
+
+// Waits for these reads (before the step's own stores are queued behind
+// them).
+template <int BS, int NL>
+__device__ __forceinline__ void lines_settle(const ItemDesc &it, Lines<NL> &R) {
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    if (k * BS >= it.n_lines) break;
+    settle(R.l[k].ahead.x);
+    settle(R.l[k].ahead.y);
+  }
+}
+
+template <int BS, int NL, bool SM>
+__device__ __forceinline__ void lines_step(const DevCtx &c, const ItemDesc &it, const View<SM> &v, Lines<NL> &R,
+                                           int64_t n, double *st_i, double *st_u) {
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    if ((int)threadIdx.x + k * BS >= it.n_lines) break;
+    line_step<SM>(v, R.l[k], n, st_i, st_u);
+  }
+  for (int q = (int)threadIdx.x + NL * BS; q < it.n_lines; q += BS) {
+    LineLane l;
+    line_load(c, it, q, l);
+    l.prev = ring_read(l, n - l.d0);
+    l.ahead = l.d0 > 1 ? ring_read(l, n + 1 - l.d0) : make_double2(0.0, 0.0);
+    line_step<SM>(v, l, n, st_i, st_u);
   }
 }
 
@@ -893,44 +1041,96 @@ __device__ __forceinline__ void line_pass(const DevCtx &c, const ItemDesc &it, c
 // pass, which reads h_p = -J and writes J = -h'_p (when inj) and the state
 // (when st_i is set). With init, (i, u) are the stored state instead (the
 // start of a launch) and only the injections are written. The members take
-// no events, so the coefficients of topology 0 hold in every topology.
-template <int BS, bool SM>
-__device__ __forceinline__ void group_pass(const DevCtx &c, const ItemDesc &it, const View<SM> &v, bool init,
-                                           bool inj, double *st_i, double *st_u) {
-  for (int q = lane_id(); q < it.n_groups; q += BS) {
-    const GroupDesc gd = c.group_tab[it.groups + q];
-    const int64_t k0 = it.coef + gd.b[0];
-    const double g = c.cg[k0], go = c.cgo[k0], be = c.cb[k0], bo = c.cbo[k0];
-    const double sg = (double)gd.sgn;
-    double u[3], i[3];
-    if (init) {
+// no events, so the coefficients of topology 0 hold in every topology. A
+// lane's first kGroupRegs groups' descriptors and coefficients stay in
+// registers.
+struct GroupLane {
+  uint32_t b01, b2, t[3];  // members' branches (b2's bit 16: a C group); terminals k | m << 16
+  double g, go, be, bo;
+  __device__ __forceinline__ int b(int p) const {
+    return (int)(p == 0 ? b01 & 0xFFFF : (p == 1 ? b01 >> 16 : b2 & 0xFFFF));
+  }
+};
+
+__device__ __forceinline__ void group_load(const DevCtx &c, const ItemDesc &it, int q, GroupLane &l) {
+  const GroupDesc d = c.group_tab[it.groups + q];
+  l.b01 = (uint32_t)d.b[0] | ((uint32_t)d.b[1] << 16);
+  l.b2 = (uint32_t)d.b[2] | (d.sgn < 0 ? 0x10000u : 0u);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) l.t[p] = (uint32_t)d.k[p] | ((uint32_t)d.m[p] << 16);
+  const int64_t k0 = it.coef + d.b[0];
+  l.g = c.cg[k0];
+  l.go = c.cgo[k0];
+  l.be = c.cb[k0];
+  l.bo = c.cbo[k0];
+}
+
+template <bool SM>
+__device__ __forceinline__ void group_step(const DevCtx &c, const ItemDesc &it, const View<SM> &v,
+                                           const GroupLane &l, bool init, bool inj, double *st_i, double *st_u) {
+  const double sg = (l.b2 >> 16) ? -1.0 : 1.0;
+  double u[3], i[3];
+  if (init) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      u[p] = c.su[it.br + l.b(p)];
+      i[p] = c.si[it.br + l.b(p)];
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) u[p] = v.x[(int)(l.t[p] & 0xFFFF)] - v.x[(int)(l.t[p] >> 16)];
+    const double su = u[0] + u[1] + u[2];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) i[p] = (l.g * u[p] - v.J[l.b(p)]) + l.go * (su - u[p]);
+    if (st_i) {
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        u[p] = c.su[it.br + gd.b[p]];
-        i[p] = c.si[it.br + gd.b[p]];
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < 3; ++p) u[p] = v.x[gd.k[p]] - v.x[gd.m[p]];
-      const double su = u[0] + u[1] + u[2];
-#pragma unroll
-      for (int p = 0; p < 3; ++p) i[p] = (g * u[p] - v.J[gd.b[p]]) + go * (su - u[p]);
-      if (st_i) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          st_i[gd.b[p]] = i[p];
-          st_u[gd.b[p]] = u[p];
-        }
+        st_i[l.b(p)] = i[p];
+        st_u[l.b(p)] = u[p];
       }
     }
-    if (init || inj) {
-      const double su = u[0] + u[1] + u[2], si = i[0] + i[1] + i[2];
+  }
+  if (init || inj) {
+    const double su = u[0] + u[1] + u[2], si = i[0] + i[1] + i[2];
 #pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        const double h = (be * i[p] + sg * g * u[p]) + (bo * (si - i[p]) + sg * go * (su - u[p]));
-        v.J[gd.b[p]] = -h;
-      }
+    for (int p = 0; p < 3; ++p) {
+      const double h = (l.be * i[p] + sg * l.g * u[p]) + (l.bo * (si - i[p]) + sg * l.go * (su - u[p]));
+      v.J[l.b(p)] = -h;
     }
+  }
+}
+
+template <int NG>
+struct Groups {
+  GroupLane l[NG > 0 ? NG : 1];
+};
+
+template <int BS, int NG>
+__device__ __forceinline__ void groups_load(const DevCtx &c, const ItemDesc &it, Groups<NG> &R) {
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
+    const int q = (int)threadIdx.x + k * BS;
+    if (q >= it.n_groups) break;
+    group_load(c, it, q, R.l[k]);
+    settle(R.l[k].g);
+    settle(R.l[k].go);
+    settle(R.l[k].be);
+    settle(R.l[k].bo);
+  }
+}
+
+template <int BS, int NG, bool SM>
+__device__ __forceinline__ void groups_step(const DevCtx &c, const ItemDesc &it, const View<SM> &v, const Groups<NG> &R,
+                                            bool init, bool inj, double *st_i, double *st_u) {
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
+    if ((int)threadIdx.x + k * BS >= it.n_groups) break;
+    group_step<SM>(c, it, v, R.l[k], init, inj, st_i, st_u);
+  }
+  for (int q = (int)threadIdx.x + NG * BS; q < it.n_groups; q += BS) {
+    GroupLane l;
+    group_load(c, it, q, l);
+    group_step<SM>(c, it, v, l, init, inj, st_i, st_u);
   }
 }
 
@@ -1213,14 +1413,13 @@ __device__ void refactor_dynamic(const DevCtx &c, const ItemDesc &it, View<SM> &
 // ---------------------------------------------------------------------------
 // Forward loop: steps n0+1 .. n0+nsteps for every item.
 // ---------------------------------------------------------------------------
-// EXT: the batch has distributed-parameter lines, coupled groups, diodes or
-// components solved by level passes (the variant without them carries none
-// of their code or registers).
-template <int BS, int BPT, int DT, bool SM, bool EXT>
+// KIND (device.h, StepKind): what the batch's components need besides the
+// closed-form solve; a variant carries only its own code and registers.
+template <int BS, int BPT, int DT, bool SM, int KIND>
 __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, int64_t n0, int64_t nsteps,
                                                 double *rec) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, EXT>(c, it, false);
+  View<SM> v = make_view<BS, SM, KIND == STEP_FULL>(c, it, false);
   const int64_t *topo = c.topo + it.topo;
   int t = topo_of(topo, it.n_topo, n0 + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
@@ -1228,7 +1427,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   Tail<BS, DT> w;
   load_lane<BS, BPT>(c, it, L);
   load_coefs<BS, BPT>(c, it, t, L.g, L.be);
-  const bool diodes = EXT && it.n_diodes > 0;  // diodes or controlled switches
+  const bool diodes = KIND == STEP_FULL && it.n_diodes > 0;  // diodes or controlled switches
   uint32_t dmask = 0, cmask = 0;
   if (diodes) {
 #pragma unroll
@@ -1250,10 +1449,17 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   }
   inject<BS, BPT, SM>(c, v, L, n0 + 1);
   step_barrier<BS>();
-  const bool lines = EXT && it.n_lines > 0, groups = EXT && it.n_groups > 0;
+  const bool lines = (KIND == STEP_LINES || KIND == STEP_FULL) && it.n_lines > 0;
+  const bool groups = (KIND == STEP_GROUPS || KIND == STEP_FULL) && it.n_groups > 0;
+  constexpr int NL = KIND == STEP_LINES ? kLineRegs : 0, NG = KIND == STEP_GROUPS ? kGroupRegs : 0;
+  Lines<NL> ln;
+  Groups<NG> gr;
   if (lines || groups) {
-    if (lines) line_pass<BS, SM>(c, it, v, n0 + 1, false, nullptr, nullptr);
-    if (groups) group_pass<BS, SM>(c, it, v, true, true, nullptr, nullptr);
+    if (lines) lines_start<BS, NL, SM>(c, it, v, ln, n0 + 1);
+    if (groups) {
+      groups_load<BS, NG>(c, it, gr);
+      groups_step<BS, NG, SM>(c, it, v, gr, true, true, nullptr, nullptr);
+    }
     step_barrier<BS>();
   }
   const int R = c.rec_stride;
@@ -1264,34 +1470,64 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   const int rn0 = rec0 ? v.rnode[tid0] : 0;
   double *row = rec ? rec + (int64_t)it.scen * nsteps * R : nullptr;
   double *at0 = rec0 ? row + v.rcolumn[tid0] : nullptr;
-  // steps to the next checkpoint (a 64-bit remainder each step costs more
-  // than the whole branch update)
-  int64_t to_ck = c.K > 0 ? c.K - n0 % c.K : kNever;
-  int64_t ck_at = c.K > 0 ? it.ck + (n0 / c.K + 1) * (int64_t)v.nbr : 0;
+  // steps with more to do than the plain ones: the next checkpoint (a
+  // running step number: a 64-bit remainder each step costs more than the
+  // whole branch update), the step before a topology change, the last one
+  int64_t ck_step = c.K > 0 ? (n0 / c.K + 1) * c.K : kNever;
+  auto special_step = [&]() {
+    const int64_t m = next == kNever || next - 1 > n_end ? n_end : next - 1;
+    return ck_step < m ? ck_step : m;
+  };
+  int64_t special = special_step();
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
+    if (lines) lines_ahead<BS, NL>(it, ln, n);
     gather_all<BS, SM>(v);
-    solve_after_gather<BS, DT, SM, EXT>(v, w);
+    solve_after_gather<BS, DT, SM, KIND == STEP_FULL>(v, w);
+    if (lines) lines_settle<BS, NL>(it, ln);
     // read here, stored after the update so that its own reads go ahead
     const double rv0 = rec0 ? v.x[rn0] : 0.0;
     if (v.nrec > BS && rec) {
       for (int q = tid0 + BS; q < v.nrec; q += BS) row[v.rcolumn[q]] = v.x[v.rnode[q]];
       row += R;
     }
+    if (KIND == STEP_PLAIN && n != special) {
+      update_plain<BS, BPT, SM, false>(v, L, nullptr, nullptr);
+      if (rec0) {
+        *at0 = rv0;
+        at0 += R;
+      }
+      step_barrier<BS>();
+      continue;
+    }
+    if (KIND != STEP_PLAIN && n != special && !diodes) {
+      update_plain<BS, BPT, SM, false, true>(v, L, nullptr, nullptr);
+      if (lines || groups) {
+        step_barrier<BS>();
+        if (lines) lines_step<BS, NL, SM>(c, it, v, ln, n, nullptr, nullptr);
+        if (groups) groups_step<BS, NG, SM>(c, it, v, gr, false, true, nullptr, nullptr);
+      }
+      if (rec0) {
+        *at0 = rv0;
+        at0 += R;
+      }
+      step_barrier<BS>();
+      continue;
+    }
     const bool sw = (n + 1 == next);
     const uint32_t fl = diodes ? diode_flips<BS, BPT, SM>(c, it, v, L, dmask, cmask, n) : 0u;
     double *ck_i = nullptr, *ck_u = nullptr, *st_i = nullptr, *st_u = nullptr;
-    if (--to_ck == 0) {
-      ck_i = c.ck_i + ck_at;
-      ck_u = c.ck_u + ck_at;
-      to_ck = c.K;
-      ck_at += v.nbr;
+    if (n == ck_step) {
+      const int64_t o = it.ck + (n / c.K) * (int64_t)v.nbr;
+      ck_i = c.ck_i + o;
+      ck_u = c.ck_u + o;
+      ck_step += c.K;
     }
     if (n == n_end) {
       st_i = c.si + it.br;
       st_u = c.su + it.br;
     }
-    update_inject<BS, BPT, SM, EXT>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
+    update_inject<BS, BPT, SM, KIND != STEP_PLAIN>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
                                n < n_end, n);
     if (rec0) {
       *at0 = rv0;
@@ -1299,8 +1535,8 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     }
     if (lines || groups) {
       step_barrier<BS>();
-      if (lines) line_pass<BS, SM>(c, it, v, n, true, st_i, st_u);
-      if (groups) group_pass<BS, SM>(c, it, v, false, n < n_end, st_i, st_u);
+      if (lines) lines_step<BS, NL, SM>(c, it, v, ln, n, st_i, st_u);
+      if (groups) groups_step<BS, NG, SM>(c, it, v, gr, false, n < n_end, st_i, st_u);
     }
     if (diodes) {
       // a diode changed state or the topology switched: the conductances
@@ -1315,6 +1551,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
       if (!diodes) select_factor<BS, DT, SM>(c, it, v, t, w);
     }
+    special = special_step();
     step_barrier<BS>();
   }
   for (int q = threadIdx.x; q < v.n; q += BS) c.sv_state[it.node + q] = v.x[q];
@@ -1405,6 +1642,11 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
     gather_all<BS, SM>(v);
     solve_after_gather<BS, DT, SM, true>(v, w);
     const int64_t o = (n - lo) * (int64_t)nbr;
+    if (n < hi && n + 1 != next) {
+      update_plain<BS, BPT, SM, true>(v, L, seg_i + o, seg_u + o);
+      step_barrier<BS>();
+      continue;
+    }
     const bool sw = (n + 1 == next) && n < hi;
     update_inject<BS, BPT, SM>(c, v, L, seg_i + o, seg_u + o, nullptr, nullptr, sw,
                                it.coef + (int64_t)(t + 1) * nbr, n < hi, n);
@@ -1434,6 +1676,14 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
   // the coefficients of step hi+1 are those of topology t_nx (unused at
   // hi = T, where hbar = 0)
   int t_nx = hi < T ? topo_of(topo, it.n_topo, hi + 1) : t;
+  // the first step of topology t (every topology starts at a step of its
+  // own); read from memory only when it changes
+  auto first_step = [&](int tt) {
+    int64_t f = tt > 0 ? topo[tt] : 0;
+    asm volatile("" : "+v"(f));
+    return f;
+  };
+  int64_t first = first_step(t);
   adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, load_seed<SM>(c, it, v, dJ, hi), dJ, hi);
   step_barrier<BS>();
   // the state of step n in the lane's slots, carried from one step (where it
@@ -1469,9 +1719,9 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
     // step n's coefficients become the next-step ones of step n-1
     t_nx = t;
     if (n - 1 >= lo + 1) {
-      const int tp = topo_of(topo, it.n_topo, n - 1);
-      if (tp != t) {
-        t = tp;
+      if (n - 1 < first) {
+        --t;
+        first = first_step(t);
         load_coefs<BS, BPT>(c, it, t, L.g, L.be);
         select_factor<BS, DT, SM>(c, it, v, t, w);
       }

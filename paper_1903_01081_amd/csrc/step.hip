@@ -1,6 +1,6 @@
 // Instantiations of the step kernels for one workgroup size (EMT_BS, set by
-// the build: 64, 256 or 512) and one kind of kernel (EMT_PART_*: FWD, EXT =
-// the forward kernel with lines, groups, diodes; ADJ; PIPE), so that they
+// the build: 64, 256 or 512) and one kind of kernel (EMT_PART_*: FWD with
+// EMT_KIND, a StepKind; ADJ; PIPE), so that they
 // compile in parallel.
 #include <hip/hip_runtime.h>
 
@@ -15,11 +15,11 @@ namespace emt {
 
 namespace {
 
-#if defined(EMT_PART_FWD) || defined(EMT_PART_EXT)
-template <int BPT, int DT, bool SM, bool EXT>
+#if defined(EMT_PART_FWD)
+template <int BPT, int DT, bool SM>
 hipError_t fwd(const DevCtx &c, const int32_t *order, int n_items, int64_t n0, int64_t ns, double *rec,
                size_t lds, hipStream_t st) {
-  auto k = step::k_forward<EMT_BS, BPT, DT, SM, EXT>;
+  auto k = step::k_forward<EMT_BS, BPT, DT, SM, EMT_KIND>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -86,23 +86,12 @@ hipError_t adj_pipe_occupancy(size_t lds, int *blocks) {
 #endif
 
 #ifdef EMT_PART_FWD
-hipError_t EMT_CAT(launch_forward_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order, int n_items,
-                               int64_t n0, int64_t ns, double *rec, hipStream_t st) {
+template <>
+hipError_t launch_forward<EMT_BS, EMT_KIND>(const DevCtx &c, const KernelShape &ks, const int32_t *order, int n_items,
+                                            int64_t n0, int64_t ns, double *rec, hipStream_t st) {
 #define EMT_CASE(BPT, DT, SM)                      \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) \
-    return fwd<BPT, DT, SM, false>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st);
-  EMT_SHAPES(EMT_CASE)
-#undef EMT_CASE
-  return hipErrorInvalidValue;
-}
-#endif
-
-#ifdef EMT_PART_EXT
-hipError_t EMT_CAT(launch_forward_ext_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order, int n_items,
-                               int64_t n0, int64_t ns, double *rec, hipStream_t st) {
-#define EMT_CASE(BPT, DT, SM)                      \
-  if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) \
-    return fwd<BPT, DT, SM, true>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st);
+    return fwd<BPT, DT, SM>(c, order, n_items, n0, ns, rec, ks.lds_fwd, st);
   EMT_SHAPES(EMT_CASE)
 #undef EMT_CASE
   return hipErrorInvalidValue;
