@@ -145,6 +145,14 @@ int tail_max(int bs) { return bs >= 512 ? 128 : (bs >= 256 ? 64 : 32); }
 // Largest dense tail of the closed form: the kernels' largest capacities.
 int closed_tail_max(int bs) { return bs >= 512 ? 192 : (bs >= 256 ? 128 : 64); }
 
+// The launcher for a block size and an adjoint's GEN.
+template <class F>
+F by_size(int bs, bool gen, F f64, F g64, F f256, F g256, F f512, F g512) {
+  if (bs == 64) return gen ? g64 : f64;
+  if (bs == 256) return gen ? g256 : f256;
+  return gen ? g512 : f512;
+}
+
 // Capacity (KernelShape::dt) that holds a tail of d nodes; 0 = none.
 int tail_capacity(int bs, int d) {
   for (int cap : {32, 64, 128, 192})
@@ -653,7 +661,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   const int K = sim.checkpoint_every;
   const int64_t T = sim.n_steps;
   const int64_t n_ck = K > 0 ? T / K + 1 : 0;
-  const int64_t seg_rows = K > 0 ? std::min<int64_t>(K, T) + 1 : 0;
+  const int64_t seg_rows = K > 0 ? std::min<int64_t>(K, T) : 0;
   const int NI = (int)A.items.size();
 
   // Limits of the packed (15/16-bit) index formats.
@@ -950,9 +958,16 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global;
   };
   lds_figures();
-  if (!comp && !sim.sweep_from_global && (f_sm > (size_t)max_lds || (K > 0 && a_sm > (size_t)max_lds))) {
-    // Closed-form values that overflow the LDS: stage as many as every item
-    // of the batch has room for, the others stay in L2.
+  // LDS a workgroup may take: all of a compute unit's, or half where the
+  // batch has more items than the device has compute units (two workgroups
+  // share one then; a 502-item batch at 107 KB each ran in two rounds).
+  int n_cu_lds = 0, n_one = 0;
+  hip_check(hipDeviceGetAttribute(&n_cu_lds, hipDeviceAttributeMultiprocessorCount, c.device), "CU count");
+  for (int q = 0; q < NI; ++q) n_one += c.is_split[q] ? 0 : 1;
+  const size_t lds_share = n_one > n_cu_lds ? max_lds / 2 : max_lds;
+  if (!comp && !sim.sweep_from_global && (f_sm > lds_share || (K > 0 && a_sm > lds_share))) {
+    // Closed-form values that overflow it: stage as many as every item of the
+    // batch has room for, the others stay in L2.
     int64_t cap = INT32_MAX / 512 * 256;
     for (int q = 0; q < NI; ++q) {
       if (c.is_split[q]) continue;
@@ -961,7 +976,8 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
         StepShape z = step_shape(q, adj);
         if (!closed[A.items[q].sym]) continue;
         z.nsv = 0;
-        cap = std::min(cap, ((int64_t)max_lds - (int64_t)step_lds(z, true, adj).total) / 8);
+        const int64_t rest = (int64_t)step_lds(z, true, adj).total;
+        cap = std::min(cap, ((int64_t)(rest > (int64_t)lds_share ? max_lds : lds_share) - rest) / 8);
       }
     }
     if (cap >= 0) {
@@ -996,6 +1012,17 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   c.ks.lds_adj = c.sm_adj ? a_sm : a_gl;
   if (f_gl > (size_t)max_lds) throw Error{EMT_EINVAL, "a connected component needs more LDS than a workgroup has"};
   c.ks_adj_ok = a_gl <= (size_t)max_lds;
+  // Trajectory rows (checkpoints): all T steps where they fit a sixteenth of
+  // the device's memory, else one segment's (two for the pipelined adjoint).
+  bool vt_full = false;
+  if (K > 0) {
+    double per_step = 0.0;
+    for (const Item &it : A.items) per_step += 8.0 * (it.n + it.n_src);
+    size_t free_b = 0, total_b = 0;
+    hip_check(hipMemGetInfo(&free_b, &total_b), "memory size");
+    vt_full = per_step * (double)T <= std::min((double)total_b / 16.0, (double)free_b / 2.0);
+  }
+  c.ks.gen = !vt_full || any_full;
   // Pipelined adjoint where both workgroups of every item fit on the device
   // at once (cooperative launch) and it was not turned off.
   c.adj_pipe = false;
@@ -1005,9 +1032,9 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     if (!ks.sm) ks.bpt = c.bpt_global;
     int per_cu = 0, n_cu = 0, n_fwd = 0;
     for (int q = 0; q < NI; ++q) n_fwd += c.is_split[q] ? 0 : 1;
-    hipError_t e = bs == 64 ? adjoint_pipe_blocks_per_cu_bs64(ks, &per_cu)
-                            : (bs == 256 ? adjoint_pipe_blocks_per_cu_bs256(ks, &per_cu)
-                                         : adjoint_pipe_blocks_per_cu_bs512(ks, &per_cu));
+    hipError_t e = by_size(bs, ks.gen, adjoint_pipe_blocks_per_cu<64, false>, adjoint_pipe_blocks_per_cu<64, true>,
+                           adjoint_pipe_blocks_per_cu<256, false>, adjoint_pipe_blocks_per_cu<256, true>,
+                           adjoint_pipe_blocks_per_cu<512, false>, adjoint_pipe_blocks_per_cu<512, true>)(ks, &per_cu);
     hip_check(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c.device), "CU count");
     c.adj_pipe = e == hipSuccess && (int64_t)per_cu * n_cu >= 2 * (int64_t)n_fwd;
   }
@@ -1165,6 +1192,8 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   std::vector<uint16_t> nent, rnode, rcolumn;
   int64_t coef_off = 0, fac_off = 0, dfac_off = 0, sv_off = 0, w_off = 0, ck_off = 0, seg_off = 0, node_off = 0;
   int64_t dyn_off = 0;
+  int64_t vt_off = 0;
+  const int64_t vt_rows = K > 0 ? (vt_full ? T : (c.adj_pipe ? 2 : 1) * seg_rows) : 0;
   std::vector<GroupDesc> group_tab;
   std::vector<int32_t> mptr_all, ment_all;
   std::vector<LineDesc> line_tab;
@@ -1204,6 +1233,8 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     if (prog_a[q] >= 0) d.ga = gdesc[prog_a[q]];
     d.ck = ck_off;
     d.seg = seg_off;
+    d.n_real = it.n_br_real;
+    d.vt = vt_off;
     d.n_diodes = 0;
     for (int b : it.br)
       if (b >= 0 && (nets[it.scen].kind[b] == EMT_DIODE || nets[it.scen].kind[b] == EMT_CSWITCH)) d.n_diodes++;
@@ -1276,6 +1307,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     w_off += (int64_t)sc.n_topo * P.d * P.d;
     ck_off += n_ck * it.n_br;
     seg_off += (c.adj_pipe ? 2 : 1) * seg_rows * it.n_br;
+    vt_off += vt_rows * (int64_t)(it.n + it.n_src);
     node_off += it.n;
     for (int t = 0; t < sc.n_topo; ++t) {
       (closed[it.sym] ? closed_pairs : pairs).push_back(q);
@@ -1406,7 +1438,8 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.ck_i = K > 0 ? c.alloc<double>(ck_off) : nullptr;
   dc.ck_u = K > 0 ? c.alloc<double>(ck_off) : nullptr;
   dc.seg_i = K > 0 ? c.alloc<double>(seg_off) : nullptr;
-  dc.seg_u = K > 0 ? c.alloc<double>(seg_off) : nullptr;
+  dc.vt = K > 0 ? c.alloc<double>(vt_off) : nullptr;
+  dc.vt_full = vt_full ? 1 : 0;
   if (c.adj_pipe) c.d_pipe = c.alloc<int32_t>(2 * (size_t)NI);
   dc.line_tab = line_tab.empty() ? nullptr : c.upload(line_tab);
   dc.line_gf = line_gf.empty() ? nullptr : c.upload(line_gf);
@@ -1645,11 +1678,9 @@ static hipError_t launch_adjoint(emt_ctx &c, const double *dJ, hipStream_t st) {
   emt::KernelShape ks = c.ks;
   ks.sm = c.sm_adj;
   if (!ks.sm) ks.bpt = c.bpt_global;
-  switch (ks.bs) {
-    case 64: return emt::launch_adjoint_bs64(c.dc, ks, c.d_order, c.n_fwd, dJ, st);
-    case 256: return emt::launch_adjoint_bs256(c.dc, ks, c.d_order, c.n_fwd, dJ, st);
-    default: return emt::launch_adjoint_bs512(c.dc, ks, c.d_order, c.n_fwd, dJ, st);
-  }
+  return by_size(ks.bs, ks.gen, emt::launch_adjoint<64, false>, emt::launch_adjoint<64, true>,
+                 emt::launch_adjoint<256, false>, emt::launch_adjoint<256, true>, emt::launch_adjoint<512, false>,
+                 emt::launch_adjoint<512, true>)(c.dc, ks, c.d_order, c.n_fwd, dJ, st);
 }
 
 extern "C" {
@@ -1993,10 +2024,10 @@ emt_status emt_adjoint(emt_ctx *ctx, const double *dJ_drec_dev, double *grad_dev
       hip_check(emt::launch_fill_i32(ctx->d_pipe, 2 * (int64_t)ctx->A.items.size(), 0, st), "pipe counters");
       hip_check(emt::launch_fill_i32(ctx->dc.flags + 2, 1, 0, st), "pipe error flag");
       const int n = ctx->n_fwd;
-      hip_check(ks.bs == 64 ? emt::launch_adjoint_pipe_bs64(ctx->dc, ks, ctx->d_order, n, dJ_drec_dev, ctx->d_pipe, st)
-                : ks.bs == 256
-                    ? emt::launch_adjoint_pipe_bs256(ctx->dc, ks, ctx->d_order, n, dJ_drec_dev, ctx->d_pipe, st)
-                    : emt::launch_adjoint_pipe_bs512(ctx->dc, ks, ctx->d_order, n, dJ_drec_dev, ctx->d_pipe, st),
+      hip_check(by_size(ks.bs, ks.gen, emt::launch_adjoint_pipe<64, false>, emt::launch_adjoint_pipe<64, true>,
+                        emt::launch_adjoint_pipe<256, false>, emt::launch_adjoint_pipe<256, true>,
+                        emt::launch_adjoint_pipe<512, false>, emt::launch_adjoint_pipe<512, true>)(
+                    ctx->dc, ks, ctx->d_order, n, dJ_drec_dev, ctx->d_pipe, st),
                 "adjoint");
       ctx->adjoint_pending = true;
     } else {

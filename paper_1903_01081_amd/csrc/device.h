@@ -77,9 +77,10 @@ struct ItemDesc {
   int64_t rec;   // recorded pairs (uint16 local node, uint16 column) [n_rec]
   int64_t topo;  // scenario topology start steps [n_topo]
   int64_t ck;    // checkpoints (i, u) [n_ck][n_br]
-  int64_t seg;   // adjoint segment buffer (i, u) [K+1][n_br]
+  int64_t seg;   // adjoint segment buffer (i of each step) [K][n_br]
+  int64_t vt;    // adjoint: trajectory rows (node voltages, then the sources' EMFs) [T or K][n + n_src]
   int64_t lines; // distributed-parameter lines: first entry of line_tab / line_gf
-  int32_t n_groups, pad2;  // coupled three-phase groups
+  int32_t n_groups, n_real;  // coupled three-phase groups; branches before the padding to whole slots
   int64_t groups;  // first entry of group_tab
   int64_t mptr;    // mutual stamps by row of L [n+1] (int32), into ment
   int64_t ment;    // mutual stamps: (L position, local branch << 1 | negative) pairs (int32)
@@ -97,7 +98,7 @@ struct StepShape {
   int bs;
 };
 struct StepLds {
-  uint32_t cD, xr, J, flag, emf, pass, sv, dinv, fdesc, bdesc, fcol, brow, bpos, gmeta, gcode, grow, fmeta, fcode,
+  uint32_t cD, xr, J, flag, emf, vrow, pass, sv, dinv, fdesc, bdesc, fcol, brow, bpos, gmeta, gcode, grow, fmeta, fcode,
       frow, bmeta, bcode, brw, rnode, rcolumn, rf_rowptr, rf_flev, rf_fent, rf_rows, rf_nptr, rf_nent, total;
 };
 inline
@@ -118,6 +119,7 @@ inline
   o.J = take(s.nbr + 1 + (adjoint ? s.nrec : 0), 8);  // branch injections, a zero, the adjoint's seeds
   o.flag = take(adjoint ? 1 : 0, 4);
   o.emf = take(s.nsrc > 0 ? s.bs : 0, 8);
+  o.vrow = take(adjoint ? s.n + 1 + s.nsrc : 0, 8);  // the earlier step's trajectory row, a zero between its parts
   if (!s.closed) o.pass = take(2 * (s.nfpass + s.nbpass + 2), 4);
   if (sm) {
     o.gmeta = take(waves + 1 + s.gb, 4);
@@ -260,7 +262,12 @@ struct DevCtx {
   // numeric factors
   double *lfull, *dpiv, *dinv, *svals, *wtail;
   const int64_t *topo;
-  double *ck_i, *ck_u, *seg_i, *seg_u;
+  double *ck_i, *ck_u, *seg_i;
+  // trajectory rows: of every step, written by the forward run (vt_full), or
+  // of one checkpoint segment, written by its recomputation; null without
+  // checkpoints
+  double *vt;
+  int32_t vt_full;
   int32_t *flags;  // [0] = bad pivots
   double dt;
   int64_t T;

@@ -73,6 +73,12 @@ __device__ __forceinline__ int lane_id() {
   return t;
 }
 
+// The same for a packed branch descriptor, where registers are short.
+__device__ __forceinline__ uint32_t opaque(uint32_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // Workgroup barrier that orders LDS only. Lanes of a workgroup exchange
 // data only through LDS here; global stores (recorded outputs, checkpoints,
 // state) are read by later kernels or by the same lane, so a barrier need
@@ -147,13 +153,13 @@ struct Rows {
 // LDS (SM = true) or global memory.
 template <bool SM>
 struct View {
-  int n, d, ns, nbr, nsrc, nsv, nrec;  // nbr: padded to whole lane slots
+  int n, d, ns, nbr, nreal, nsrc, nsv, nrec;  // nbr: padded to whole lane slots; nreal: not
   int closed, nfpass, nbpass, fvals;   // fvals: values of the forward program
   Rows<SM> gather, fwd, bwd;
   Lds<int32_t> pass;  // level passes: (first descriptor, log2 lanes) pairs, forward then backward
   Ref<uint64_t, SM> fdesc, bdesc;
   Ref<uint16_t, SM> fcol, brow, bpos, rnode, rcolumn;
-  Lds<double> r, x, J, cD, sv_s, dinv_s, emf;  // x has n+1 entries, x[n] = 0; r: where the gather writes
+  Lds<double> r, x, J, cD, sv_s, dinv_s, emf, vrow;  // x has n+1 entries, x[n] = 0; r: where the gather writes
   Lds<int32_t> flag;                           // adjoint: a word for broadcasts
   Ref<double, SM> sv, dinv;
   int lim;           // pairs of closed-form values staged in LDS (the rest: svg)
@@ -220,13 +226,14 @@ __device__ __forceinline__ void load_rows(const DevCtx &c, const RowProg &p, uin
 // LEV: the batch may hold components solved by level passes (the kernels
 // without them carry none of their scalars: those of both together spill).
 template <int BS, bool SM, bool LEV>
-__device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint) {
+__device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint) {
   const SymDesc sd = c.syms[it.sym];
   View<SM> v;
   v.n = it.n;
   v.d = sd.d;
   v.ns = sd.ns;
   v.nbr = it.n_br;
+  v.nreal = it.n_real;
   v.nsrc = it.n_src;
   v.nsv = sd.nsv;
   v.nrec = it.n_rec;
@@ -254,10 +261,12 @@ __device__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint)
   v.J.off = o.J;
   v.flag.off = o.flag;
   v.emf.off = o.emf;
+  v.vrow.off = o.vrow;
   for (int q = threadIdx.x; q < (v.d + 31) / 32 * 32; q += BS) v.cD[q] = 0.0;
   if (threadIdx.x == 0) {
     v.x[v.n] = 0.0;  // the ground: every grounded terminal points here
     v.J[v.nbr] = 0.0;
+    if (adjoint) v.vrow[v.n] = 0.0;
     reinterpret_cast<double *>(emt_lds + o.xr)[v.n] = 0.0;
   }
   load_rows<BS, SM>(c, gp, o.gmeta, o.gcode, o.grow, v.gather);
@@ -448,7 +457,8 @@ __device__ __forceinline__ void select_factor(const DevCtx &c, const ItemDesc &i
     v.dinv.p = di;
   }
   load_tail<BS, DT>(c.wtail + it.w + (int64_t)t * v.d * v.d, v.d, T);
-  for (double &w : T.w) settle(w);
+#pragma unroll
+  for (int k = 0; k < 2 * Tail<BS, DT>::R * Tail<BS, DT>::Q; ++k) settle(T.w[k]);
 }
 
 // DPP row_shr:K of a double: lane i receives lane i-K of its 16-lane row
@@ -803,16 +813,27 @@ __device__ __forceinline__ void inject(const DevCtx &c, const View<SM> &v, Lane<
   v.J[tid] = L.g[0] * L.e0 - L.h0;
 }
 
+// A trajectory row: the node voltages of the step just solved and the EMFs
+// that entered it.
+template <int BS, int BPT, bool SM>
+__device__ __forceinline__ void store_row(const View<SM> &v, const Lane<BPT> &L, double *row) {
+  const int tid = (int)threadIdx.x;
+  for (int r = tid; r < v.n; r += BS) row[r] = v.x[r];
+  if (tid < v.nsrc) row[v.n + tid] = L.e0;
+}
+
 // Branch phase of a step after which no coefficients change and which is
 // not the launch's last: the same arithmetic as update_inject below without
-// its cases (each a branch that every step would take). STORE: (i, u) of
-// every slot go to st_i, st_u.
+// its cases (each a branch that every step would take). STORE: i of every
+// slot goes to st_i. Slot pairs that are all padding are skipped (components
+// of an uneven batch are padded to the largest one's slots).
 template <int BS, int BPT, bool SM, bool STORE, bool PASS = false>
-__device__ __forceinline__ void update_plain(const View<SM> &v, Lane<BPT> &L, double *st_i, double *st_u) {
+__device__ __forceinline__ void update_plain(const View<SM> &v, Lane<BPT> &L, double *st_i) {
   const int tid = lane_id();
   const double e_next = slot0_emf<BPT, SM>(v, L, tid);
 #pragma unroll
   for (int j = 0; j < BPT; ++j) {
+    if (j > 0 && (j & 1) == 0 && j * BS >= v.nreal) break;
     const int b = tid + j * BS;
     const uint32_t pk = L.pk[j];
     const double vk = v.x[pk & kTermGround], vm = v.x[(pk >> 15) & kTermGround];
@@ -821,10 +842,7 @@ __device__ __forceinline__ void update_plain(const View<SM> &v, Lane<BPT> &L, do
     const double u = j == 0 ? (vk - vm) - L.e0 : vk - vm;
     const double gu = L.g[j] * u;
     const double i = gu + h;
-    if constexpr (STORE) {
-      st_i[b] = i;
-      st_u[b] = L.g[j] == 0.0 ? 0.0 : u;
-    }
+    if constexpr (STORE) st_i[b] = i;
     const double hn = L.be[j] * i + gamma_times(pk, gu);
     if (j == 0) {
       L.h0 = hn;
@@ -865,7 +883,7 @@ __device__ __forceinline__ void update_inject(const DevCtx &c, const View<SM> &v
     const double i = gu + h;
     if (st_i && !line) {
       st_i[b] = i;
-      st_u[b] = u;
+      if (st_u) st_u[b] = u;
     }
     if (st2_i && !line) {
       st2_i[b] = i;
@@ -1327,7 +1345,7 @@ __device__ __forceinline__ void ldl_levels(int nlev, const RP &rowptr, const LV 
 // sweeps then read (staged into LDS under SM). Such items have no dense
 // tail. Non-positive pivots are counted in c.flags[4].
 template <int BS, int BPT, bool SM>
-__device__ void refactor_dynamic(const DevCtx &c, const ItemDesc &it, View<SM> &v, const Lane<BPT> &L) {
+__device__ __forceinline__ void refactor_dynamic(const DevCtx &c, const ItemDesc &it, View<SM> &v, const Lane<BPT> &L) {
   const SymDesc sd = c.syms[it.sym];
   const int n = it.n;
   double *gcur = c.dyn + it.dyn;
@@ -1442,7 +1460,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   if (diodes) {
     // no dense tail: w stays zero
 #pragma unroll
-    for (double &e : w.w) e = 0.0;
+    for (int k = 0; k < 2 * Tail<BS, DT>::R * Tail<BS, DT>::Q; ++k) w.w[k] = 0.0;
     refactor_dynamic<BS, BPT, SM>(c, it, v, L);
   } else {
     select_factor<BS, DT, SM>(c, it, v, t, w);
@@ -1479,12 +1497,20 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     return ck_step < m ? ck_step : m;
   };
   int64_t special = special_step();
+  // the adjoint's trajectory rows (batches with checkpoints have no lines,
+  // groups or diodes)
+  double *rows = nullptr;
+  if ((KIND == STEP_PLAIN || KIND == STEP_FULL) && c.vt_full) rows = c.vt + it.vt + n0 * (int64_t)(v.n + v.nsrc);
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     if (lines) lines_ahead<BS, NL>(it, ln, n);
     gather_all<BS, SM>(v);
     solve_after_gather<BS, DT, SM, KIND == STEP_FULL>(v, w);
     if (lines) lines_settle<BS, NL>(it, ln);
+    if (rows) {
+      store_row<BS, BPT, SM>(v, L, rows);
+      rows += v.n + v.nsrc;
+    }
     // read here, stored after the update so that its own reads go ahead
     const double rv0 = rec0 ? v.x[rn0] : 0.0;
     if (v.nrec > BS && rec) {
@@ -1492,7 +1518,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       row += R;
     }
     if (KIND == STEP_PLAIN && n != special) {
-      update_plain<BS, BPT, SM, false>(v, L, nullptr, nullptr);
+      update_plain<BS, BPT, SM, false>(v, L, nullptr);
       if (rec0) {
         *at0 = rv0;
         at0 += R;
@@ -1501,7 +1527,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       continue;
     }
     if (KIND != STEP_PLAIN && n != special && !diodes) {
-      update_plain<BS, BPT, SM, false, true>(v, L, nullptr, nullptr);
+      update_plain<BS, BPT, SM, false, true>(v, L, nullptr);
       if (lines || groups) {
         step_barrier<BS>();
         if (lines) lines_step<BS, NL, SM>(c, it, v, ln, n, nullptr, nullptr);
@@ -1573,10 +1599,13 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
 // unrolled loops, so every slot index is a constant.
 template <int BS, int BPT, class F>
 __device__ __forceinline__ void with_next_coefs(const DevCtx &c, const ItemDesc &it, const Lane<BPT> &L, int t,
-                                                int t_nx, F &&f) {
+                                                int t_nx, int nreal, F &&f) {
   if (t_nx == t) {
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) f(j, L.g[j], L.be[j]);
+    for (int j = 0; j < BPT; ++j) {
+      if (j > 0 && (j & 1) == 0 && j * BS >= nreal) break;  // padding
+      f(j, L.g[j], L.be[j]);
+    }
   } else {
     const int64_t o = it.coef + (int64_t)t_nx * it.n_br + lane_id();
 #pragma unroll
@@ -1589,7 +1618,7 @@ __device__ __forceinline__ void adjoint_seed(const DevCtx &c, const ItemDesc &it
                                              const Lane<BPT> &L, int t, int t_nx, const double (&hb_nx)[BPT],
                                              double seed0, const double *dJ, int64_t n) {
   const int tid = lane_id();
-  with_next_coefs<BS, BPT>(c, it, L, t, t_nx, [&](int j, double g_nx, double be_nx) {
+  with_next_coefs<BS, BPT>(c, it, L, t, t_nx, v.nreal, [&](int j, double g_nx, double be_nx) {
     const int b = tid + j * BS;
     const double ibar = be_nx * hb_nx[j];
     const double ga_nx = gamma_of(L.pk[j], g_nx);
@@ -1611,23 +1640,25 @@ __device__ __forceinline__ double load_seed(const DevCtx &c, const ItemDesc &it,
   return tid < v.nrec ? dJ[((int64_t)it.scen * c.T + (n - 1)) * c.rec_stride + v.rcolumn[tid]] : 0.0;
 }
 
-// Recomputes steps lo+1..hi of segment s from its checkpoint into a
-// segment buffer (row 0 = the checkpoint, row n-lo = step n). Afterwards L's
+// The checkpoint segments. The reversal of a segment needs every step's
+// branch currents and voltages. Where the forward run has kept the
+// trajectory rows (all voltages and EMFs), a segment's currents follow from
+// its checkpoint branch by branch, without a solve or a barrier
+// (rebuild_segment); otherwise its steps are run again and leave rows of
+// their own (recompute_segment). Either way the currents go to the segment
+// buffer (row n - lo - 1 = step n) and the voltages are formed from the rows.
+// A row is 8 (n + n_src) bytes a step, the branch state it stands for about
+// 50 n; running the steps again took as long as the reversal itself.
+
+// Runs steps lo+1..hi of segment s again from its checkpoint. Afterwards L's
 // coefficients and the factors are those of step hi.
 template <int BS, int BPT, int DT, bool SM>
-__device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v,
-                                                  Lane<BPT> &L, Tail<BS, DT> &w, int64_t s, double *seg_i,
-                                                  double *seg_u) {
+__device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v, Lane<BPT> &L,
+                                                  Tail<BS, DT> &w, int64_t s, double *seg_i, double *rows) {
   const int64_t *topo = c.topo + it.topo;
   const int nbr = v.nbr;
   const int64_t lo = s * c.K, hi = (lo + c.K < c.T) ? lo + c.K : c.T;
   const int64_t cko = it.ck + s * (int64_t)nbr;
-#pragma unroll
-  for (int j = 0; j < BPT; ++j) {
-    const int b = threadIdx.x + j * BS;
-    seg_i[b] = c.ck_i[cko + b];
-    seg_u[b] = c.ck_u[cko + b];
-  }
   // the gather's seeds are zero in the forward steps
   for (int q = threadIdx.x; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = 0.0;
   int t = topo_of(topo, it.n_topo, lo + 1);
@@ -1641,15 +1672,16 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     gather_all<BS, SM>(v);
     solve_after_gather<BS, DT, SM, true>(v, w);
-    const int64_t o = (n - lo) * (int64_t)nbr;
+    double *st_i = seg_i + (n - lo - 1) * (int64_t)nbr;
+    store_row<BS, BPT, SM>(v, L, rows + (n - lo - 1) * (int64_t)(v.n + v.nsrc));
     if (n < hi && n + 1 != next) {
-      update_plain<BS, BPT, SM, true>(v, L, seg_i + o, seg_u + o);
+      update_plain<BS, BPT, SM, true>(v, L, st_i);
       step_barrier<BS>();
       continue;
     }
     const bool sw = (n + 1 == next) && n < hi;
-    update_inject<BS, BPT, SM>(c, v, L, seg_i + o, seg_u + o, nullptr, nullptr, sw,
-                               it.coef + (int64_t)(t + 1) * nbr, n < hi, n);
+    update_inject<BS, BPT, SM>(c, v, L, st_i, nullptr, nullptr, nullptr, sw, it.coef + (int64_t)(t + 1) * nbr, n < hi,
+                               n);
     if (sw) {
       ++t;
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
@@ -1659,20 +1691,115 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
   }
 }
 
-// Reverses steps hi..lo+1 of segment s from its buffer. On entry L's
-// coefficients and the factors are those of step hi (topology t) and hb_nx
-// holds hbar of step hi+1 (0 past the horizon); on exit hb_nx holds hbar of
-// step lo+1, and the gradient accumulators have taken the segment's terms.
-template <int BS, int BPT, int DT, bool SM>
-__device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v,
-                                                Lane<BPT> &L, Tail<BS, DT> &w, int64_t s, int t,
-                                                const double *seg_i, const double *seg_u, double (&hb_nx)[BPT],
-                                                double (&gb)[BPT], double (&bb)[BPT], double (&cb)[BPT],
-                                                const double *dJ) {
+// The branch currents of steps lo+1..hi of segment s from its checkpoint and
+// its trajectory rows, every slot for itself. Rows come in blocks through the
+// LDS of the right-hand side, solution and injections (idle here), the next
+// block read into registers while this one's steps run: gathered from memory
+// row by row a step was one trip to it. Afterwards L's coefficients are those
+// of step hi.
+template <int BS, int BPT, bool SM>
+__device__ __forceinline__ void rebuild_segment(const DevCtx &c, const ItemDesc &it, const View<SM> &v, Lane<BPT> &L,
+                                                int64_t s, double *seg_i, const double *rows) {
+  constexpr int kRegs = 8;  // doubles per lane of a block
   const int64_t *topo = c.topo + it.topo;
-  const int nbr = v.nbr;
+  const int nbr = it.n_br, len = it.n + it.n_src;
+  const int64_t lo = s * c.K, hi = (lo + c.K < c.T) ? lo + c.K : c.T;
+  const int64_t cko = it.ck + s * (int64_t)nbr;
+  double *buf = reinterpret_cast<double *>(emt_lds + (v.closed ? v.x.off - (uint32_t)(v.n + 1) * 8u : v.x.off));
+  const int room = (int)(v.J.off - (uint32_t)((char *)buf - emt_lds)) / 8 + nbr;
+  int per = (room < kRegs * BS ? room : kRegs * BS) / len;  // steps per block
+  if (per < 1) per = 1;  // (a row of more than kRegs * BS entries: see below)
+  int t = topo_of(topo, it.n_topo, lo + 1);
+  int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
+  load_coefs<BS, BPT>(c, it, t, L.g, L.be);
+  double h[BPT];
+#pragma unroll
+  for (int j = 0; j < BPT; ++j) {
+    const int64_t b = cko + (int)threadIdx.x + j * BS;
+    h[j] = L.be[j] * c.ck_i[b] + gamma_of(L.pk[j], L.g[j]) * c.ck_u[b];
+  }
+  double ahead[kRegs];
+  auto read_block = [&](int64_t n, int cnt) {  // entries of steps n .. of a block
+    const double *r = rows + (n - lo - 1) * (int64_t)len;
+#pragma unroll
+    for (int k = 0; k < kRegs; ++k) {
+      const int q = lane_id() + k * BS;
+      ahead[k] = q < cnt ? r[q] : 0.0;
+    }
+  };
+  auto steps_from = [&](int64_t n) { return (int)(hi - n + 1 < per ? hi - n + 1 : per); };
+  read_block(lo + 1, steps_from(lo + 1) * len);
+  for (int64_t n0 = lo + 1; n0 <= hi; n0 += per) {
+    const int m = steps_from(n0), cnt = m * len;
+    __syncthreads();  // the block before has been read
+#pragma unroll
+    for (int k = 0; k < kRegs; ++k) {
+      const int q = lane_id() + k * BS;
+      if (q < cnt) buf[q] = ahead[k];
+    }
+    // what the registers do not hold of a very long row
+    for (int q = (int)threadIdx.x + kRegs * BS; q < cnt; q += BS) buf[q] = rows[(n0 - lo - 1) * (int64_t)len + q];
+    __syncthreads();
+    if (n0 + m <= hi) read_block(n0 + m, steps_from(n0 + m) * len);
+    for (int d = 0; d < m; ++d) {
+      const int64_t n = n0 + d;
+      const double *row = buf + d * len;
+      const bool sw = n + 1 == next && n < hi;
+      const int tid = lane_id();
+#pragma unroll
+      for (int j = 0; j < BPT; ++j) {
+        if (j > 0 && (j & 1) == 0 && j * BS >= it.n_real) break;
+        const uint32_t pk = opaque(L.pk[j]);
+        const int k = (int)(pk & kTermGround), q = (int)((pk >> 15) & kTermGround);
+        const double vk = k < it.n ? row[k] : 0.0, vm = q < it.n ? row[q] : 0.0;
+        double u = vk - vm;
+        if (j == 0) u = u - (tid < it.n_src ? row[it.n + tid] : 0.0);
+        if (sw && L.g[j] == 0.0) u = 0.0;
+        const double gu = L.g[j] * u;
+        const double i = gu + h[j];
+        seg_i[tid + j * BS] = i;
+        double gam = gamma_times(pk, gu);
+        if (sw) {
+          const int64_t o = it.coef + (int64_t)(t + 1) * nbr + tid + j * BS;
+          L.g[j] = c.cg[o];
+          L.be[j] = c.cb[o];
+          settle(L.g[j]);
+          settle(L.be[j]);
+          gam = gamma_of(pk, L.g[j]) * u;
+        }
+        h[j] = L.be[j] * i + gam;
+      }
+      seg_i += nbr;
+      if (sw) {
+        ++t;
+        next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
+      }
+    }
+  }
+  __syncthreads();
+  // the zeros that the block overwrote
+  if (threadIdx.x == 0) {
+    v.x[v.n] = 0.0;
+    v.J[nbr] = 0.0;
+    *reinterpret_cast<double *>(emt_lds + (v.closed ? v.x.off - 8u : v.x.off + (uint32_t)v.n * 8u)) = 0.0;
+  }
+}
+
+// Reverses steps hi..lo+1 of segment s from its currents and rows. On entry
+// L's coefficients and the factors are those of step hi (topology t) and
+// hb_nx holds hbar of step hi+1 (0 past the horizon); on exit hb_nx holds
+// hbar of step lo+1, and the gradient accumulators have taken the segment's
+// terms.
+template <int BS, int BPT, int DT, bool SM, bool GEN>
+__device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v, Lane<BPT> &L,
+                                                Tail<BS, DT> &w, int64_t s, int t, const double *seg_i,
+                                                const double *rows, double (&hb_nx)[BPT], double (&gb)[BPT],
+                                                double (&bb)[BPT], double (&cb)[BPT], const double *dJ) {
+  const int64_t *topo = c.topo + it.topo;
+  const int nbr = v.nbr, len = v.n + v.nsrc, tid0 = (int)threadIdx.x;
   const int64_t T = c.T;
   const int64_t lo = s * c.K, hi = (lo + c.K < T) ? lo + c.K : T;
+  const int64_t cko = it.ck + s * (int64_t)nbr;
   // the coefficients of step hi+1 are those of topology t_nx (unused at
   // hi = T, where hbar = 0)
   int t_nx = hi < T ? topo_of(topo, it.n_topo, hi + 1) : t;
@@ -1685,40 +1812,112 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
   };
   int64_t first = first_step(t);
   adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, load_seed<SM>(c, it, v, dJ, hi), dJ, hi);
+  // a row's entry q in v.vrow: past the voltages comes the ground's zero
+  auto at = [&](int q) { return q < v.n ? q : q + 1; };
+  // the voltages of a row in the lane's slots, with the conductances that
+  // tell a branch out of service
+  auto row_u = [&](int j, double g) {
+    const uint32_t pk = opaque(L.pk[j]);
+    const double vk = v.vrow[pk & kTermGround], vm = v.vrow[(pk >> 15) & kTermGround];
+    const double e = j == 0 && tid0 < v.nsrc ? v.vrow[v.n + 1 + tid0] : 0.0;
+    const double u = j == 0 ? (vk - vm) - e : vk - vm;
+    return g == 0.0 ? 0.0 : u;
+  };
+  {
+    const double *row = rows + (hi - lo - 1) * (int64_t)len;
+    for (int q = tid0; q < len; q += BS) v.vrow[at(q)] = row[q];
+  }
   step_barrier<BS>();
-  // the state of step n in the lane's slots, carried from one step (where it
-  // was the earlier one) to the next
+  // u of step n in the lane's slots, carried from one step (where it was the
+  // earlier one) to the next
   double un[BPT];
 #pragma unroll
-  for (int j = 0; j < BPT; ++j) un[j] = seg_u[(hi - lo) * (int64_t)nbr + threadIdx.x + j * BS];
+  for (int j = 0; j < BPT; ++j) un[j] = row_u(j, L.g[j]);
+  // the lane's entries of row m, read a step before they are needed
+  double r0 = 0.0, r1 = 0.0;
+  auto read_ahead = [&](int64_t m) {
+    if (m <= lo) return;
+    const double *row = rows + (m - lo - 1) * (int64_t)len;
+    if (tid0 < len) r0 = row[tid0];
+    if (tid0 + BS < len) r1 = row[tid0 + BS];
+  };
+  read_ahead(hi - 1);
+  step_barrier<BS>();
   for (int64_t n = hi; n >= lo + 1; --n) {
-    // global reads of this step's update and the next step's seeds, issued
-    // ahead of the solve
-    const int64_t op = (n - 1 - lo) * (int64_t)nbr + threadIdx.x;
-    double ip[BPT], up[BPT];
+    // global reads of this step's update (currents and row of step n - 1; at
+    // the segment's first step the checkpoint) and the next step's seeds,
+    // issued ahead of the solve
+    const bool from_ck = n - 1 == lo;
+    const double *i0 = from_ck ? c.ck_i + cko : seg_i + (n - lo - 2) * (int64_t)nbr;
+    const double *row = rows + (n - lo - 2) * (int64_t)len;
+    const int tid = lane_id();
+    if (!from_ck) {
+      if (tid0 < len) v.vrow[at(tid0)] = r0;
+      if (tid0 + BS < len) v.vrow[at(tid0 + BS)] = r1;
+      for (int q = tid0 + 2 * BS; q < len; q += BS) v.vrow[at(q)] = row[q];
+    }
+    double ip[BPT];
 #pragma unroll
     for (int j = 0; j < BPT; ++j) {
-      ip[j] = seg_i[op + j * BS];
-      up[j] = seg_u[op + j * BS];
+      ip[j] = 0.0;
+      if (j > 0 && j * BS >= v.nreal) continue;
+      ip[j] = i0[tid + j * BS];
     }
-    const double seed0 = n - 1 >= lo + 1 ? load_seed<SM>(c, it, v, dJ, n - 1) : 0.0;
+    read_ahead(n - 2);
+    const double seed0 = from_ck ? 0.0 : load_seed<SM>(c, it, v, dJ, n - 1);
     gather_all<BS, SM>(v);
-    solve_after_gather<BS, DT, SM, true>(v, w);
-    with_next_coefs<BS, BPT>(c, it, L, t, t_nx, [&](int j, double g_nx, double be_nx) {
+    solve_after_gather<BS, DT, SM, GEN>(v, w);
+    if (!from_ck && n - 1 >= first && t_nx == t) {
+      // no checkpoint and no topology change on either side: the update and
+      // the next step's injections slot by slot (out of service: hbar = 0,
+      // and u only ever meets that zero)
+      const double e = tid < v.nsrc ? v.vrow[v.n + 1 + tid] : 0.0;
+#pragma unroll
+      for (int j = 0; j < BPT; ++j) {
+        if (j > 0 && (j & 1) == 0 && j * BS >= v.nreal) break;
+        const uint32_t pk = opaque(L.pk[j]);
+        const int k = (int)(pk & kTermGround), m = (int)((pk >> 15) & kTermGround);
+        const double wk = v.x[k], wm = v.x[m], vk = v.vrow[k], vm = v.vrow[m];
+        const double up = j == 0 ? (vk - vm) - e : vk - vm;
+        const double hb = L.g[j] != 0.0 ? L.be[j] * hb_nx[j] - (wk - wm) : 0.0;
+        gb[j] = __builtin_fma(hb, un[j], gb[j]);
+        bb[j] = __builtin_fma(hb, ip[j], bb[j]);
+        cb[j] = __builtin_fma(hb, up, cb[j]);
+        un[j] = up;
+        hb_nx[j] = hb;
+        v.J[tid + j * BS] = gamma_times(pk, L.g[j] * hb) + L.g[j] * (L.be[j] * hb);
+      }
+      if (tid < v.nrec) v.J[v.nbr + 1 + tid] = seed0;
+      if (v.nrec > BS) {
+        const double *drow = dJ + ((int64_t)it.scen * c.T + (n - 2)) * c.rec_stride;
+        for (int q = tid + BS; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = drow[v.rcolumn[q]];
+      }
+      step_barrier<BS>();
+      continue;
+    }
+    // a topology change between step n - 1 and step n: the earlier one's
+    // conductances decide which of its branches were out of service
+    const bool earlier = n - 1 < first && t > 0;
+    with_next_coefs<BS, BPT>(c, it, L, t, t_nx, v.nreal, [&](int j, double g_nx, double be_nx) {
       (void)g_nx;
-      const uint32_t pk = L.pk[j];
+      const uint32_t pk = opaque(L.pk[j]);
       const double wk = v.x[pk & kTermGround], wm = v.x[(pk >> 15) & kTermGround];
+      double up;
+      if (from_ck)
+        up = c.ck_u[cko + tid + j * BS];
+      else
+        up = row_u(j, earlier ? c.cg[it.coef + (int64_t)(t - 1) * nbr + tid + j * BS] : L.g[j]);
       const double ibar = be_nx * hb_nx[j];
       const double hb = (L.g[j] != 0.0) ? ibar - (wk - wm) : 0.0;
-      gb[j] = gb[j] + hb * un[j];
-      bb[j] = bb[j] + hb * ip[j];
-      cb[j] = cb[j] + hb * up[j];
-      un[j] = up[j];
+      gb[j] = __builtin_fma(hb, un[j], gb[j]);
+      bb[j] = __builtin_fma(hb, ip[j], bb[j]);
+      cb[j] = __builtin_fma(hb, up, cb[j]);
+      un[j] = up;
       hb_nx[j] = hb;
     });
     // step n's coefficients become the next-step ones of step n-1
     t_nx = t;
-    if (n - 1 >= lo + 1) {
+    if (!from_ck) {
       if (n - 1 < first) {
         --t;
         first = first_step(t);
@@ -1743,18 +1942,20 @@ __device__ __forceinline__ void store_branch_adjoints(const DevCtx &c, const Ite
   }
 }
 
-// Serial adjoint: one workgroup per item recomputes and reverses each
-// segment in turn, last segment first. With 256 lanes the register budget
+// Serial adjoint: one workgroup per item rebuilds (or recomputes) and
+// reverses each segment in turn, last segment first. With 256 lanes the register budget
 // is held to two waves per SIMD (two workgroups per compute unit), so a
 // batch of many components runs in fewer rounds than at the one wave per
-// SIMD that its largest branch-slot counts would otherwise take.
-template <int BS, int BPT, int DT, bool SM>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 ? 2 : 1))) void k_adjoint(
+// SIMD that its largest branch-slot counts would otherwise take. GEN: the
+// batch has level passes or no whole trajectory (the kernels without carry
+// none of their code and registers).
+template <int BS, int BPT, int DT, bool SM, bool GEN>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1))) void k_adjoint(
     DevCtx c, const int32_t *order, const double *dJ) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, true>(c, it, true);
+  View<SM> v = make_view<BS, SM, GEN>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
-  double *seg_i = c.seg_i + it.seg, *seg_u = c.seg_u + it.seg;
+  double *seg_i = c.seg_i + it.seg;
   Lane<BPT> L;
   Tail<BS, DT> w;
   load_lane<BS, BPT>(c, it, L);
@@ -1762,11 +1963,24 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 ? 
   double hb_nx[BPT], gb[BPT], bb[BPT], cb[BPT];
 #pragma unroll
   for (int j = 0; j < BPT; ++j) hb_nx[j] = gb[j] = bb[j] = cb[j] = 0.0;
+  int t_w = -1;  // the topology whose factors are loaded
   for (int64_t s = nseg - 1; s >= 0; --s) {
-    recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, seg_i, seg_u);
     const int64_t hi = (s * c.K + c.K < c.T) ? s * c.K + c.K : c.T;
     const int t = topo_of(c.topo + it.topo, it.n_topo, hi);
-    reverse_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, t, seg_i, seg_u, hb_nx, gb, bb, cb, dJ);
+    double *rows = c.vt + it.vt;
+    if (!GEN || c.vt_full) {
+      rows += s * c.K * (int64_t)(v.n + v.nsrc);
+      rebuild_segment<BS, BPT, SM>(c, it, v, L, s, seg_i, rows);
+      if (t != t_w) {
+        select_factor<BS, DT, SM>(c, it, v, t, w);
+        t_w = t;
+      }
+    } else {
+      recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, seg_i, rows);
+    }
+    __syncthreads();
+    reverse_segment<BS, BPT, DT, SM, GEN>(c, it, v, L, w, s, t, seg_i, rows, hb_nx, gb, bb, cb, dJ);
+    t_w = topo_of(c.topo + it.topo, it.n_topo, s * c.K + 1);
   }
   store_branch_adjoints<BS, BPT>(c, it, gb, bb, cb);
 }
@@ -1815,15 +2029,20 @@ __device__ __forceinline__ void publish_flag(int32_t *flag, int32_t value) {
 // recompute of segment s-1 overlaps the reversal of segment s. Per item,
 // pipe[2q] counts recomputed segments and pipe[2q+1] reversed ones; the
 // recompute of the k-th segment waits until the (k-2)-th is reversed.
-template <int BS, int BPT, int DT, bool SM>
+template <int BS, int BPT, int DT, bool SM, bool GEN>
 __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *order, int n_items,
                                                      const double *dJ, int32_t *pipe) {
   const bool recompute = (int)blockIdx.x >= n_items;
   const int q = order[recompute ? blockIdx.x - n_items : blockIdx.x];
   const ItemDesc it = c.items[q];
-  View<SM> v = make_view<BS, SM, true>(c, it, true);
+  View<SM> v = make_view<BS, SM, GEN>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
-  const int64_t seg_len = ((c.K < c.T ? c.K : c.T) + 1) * (int64_t)v.nbr;
+  const int64_t steps = c.K < c.T ? c.K : c.T;
+  const int64_t seg_len = steps * (int64_t)v.nbr, row_len = v.n + v.nsrc;
+  // the rows of the k-th segment handled
+  auto rows_of = [&](int64_t k) {
+    return c.vt + it.vt + (!GEN || c.vt_full ? (nseg - 1 - k) * c.K : (k & 1) * steps) * row_len;
+  };
   int32_t *ready = pipe + 2 * q, *done = pipe + 2 * q + 1;
   Lane<BPT> L;
   Tail<BS, DT> w;
@@ -1832,7 +2051,10 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
     for (int64_t k = 0; k < nseg; ++k) {
       if (k >= 2 && !wait_flag(done, (int32_t)(k - 1), c.flags + 2, v.flag)) return;
       const int64_t o = it.seg + (k & 1) * seg_len;
-      recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, nseg - 1 - k, c.seg_i + o, c.seg_u + o);
+      if (!GEN || c.vt_full)
+        rebuild_segment<BS, BPT, SM>(c, it, v, L, nseg - 1 - k, c.seg_i + o, rows_of(k));
+      else
+        recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, nseg - 1 - k, c.seg_i + o, rows_of(k));
       publish_flag(ready, (int32_t)(k + 1));
     }
     return;
@@ -1849,7 +2071,7 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
     select_factor<BS, DT, SM>(c, it, v, t, w);
     step_barrier<BS>();
     const int64_t o = it.seg + (k & 1) * seg_len;
-    reverse_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, t, c.seg_i + o, c.seg_u + o, hb_nx, gb, bb, cb, dJ);
+    reverse_segment<BS, BPT, DT, SM, GEN>(c, it, v, L, w, s, t, c.seg_i + o, rows_of(k), hb_nx, gb, bb, cb, dJ);
     publish_flag(done, (int32_t)(k + 1));
   }
   store_branch_adjoints<BS, BPT>(c, it, gb, bb, cb);

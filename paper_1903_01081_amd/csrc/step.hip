@@ -1,6 +1,6 @@
 // Instantiations of the step kernels for one workgroup size (EMT_BS, set by
 // the build: 64, 256 or 512) and one kind of kernel (EMT_PART_*: FWD with
-// EMT_KIND, a StepKind; ADJ; PIPE), so that they
+// EMT_KIND, a StepKind; ADJ and PIPE with EMT_KIND 0 or 1 = GEN), so that they
 // compile in parallel.
 #include <hip/hip_runtime.h>
 
@@ -31,7 +31,7 @@ hipError_t fwd(const DevCtx &c, const int32_t *order, int n_items, int64_t n0, i
 template <int BPT, int DT, bool SM>
 hipError_t adj(const DevCtx &c, const int32_t *order, int n_items, const double *dJ, size_t lds,
                hipStream_t st) {
-  auto k = step::k_adjoint<EMT_BS, BPT, DT, SM>;
+  auto k = step::k_adjoint<EMT_BS, BPT, DT, SM, EMT_KIND != 0>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -43,7 +43,7 @@ hipError_t adj(const DevCtx &c, const int32_t *order, int n_items, const double 
 template <int BPT, int DT, bool SM>
 hipError_t adj_pipe(const DevCtx &c, const int32_t *order, int n_items, const double *dJ, int32_t *pipe,
                     size_t lds, hipStream_t st) {
-  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM>;
+  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM, EMT_KIND != 0>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -59,7 +59,7 @@ hipError_t adj_pipe(const DevCtx &c, const int32_t *order, int n_items, const do
 
 template <int BPT, int DT, bool SM>
 hipError_t adj_pipe_occupancy(size_t lds, int *blocks) {
-  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM>;
+  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM, EMT_KIND != 0>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -68,9 +68,6 @@ hipError_t adj_pipe_occupancy(size_t lds, int *blocks) {
 #endif
 
 }  // namespace
-
-#define EMT_CAT2(a, b) a##b
-#define EMT_CAT(a, b) EMT_CAT2(a, b)
 
 // Branches per lane x dense-tail capacity (KernelShape::dt): LDS-staged
 // variants for every count, global-memory fallbacks for the larger ones.
@@ -99,7 +96,8 @@ hipError_t launch_forward<EMT_BS, EMT_KIND>(const DevCtx &c, const KernelShape &
 #endif
 
 #ifdef EMT_PART_ADJ
-hipError_t EMT_CAT(launch_adjoint_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order,
+template <>
+hipError_t launch_adjoint<EMT_BS, EMT_KIND != 0>(const DevCtx &c, const KernelShape &ks, const int32_t *order,
                                               int n_items, const double *dJ, hipStream_t st) {
 #define EMT_CASE(BPT, DT, SM) \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj<BPT, DT, SM>(c, order, n_items, dJ, ks.lds_adj, st);
@@ -111,7 +109,8 @@ hipError_t EMT_CAT(launch_adjoint_bs, EMT_BS)(const DevCtx &c, const KernelShape
 #endif
 
 #ifdef EMT_PART_PIPE
-hipError_t EMT_CAT(launch_adjoint_pipe_bs, EMT_BS)(const DevCtx &c, const KernelShape &ks, const int32_t *order,
+template <>
+hipError_t launch_adjoint_pipe<EMT_BS, EMT_KIND != 0>(const DevCtx &c, const KernelShape &ks, const int32_t *order,
                                                    int n_items, const double *dJ, int32_t *pipe, hipStream_t st) {
 #define EMT_CASE(BPT, DT, SM) \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj_pipe<BPT, DT, SM>(c, order, n_items, dJ, pipe, ks.lds_adj, st);
@@ -120,7 +119,8 @@ hipError_t EMT_CAT(launch_adjoint_pipe_bs, EMT_BS)(const DevCtx &c, const Kernel
   return hipErrorInvalidValue;
 }
 
-hipError_t EMT_CAT(adjoint_pipe_blocks_per_cu_bs, EMT_BS)(const KernelShape &ks, int *blocks) {
+template <>
+hipError_t adjoint_pipe_blocks_per_cu<EMT_BS, EMT_KIND != 0>(const KernelShape &ks, int *blocks) {
 #define EMT_CASE(BPT, DT, SM) \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj_pipe_occupancy<BPT, DT, SM>(ks.lds_adj, blocks);
   EMT_SHAPES(EMT_CASE)
