@@ -178,13 +178,14 @@ struct DSU {
 };
 
 // Minimum-degree elimination on an explicit elimination graph (ties broken
-// by the smaller node id, so the result is deterministic). Returns the order
-// (position -> node) and, per eliminated node, its neighbours at elimination
+// by the smaller node id, so the result is deterministic); nodes marked `last`
+// come after all others. Returns the order (position -> node) and, per eliminated node, its neighbours at elimination
 // time: exactly the row indices of its column of L.
-void min_degree(int n, std::vector<std::vector<int>> adj, std::vector<int> &order,
+void min_degree(int n, std::vector<std::vector<int>> adj, const std::vector<uint8_t> &last, std::vector<int> &order,
                 std::vector<std::vector<int>> &reach) {
   std::set<std::pair<int, int>> pq;
-  for (int v = 0; v < n; ++v) pq.insert({(int)adj[v].size(), v});
+  auto key = [&](int v) { return std::make_pair((int)adj[v].size() + (last[v] ? n : 0), v); };
+  for (int v = 0; v < n; ++v) pq.insert(key(v));
   std::vector<uint8_t> gone(n, 0);
   order.clear();
   reach.assign(n, {});
@@ -197,24 +198,26 @@ void min_degree(int n, std::vector<std::vector<int>> adj, std::vector<int> &orde
     const std::vector<int> nb = adj[p];
     reach[p] = nb;
     for (int q : nb) {
-      pq.erase({(int)adj[q].size(), q});
+      pq.erase(key(q));
       tmp.clear();
       std::set_union(adj[q].begin(), adj[q].end(), nb.begin(), nb.end(), std::back_inserter(tmp));
       adj[q].clear();
       for (int x : tmp)
         if (x != q && x != p && !gone[x]) adj[q].push_back(x);
-      pq.insert({(int)adj[q].size(), q});
+      pq.insert(key(q));
     }
     adj[p].clear();
   }
 }
 
 // Builds the symbolic factor of a component given in canonical labels
-// (0..n-1) with sorted adjacency lists. perm[canonical] = local id.
-void symbolic(int n, const std::vector<std::vector<int>> &adj, Symbolic &S, std::vector<int> &perm) {
+// (0..n-1) with sorted adjacency lists, nodes marked `last` at the end of
+// the order. perm[canonical] = local id.
+void symbolic(int n, const std::vector<std::vector<int>> &adj, const std::vector<uint8_t> &last, Symbolic &S,
+              std::vector<int> &perm) {
   std::vector<int> order;
   std::vector<std::vector<int>> reach;
-  min_degree(n, adj, order, reach);
+  min_degree(n, adj, last, order, reach);
   perm.assign(n, 0);
   for (int i = 0; i < n; ++i) perm[order[i]] = i;
   S.n = n;
@@ -597,6 +600,25 @@ Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim) {
       }
       for (auto &a : adj) std::sort(a.begin(), a.end());
 
+      // Terminals of diodes and controlled switches go last, where they can
+      // all lie in the dense tail: a change of their state then changes the
+      // tail's matrix alone (closed.h). Not for solvers without a tail.
+      std::vector<uint8_t> last(n, 0);
+      if (sim.solver == EMT_SOLVER_AUTO) {
+        int cnt = 0;
+        for (int b = 0; b < B; ++b) {
+          if (net.kind[b] != EMT_DIODE && net.kind[b] != EMT_CSWITCH) continue;
+          for (int t : {net.k[b], net.m[b]})
+            if (t >= 0 && item_key(t) == kv.first && !last[canon[t]]) {
+              last[canon[t]] = 1;
+              ++cnt;
+            }
+        }
+        if (cnt > kMaxSwitchNodes) std::fill(last.begin(), last.end(), 0);
+        for (int v = 0; v < n; ++v)
+          if (last[v]) key.push_back(-1 - (int64_t)v);
+      }
+
       int sym_id;
       std::vector<int> perm;
       auto it = sym_cache.find(key);
@@ -605,7 +627,7 @@ Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim) {
         perm = it->second.second;
       } else {
         Symbolic S;
-        symbolic(n, adj, S, perm);
+        symbolic(n, adj, last, S, perm);
         sym_id = (int)A.syms.size();
         A.syms.push_back(std::move(S));
         sym_cache.emplace(std::move(key), std::make_pair(sym_id, perm));

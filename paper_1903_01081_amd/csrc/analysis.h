@@ -67,6 +67,10 @@ SweepPlan plan_sweeps(const Symbolic &S, int d);
 // per tail node, over d <= dmax.
 int choose_tail(const Symbolic &S, int dmax);
 
+// Most diode and controlled-switch terminals of a component that are ordered
+// last (they must fit the dense tail of the closed form).
+constexpr int kMaxSwitchNodes = 128;
+
 // One work item: one connected component of one scenario.
 struct Item {
   int scen = 0, sym = 0, n = 0, n_br = 0, n_src = 0;

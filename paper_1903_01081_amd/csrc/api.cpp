@@ -818,13 +818,28 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       may = true;
     }
     plans[q] = plan_sweeps(A.syms[q], d);
+    // diodes and controlled switches: their terminals, ordered last, must lie
+    // in the tail
+    int d_min = 0;
+    if (sym_diode[q] && solver == EMT_SOLVER_AUTO) {
+      for (const Item &it : A.items) {
+        if (it.sym != (int)q) continue;
+        for (int j = 0; j < it.n_br; ++j) {
+          const int b = it.br[j];
+          if (b < 0 || (nets[it.scen].kind[b] != EMT_DIODE && nets[it.scen].kind[b] != EMT_CSWITCH)) continue;
+          for (int v : {it.bk[j], it.bm[j]})
+            if (v >= 0) d_min = std::max(d_min, n - v);
+        }
+      }
+      may = d_min <= closed_tail_max(bs);
+    }
     if (!may || 2 * (n + 1) > 65535) continue;
-    const bool fixed = solver == EMT_SOLVER_DENSE || forced_tail >= 0;
+    const bool fixed = solver == EMT_SOLVER_DENSE || (forced_tail >= 0 && !sym_diode[q]);
     const std::vector<ClosedSize> z = closed_sizes(A.syms[q], fixed ? d : closed_tail_max(bs));
     double best = levels_cost(plans[q]);
     const double room = max_lds - sym_lds[q] - 16.0 * (n + 1) - 8.0 * bs;
     int best_d = -1;
-    for (int e = fixed ? d : 0; e < (int)z.size(); ++e) {
+    for (int e = fixed ? d : d_min; e < (int)z.size(); ++e) {
       if (2 + z[e].q + z[e].nn > kClosedValues) continue;
       const double cost = closed_cost(z[e], e, n, bs, room);
       if (cost < best) {
@@ -833,21 +848,34 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       }
     }
     if (best_d < 0) continue;
-    closed[q] = 1;
+    closed[q] = sym_diode[q] ? 2 : 1;
     if (best_d != d) plans[q] = plan_sweeps(A.syms[q], best_d);
   }
   // the forward kernel's kind
-  bool any_line = false, any_group = false, any_full = false;
+  bool any_line = false, any_group = false, any_level = false, any_switch = false;
   for (const Item &it : A.items) {
     if (c.is_split[&it - &A.items[0]]) continue;
     any_line = any_line || !it.line_bk.empty();
     any_group = any_group || !it.grp_b.empty();
-    any_full = any_full || !closed[it.sym];
+    any_level = any_level || !closed[it.sym];
+    any_switch = any_switch || closed[it.sym] == 2;
   }
-  c.ks.kind = any_full || (any_line && any_group) ? STEP_FULL
-              : any_line                          ? STEP_LINES
-              : any_group                         ? STEP_GROUPS
-                                                  : STEP_PLAIN;
+  if (any_switch && (any_line || any_group || any_level)) {
+    // only the general kernel runs these together, and it factorises
+    // components with diodes or controlled switches by levels
+    for (size_t q = 0; q < A.syms.size(); ++q)
+      if (closed[q] == 2) {
+        closed[q] = 0;
+        plans[q] = plan_sweeps(A.syms[q], 0);
+      }
+    any_level = true;
+    any_switch = false;
+  }
+  c.ks.kind = any_level || (any_line && any_group) ? STEP_FULL
+              : any_line                           ? STEP_LINES
+              : any_group                          ? STEP_GROUPS
+              : any_switch                         ? STEP_SWITCH
+                                                   : STEP_PLAIN;
   std::vector<ClosedPlan> cplans(A.syms.size());
   auto plan_closed_of = [&](size_t q) {
     if (closed[q]) cplans[q] = plan_closed(A.syms[q], gpos[q], plans[q].d, bs);
@@ -922,8 +950,15 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     z.fq = C.fwd.quads;
     z.bb = C.bwd.batches;
     z.bq = C.bwd.quads;
-    z.nlev = item_diode[q] ? A.syms[it.sym].levels_f() : 0;
-    z.nent = item_diode[q] ? it.nptr[it.n] : 0;
+    z.closed = closed[it.sym] ? 1 : 0;
+    if (closed[it.sym] == 2) {
+      for (int b : it.br)
+        if (b >= 0 && (nets[it.scen].kind[b] == EMT_DIODE || nets[it.scen].kind[b] == EMT_CSWITCH)) z.nsw++;
+      if (z.nsw > 0) z.line = 4 * c.ks.dt;
+    } else if (item_diode[q]) {
+      z.nlev = A.syms[it.sym].levels_f();
+      z.nent = it.nptr[it.n];
+    }
     z.bs = bs;
     return z;
   };
@@ -943,6 +978,10 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   auto lds_figures = [&]() {
     f_sm = a_sm = f_gl = a_gl = 0;
     max_d = 0;
+    for (int q = 0; q < NI; ++q)
+      if (!c.is_split[q] && !comp) max_d = std::max(max_d, plans[A.items[q].sym].d);
+    c.ks.dt = tail_capacity(bs, max_d);
+    if (c.ks.dt == 0) throw Error{EMT_EINVAL, "internal: dense tail too large for the block size"};
     for (int q = 0; q < NI; ++q) {
       if (c.is_split[q] || comp) continue;
       const Item &it = A.items[q];
@@ -950,7 +989,6 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       f_gl = std::max(f_gl, (size_t)step_lds(step_shape(q, false), false, false).total);
       a_sm = std::max(a_sm, (size_t)step_lds(step_shape(q, K > 0), true, true).total);
       a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, K > 0), false, true).total);
-      max_d = std::max(max_d, plans[it.sym].d);
       if (!closed[it.sym] && plans[it.sym].nsv() > 65535)
         throw Error{EMT_EINVAL, "a connected component's factor is too large"};
     }
@@ -1004,10 +1042,6 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   for (const Item &it : A.items)
     if (!c.is_split[&it - &A.items[0]] && it.n_br != bs * c.ks.bpt)
       throw Error{EMT_EDEVICE, "internal: an item's branch padding differs from the step kernels' slots"};
-  if (!comp) {
-    c.ks.dt = tail_capacity(bs, max_d);
-    if (c.ks.dt == 0) throw Error{EMT_EINVAL, "internal: dense tail too large for the block size"};
-  }
   c.ks.lds_fwd = c.sm_fwd ? f_sm : f_gl;
   c.ks.lds_adj = c.sm_adj ? a_sm : a_gl;
   if (f_gl > (size_t)max_lds) throw Error{EMT_EINVAL, "a connected component needs more LDS than a workgroup has"};
@@ -1022,7 +1056,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     hip_check(hipMemGetInfo(&free_b, &total_b), "memory size");
     vt_full = per_step * (double)T <= std::min((double)total_b / 16.0, (double)free_b / 2.0);
   }
-  c.ks.gen = !vt_full || any_full;
+  c.ks.gen = !vt_full || any_level;
   // Pipelined adjoint where both workgroups of every item fit on the device
   // at once (cooperative launch) and it was not turned off.
   c.adj_pipe = false;
@@ -1114,7 +1148,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     d.brow = puth(P.brow);
     d.bpos = puth(P.bpos);
     d.rent = d.rpair = -1;
-    if (sym_diode[q]) {
+    if (sym_diode[q] && !closed[q]) {
       // update pairs of the factorisation inside the loop, level entry by
       // level entry, columns ascending (the order of a merge of the rows)
       std::vector<int> rent, rpair;
@@ -1196,6 +1230,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   const int64_t vt_rows = K > 0 ? (vt_full ? T : (c.adj_pipe ? 2 : 1) * seg_rows) : 0;
   std::vector<GroupDesc> group_tab;
   std::vector<int32_t> mptr_all, ment_all;
+  std::vector<SwitchDesc> sw_tab;
   std::vector<LineDesc> line_tab;
   std::vector<double> line_gf;
   int64_t ring_off = 0;
@@ -1239,7 +1274,53 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     for (int b : it.br)
       if (b >= 0 && (nets[it.scen].kind[b] == EMT_DIODE || nets[it.scen].kind[b] == EMT_CSWITCH)) d.n_diodes++;
     d.dyn = dyn_off;
-    if (d.n_diodes > 0) dyn_off += (int64_t)it.n_br + S.nnz() + 2 * (int64_t)it.n + plans[it.sym].nsv();
+    if (d.n_diodes > 0 && closed[it.sym] == 2) {
+      // the switches, and the entries of the tail's matrix they stamp
+      const int nt = P.d, n0 = P.ns;
+      dyn_off += std::max<int64_t>(1, ((int64_t)d.n_topo + 1) * nt * nt);
+      d.swt = (int64_t)sw_tab.size();
+      std::map<int, std::vector<int>> stamps;
+      int idx = 0;
+      for (int j = 0; j < it.n_br; ++j) {
+        const int b = it.br[j];
+        const emt_net &net = nets[it.scen];
+        if (b < 0 || (net.kind[b] != EMT_DIODE && net.kind[b] != EMT_CSWITCH)) continue;
+        SwitchDesc sd{};
+        sd.br = j;
+        sd.k = it.bk[j] >= 0 ? it.bk[j] : it.n;
+        sd.m = it.bm[j] >= 0 ? it.bm[j] : it.n;
+        sd.a = sd.b = it.n;
+        sd.control = net.kind[b] == EMT_CSWITCH ? 1 : 0;
+        if (sd.control)
+          for (int e = 0; e < 2; ++e) {
+            const int a = net.meas[2 * b + e];
+            if (a >= 0 && sc.node_item[a] != q)
+              throw Error{EMT_EDEVICE, "internal: a controlled switch measures a node of another work item"};
+            if (a >= 0) (e == 0 ? sd.a : sd.b) = sc.node_local[a];
+          }
+        sw_tab.push_back(sd);
+        const int k = it.bk[j] >= 0 ? it.bk[j] - n0 : -1, m = it.bm[j] >= 0 ? it.bm[j] - n0 : -1;
+        if ((it.bk[j] >= 0 && k < 0) || (it.bm[j] >= 0 && m < 0))
+          throw Error{EMT_EDEVICE, "internal: a switch terminal lies outside the dense tail"};
+        for (int e : {k, m})
+          if (e >= 0) stamps[e * nt + e].push_back(idx << 1);
+        if (k >= 0 && m >= 0) {
+          stamps[k * nt + m].push_back((idx << 1) | 1);
+          stamps[m * nt + k].push_back((idx << 1) | 1);
+        }
+        ++idx;
+      }
+      std::vector<int> key, ptr{0}, term;
+      for (auto &s : stamps) {
+        key.push_back(s.first);
+        term.insert(term.end(), s.second.begin(), s.second.end());
+        ptr.push_back((int)term.size());
+      }
+      d.n_swkey = (int32_t)key.size();
+      d.swkey = put(key);
+      d.swptr = put(ptr);
+      d.swterm = put(term);
+    } else if (d.n_diodes > 0) dyn_off += (int64_t)it.n_br + S.nnz() + 2 * (int64_t)it.n + plans[it.sym].nsv();
     d.n_groups = (int32_t)(it.grp_b.size() / 3);
     d.groups = (int64_t)group_tab.size();
     for (size_t g = 0; g + 2 < it.grp_b.size(); g += 3) {
@@ -1441,6 +1522,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.vt = K > 0 ? c.alloc<double>(vt_off) : nullptr;
   dc.vt_full = vt_full ? 1 : 0;
   if (c.adj_pipe) c.d_pipe = c.alloc<int32_t>(2 * (size_t)NI);
+  dc.sw_tab = sw_tab.empty() ? nullptr : c.upload(sw_tab);
   dc.line_tab = line_tab.empty() ? nullptr : c.upload(line_tab);
   dc.line_gf = line_gf.empty() ? nullptr : c.upload(line_gf);
   dc.ring = ring_off > 0 ? c.alloc<double>(ring_off) : nullptr;
@@ -1586,12 +1668,13 @@ static hipError_t launch_forward(emt_ctx &c, int64_t n0, int64_t ns, double *rec
   if (!ks.sm) ks.bpt = c.bpt_global;
   using Launch = hipError_t (*)(const emt::DevCtx &, const emt::KernelShape &, const int32_t *, int, int64_t, int64_t,
                                 double *, hipStream_t);
-  static const Launch table[3][4] = {
-      {emt::launch_forward<64, 0>, emt::launch_forward<64, 1>, emt::launch_forward<64, 2>, emt::launch_forward<64, 3>},
+  static const Launch table[3][5] = {
+      {emt::launch_forward<64, 0>, emt::launch_forward<64, 1>, emt::launch_forward<64, 2>, emt::launch_forward<64, 3>,
+       emt::launch_forward<64, 4>},
       {emt::launch_forward<256, 0>, emt::launch_forward<256, 1>, emt::launch_forward<256, 2>,
-       emt::launch_forward<256, 3>},
+       emt::launch_forward<256, 3>, emt::launch_forward<256, 4>},
       {emt::launch_forward<512, 0>, emt::launch_forward<512, 1>, emt::launch_forward<512, 2>,
-       emt::launch_forward<512, 3>}};
+       emt::launch_forward<512, 3>, emt::launch_forward<512, 4>}};
   return table[ks.bs == 64 ? 0 : (ks.bs == 256 ? 1 : 2)][ks.kind](c.dc, ks, c.d_order, c.n_fwd, n0, ns, rec, st);
 }
 

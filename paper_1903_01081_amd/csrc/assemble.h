@@ -10,8 +10,9 @@ namespace emt {
 
 // G of one (item, topology), row by row from the node CSR in a fixed order:
 // its strictly lower entries at L's row positions (Lr), its diagonal in D.
-// The caller places the barrier.
-template <int BS>
+// STATIC leaves out diodes and controlled switches, whose conductances follow
+// their state. The caller places the barrier.
+template <int BS, bool STATIC = false>
 __device__ __forceinline__ void assemble_g(const DevCtx &c, const ItemDesc &it, const SymDesc &sd, int t, double *Lr,
                                            double *D) {
   const int32_t *rowptr = c.symi + sd.rowptr;
@@ -25,7 +26,11 @@ __device__ __forceinline__ void assemble_g(const DevCtx &c, const ItemDesc &it, 
     for (int e = nptr[r]; e < nptr[r + 1]; ++e) {
       const int ent = nent[e];
       const int b = ent >> 1;
-      const double gv = g[b];
+      double gv = g[b];
+      if constexpr (STATIC) {
+        const int kind = c.bkind[it.br + b];
+        if (kind == KIND_DIODE || kind == KIND_CSWITCH) gv = 0.0;
+      }
       d = d + gv;
       const int other = (ent & 1) ? bk[b] : bm[b];
       if (other >= 0 && other < r) Lr[gpos[b]] = Lr[gpos[b]] - gv;

@@ -70,7 +70,10 @@ __global__ __launch_bounds__(BS) void k_closed(DevCtx c, const int32_t *pairs, i
   const int n = it.n, d = sd.d, ns = sd.ns, tid = (int)threadIdx.x;
   double *Lr = c.lfull + it.fac + (int64_t)t * sd.nnz;
   double *D = c.dpiv + it.dfac + (int64_t)t * n;
-  assemble_g<BS>(c, it, sd, t, Lr, D);
+  if (sd.closed == 2)
+    assemble_g<BS, true>(c, it, sd, t, Lr, D);
+  else
+    assemble_g<BS>(c, it, sd, t, Lr, D);
   double *N = V + 2, *Q = N + sd.n_n;
   if (tid < 2) V[tid] = (double)tid;
   for (int q = tid; q < sd.n_q; q += BS) Q[q] = 0.0;
@@ -129,8 +132,31 @@ __global__ __launch_bounds__(BS) void k_closed(DevCtx c, const int32_t *pairs, i
   __syncthreads();
   T w;
   step::load_tail<BS, DT>(W, d, w);
+  if (sd.closed == 2) {
+    // with switches the step kernel inverts; here the matrix stays and its
+    // pivots are checked with the switches' initial states
+    __syncthreads();
+    double *S = c.dyn + it.dyn + (int64_t)t * d * d;
+    for (int q = tid; q < d * d; q += BS) S[q] = W[q];
+    __syncthreads();
+    const uint8_t *ins = c.cins + it.coef + (int64_t)t * it.n_br;
+    for (int k = tid; k < it.n_swkey; k += BS) {
+      const int key = I[it.swkey + k];
+      double s = W[key];
+      for (int q = I[it.swptr + k]; q < I[it.swptr + k + 1]; ++q) {
+        const int term = I[it.swterm + q];
+        const int br = c.sw_tab[it.swt + (term >> 1)].br;
+        const double gs = ins[br] ? 1.0 / c.bR[it.br + br] : 0.0;
+        s = (term & 1) ? s - gs : s + gs;
+      }
+      S[key] = s;
+    }
+    __syncthreads();
+    step::load_tail<BS, DT>(S, d, w);
+  }
   const int bad = step::invert_tail<BS, DT>(w, d, line);
   if (bad && tid == 0) atomicAdd(c.flags, bad);
+  if (sd.closed == 2) return;
   const int g = tid >> 4, j = tid & 15;
 #pragma unroll
   for (int k = 0; k < T::R; ++k) {
@@ -147,7 +173,7 @@ __global__ __launch_bounds__(BS) void k_closed(DevCtx c, const int32_t *pairs, i
 template <int BS, int DT>
 hipError_t closed_launch(const DevCtx &c, const int32_t *pairs, int n_pairs, int values, hipStream_t st) {
   auto k = k_closed<BS, DT>;
-  const size_t lds = ((size_t)(values + 1) / 2 * 2 + step::tail_lines<BS, DT>()) * sizeof(double);
+  const size_t lds = ((size_t)(values + 1) / 2 * 2 + step::tail_lines(DT)) * sizeof(double);
   hipError_t e =
       hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

@@ -36,7 +36,9 @@ struct RowProg {
 struct SymDesc {
   int32_t n, d, ns, nnz;        // nodes, dense-tail size, leading size, nonzeros of L
   int32_t nsv, nfpass, nbpass, nlev;  // sweep entries, sweep passes, factor levels
-  int32_t nfdesc, nbdesc, nlevb, closed;  // row descriptors of the passes; backward levels; closed-form solve
+  // row descriptors of the passes; backward levels; closed-form solve (0: level passes; 2: with diodes or controlled
+  // switches, whose tail matrix, without them, is kept instead of its inverse)
+  int32_t nfdesc, nbdesc, nlevb, closed;
   // int32 (symi): full factor structure for the numeric factorisation
   int64_t rowptr, rowcol, colptr, colrow, colpos, flevptr, flevrows, fentptr, fent;
   // int32 (symi): backward levels over all n rows (explicit inverse)
@@ -85,6 +87,10 @@ struct ItemDesc {
   int64_t mptr;    // mutual stamps by row of L [n+1] (int32), into ment
   int64_t ment;    // mutual stamps: (L position, local branch << 1 | negative) pairs (int32)
   int32_t n_diodes, pad3;  // ideal diodes (state-dependent switches)
+  // closed form with switches: their table, and the entries of the tail's
+  // matrix they stamp: a * d + b, first term; terms (index << 1 | negative)
+  int64_t swt, swkey, swptr, swterm;
+  int32_t n_swkey, pad4;
   int64_t dyn;     // items with diodes: the factor refreshed inside the time loop, in DevCtx::dyn:
                    // current conductances [n_br], L [nnz], D [n], sweep values [nsv], 1/D [n]
 };
@@ -95,11 +101,12 @@ struct StepShape {
   int n, d, ns, nbr, nsrc, nrec, closed, nfpass, nbpass, nsv, nfdesc, nbdesc;
   int gb, gq, fb, fq, bb, bq;  // batches and quads of the gather, forward and backward programs
   int nlev, nent;              // factor levels and node-CSR entries of an item refactorised inside the loop, else 0
+  int nsw, line;               // closed form with switches: their number, doubles of the tail inversion's lines
   int bs;
 };
 struct StepLds {
   uint32_t cD, xr, J, flag, emf, vrow, pass, sv, dinv, fdesc, bdesc, fcol, brow, bpos, gmeta, gcode, grow, fmeta, fcode,
-      frow, bmeta, bcode, brw, rnode, rcolumn, rf_rowptr, rf_flev, rf_fent, rf_rows, rf_nptr, rf_nent, total;
+      frow, bmeta, bcode, brw, rnode, rcolumn, rf_rowptr, rf_flev, rf_fent, rf_rows, rf_nptr, rf_nent, line, gsw, swflag, total;
 };
 inline
 #ifdef __HIPCC__
@@ -119,6 +126,9 @@ inline
   o.J = take(s.nbr + 1 + (adjoint ? s.nrec : 0), 8);  // branch injections, a zero, the adjoint's seeds
   o.flag = take(adjoint ? 1 : 0, 4);
   o.emf = take(s.nsrc > 0 ? s.bs : 0, 8);
+  o.line = take(s.line, 8);
+  o.gsw = take(s.nsw, 8);
+  o.swflag = take(s.nsw > 0 ? 1 : 0, 4);
   o.vrow = take(adjoint ? s.n + 1 + s.nsrc : 0, 8);  // the earlier step's trajectory row, a zero between its parts
   if (!s.closed) o.pass = take(2 * (s.nfpass + s.nbpass + 2), 4);
   if (sm) {
@@ -162,7 +172,15 @@ enum StepKind : int {
   STEP_PLAIN = 0,   // nothing
   STEP_LINES = 1,   // distributed-parameter lines
   STEP_GROUPS = 2,  // coupled three-phase groups
-  STEP_FULL = 3,    // both, or level passes, diodes, controlled switches
+  STEP_FULL = 3,    // several of these, or level passes (in-loop LDL^T of diodes and controlled switches)
+  STEP_SWITCH = 4,  // diodes or controlled switches, closed form
+};
+
+// One diode or controlled switch of a closed-form item: its local branch, its
+// terminals and a controlled switch's measured nodes (local; the ground is the
+// item's zero node slot n).
+struct SwitchDesc {
+  int32_t br, k, m, a, b, control;
 };
 
 // One coupled three-phase group: its members' local branches and terminals
@@ -294,6 +312,7 @@ struct DevCtx {
   // controlled switches: per item-branch the measured node pair, item-local
   // (the ground is the item's zero node slot n); null when there is none
   const int32_t *bmeas;
+  const SwitchDesc *sw_tab;  // ItemDesc::swt + q
 };
 
 }  // namespace emt

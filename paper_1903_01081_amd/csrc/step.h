@@ -135,6 +135,10 @@ struct Lds {
   __device__ __forceinline__ T &operator[](int i) const { return reinterpret_cast<T *>(emt_lds + off)[i]; }
 };
 
+// LDS doubles of the tail inversion: two pivot rows and columns of up to dt
+// (a multiple of 32) entries.
+constexpr int tail_lines(int dt) { return 4 * ((dt + 31) / 32 * 32); }
+
 // A row program (closed.h) as a wave runs it: its batches b0 .. b1 - 1, the
 // first one's batch word, quad of codes and row id held in registers, the
 // rest in LDS (SM) or global memory.
@@ -170,6 +174,10 @@ struct View {
   Ref<uint16_t, SM> nent;
   Lds<int32_t> rf_rowptr, rf_flev, rf_fent_ptr;
   Lds<uint16_t> rf_rows;
+  // closed form with switches: the tail inversion's lines, the switches'
+  // conductances, the last step that changed one
+  Lds<double> line, gsw;
+  Lds<int32_t> swflag;
 };
 
 template <int BS, class T>
@@ -225,7 +233,8 @@ __device__ __forceinline__ void load_rows(const DevCtx &c, const RowProg &p, uin
 // The LDS layout is step_lds() (device.h), which the host sizes launches by.
 // LEV: the batch may hold components solved by level passes (the kernels
 // without them carry none of their scalars: those of both together spill).
-template <int BS, bool SM, bool LEV>
+// DT > 0: its items may have diodes or controlled switches in closed form.
+template <int BS, bool SM, bool LEV, int DT = 0>
 __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint) {
   const SymDesc sd = c.syms[it.sym];
   View<SM> v;
@@ -242,7 +251,8 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   v.nbpass = sd.nbpass;
   v.fvals = sd.fwd.nq * 256;
   const int32_t *g_nptr = c.nptr + it.nptr;
-  const bool dyn = it.n_diodes > 0;
+  const bool dyn = LEV && it.n_diodes > 0;
+  const int nsw = DT > 0 ? it.n_diodes : 0;
   const int ne = dyn ? g_nptr[v.n] : 0;
   const RowProg gp = adjoint ? it.ga : it.gf;
   // the closed form's values beyond what the LDS has room for stay in L2
@@ -250,7 +260,7 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   v.lim = SM ? nstage / 2 : 0;
   const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  v.closed,
                      sd.nfpass,  sd.nbpass, nstage,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
-                     sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, BS};
+                     sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, nsw, nsw > 0 ? tail_lines(DT) : 0, BS};
   const StepLds o = step_lds(sh, SM, adjoint);
   v.cD.off = o.cD;
   // closed form: the gather writes r (the tail's right-hand side where the
@@ -262,6 +272,9 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   v.flag.off = o.flag;
   v.emf.off = o.emf;
   v.vrow.off = o.vrow;
+  v.line.off = o.line;
+  v.gsw.off = o.gsw;
+  v.swflag.off = o.swflag;
   for (int q = threadIdx.x; q < (v.d + 31) / 32 * 32; q += BS) v.cD[q] = 0.0;
   if (threadIdx.x == 0) {
     v.x[v.n] = 0.0;  // the ground: every grounded terminal points here
@@ -361,18 +374,15 @@ __device__ __forceinline__ void load_tail(const double *W, int d, Tail<BS, DT> &
 
 // In-place Gauss-Jordan inverse of the symmetric positive definite d x d
 // matrix held in T's layout (zero past d): pivot p's row and column go
-// through `line` (LDS, tail_lines() doubles), one barrier per pivot. Returns
+// through `line` (LDS, tail_lines(DT) doubles), one barrier per pivot. Returns
 // the number of non-positive or non-finite pivots (the same in every lane).
 // Entries of the pivot's row and column take the general update a - c r / p
 // with (a, c) = (0, -1) and (a, r) = (0, 1).
 template <int BS, int DT>
-constexpr int tail_lines() {
-  return 2 * (Tail<BS, DT>::Q * 32 + Tail<BS, DT>::R * Tail<BS, DT>::G);
-}
-template <int BS, int DT>
 __device__ __forceinline__ int invert_tail(Tail<BS, DT> &T, int d, double *line) {
   constexpr int G = Tail<BS, DT>::G, R = Tail<BS, DT>::R, Q = Tail<BS, DT>::Q;
   static_assert(32 % G == 0, "a group's pivots share a column pair block");
+  static_assert(2 * (Q * 32 + R * G) <= tail_lines(DT), "two pivot rows and columns");
   constexpr int kBuf = Q * 32 + R * G;
   const int tid = (int)threadIdx.x;
   const int g = tid >> 4, j = tid & 15;
@@ -438,6 +448,121 @@ __device__ __forceinline__ int invert_tail(Tail<BS, DT> &T, int d, double *line)
       }
     }
   }
+  return bad;
+}
+
+// In-place factor of such a matrix A = L D L^T for a solve in two triangular
+// products: T ends as L^-1 on and below the diagonal and as its transpose
+// above it, dv as 1/D of the rows whose sums the lane gets in tail_solve
+// (A^-1 = L^-T D^-1 L^-1). For a component that a set of open switches leaves
+// nearly floating, a product with the explicit inverse rounds each row of a
+// large common potential by itself, and the differences between nodes are lost
+// (6e-8 in a six-pulse bridge; 2e-10 if the rows of L^-1 are scaled by
+// D^-1/2); here the common part is one number, injections into a floating
+// part cancel exactly, and L^-1 of an M-matrix is formed without
+// cancellation. Elimination below the pivot only, one barrier per pivot;
+// `tmp` holds d * d doubles of global memory.
+template <int BS, int DT>
+__device__ __forceinline__ int factor_tail(Tail<BS, DT> &T, int d, double *line, double *tmp,
+                                           double (&dv)[(Tail<BS, DT>::R + 3) / 4]) {
+  constexpr int G = Tail<BS, DT>::G, R = Tail<BS, DT>::R, Q = Tail<BS, DT>::Q;
+  static_assert(DT <= BS, "one lane per pivot's scale");
+  constexpr int kBuf = Q * 32 + R * G;
+  const int tid = (int)threadIdx.x;
+  const int g = tid >> 4, j = tid & 15;
+  int bad = 0;
+  double scale = 0.0;  // 1/D of pivot tid
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    constexpr int kStep = 2;
+    const int qk = k * G / 32;
+    for (int r0 = 0; r0 < G && k * G + r0 < d; r0 += kStep) {
+#pragma unroll
+      for (int b = 0; b < kStep; ++b) {
+        const int r = r0 + b, p = k * G + r;
+        if (p >= d) break;
+        double *prow = line + b * kBuf, *pcol = prow + Q * 32;
+        const bool in_col = j == ((p & 31) >> 1);
+        if (g == r) {
+#pragma unroll
+          for (int q = 0; q < Q; ++q)
+            reinterpret_cast<double2 *>(prow)[16 * q + j] =
+                make_double2(T.w[2 * (k * Q + q)], T.w[2 * (k * Q + q) + 1]);
+        }
+        if (in_col) {
+#pragma unroll
+          for (int i = k; i < R; ++i) pcol[g + i * G] = T.w[2 * (i * Q + qk) + b];
+        }
+        step_barrier<BS>();
+        const double piv = prow[p];
+        const bool ok = piv > 0.0 && piv < INFINITY;
+        bad += ok ? 0 : 1;
+        const double inv = ok ? 1.0 / piv : 0.0;
+        if (tid == p) scale = inv;
+        double rx[Q], ry[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const double2 rr = reinterpret_cast<const double2 *>(prow)[16 * q + j];
+          rx[q] = rr.x;
+          ry[q] = rr.y;
+        }
+        if (in_col) {
+          if (b == 0)
+            rx[qk] = 1.0;
+          else
+            ry[qk] = 1.0;
+        }
+#pragma unroll
+        for (int i = k; i < R; ++i) {
+          const bool below = i > k || g > r;
+          const double a = below ? pcol[g + i * G] : 0.0;
+          // a / piv to the last place: 1 where a floating part's row is the
+          // pivot's negative
+          double l = a * inv;
+          l = __builtin_fma(__builtin_fma(-l, piv, a), inv, l);
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            double wx = T.w[2 * (i * Q + q)], wy = T.w[2 * (i * Q + q) + 1];
+            if (q == qk && in_col && below) {
+              if (b == 0)
+                wx = 0.0;
+              else
+                wy = 0.0;
+            }
+            T.w[2 * (i * Q + q)] = __builtin_fma(-l, rx[q], wx);
+            T.w[2 * (i * Q + q) + 1] = __builtin_fma(-l, ry[q], wy);
+          }
+        }
+      }
+    }
+  }
+  // the transpose through memory, 1/D through LDS
+  __syncthreads();
+  if (tid < DT) line[tid] = scale;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int row = g + k * G;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int col = 32 * q + 2 * j + b;
+        if (row >= d || col > row) continue;
+        const double a = col == row ? 1.0 : T.w[2 * (k * Q + q) + b];
+        tmp[row * d + col] = a;
+        tmp[col * d + row] = a;
+      }
+  }
+  __syncthreads();
+  load_tail<BS, DT>(tmp, d, T);
+#pragma unroll
+  for (int k = 0; k < 2 * R * Q; ++k) settle(T.w[k]);
+#pragma unroll
+  for (int k = 0; k < R; k += 4) {
+    const int row = g + (k + (j & 3)) * G;
+    dv[k / 4] = row < d ? line[row] : 0.0;
+  }
+  __syncthreads();  // line and tmp are written again
   return bad;
 }
 
@@ -681,18 +806,70 @@ __device__ __forceinline__ void tail_solve(const View<SM> &v, const Tail<BS, DT>
   step_barrier<BS>();
 }
 
+// x_D = L^-T (D^-1 (L^-1 c)) with factor_tail's layout: two triangular
+// products, the vector between them in `line`. Blocks of a register row wholly on one side
+// of the diagonal take part in one of them only.
+template <int BS, int DT, bool SM>
+__device__ __forceinline__ void tail_solve_factored(const View<SM> &v, const Tail<BS, DT> &T, const double *dv) {
+  constexpr int G = Tail<BS, DT>::G, R = Tail<BS, DT>::R, Q = Tail<BS, DT>::Q;
+  const int tid = lane_id();
+  const int g = tid >> 4, j = tid & 15;
+  const bool b0 = j & 1, b1 = j & 2;
+  auto product = [&](int in, bool lower, auto out) {
+    const double2 *c = reinterpret_cast<const double2 *>(emt_lds + in);
+    double2 cc[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cc[q] = c[16 * q + j];
+#pragma unroll
+    for (int k0 = 0; k0 < R; k0 += 4) {
+      if (k0 > 0 && k0 * G >= v.d) break;
+      double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (q > 0 && 32 * q >= v.d) break;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int first = (k0 + k) * G, last = first + G - 1;  // the register row's rows
+          if (k0 + k >= R || (lower ? last < 32 * q : first > 32 * q + 31)) continue;
+          double cx = cc[q].x, cy = cc[q].y;
+          if (lower ? first < 32 * q + 31 : last > 32 * q) {
+            const int row = g + first, col = 32 * q + 2 * j;
+            if (lower ? col > row : col < row) cx = 0.0;
+            if (lower ? col + 1 > row : col + 1 < row) cy = 0.0;
+          }
+          acc[k] = __builtin_fma(T.w[2 * ((k0 + k) * Q + q)], cx, acc[k]);
+          acc[k] = __builtin_fma(T.w[2 * ((k0 + k) * Q + q) + 1], cy, acc[k]);
+        }
+      }
+      const double sum = sum16x4(acc[0], acc[1], acc[2], acc[3], b0, b1);
+      if (j < 4) out(g + (k0 + j) * G, k0 / 4, sum);
+    }
+    step_barrier<BS>();
+  };
+  product(v.cD.off, true, [&](int row, int k, double s) {
+    if (row < Q * 32) v.line[row] = s * dv[k];  // zero past d
+  });
+  product(v.line.off, false, [&](int row, int, double s) {
+    if (row < v.d) v.x[v.ns + row] = s;
+  });
+}
+
 // The solve after the gather: closed form (c = r_D + N r_S, x_D = W c,
 // x_S = Q r_S + N^T x_D; a component that is all tail gathers straight into
 // c), or the level passes around the tail.
-template <int BS, int DT, bool SM, bool LEV>
-__device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail<BS, DT> &T) {
+template <int BS, int DT, bool SM, bool LEV, bool SW = false>
+__device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail<BS, DT> &T, const double *dv = nullptr,
+                                                   bool factored = false) {
   if (!LEV || v.closed) {
     if (v.d > 0) {
       if (v.ns > 0) {
         value_rows<SM>(v, v.fwd, 0, [&](int row, double s) { v.cD[row] = s; });
         step_barrier<BS>();
       }
-      tail_solve<BS, DT, SM>(v, T);
+      if (SW && factored)
+        tail_solve_factored<BS, DT, SM>(v, T, dv);
+      else
+        tail_solve<BS, DT, SM>(v, T);
     }
     if (v.ns > 0) {
       value_rows<SM>(v, v.bwd, v.fvals, [&](int row, double s) { v.x[row] = s; });
@@ -1193,6 +1370,88 @@ __device__ __forceinline__ uint32_t diode_flips(const DevCtx &c, const ItemDesc 
   return fl;
 }
 
+// Diodes and controlled switches of a closed-form item (the rules are
+// diode_flips'), one lane each, whose parameters and state stay in registers;
+// any past BS lanes go through memory. A change is noted in the stored state,
+// the conductance list and the flag; the tail's matrix and the branch slots
+// follow at the start of the next step.
+struct SwitchLane {
+  SwitchDesc d;
+  double E, w, ph, C, h, gon, ref;
+  bool on;
+};
+
+__device__ __forceinline__ void switch_load(const DevCtx &c, const ItemDesc &it, int q, SwitchLane &s) {
+  s.d = c.sw_tab[it.swt + q];
+  const int64_t gb = it.br + s.d.br;
+  s.E = c.bE[gb];
+  s.w = c.bw[gb];
+  s.ph = c.bph[gb];
+  s.C = c.bC[gb];
+  s.h = c.bL[gb];
+  s.gon = 1.0 / c.bR[gb];
+  s.on = c.dstate[gb] != 0;
+}
+
+// A controlled switch's reference at step n (ahead of the solve).
+__device__ __forceinline__ void switch_reference(const DevCtx &c, SwitchLane &s, int64_t n) {
+  if (!s.d.control) return;
+  s.ref = s.C;
+  if (s.E != 0.0) s.ref = s.E * emf_cos(s.w * ((double)n * c.dt) + s.ph) + s.C;
+}
+
+// The state from step n + 1 on.
+template <bool SM>
+__device__ __forceinline__ void switch_step(const DevCtx &c, const ItemDesc &it, const View<SM> &v, SwitchLane &s,
+                                            int q, int64_t n) {
+  bool next;
+  if (s.d.control) {
+    const double e = s.ref - (v.x[s.d.a] - v.x[s.d.b]);
+    next = e > s.h ? true : (e < -s.h ? false : s.on);
+  } else {
+    const double du = v.x[s.d.k] - v.x[s.d.m];
+    next = s.on ? !(s.gon * du < 0.0) : (du > 0.0);
+  }
+  if (next != s.on) {
+    s.on = next;
+    c.dstate[it.br + s.d.br] = next ? 1 : 0;
+    v.gsw[q] = next ? s.gon : 0.0;
+    v.swflag[0] = (int)n;
+  }
+}
+
+// The tail's factor of a closed-form item with switches: their conductances stamped on the
+// tail's matrix S (k_closed left a copy per topology in the item's scratch),
+// inverted in the lanes' registers. The clusters' parts Q and N do not see
+// them. One barrier per pivot of the tail, about 450 cycles each, against two
+// barriers of about 2 us per level of the whole elimination tree (and no
+// dense tail for the steps in between) when the component was factorised
+// anew.
+template <int BS, int DT, bool SM>
+__device__ __forceinline__ void refactor_tail(const DevCtx &c, const ItemDesc &it, const View<SM> &v, int t,
+                                              Tail<BS, DT> &w, double (&dv)[(Tail<BS, DT>::R + 3) / 4]) {
+  const int d = v.d;
+  const double *S0 = c.wtail + it.w + (int64_t)t * d * d;
+  double *S = c.dyn + it.dyn + (int64_t)t * d * d;
+  for (int k = (int)threadIdx.x; k < it.n_swkey; k += BS) {
+    const int key = c.symi[it.swkey + k], e1 = c.symi[it.swptr + k + 1];
+    double s = S0[key];
+    for (int e = c.symi[it.swptr + k]; e < e1; ++e) {
+      const int term = c.symi[it.swterm + e];
+      const double g = v.gsw[term >> 1];
+      s = (term & 1) ? s - g : s + g;
+    }
+    S[key] = s;
+  }
+  __syncthreads();
+  load_tail<BS, DT>(S, d, w);
+#pragma unroll
+  for (int k = 0; k < 2 * Tail<BS, DT>::R * Tail<BS, DT>::Q; ++k) settle(w.w[k]);
+  const int bad = factor_tail<BS, DT>(w, d, reinterpret_cast<double *>(emt_lds + v.line.off),
+                                      c.dyn + it.dyn + (int64_t)it.n_topo * d * d, dv);
+  if (bad && threadIdx.x == 0) atomicAdd(c.flags + 4, bad);
+}
+
 // The diode slots' conductances from their stored state.
 template <int BS, int BPT>
 __device__ __forceinline__ void diode_conductances(const DevCtx &c, const ItemDesc &it, Lane<BPT> &L,
@@ -1437,7 +1696,7 @@ template <int BS, int BPT, int DT, bool SM, int KIND>
 __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, int64_t n0, int64_t nsteps,
                                                 double *rec) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, KIND == STEP_FULL>(c, it, false);
+  View<SM> v = make_view<BS, SM, KIND == STEP_FULL, KIND == STEP_SWITCH ? DT : 0>(c, it, false);
   const int64_t *topo = c.topo + it.topo;
   int t = topo_of(topo, it.n_topo, n0 + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
@@ -1445,9 +1704,12 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   Tail<BS, DT> w;
   load_lane<BS, BPT>(c, it, L);
   load_coefs<BS, BPT>(c, it, t, L.g, L.be);
-  const bool diodes = KIND == STEP_FULL && it.n_diodes > 0;  // diodes or controlled switches
+  // diodes or controlled switches: refactorised by levels, or (switches) the
+  // closed form's tail
+  const bool diodes = KIND == STEP_FULL && it.n_diodes > 0;
+  const bool switches = KIND == STEP_SWITCH && it.n_diodes > 0;
   uint32_t dmask = 0, cmask = 0;
-  if (diodes) {
+  if (diodes || switches) {
 #pragma unroll
     for (int j = 0; j < BPT; ++j) {
       const int kd = c.bkind[it.br + threadIdx.x + j * BS];
@@ -1464,6 +1726,25 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     refactor_dynamic<BS, BPT, SM>(c, it, v, L);
   } else {
     select_factor<BS, DT, SM>(c, it, v, t, w);
+  }
+  double dv[(Tail<BS, DT>::R + 3) / 4];
+  SwitchLane sl;
+  sl.on = false;
+  sl.d.control = 0;
+  if (switches) {
+    const int nsw = it.n_diodes;
+    for (int q = (int)threadIdx.x + BS; q < nsw; q += BS) {
+      SwitchLane s;
+      switch_load(c, it, q, s);
+      v.gsw[q] = s.on ? s.gon : 0.0;
+    }
+    if ((int)threadIdx.x < nsw) {
+      switch_load(c, it, (int)threadIdx.x, sl);
+      v.gsw[(int)threadIdx.x] = sl.on ? sl.gon : 0.0;
+    }
+    if (threadIdx.x == 0) v.swflag[0] = (int)n0 - 1;
+    __syncthreads();
+    refactor_tail<BS, DT, SM>(c, it, v, t, w, dv);
   }
   inject<BS, BPT, SM>(c, v, L, n0 + 1);
   step_barrier<BS>();
@@ -1497,6 +1778,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     return ck_step < m ? ck_step : m;
   };
   int64_t special = special_step();
+  bool fresh = false;  // switches: the topology changed
   // the adjoint's trajectory rows (batches with checkpoints have no lines,
   // groups or diodes)
   double *rows = nullptr;
@@ -1504,8 +1786,33 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     if (lines) lines_ahead<BS, NL>(it, ln, n);
+    int changed = 0;
+    if (switches) {
+      changed = v.swflag[0];
+      if ((int)threadIdx.x < it.n_diodes) switch_reference(c, sl, n);
+    }
     gather_all<BS, SM>(v);
-    solve_after_gather<BS, DT, SM, KIND == STEP_FULL>(v, w);
+    if (switches) {
+      // a switch changed state after the last step, or the topology changed
+      if (fresh || __builtin_amdgcn_readfirstlane(changed) == (int)n - 1) {
+        __syncthreads();  // the states stored by other lanes
+        diode_conductances<BS, BPT>(c, it, L, dmask);
+#pragma unroll
+        for (int j = 0; j < BPT; ++j) settle(L.g[j]);
+        refactor_tail<BS, DT, SM>(c, it, v, t, w, dv);
+        fresh = false;
+      }
+    }
+    solve_after_gather<BS, DT, SM, KIND == STEP_FULL, KIND == STEP_SWITCH>(v, w, dv, switches);
+    if (switches) {
+      if ((int)threadIdx.x < it.n_diodes) switch_step<SM>(c, it, v, sl, (int)threadIdx.x, n);
+      for (int q = (int)threadIdx.x + BS; q < it.n_diodes; q += BS) {
+        SwitchLane s;
+        switch_load(c, it, q, s);
+        switch_reference(c, s, n);
+        switch_step<SM>(c, it, v, s, q, n);
+      }
+    }
     if (lines) lines_settle<BS, NL>(it, ln);
     if (rows) {
       store_row<BS, BPT, SM>(v, L, rows);
@@ -1517,7 +1824,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       for (int q = tid0 + BS; q < v.nrec; q += BS) row[v.rcolumn[q]] = v.x[v.rnode[q]];
       row += R;
     }
-    if (KIND == STEP_PLAIN && n != special) {
+    if ((KIND == STEP_PLAIN || KIND == STEP_SWITCH) && n != special) {
       update_plain<BS, BPT, SM, false>(v, L, nullptr);
       if (rec0) {
         *at0 = rv0;
@@ -1526,7 +1833,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       step_barrier<BS>();
       continue;
     }
-    if (KIND != STEP_PLAIN && n != special && !diodes) {
+    if (KIND != STEP_PLAIN && KIND != STEP_SWITCH && n != special && !diodes) {
       update_plain<BS, BPT, SM, false, true>(v, L, nullptr);
       if (lines || groups) {
         step_barrier<BS>();
@@ -1553,7 +1860,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       st_i = c.si + it.br;
       st_u = c.su + it.br;
     }
-    update_inject<BS, BPT, SM, KIND != STEP_PLAIN>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
+    update_inject<BS, BPT, SM, KIND != STEP_PLAIN && KIND != STEP_SWITCH>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
                                n < n_end, n);
     if (rec0) {
       *at0 = rv0;
@@ -1576,6 +1883,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       ++t;
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
       if (!diodes) select_factor<BS, DT, SM>(c, it, v, t, w);
+      fresh = switches;
     }
     special = special_step();
     step_barrier<BS>();
