@@ -422,7 +422,7 @@ int choose_tail(const Symbolic &S, int dmax) {
   return best_d;
 }
 
-Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim) {
+Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim, bool switches_last) {
   if (!nets || n_scen < 1) fail(EMT_EINVAL, "need at least one network");
   if (!(sim.dt > 0) || !std::isfinite(sim.dt)) fail(EMT_EINVAL, "dt must be positive and finite");
   if (sim.n_steps < 1) fail(EMT_EINVAL, "n_steps must be >= 1");
@@ -604,7 +604,7 @@ Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim) {
       // all lie in the dense tail: a change of their state then changes the
       // tail's matrix alone (closed.h). Not for solvers without a tail.
       std::vector<uint8_t> last(n, 0);
-      if (sim.solver == EMT_SOLVER_AUTO) {
+      if (sim.solver == EMT_SOLVER_AUTO && switches_last) {
         int cnt = 0;
         for (int b = 0; b < B; ++b) {
           if (net.kind[b] != EMT_DIODE && net.kind[b] != EMT_CSWITCH) continue;
@@ -615,6 +615,7 @@ Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim) {
             }
         }
         if (cnt > kMaxSwitchNodes) std::fill(last.begin(), last.end(), 0);
+        A.switches_last = A.switches_last || (cnt > 0 && cnt <= kMaxSwitchNodes);
         for (int v = 0; v < n; ++v)
           if (last[v]) key.push_back(-1 - (int64_t)v);
       }

@@ -108,10 +108,13 @@ struct Analysis {
   std::vector<Item> items;
   std::vector<Scenario> scens;
   int rec_stride = 0, param_stride = 0, max_topo = 1;
+  bool switches_last = false;  // some component's switch terminals are ordered last
 };
 
 // Validates and analyses; throws Error on invalid input or singular topology.
-Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim);
+// switches_last: order the terminals of diodes and controlled switches last
+// (for the closed form; it costs fill where the factor is used as it is).
+Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim, bool switches_last = true);
 
 void fill_info(const Analysis &a, emt_info *info);
 

@@ -654,6 +654,11 @@ static void build_comp(emt_ctx &c, const emt_net *nets) {
   c.comp_max_rank = P.max_rank;
 }
 
+// Thrown by upload_all where components with diodes or controlled switches,
+// whose terminals the analysis ordered last, are factorised by levels: the
+// build starts again without that order.
+struct SwitchesByLevels {};
+
 static void upload_all(emt_ctx &c, const emt_net *nets) {
   using namespace emt;
   Analysis &A = c.A;
@@ -797,6 +802,17 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   // closed form would be too dense.
   std::vector<char> closed(A.syms.size(), 0);
   std::vector<double> sym_lds(A.syms.size(), 0.0);  // injections and their sums' codes
+  // what the closed form keeps in LDS whatever is staged there (step_lds),
+  // and whether every item of the pattern has switches where one has
+  std::vector<int64_t> sym_fixed(A.syms.size(), 0);
+  std::vector<char> all_diode(A.syms.size(), 1);
+  for (size_t q = 0; q < A.items.size(); ++q) {
+    const Item &it = A.items[q];
+    const int64_t nrec = K > 0 ? (int64_t)it.rec_node.size() : 0;
+    sym_fixed[it.sym] = std::max(sym_fixed[it.sym], 8 * (2 * ((int64_t)it.n + 1) + it.n_br + 1 + nrec + bs + 192) + 256);
+    if (item_diode[q]) sym_fixed[it.sym] = std::max(sym_fixed[it.sym], 8 * (2 * ((int64_t)it.n + 1) + 2 * (int64_t)it.n_br + bs + 5 * 192) + 256);
+    all_diode[it.sym] = all_diode[it.sym] && item_diode[q];
+  }
   for (const Item &it : A.items)
     sym_lds[it.sym] = std::max(sym_lds[it.sym], 8.0 * it.n_br + 3.0 * it.nptr[it.n] + 4.0 * (double)it.rec_node.size());
   for (size_t q = 0; q < A.syms.size(); ++q) {
@@ -831,9 +847,12 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
             if (v >= 0) d_min = std::max(d_min, n - v);
         }
       }
-      may = d_min <= closed_tail_max(bs);
+      // (an item of the same pattern without any, where they are not ordered
+      // last, would need the tail's inverse beside the matrix)
+      may = d_min <= closed_tail_max(bs) && all_diode[q] && A.switches_last;
     }
-    if (!may || 2 * (n + 1) > 65535) continue;
+    // level passes need less LDS
+    if (!may || sym_fixed[q] > max_lds || 2 * (n + 1) > 65535) continue;
     const bool fixed = solver == EMT_SOLVER_DENSE || (forced_tail >= 0 && !sym_diode[q]);
     const std::vector<ClosedSize> z = closed_sizes(A.syms[q], fixed ? d : closed_tail_max(bs));
     double best = levels_cost(plans[q]);
@@ -851,6 +870,13 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     closed[q] = sym_diode[q] ? 2 : 1;
     if (best_d != d) plans[q] = plan_sweeps(A.syms[q], best_d);
   }
+  // Components with switches that go by levels after all: their terminals
+  // are not ordered last then.
+  auto by_levels = [&]() {
+    if (A.switches_last) throw SwitchesByLevels{};
+  };
+  for (size_t q = 0; q < A.syms.size(); ++q)
+    if (sym_diode[q] && !closed[q] && !sym_split[q] && solver == EMT_SOLVER_AUTO) by_levels();
   // the forward kernel's kind
   bool any_line = false, any_group = false, any_level = false, any_switch = false;
   for (const Item &it : A.items) {
@@ -863,6 +889,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   if (any_switch && (any_line || any_group || any_level)) {
     // only the general kernel runs these together, and it factorises
     // components with diodes or controlled switches by levels
+    by_levels();
     for (size_t q = 0; q < A.syms.size(); ++q)
       if (closed[q] == 2) {
         closed[q] = 0;
@@ -924,6 +951,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   };
   plan_gathers();
   int sv_cap = INT32_MAX / 512 * 256;
+  int row_global = 0;
   auto step_shape = [&](int q, bool adj) {
     const Item &it = A.items[q];
     const SweepPlan &P = plans[it.sym];
@@ -960,6 +988,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       z.nent = it.nptr[it.n];
     }
     z.bs = bs;
+    z.row_global = row_global;
     return z;
   };
   auto item_lds = [&](int q, bool adj) { return (size_t)step_lds(step_shape(q, adj), true, adj).total; };
@@ -991,6 +1020,13 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, K > 0), false, true).total);
       if (!closed[it.sym] && plans[it.sym].nsv() > 65535)
         throw Error{EMT_EINVAL, "a connected component's factor is too large"};
+    }
+    // no room for the adjoint's trajectory row beside an item's other arrays
+    if (K > 0 && a_gl > (size_t)max_lds && !row_global) {
+      row_global = 1;
+      a_gl = 0;
+      for (int q = 0; q < NI; ++q)
+        if (!c.is_split[q] && !comp) a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, true), false, true).total);
     }
     c.sm_fwd = f_sm <= (size_t)max_lds && !sim.sweep_from_global;
     c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global;
@@ -1585,6 +1621,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.K = K;
   dc.rec_stride = A.rec_stride;
   dc.sv_cap = sv_cap;
+  dc.row_global = row_global;
   c.d_order = c.upload(order);
   c.d_pairs = c.upload(pairs);
   c.d_closed = c.upload(closed_pairs);
@@ -1792,10 +1829,18 @@ emt_status emt_build(const emt_net *nets, int32_t n_scen, const emt_sim *sim, em
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return set_error(EMT_EDEVICE, "no HIP device");
     std::unique_ptr<emt_ctx> c(new emt_ctx);
-    c->A = std::move(A);
-    c->sim = *sim;
-    hip_check(hipGetDevice(&c->device), "hipGetDevice");
-    upload_all(*c, nets);
+    auto upload = [&](emt::Analysis a) {
+      c->A = std::move(a);
+      c->sim = *sim;
+      hip_check(hipGetDevice(&c->device), "hipGetDevice");
+      upload_all(*c, nets);
+    };
+    try {
+      upload(std::move(A));
+    } catch (const SwitchesByLevels &) {
+      c.reset(new emt_ctx);
+      upload(emt::analyze(nets, n_scen, *sim, false));
+    }
     hip_check(emt::launch_companions(c->dc, c->ca, nullptr), "companions");
     hip_check(emt::launch_reset(c->dc, c->d_bitem, c->d_blocal, c->nbr_total, c->nodes_total, c->ring_doubles, nullptr), "reset");
     hip_check(hipDeviceSynchronize(), "build");

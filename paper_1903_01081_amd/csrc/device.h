@@ -103,6 +103,7 @@ struct StepShape {
   int nlev, nent;              // factor levels and node-CSR entries of an item refactorised inside the loop, else 0
   int nsw, line;               // closed form with switches: their number, doubles of the tail inversion's lines
   int bs;
+  int row_global;              // adjoint: the earlier step's trajectory row is read from memory
 };
 struct StepLds {
   uint32_t cD, xr, J, flag, emf, vrow, pass, sv, dinv, fdesc, bdesc, fcol, brow, bpos, gmeta, gcode, grow, fmeta, fcode,
@@ -129,8 +130,7 @@ inline
   o.line = take(s.line, 8);
   o.gsw = take(s.nsw, 8);
   o.swflag = take(s.nsw > 0 ? 1 : 0, 4);
-  o.vrow = take(adjoint ? s.n + 1 + s.nsrc : 0, 8);  // the earlier step's trajectory row, a zero between its parts
-  if (!s.closed) o.pass = take(2 * (s.nfpass + s.nbpass + 2), 4);
+  o.vrow = take(adjoint && !s.row_global ? s.n + 1 + s.nsrc : 0, 8);  // the earlier step's trajectory row, a zero between its parts
   if (sm) {
     o.gmeta = take(waves + 1 + s.gb, 4);
     o.gcode = take(s.gq * 256, 2);
@@ -144,6 +144,7 @@ inline
       o.bcode = take(s.bq * 256, 2);
       o.brw = take(s.bb * 64, 2);
     } else {
+      o.pass = take(2 * (s.nfpass + s.nbpass + 2), 4);
       o.dinv = take(s.ns, 8);
       o.fdesc = take(s.nfdesc, 8);
       o.bdesc = take(s.nbdesc, 8);
@@ -286,6 +287,9 @@ struct DevCtx {
   // checkpoints
   double *vt;
   int32_t vt_full;
+  // 1: no room in the LDS for a trajectory row beside the largest component's
+  // arrays (the adjoint's kernels without staged factors only)
+  int32_t row_global;
   int32_t *flags;  // [0] = bad pivots
   double dt;
   int64_t T;

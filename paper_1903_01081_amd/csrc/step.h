@@ -160,7 +160,7 @@ struct View {
   int n, d, ns, nbr, nreal, nsrc, nsv, nrec;  // nbr: padded to whole lane slots; nreal: not
   int closed, nfpass, nbpass, fvals;   // fvals: values of the forward program
   Rows<SM> gather, fwd, bwd;
-  Lds<int32_t> pass;  // level passes: (first descriptor, log2 lanes) pairs, forward then backward
+  Ref<int32_t, SM> fpass, bpass;  // level passes: (first descriptor, log2 lanes) pairs
   Ref<uint64_t, SM> fdesc, bdesc;
   Ref<uint16_t, SM> fcol, brow, bpos, rnode, rcolumn;
   Lds<double> r, x, J, cD, sv_s, dinv_s, emf, vrow;  // x has n+1 entries, x[n] = 0; r: where the gather writes
@@ -260,7 +260,8 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   v.lim = SM ? nstage / 2 : 0;
   const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  v.closed,
                      sd.nfpass,  sd.nbpass, nstage,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
-                     sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, nsw, nsw > 0 ? tail_lines(DT) : 0, BS};
+                     sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, nsw, nsw > 0 ? tail_lines(DT) : 0, BS,
+                     SM ? 0 : c.row_global};
   const StepLds o = step_lds(sh, SM, adjoint);
   v.cD.off = o.cD;
   // closed form: the gather writes r (the tail's right-hand side where the
@@ -279,18 +280,22 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   if (threadIdx.x == 0) {
     v.x[v.n] = 0.0;  // the ground: every grounded terminal points here
     v.J[v.nbr] = 0.0;
-    if (adjoint) v.vrow[v.n] = 0.0;
+    if (adjoint && (SM || !c.row_global)) v.vrow[v.n] = 0.0;
     reinterpret_cast<double *>(emt_lds + o.xr)[v.n] = 0.0;
   }
   load_rows<BS, SM>(c, gp, o.gmeta, o.gcode, o.grow, v.gather);
   if (v.closed) {
     load_rows<BS, SM>(c, sd.fwd, o.fmeta, o.fcode, o.frow, v.fwd);
     load_rows<BS, SM>(c, sd.bwd, o.bmeta, o.bcode, o.brw, v.bwd);
-  } else {
-    v.pass.off = o.pass;
+  } else if constexpr (SM) {
     const int nf = 2 * (v.nfpass + 1), nb = 2 * (v.nbpass + 1);
+    v.fpass.off = o.pass;
+    v.bpass.off = o.pass + 4 * nf;
     copy_to<BS>(o.pass, c.symi + sd.fpass, nf);
     copy_to<BS>(o.pass + 4 * nf, c.symi + sd.bpass, nb);
+  } else {
+    v.fpass.p = c.symi + sd.fpass;
+    v.bpass.p = c.symi + sd.bpass;
   }
   if constexpr (SM) {
     v.sv_s.off = v.sv.off = o.sv;
@@ -877,17 +882,16 @@ __device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail
     }
     return;
   }
-  auto pass = [&](int i) { return __builtin_amdgcn_readfirstlane(v.pass[i]); };
+  auto pass = [](const Ref<int32_t, SM> &p, int i) { return __builtin_amdgcn_readfirstlane(p[i]); };
   for (int k = 0; k < v.nfpass; ++k) {
-    const int p0 = pass(2 * k), lg = pass(2 * k + 1), p1 = pass(2 * k + 2);
+    const int p0 = pass(v.fpass, 2 * k), lg = pass(v.fpass, 2 * k + 1), p1 = pass(v.fpass, 2 * k + 2);
     // the last forward pass of an item with a dense tail is the tail rows'
     const bool tail_rows = v.d > 0 && k == v.nfpass - 1;
     forward_pass<BS, SM>(v, p0, p1, lg, tail_rows ? v.cD.off : v.x.off, tail_rows ? v.ns : 0);
   }
   if (v.d > 0) tail_solve<BS, DT, SM>(v, T);
-  const int o = 2 * (v.nfpass + 1);
   for (int k = 0; k < v.nbpass; ++k) {
-    const int p0 = pass(o + 2 * k), lg = pass(o + 2 * k + 1), p1 = pass(o + 2 * k + 2);
+    const int p0 = pass(v.bpass, 2 * k), lg = pass(v.bpass, 2 * k + 1), p1 = pass(v.bpass, 2 * k + 2);
     backward_pass<BS, SM>(v, p0, p1, lg);
   }
 }
@@ -2122,17 +2126,25 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
   adjoint_seed<BS, BPT, SM>(c, it, v, L, t, t_nx, hb_nx, load_seed<SM>(c, it, v, dJ, hi), dJ, hi);
   // a row's entry q in v.vrow: past the voltages comes the ground's zero
   auto at = [&](int q) { return q < v.n ? q : q + 1; };
+  // the row at hand: in LDS, or (a component whose arrays leave no room for
+  // it) in memory, without the zero
+  const bool row_lds = SM || !c.row_global;
+  const double *at_row = rows + (hi - lo - 1) * (int64_t)len;
+  auto row_at = [&](int q) {
+    if (row_lds) return (double)v.vrow[q];
+    return q == v.n ? 0.0 : at_row[q < v.n ? q : q - 1];
+  };
   // the voltages of a row in the lane's slots, with the conductances that
   // tell a branch out of service
   auto row_u = [&](int j, double g) {
     const uint32_t pk = opaque(L.pk[j]);
-    const double vk = v.vrow[pk & kTermGround], vm = v.vrow[(pk >> 15) & kTermGround];
-    const double e = j == 0 && tid0 < v.nsrc ? v.vrow[v.n + 1 + tid0] : 0.0;
+    const double vk = row_at((int)(pk & kTermGround)), vm = row_at((int)((pk >> 15) & kTermGround));
+    const double e = j == 0 && tid0 < v.nsrc ? row_at(v.n + 1 + tid0) : 0.0;
     const double u = j == 0 ? (vk - vm) - e : vk - vm;
     return g == 0.0 ? 0.0 : u;
   };
-  {
-    const double *row = rows + (hi - lo - 1) * (int64_t)len;
+  if (row_lds) {
+    const double *row = at_row;
     for (int q = tid0; q < len; q += BS) v.vrow[at(q)] = row[q];
   }
   step_barrier<BS>();
@@ -2144,7 +2156,7 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
   // the lane's entries of row m, read a step before they are needed
   double r0 = 0.0, r1 = 0.0;
   auto read_ahead = [&](int64_t m) {
-    if (m <= lo) return;
+    if (m <= lo || !row_lds) return;
     const double *row = rows + (m - lo - 1) * (int64_t)len;
     if (tid0 < len) r0 = row[tid0];
     if (tid0 + BS < len) r1 = row[tid0 + BS];
@@ -2159,7 +2171,8 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
     const double *i0 = from_ck ? c.ck_i + cko : seg_i + (n - lo - 2) * (int64_t)nbr;
     const double *row = rows + (n - lo - 2) * (int64_t)len;
     const int tid = lane_id();
-    if (!from_ck) {
+    at_row = row;
+    if (!from_ck && row_lds) {
       if (tid0 < len) v.vrow[at(tid0)] = r0;
       if (tid0 + BS < len) v.vrow[at(tid0 + BS)] = r1;
       for (int q = tid0 + 2 * BS; q < len; q += BS) v.vrow[at(q)] = row[q];
@@ -2179,13 +2192,13 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
       // no checkpoint and no topology change on either side: the update and
       // the next step's injections slot by slot (out of service: hbar = 0,
       // and u only ever meets that zero)
-      const double e = tid < v.nsrc ? v.vrow[v.n + 1 + tid] : 0.0;
+      const double e = tid < v.nsrc ? row_at(v.n + 1 + tid) : 0.0;
 #pragma unroll
       for (int j = 0; j < BPT; ++j) {
         if (j > 0 && (j & 1) == 0 && j * BS >= v.nreal) break;
         const uint32_t pk = opaque(L.pk[j]);
         const int k = (int)(pk & kTermGround), m = (int)((pk >> 15) & kTermGround);
-        const double wk = v.x[k], wm = v.x[m], vk = v.vrow[k], vm = v.vrow[m];
+        const double wk = v.x[k], wm = v.x[m], vk = row_at(k), vm = row_at(m);
         const double up = j == 0 ? (vk - vm) - e : vk - vm;
         const double hb = L.g[j] != 0.0 ? L.be[j] * hb_nx[j] - (wk - wm) : 0.0;
         gb[j] = __builtin_fma(hb, un[j], gb[j]);
