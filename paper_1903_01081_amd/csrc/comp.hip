@@ -238,6 +238,23 @@ __device__ __forceinline__ int64_t uni64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// acc += z[u] * x of lane u of the lane's 16-lane row, u = 0 .. 7 in turn: the
+// row's lanes hold eight consecutive entries of the right-hand side (twice)
+// and the multiply-add itself broadcasts one (DPP row_newbcast): a
+// wave reads 8 bytes of LDS per lane for eight rows of Z where broadcast reads
+// took 64. By itself that gained nothing (400 x 600 nodes, 3000 steps: 42.1 ->
+// 42.9 ms), so LDS reads do not bound the product; with the row buffers below
+// it is 42.3 -> 41.1 ms and 126 -> 121 VGPRs at six slots a lane. s_nop: a DPP operand is read two wait states after a
+// VALU instruction has written it.
+__device__ __forceinline__ void fma_rows8(double &acc, double x, const double (&z)[8]) {
+#define EMT_FMA(U, Z) "v_fmac_f64_dpp %0, %1, %" #Z " row_newbcast:" #U " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" EMT_FMA(0, 2) EMT_FMA(1, 3) EMT_FMA(2, 4) EMT_FMA(3, 5) EMT_FMA(4, 6) EMT_FMA(5, 7)
+          EMT_FMA(6, 8) EMT_FMA(7, 9)
+      : "+v"(acc)
+      : "v"(x), "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]), "v"(z[4]), "v"(z[5]), "v"(z[6]), "v"(z[7]));
+#undef EMT_FMA
+}
+
 enum { M_SCEN = 0, M_NSRC, M_NREC, M_NTOPO, M_MOD0, M_R, M_K, M_M = M_K + 4 };
 enum { M64_BR = 8, M64_COEF, M64_NODE, M64_TOPO };
 
@@ -380,7 +397,7 @@ __global__ __launch_bounds__(1024) void k_comp(DevCtx c, CompCtx cc, int Q, int6
   const int kc = ((n + KS - 1) / KS + kChunk - 1) / kChunk * kChunk;
   const int KSe = (n + kc - 1) / kc;  // splits with a non-empty k range (<= KS)
   const int k0 = pg * kc, k1 = (pg + 1) * kc < n ? (pg + 1) * kc : n;
-  const bool prod = pg < KSe && pr < n;
+  const bool prod = pg < KSe;  // whole waves: every lane of a DPP row must be there
   for (int64_t s = n0 + 1; s <= n_end; ++s) {
     // gather: every (item, node) pair of the workgroup, the right-hand
     // side into the item's x in the base's node order
@@ -418,68 +435,66 @@ __global__ __launch_bounds__(1024) void k_comp(DevCtx c, CompCtx cc, int Q, int6
       double w[kCompQMax];
 #pragma unroll
       for (int q = 0; q < kCompQMax; ++q) w[q] = 0.0;
-      const double *zc = Z + opaque(pr);
       constexpr int CH = 8;
       const int nch = (k1 - k0) / CH, kf = k0 + nch * CH;
+      const uint32_t zoff = (uint32_t)(pr < n ? opaque(pr) : n - 1) * 8u;
+      const int l8 = step::lane_id() & 7;
+      // the lane's entries of eight rows of Z
+      auto load_rows = [&](double (&z)[CH], int k) {
+        const char *row = reinterpret_cast<const char *>(Z + (int64_t)k * n);
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          z[u] = *reinterpret_cast<const double *>(row + (int64_t)u * n * 8 + zoff);
+      };
+      auto multiply = [&](const double (&z)[CH], int k) {
+#pragma unroll
+        for (int q = 0; q < kCompQMax; ++q) {
+          if (q >= nq) break;
+          fma_rows8(w[q], reinterpret_cast<const double *>(emt_lds + q * S.bytes + S.x)[k + l8], z);
+        }
+      };
       // the workgroups of a family walk their chunks from different starts,
       // so that they do not all ask the same L2 channels for the same rows
       // at once
       const int c0 = nch > 0 ? (int)(blockIdx.x % (unsigned)nch) : 0;
-      double zb[CH];
+      auto row_of = [&](int ci) { return k0 + (c0 + ci < nch ? c0 + ci : c0 + ci - nch) * CH; };
+      // two buffers in turn, without copies and without a condition around
+      // the loads: either made every multiply wait for the loads just issued
+      double za[CH], zb[CH];
       if (nch > 0) {
-        const int ks = k0 + c0 * CH;
-#pragma unroll
-        for (int u = 0; u < CH; ++u) zb[u] = zc[(int64_t)(ks + u) * n];
-      }
-      for (int ci = 0; ci < nch; ++ci) {
-        int cc0 = c0 + ci;
-        if (cc0 >= nch) cc0 -= nch;
-        const int k = k0 + cc0 * CH;
-        int cn = cc0 + 1;
-        if (cn >= nch) cn -= nch;
-        const int kn = k0 + cn * CH;
-        double zn[CH];
-        const bool more = ci + 1 < nch;
-        if (more) {
-#pragma unroll
-          for (int u = 0; u < CH; ++u) zn[u] = zc[(int64_t)(kn + u) * n];
+        load_rows(za, row_of(0));
+        int ci = 0;
+        for (; ci + 2 < nch; ci += 2) {
+          load_rows(zb, row_of(ci + 1));
+          multiply(za, row_of(ci));
+          load_rows(za, row_of(ci + 2));
+          multiply(zb, row_of(ci + 1));
         }
-#pragma unroll
-        for (int q = 0; q < kCompQMax; ++q) {
-          if (q >= nq) break;
-          const double2 *xb = reinterpret_cast<const double2 *>(
-              reinterpret_cast<const double *>(emt_lds + q * S.bytes + S.x) + k);
-#pragma unroll
-          for (int u = 0; u < CH / 2; ++u) {
-            const double2 a = xb[u];
-            w[q] = __builtin_fma(zb[2 * u], a.x, w[q]);
-            w[q] = __builtin_fma(zb[2 * u + 1], a.y, w[q]);
-          }
-        }
-        if (more) {
-#pragma unroll
-          for (int u = 0; u < CH; ++u) zb[u] = zn[u];
+        if (ci + 1 < nch) {
+          load_rows(zb, row_of(ci + 1));
+          multiply(za, row_of(ci));
+          multiply(zb, row_of(ci + 1));
+        } else {
+          multiply(za, row_of(ci));
         }
       }
       if (kf < k1) {
-        double zt[8];
+        const char *row = reinterpret_cast<const char *>(Z + (int64_t)kf * n);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) zt[u] = (kf + u < k1) ? zc[(int64_t)(kf + u) * n] : 0.0;
+        for (int u = 0; u < CH; ++u)
+          za[u] = kf + u < k1 ? *reinterpret_cast<const double *>(row + (int64_t)u * n * 8 + zoff) : 0.0;
+        const int kl = kf + l8;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (kf + u >= k1) break;
-#pragma unroll
-          for (int q = 0; q < kCompQMax; ++q) {
-            if (q >= nq) break;
-            const double *xb = reinterpret_cast<const double *>(emt_lds + q * S.bytes + S.x);
-            w[q] = __builtin_fma(zt[u], xb[kf + u], w[q]);
-          }
+        for (int q = 0; q < kCompQMax; ++q) {
+          if (q >= nq) break;
+          const double xk = reinterpret_cast<const double *>(emt_lds + q * S.bytes + S.x)[kl < k1 ? kl : n];
+          fma_rows8(w[q], kl < k1 ? xk : 0.0, za);
         }
       }
 #pragma unroll
       for (int q = 0; q < kCompQMax; ++q) {
         if (q >= nq) break;
-        P[(pg * Q + q) * n + pr] = w[q];
+        if (pr < n) P[(pg * Q + q) * n + pr] = w[q];
       }
     }
     step::lds_barrier();
@@ -551,6 +566,8 @@ __global__ __launch_bounds__(1024) void k_comp(DevCtx c, CompCtx cc, int Q, int6
         if (swn) {
           g[j] = c.cg[ncoef + b];
           be[j] = c.cb[ncoef + b];
+          step::settle(g[j]);
+          step::settle(be[j]);
         }
         const double hn = be[j] * i + step::gamma_of(pk[j], g[j]) * u;
         if (j == 0) {
