@@ -129,7 +129,7 @@ inline
   o.emf = take(s.nsrc > 0 ? s.bs : 0, 8);
   o.line = take(s.line, 8);
   o.gsw = take(s.nsw, 8);
-  o.swflag = take(s.nsw > 0 ? 1 : 0, 4);
+  o.swflag = take(s.nsw > 0 || s.nlev > 0 ? 1 : 0, 4);
   o.vrow = take(adjoint && !s.row_global ? s.n + 1 + s.nsrc : 0, 8);  // the earlier step's trajectory row, a zero between its parts
   if (sm) {
     o.gmeta = take(waves + 1 + s.gb, 4);

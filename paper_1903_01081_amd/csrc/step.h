@@ -175,7 +175,8 @@ struct View {
   Lds<int32_t> rf_rowptr, rf_flev, rf_fent_ptr;
   Lds<uint16_t> rf_rows;
   // closed form with switches: the tail inversion's lines, the switches'
-  // conductances, the last step that changed one
+  // conductances; and, also of items refactorised inside the loop, the last
+  // step that changed a switch's state
   Lds<double> line, gsw;
   Lds<int32_t> swflag;
 };
@@ -1724,6 +1725,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   }
   history_from_state<BS, BPT, SM>(c.si + it.br, c.su + it.br, L, v);
   if (diodes) {
+    if (threadIdx.x == 0) v.swflag[0] = (int)n0 - 1;
     // no dense tail: w stays zero
 #pragma unroll
     for (int k = 0; k < 2 * Tail<BS, DT>::R * Tail<BS, DT>::Q; ++k) w.w[k] = 0.0;
@@ -1877,8 +1879,12 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     }
     if (diodes) {
       // a diode changed state or the topology switched: the conductances
-      // of step n+1 and their factor, inside the loop
-      if (__syncthreads_or(fl != 0u) || sw) {
+      // of step n+1 and their factor, inside the loop (a word of the
+      // kernel's own LDS: __syncthreads_or takes 256 bytes that the host's
+      // layout does not know)
+      if (fl != 0u) v.swflag[0] = (int)n;
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(v.swflag[0]) == (int)n || sw) {
         diode_conductances<BS, BPT>(c, it, L, dmask);
         refactor_dynamic<BS, BPT, SM>(c, it, v, L);
       }

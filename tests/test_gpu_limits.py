@@ -1,0 +1,82 @@
+"""Networks at the limits of the step kernels' formats and of the LDS. Against
+the CPU oracle, a smaller network with the same solution, or the same network
+recorded differently."""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1903_01081_amd import netgen
+from paper_1903_01081_amd.netgen import CAP, DIODE, RES, RL, SRC
+
+pytestmark = pytest.mark.gpu
+
+W60 = 2 * math.pi * 60
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    return torch
+
+
+def rel(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+def feeder(n, seed, rec_nodes):
+    """A radial feeder of n nodes whose every section is a pi line."""
+    rng = np.random.default_rng(seed)
+    br = [dict(k=0, m=-1, kind=SRC, R=0.5, L=10e-3, E=1.0, omega=W60, phase=0.3)]
+    for j in range(n - 1):
+        br.append(dict(k=j, m=j + 1, kind=RL, R=rng.uniform(0.1, 0.5), L=rng.uniform(1e-4, 2e-4), line=j))
+        if j % 2 == 0:
+            br.append(dict(k=j + 1, m=-1, kind=CAP, C=0.5 * rng.uniform(8e-9, 12e-9), line=j))
+    return netgen.circuit(n, br, rec_nodes=rec_nodes)
+
+
+def rectifier():
+    """A half-wave rectifier: a source, a diode, an R-C load."""
+    return [dict(k=0, m=-1, kind=SRC, R=0.5, L=1e-3, E=10.0, omega=W60, phase=-1.2),
+            dict(k=0, m=1, kind=DIODE, R=1e-2, ins=0), dict(k=1, m=-1, kind=CAP, C=1e-4),
+            dict(k=1, m=-1, kind=RES, R=20.0), dict(k=0, m=-1, kind=RES, R=1e3)]
+
+
+@pytest.mark.parametrize("what", ["plain", "diode"])
+def test_staged_batch_that_fills_the_lds(torch_cuda, what):
+    # as many recorded columns as the LDS of a compute unit takes beside the
+    # rest of a batch that goes by level passes
+    from paper_1903_01081_amd.sim import Simulator
+    T = 300
+
+    def build(n_col):
+        net = feeder(8, 3, [5] * n_col) if what == "plain" else netgen.circuit(2, rectifier(), rec_nodes=[1] * n_col)
+        return Simulator([net], 20e-6, T, solver="sparse")
+
+    sim = build(30000)
+    info = sim.info()
+    assert info["lds_staged"]
+    sim.close()
+    for n_col in range(30000 + (info["lds_limit"] - info["lds_bytes"]) // 4, 30000, -4):
+        sim = build(n_col)
+        if sim.info()["lds_staged"]:
+            break
+        sim.close()
+    assert sim.info()["lds_bytes"] > info["lds_limit"] - 64
+    say(f"{what}: {n_col} columns, {sim.info()['lds_bytes']} bytes of LDS")
+    sim.factor()
+    got = sim.step(T).cpu().numpy()[0]
+    sim.sync()
+    sim.close()
+    one = build(1)
+    one.factor()
+    ref = one.step(T).cpu().numpy()[0]
+    assert np.max(np.abs(ref)) > 0 and np.array_equal(got, np.repeat(ref, n_col, axis=1))
