@@ -913,11 +913,22 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   // compensation components, whose kernels sum by the CSR.
   std::vector<RowProgram> gprogs;
   std::vector<int> prog_f(NI, -1), prog_a(NI, -1);
+  int seeds_global = 0;  // the adjoint's seeds from memory (DevCtx)
   std::map<std::vector<int>, int> prog_ids;
   auto plan_gathers = [&]() {
     gprogs.clear();
     prog_ids.clear();
     if (comp) return;
+    // a node recorded so often that a row program cannot hold its sum, or
+    // more recorded columns than the programs' codes reach
+    for (int q = 0; q < NI && K > 0; ++q) {
+      const Item &it = A.items[q];
+      std::vector<int> ends(it.n, 0);
+      for (int r = 0; r < it.n; ++r) ends[r] = it.nptr[r + 1] - it.nptr[r];
+      for (int a : it.rec_node)
+        if (++ends[a] > kMaxRowEntries) seeds_global = 1;
+      if (((int64_t)it.n_br + 1 + (int64_t)it.rec_node.size()) * 2 > 65535) seeds_global = 1;
+    }
     for (int q = 0; q < NI; ++q) {
       const Item &it = A.items[q];
       if (c.is_split[q]) continue;
@@ -936,11 +947,11 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       };
       prog_f[q] = program(key);
       if (K <= 0) continue;
+      prog_a[q] = prog_f[q];
+      if (seeds_global) continue;
       // seed q of the adjoint is the q-th recorded node in node order
       std::vector<int> nodes = it.rec_node;
       std::sort(nodes.begin(), nodes.end());
-      if (((int64_t)it.n_br + 1 + (int64_t)nodes.size()) * 2 > 65535)
-        throw Error{EMT_EINVAL, "a connected component has too many branches and recorded nodes for the adjoint"};
       for (size_t e = 0; e < nodes.size(); ++e) {
         rows[nodes[e]].e.push_back({(it.n_br + 1 + (int)e) << 1, 0});
         key.push_back(nodes[e]);
@@ -962,7 +973,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     z.ns = P.ns;
     z.nbr = it.n_br;
     z.nsrc = it.n_src;
-    z.nrec = (int)it.rec_node.size();
+    z.nrec = adj && seeds_global ? 0 : (int)it.rec_node.size();
     z.closed = closed[it.sym];
     z.nfpass = P.nfpass();
     z.nbpass = P.nbpass();
@@ -1029,7 +1040,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
         if (!c.is_split[q] && !comp) a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, true), false, true).total);
     }
     c.sm_fwd = f_sm <= (size_t)max_lds && !sim.sweep_from_global;
-    c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global;
+    c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global && !seeds_global;
   };
   lds_figures();
   // LDS a workgroup may take: all of a compute unit's, or half where the
@@ -1622,6 +1633,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.rec_stride = A.rec_stride;
   dc.sv_cap = sv_cap;
   dc.row_global = row_global;
+  dc.seeds_global = seeds_global;
   c.d_order = c.upload(order);
   c.d_pairs = c.upload(pairs);
   c.d_closed = c.upload(closed_pairs);

@@ -90,6 +90,9 @@ RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_cod
         best_wave = std::move(w);
       }
     }
+  for (const RowSum &r : rows)
+    if ((int)r.e.size() > kMaxRowEntries)
+      throw Error{EMT_EINVAL, "a row of a component's sums has more than " + std::to_string(kMaxRowEntries) + " entries"};
   RowProgram p;
   p.meta.assign(waves + 1, 0);
   std::vector<int32_t> words;

@@ -39,6 +39,13 @@ struct RowSum {
   std::vector<std::pair<int, int>> e;  // (code, value index)
 };
 
+// Most entries of a row: a batch word counts a lane's quads in 8 bits and at
+// most 16 lanes share a row. Wider counts cost every batch of every step their
+// decoding (400-bus grid, 2000 steps: 5.40 -> 5.55 ms); a row is longer only
+// where a node is recorded in more columns than that.
+constexpr int kMaxRowEntries = 255 * 4 * 16;
+
+// Throws Error (EMT_EINVAL) on a longer row.
 RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_code, int pad_src);
 
 // Sizes of the closed form at one cut.

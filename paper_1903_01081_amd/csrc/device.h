@@ -290,6 +290,9 @@ struct DevCtx {
   // 1: no room in the LDS for a trajectory row beside the largest component's
   // arrays (the adjoint's kernels without staged factors only)
   int32_t row_global;
+  // 1: a node's recorded columns are too many for the adjoint's row sums; the
+  // cotangents are then added from memory (in the same kernels)
+  int32_t seeds_global;
   int32_t *flags;  // [0] = bad pivots
   double dt;
   int64_t T;

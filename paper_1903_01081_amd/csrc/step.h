@@ -255,11 +255,12 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   const bool dyn = LEV && it.n_diodes > 0;
   const int nsw = DT > 0 ? it.n_diodes : 0;
   const int ne = dyn ? g_nptr[v.n] : 0;
-  const RowProg gp = adjoint ? it.ga : it.gf;
+  const bool seeds = adjoint && (SM || !c.seeds_global);  // recorded columns' cotangents in LDS
+  const RowProg gp = seeds ? it.ga : it.gf;
   // the closed form's values beyond what the LDS has room for stay in L2
   const int nstage = v.closed && sd.nsv > c.sv_cap ? c.sv_cap : sd.nsv;
   v.lim = SM ? nstage / 2 : 0;
-  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  v.closed,
+  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  seeds || !adjoint ? it.n_rec : 0, v.closed,
                      sd.nfpass,  sd.nbpass, nstage,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
                      sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, nsw, nsw > 0 ? tail_lines(DT) : 0, BS,
                      SM ? 0 : c.row_global};
@@ -1943,11 +1944,29 @@ __device__ __forceinline__ void adjoint_seed(const DevCtx &c, const ItemDesc &it
     v.J[b] = (L.g[j] != 0.0) ? ga_nx * hb_nx[j] + L.g[j] * ibar : 0.0;
   });
   // the recorded columns' cotangents, which the gather adds at their nodes
+  if (!SM && c.seeds_global) return;
   if (tid < v.nrec) v.J[v.nbr + 1 + tid] = seed0;
   if (v.nrec > BS) {
     const double *drow = dJ + ((int64_t)it.scen * c.T + (n - 1)) * c.rec_stride;
     for (int q = tid + BS; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = drow[v.rcolumn[q]];
   }
+}
+
+// The cotangents of step n from memory, where they are no part of the gather:
+// a lane per node adds up its columns.
+template <int BS, bool SM>
+__device__ __forceinline__ void add_seeds(const DevCtx &c, const ItemDesc &it, const View<SM> &v, const double *dJ,
+                                          int64_t n) {
+  const int32_t *rp = c.rptr + it.nptr;
+  const uint16_t *col = c.rcolumn + it.rec;
+  const double *drow = dJ + ((int64_t)it.scen * c.T + (n - 1)) * c.rec_stride;
+  for (int r = (int)threadIdx.x; r < v.n; r += BS) {
+    const int q1 = rp[r + 1];
+    double s = v.r[r];
+    for (int q = rp[r]; q < q1; ++q) s = s + drow[col[q]];
+    v.r[r] = s;
+  }
+  step_barrier<BS>();
 }
 
 // The cotangent of step n in the lane's first recorded column.
@@ -1978,7 +1997,8 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
   const int64_t lo = s * c.K, hi = (lo + c.K < c.T) ? lo + c.K : c.T;
   const int64_t cko = it.ck + s * (int64_t)nbr;
   // the gather's seeds are zero in the forward steps
-  for (int q = threadIdx.x; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = 0.0;
+  if (SM || !c.seeds_global)
+    for (int q = threadIdx.x; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = 0.0;
   int t = topo_of(topo, it.n_topo, lo + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
   load_coefs<BS, BPT>(c, it, t, L.g, L.be);
@@ -2193,6 +2213,7 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
     read_ahead(n - 2);
     const double seed0 = from_ck ? 0.0 : load_seed<SM>(c, it, v, dJ, n - 1);
     gather_all<BS, SM>(v);
+    if (!SM && c.seeds_global) add_seeds<BS, SM>(c, it, v, dJ, n);
     solve_after_gather<BS, DT, SM, GEN>(v, w);
     if (!from_ck && n - 1 >= first && t_nx == t) {
       // no checkpoint and no topology change on either side: the update and
@@ -2214,8 +2235,10 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
         hb_nx[j] = hb;
         v.J[tid + j * BS] = gamma_times(pk, L.g[j] * hb) + L.g[j] * (L.be[j] * hb);
       }
-      if (tid < v.nrec) v.J[v.nbr + 1 + tid] = seed0;
-      if (v.nrec > BS) {
+      if (SM || !c.seeds_global) {
+        if (tid < v.nrec) v.J[v.nbr + 1 + tid] = seed0;
+      }
+      if (v.nrec > BS && (SM || !c.seeds_global)) {
         const double *drow = dJ + ((int64_t)it.scen * c.T + (n - 2)) * c.rec_stride;
         for (int q = tid + BS; q < v.nrec; q += BS) v.J[v.nbr + 1 + q] = drow[v.rcolumn[q]];
       }

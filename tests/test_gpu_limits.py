@@ -43,6 +43,29 @@ def feeder(n, seed, rec_nodes):
     return netgen.circuit(n, br, rec_nodes=rec_nodes)
 
 
+def gradient(torch, net, T, K, cot, **kw):
+    from paper_1903_01081_amd.sim import Simulator
+    sim = Simulator([net], 20e-6, T, checkpoint_every=K, **kw)
+    sim.factor()
+    sim.step(T, record=False)
+    g = sim.adjoint(torch.tensor(cot[None], device=sim.device)).cpu().numpy()[0]
+    sim.sync()
+    sim.close()
+    return g
+
+
+@pytest.mark.parametrize("n_col,kw", [(16000, {}), (16321, {}), (16400, dict(serial_adjoint=True)), (40000, {})])
+def test_one_node_recorded_in_many_columns(torch_cuda, n_col, kw):
+    # the node's cotangent is the sum over its columns; the sums' rounding
+    # (40000 terms of order one, in two orders) is below 1e-11 of it
+    T, K = 9, 4
+    cot = 1.0 + np.random.default_rng(1).random((T, n_col))
+    say(f"one node in {n_col} columns")
+    got = gradient(torch_cuda, feeder(8, 3, [5] * n_col), T, K, cot, **kw)
+    ref = gradient(torch_cuda, feeder(8, 3, [5]), T, K, cot.sum(1, keepdims=True))
+    assert np.max(np.abs(ref)) > 0 and rel(got, ref) < 1e-10
+
+
 def rectifier():
     """A half-wave rectifier: a source, a diode, an R-C load."""
     return [dict(k=0, m=-1, kind=SRC, R=0.5, L=1e-3, E=10.0, omega=W60, phase=-1.2),
