@@ -963,7 +963,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   plan_gathers();
   int sv_cap = INT32_MAX / 512 * 256;
   int row_global = 0;
-  auto step_shape = [&](int q, bool adj) {
+  auto step_shape = [&](int q, bool sm, bool adj) {
     const Item &it = A.items[q];
     const SweepPlan &P = plans[it.sym];
     const ClosedPlan &C = cplans[it.sym];
@@ -973,7 +973,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     z.ns = P.ns;
     z.nbr = it.n_br;
     z.nsrc = it.n_src;
-    z.nrec = adj && seeds_global ? 0 : (int)it.rec_node.size();
+    z.nrec = (int)it.rec_node.size();
     z.closed = closed[it.sym];
     z.nfpass = P.nfpass();
     z.nbpass = P.nbpass();
@@ -999,16 +999,20 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       z.nent = it.nptr[it.n];
     }
     z.bs = bs;
-    z.row_global = row_global;
+    // (the kernels that stage their factors keep these in LDS)
+    z.row_global = sm ? 0 : row_global;
+    z.seeds_global = sm ? 0 : seeds_global;
     return z;
   };
-  auto item_lds = [&](int q, bool adj) { return (size_t)step_lds(step_shape(q, adj), true, adj).total; };
+  auto item_lds = [&](int q, bool sm, bool adj) {
+    return (size_t)step_lds(step_shape(q, sm, adj && K > 0), sm, adj).total;
+  };
   if (solver == EMT_SOLVER_AUTO) {
     for (int q = 0; q < NI; ++q) {
       if (c.is_split[q]) continue;
       const Item &it = A.items[q];
       SweepPlan &P = plans[it.sym];
-      if (!sym_diode[it.sym] && !closed[it.sym] && item_lds(q, false) > (size_t)max_lds &&
+      if (!sym_diode[it.sym] && !closed[it.sym] && item_lds(q, true, false) > (size_t)max_lds &&
           P.d < std::min(c.ks.dmax, it.n))
         P = plan_sweeps(A.syms[it.sym], std::min(c.ks.dmax, it.n));
     }
@@ -1025,19 +1029,22 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     for (int q = 0; q < NI; ++q) {
       if (c.is_split[q] || comp) continue;
       const Item &it = A.items[q];
-      f_sm = std::max(f_sm, (size_t)step_lds(step_shape(q, false), true, false).total);
-      f_gl = std::max(f_gl, (size_t)step_lds(step_shape(q, false), false, false).total);
-      a_sm = std::max(a_sm, (size_t)step_lds(step_shape(q, K > 0), true, true).total);
-      a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, K > 0), false, true).total);
+      f_sm = std::max(f_sm, item_lds(q, true, false));
+      f_gl = std::max(f_gl, item_lds(q, false, false));
+      a_sm = std::max(a_sm, item_lds(q, true, true));
+      a_gl = std::max(a_gl, item_lds(q, false, true));
       if (!closed[it.sym] && plans[it.sym].nsv() > 65535)
         throw Error{EMT_EINVAL, "a connected component's factor is too large"};
     }
-    // no room for the adjoint's trajectory row beside an item's other arrays
-    if (K > 0 && a_gl > (size_t)max_lds && !row_global) {
-      row_global = 1;
+    // no room for the adjoint's trajectory row beside an item's other arrays,
+    // and then none for its cotangents and EMF table
+    for (int *from_memory : {&row_global, &seeds_global}) {
+      if (K <= 0 || a_gl <= (size_t)max_lds || *from_memory) continue;
+      *from_memory = 1;
+      if (from_memory == &seeds_global) plan_gathers();
       a_gl = 0;
       for (int q = 0; q < NI; ++q)
-        if (!c.is_split[q] && !comp) a_gl = std::max(a_gl, (size_t)step_lds(step_shape(q, true), false, true).total);
+        if (!c.is_split[q] && !comp) a_gl = std::max(a_gl, item_lds(q, false, true));
     }
     c.sm_fwd = f_sm <= (size_t)max_lds && !sim.sweep_from_global;
     c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global && !seeds_global;
@@ -1058,7 +1065,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       if (c.is_split[q]) continue;
       for (bool adj : {false, true}) {
         if (adj && K <= 0) continue;
-        StepShape z = step_shape(q, adj);
+        StepShape z = step_shape(q, true, adj);
         if (!closed[A.items[q].sym]) continue;
         z.nsv = 0;
         const int64_t rest = (int64_t)step_lds(z, true, adj).total;

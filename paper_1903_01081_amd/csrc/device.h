@@ -103,7 +103,9 @@ struct StepShape {
   int nlev, nent;              // factor levels and node-CSR entries of an item refactorised inside the loop, else 0
   int nsw, line;               // closed form with switches: their number, doubles of the tail inversion's lines
   int bs;
-  int row_global;              // adjoint: the earlier step's trajectory row is read from memory
+  // adjoint: the earlier step's trajectory row is read from memory; the
+  // recorded columns' cotangents are, and EMFs are evaluated step by step
+  int row_global, seeds_global;
 };
 struct StepLds {
   uint32_t cD, xr, J, flag, emf, vrow, pass, sv, dinv, fdesc, bdesc, fcol, brow, bpos, gmeta, gcode, grow, fmeta, fcode,
@@ -124,9 +126,9 @@ inline
   const int waves = s.bs / 64;
   o.cD = take((s.d + 31) / 32 * 32, 8);               // the tail's right-hand side, zero past d
   o.xr = take((s.closed ? 2 : 1) * (s.n + 1), 8);     // right-hand side (closed form), then the solution
-  o.J = take(s.nbr + 1 + (adjoint ? s.nrec : 0), 8);  // branch injections, a zero, the adjoint's seeds
+  o.J = take(s.nbr + 1 + (adjoint && !s.seeds_global ? s.nrec : 0), 8);  // branch injections, a zero, the adjoint's seeds
   o.flag = take(adjoint ? 1 : 0, 4);
-  o.emf = take(s.nsrc > 0 ? s.bs : 0, 8);
+  o.emf = take(s.nsrc > 0 && !(adjoint && s.seeds_global) ? s.bs : 0, 8);
   o.line = take(s.line, 8);
   o.gsw = take(s.nsw, 8);
   o.swflag = take(s.nsw > 0 || s.nlev > 0 ? 1 : 0, 4);
@@ -290,8 +292,9 @@ struct DevCtx {
   // 1: no room in the LDS for a trajectory row beside the largest component's
   // arrays (the adjoint's kernels without staged factors only)
   int32_t row_global;
-  // 1: a node's recorded columns are too many for the adjoint's row sums; the
-  // cotangents are then added from memory (in the same kernels)
+  // 1: nor for the recorded columns' cotangents and the EMF table, or a node's
+  // columns are too many for the adjoint's row sums; the cotangents are then
+  // added from memory and EMFs evaluated every step (in the same kernels)
   int32_t seeds_global;
   int32_t *flags;  // [0] = bad pivots
   double dt;

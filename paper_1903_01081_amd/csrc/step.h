@@ -165,6 +165,7 @@ struct View {
   Ref<uint16_t, SM> fcol, brow, bpos, rnode, rcolumn;
   Lds<double> r, x, J, cD, sv_s, dinv_s, emf, vrow;  // x has n+1 entries, x[n] = 0; r: where the gather writes
   Lds<int32_t> flag;                           // adjoint: a word for broadcasts
+  bool emf_direct;                             // no EMF table (not under SM)
   Ref<double, SM> sv, dinv;
   int lim;           // pairs of closed-form values staged in LDS (the rest: svg)
   const double *svg;  // the topology's closed-form values in global memory
@@ -260,10 +261,10 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   // the closed form's values beyond what the LDS has room for stay in L2
   const int nstage = v.closed && sd.nsv > c.sv_cap ? c.sv_cap : sd.nsv;
   v.lim = SM ? nstage / 2 : 0;
-  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  seeds || !adjoint ? it.n_rec : 0, v.closed,
+  const StepShape sh{it.n,       sd.d,      sd.ns,     it.n_br,   it.n_src,  it.n_rec,  v.closed,
                      sd.nfpass,  sd.nbpass, nstage,    sd.nfdesc, sd.nbdesc, gp.nb,     gp.nq,
                      sd.fwd.nb,  sd.fwd.nq, sd.bwd.nb, sd.bwd.nq, dyn ? sd.nlev : 0, ne, nsw, nsw > 0 ? tail_lines(DT) : 0, BS,
-                     SM ? 0 : c.row_global};
+                     SM ? 0 : c.row_global, SM ? 0 : c.seeds_global};
   const StepLds o = step_lds(sh, SM, adjoint);
   v.cD.off = o.cD;
   // closed form: the gather writes r (the tail's right-hand side where the
@@ -274,6 +275,7 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   v.J.off = o.J;
   v.flag.off = o.flag;
   v.emf.off = o.emf;
+  v.emf_direct = adjoint && !seeds;
   v.vrow.off = o.vrow;
   v.line.off = o.line;
   v.gsw.off = o.gsw;
@@ -916,6 +918,7 @@ struct Lane {
   // the source lanes each step it stood in the branch update's way.
   double sE, sw, sph;
   int ek, eper, enext;  // enext: the next step's place in the table
+  double ed;            // without the table: the next step's EMF
 };
 
 template <int BS, int BPT>
@@ -939,6 +942,12 @@ __device__ __forceinline__ void load_lane(const DevCtx &c, const ItemDesc &it, L
 // and one lie between its last reader and this call).
 template <int BPT, bool SM>
 __device__ __forceinline__ void emf_advance(const DevCtx &c, const View<SM> &v, Lane<BPT> &L, int64_t n, bool fresh) {
+  if constexpr (!SM) {
+    if (v.emf_direct) {
+      L.ed = (int)threadIdx.x < v.nsrc ? L.sE * emf_cos(L.sw * ((double)n * c.dt) + L.sph) : 0.0;
+      return;
+    }
+  }
   if (L.eper == 0) return;
   if (!fresh && ++L.enext < L.eper) return;
   L.enext = 0;
@@ -982,6 +991,9 @@ __device__ __forceinline__ void history_from_state(const double *si, const doubl
 // source).
 template <int BPT, bool SM>
 __device__ __forceinline__ double slot0_emf(const View<SM> &v, const Lane<BPT> &L, int tid) {
+  if constexpr (!SM) {
+    if (v.emf_direct) return L.ed;
+  }
   return tid < v.nsrc ? v.emf[L.enext * v.nsrc + tid] : 0.0;
 }
 

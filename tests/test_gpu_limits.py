@@ -32,13 +32,14 @@ def rel(a, b):
     return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
 
 
-def feeder(n, seed, rec_nodes):
-    """A radial feeder of n nodes whose every section is a pi line."""
+def feeder(n, seed, rec_nodes, cap_every=2):
+    """A radial feeder of n nodes whose sections are pi lines, every
+    cap_every-th with its capacitor."""
     rng = np.random.default_rng(seed)
     br = [dict(k=0, m=-1, kind=SRC, R=0.5, L=10e-3, E=1.0, omega=W60, phase=0.3)]
     for j in range(n - 1):
         br.append(dict(k=j, m=j + 1, kind=RL, R=rng.uniform(0.1, 0.5), L=rng.uniform(1e-4, 2e-4), line=j))
-        if j % 2 == 0:
+        if j % cap_every == 0:
             br.append(dict(k=j + 1, m=-1, kind=CAP, C=0.5 * rng.uniform(8e-9, 12e-9), line=j))
     return netgen.circuit(n, br, rec_nodes=rec_nodes)
 
@@ -64,6 +65,24 @@ def test_one_node_recorded_in_many_columns(torch_cuda, n_col, kw):
     got = gradient(torch_cuda, feeder(8, 3, [5] * n_col), T, K, cot, **kw)
     ref = gradient(torch_cuda, feeder(8, 3, [5]), T, K, cot.sum(1, keepdims=True))
     assert np.max(np.abs(ref)) > 0 and rel(got, ref) < 1e-10
+
+
+@pytest.mark.parametrize("n,kw", [(4500, {}), (5800, {}), (6000, {}), (6000, dict(serial_adjoint=True))])
+def test_adjoint_of_large_components_with_every_node_recorded(torch_cuda, n, kw):
+    # the LDS has no room for the trajectory row and, from about 5820 nodes on,
+    # none for the cotangents and EMFs either; with 30 recorded nodes it has,
+    # and the same cotangent gives the same gradient (its terms meet in another
+    # order: 9 steps of sums of order one, 1e-11 of the largest)
+    T, K = 9, 4
+    rng = np.random.default_rng(2)
+    few = np.sort(rng.choice(n, 30, replace=False))
+    w = rng.standard_normal((T, 30))
+    cot = np.zeros((T, n))
+    cot[:, few] = w
+    say(f"feeder of {n} nodes, all recorded, {kw}")
+    got = gradient(torch_cuda, feeder(n, 2, list(range(n)), 3), T, K, cot, **kw)
+    ref = gradient(torch_cuda, feeder(n, 2, few.tolist(), 3), T, K, w, **kw)
+    assert np.all(np.isfinite(ref)) and np.max(np.abs(ref)) > 0 and rel(got, ref) < 1e-11
 
 
 def rectifier():
