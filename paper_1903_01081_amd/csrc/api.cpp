@@ -898,11 +898,13 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     any_level = true;
     any_switch = false;
   }
-  c.ks.kind = any_level || (any_line && any_group) ? STEP_FULL
-              : any_line                           ? STEP_LINES
-              : any_group                          ? STEP_GROUPS
-              : any_switch                         ? STEP_SWITCH
-                                                   : STEP_PLAIN;
+  const bool any_diode = std::count(item_diode.begin(), item_diode.end(), 1) > 0;
+  c.ks.kind = any_level && !any_line && !any_group && !any_diode ? STEP_LEVELS
+              : any_level || (any_line && any_group)             ? STEP_FULL
+              : any_line                                         ? STEP_LINES
+              : any_group                                        ? STEP_GROUPS
+              : any_switch                                       ? STEP_SWITCH
+                                                                 : STEP_PLAIN;
   std::vector<ClosedPlan> cplans(A.syms.size());
   auto plan_closed_of = [&](size_t q) {
     if (closed[q]) cplans[q] = plan_closed(A.syms[q], gpos[q], plans[q].d, bs);
@@ -1724,13 +1726,13 @@ static hipError_t launch_forward(emt_ctx &c, int64_t n0, int64_t ns, double *rec
   if (!ks.sm) ks.bpt = c.bpt_global;
   using Launch = hipError_t (*)(const emt::DevCtx &, const emt::KernelShape &, const int32_t *, int, int64_t, int64_t,
                                 double *, hipStream_t);
-  static const Launch table[3][5] = {
+  static const Launch table[3][6] = {
       {emt::launch_forward<64, 0>, emt::launch_forward<64, 1>, emt::launch_forward<64, 2>, emt::launch_forward<64, 3>,
-       emt::launch_forward<64, 4>},
+       emt::launch_forward<64, 4>, emt::launch_forward<64, 5>},
       {emt::launch_forward<256, 0>, emt::launch_forward<256, 1>, emt::launch_forward<256, 2>,
-       emt::launch_forward<256, 3>, emt::launch_forward<256, 4>},
+       emt::launch_forward<256, 3>, emt::launch_forward<256, 4>, emt::launch_forward<256, 5>},
       {emt::launch_forward<512, 0>, emt::launch_forward<512, 1>, emt::launch_forward<512, 2>,
-       emt::launch_forward<512, 3>, emt::launch_forward<512, 4>}};
+       emt::launch_forward<512, 3>, emt::launch_forward<512, 4>, emt::launch_forward<512, 5>}};
   return table[ks.bs == 64 ? 0 : (ks.bs == 256 ? 1 : 2)][ks.kind](c.dc, ks, c.d_order, c.n_fwd, n0, ns, rec, st);
 }
 

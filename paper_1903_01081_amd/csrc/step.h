@@ -1713,8 +1713,11 @@ __device__ __forceinline__ void refactor_dynamic(const DevCtx &c, const ItemDesc
 template <int BS, int BPT, int DT, bool SM, int KIND>
 __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, int64_t n0, int64_t nsteps,
                                                 double *rec) {
+  constexpr bool kLevels = KIND == STEP_FULL || KIND == STEP_LEVELS;
+  // line ends or coupled members
+  constexpr bool kPass = KIND == STEP_LINES || KIND == STEP_GROUPS || KIND == STEP_FULL;
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, KIND == STEP_FULL, KIND == STEP_SWITCH ? DT : 0>(c, it, false);
+  View<SM> v = make_view<BS, SM, kLevels, KIND == STEP_SWITCH ? DT : 0>(c, it, false);
   const int64_t *topo = c.topo + it.topo;
   int t = topo_of(topo, it.n_topo, n0 + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
@@ -1801,7 +1804,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   // the adjoint's trajectory rows (batches with checkpoints have no lines,
   // groups or diodes)
   double *rows = nullptr;
-  if ((KIND == STEP_PLAIN || KIND == STEP_FULL) && c.vt_full) rows = c.vt + it.vt + n0 * (int64_t)(v.n + v.nsrc);
+  if ((KIND == STEP_PLAIN || kLevels) && c.vt_full) rows = c.vt + it.vt + n0 * (int64_t)(v.n + v.nsrc);
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     if (lines) lines_ahead<BS, NL>(it, ln, n);
@@ -1822,7 +1825,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
         fresh = false;
       }
     }
-    solve_after_gather<BS, DT, SM, KIND == STEP_FULL, KIND == STEP_SWITCH>(v, w, dv, switches);
+    solve_after_gather<BS, DT, SM, kLevels, KIND == STEP_SWITCH>(v, w, dv, switches);
     if (switches) {
       if ((int)threadIdx.x < it.n_diodes) switch_step<SM>(c, it, v, sl, (int)threadIdx.x, n);
       for (int q = (int)threadIdx.x + BS; q < it.n_diodes; q += BS) {
@@ -1843,7 +1846,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       for (int q = tid0 + BS; q < v.nrec; q += BS) row[v.rcolumn[q]] = v.x[v.rnode[q]];
       row += R;
     }
-    if ((KIND == STEP_PLAIN || KIND == STEP_SWITCH) && n != special) {
+    if (!kPass && n != special) {
       update_plain<BS, BPT, SM, false>(v, L, nullptr);
       if (rec0) {
         *at0 = rv0;
@@ -1852,7 +1855,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       step_barrier<BS>();
       continue;
     }
-    if (KIND != STEP_PLAIN && KIND != STEP_SWITCH && n != special && !diodes) {
+    if (kPass && n != special && !diodes) {
       update_plain<BS, BPT, SM, false, true>(v, L, nullptr);
       if (lines || groups) {
         step_barrier<BS>();
@@ -1879,7 +1882,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
       st_i = c.si + it.br;
       st_u = c.su + it.br;
     }
-    update_inject<BS, BPT, SM, KIND != STEP_PLAIN && KIND != STEP_SWITCH>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
+    update_inject<BS, BPT, SM, kPass>(c, v, L, ck_i, ck_u, st_i, st_u, sw, it.coef + (int64_t)(t + 1) * v.nbr,
                                n < n_end, n);
     if (rec0) {
       *at0 = rv0;
