@@ -964,7 +964,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   };
   plan_gathers();
   int sv_cap = INT32_MAX / 512 * 256;
-  int row_global = 0;
+  int row_global = 0, csr_global = 0;
   auto step_shape = [&](int q, bool sm, bool adj) {
     const Item &it = A.items[q];
     const SweepPlan &P = plans[it.sym];
@@ -998,7 +998,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       if (z.nsw > 0) z.line = 4 * c.ks.dt;
     } else if (item_diode[q]) {
       z.nlev = A.syms[it.sym].levels_f();
-      z.nent = it.nptr[it.n];
+      z.nent = sm && !csr_global ? it.nptr[it.n] : 0;
     }
     z.bs = bs;
     // (the kernels that stage their factors keep these in LDS)
@@ -1052,6 +1052,18 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
     c.sm_adj = a_sm <= (size_t)max_lds && !sim.sweep_from_global && !seeds_global;
   };
   lds_figures();
+  // In-loop refactorisation reads the node CSR once per change of a switch's
+  // state, the sweeps read what else is staged every step: the CSR goes first
+  // (640 nodes with 20 diode bridges, sparse solver: 314 us a step staged,
+  // 498 from memory).
+  if (f_sm > (size_t)max_lds && std::count(item_diode.begin(), item_diode.end(), 1) > 0) {
+    csr_global = 1;
+    lds_figures();
+    if (f_sm > (size_t)max_lds) {
+      csr_global = 0;
+      lds_figures();
+    }
+  }
   // LDS a workgroup may take: all of a compute unit's, or half where the
   // batch has more items than the device has compute units (two workgroups
   // share one then; a 502-item batch at 107 KB each ran in two rounds).
@@ -1641,6 +1653,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   dc.K = K;
   dc.rec_stride = A.rec_stride;
   dc.sv_cap = sv_cap;
+  dc.csr_global = csr_global;
   dc.row_global = row_global;
   dc.seeds_global = seeds_global;
   c.d_order = c.upload(order);

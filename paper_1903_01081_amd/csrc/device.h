@@ -100,7 +100,8 @@ struct ItemDesc {
 struct StepShape {
   int n, d, ns, nbr, nsrc, nrec, closed, nfpass, nbpass, nsv, nfdesc, nbdesc;
   int gb, gq, fb, fq, bb, bq;  // batches and quads of the gather, forward and backward programs
-  int nlev, nent;              // factor levels and node-CSR entries of an item refactorised inside the loop, else 0
+  // factor levels and (where staged) node-CSR entries of an item refactorised inside the loop, else 0
+  int nlev, nent;
   int nsw, line;               // closed form with switches: their number, doubles of the tail inversion's lines
   int bs;
   // adjoint: the earlier step's trajectory row is read from memory; the
@@ -161,7 +162,7 @@ inline
       o.rf_flev = take(s.nlev + 1, 4);
       o.rf_fent = take(s.nlev + 1, 4);
       o.rf_rows = take(s.n, 2);
-      o.rf_nptr = take(s.n + 1, 4);
+      o.rf_nptr = take(s.nent > 0 ? s.n + 1 : 0, 4);
       o.rf_nent = take(s.nent, 2);
     }
   }
@@ -303,6 +304,9 @@ struct DevCtx {
   int32_t K;
   int32_t rec_stride;
   int32_t sv_cap;  // closed-form values per item staged in LDS at most (a multiple of 256)
+  // 1: no room in the LDS for the node CSR of items refactorised inside the
+  // loop beside their other staged arrays
+  int32_t csr_global;
   // distributed-parameter lines (ItemDesc::lines + q): descriptor, (1/Z,
   // fractional delay f) pairs, and the wave rings
   const LineDesc *line_tab;

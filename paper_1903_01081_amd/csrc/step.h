@@ -169,10 +169,10 @@ struct View {
   Ref<double, SM> sv, dinv;
   int lim;           // pairs of closed-form values staged in LDS (the rest: svg)
   const double *svg;  // the topology's closed-form values in global memory
-  // items refactorised inside the loop: node CSR, and under SM the
+  // items refactorised inside the loop, under SM: node CSR (where staged), the
   // factorisation's row pointers, level pointers (rows, entries), level rows
-  Ref<int32_t, SM> nptr;
-  Ref<uint16_t, SM> nent;
+  Lds<int32_t> nptr;
+  Lds<uint16_t> nent;
   Lds<int32_t> rf_rowptr, rf_flev, rf_fent_ptr;
   Lds<uint16_t> rf_rows;
   // closed form with switches: the tail inversion's lines, the switches'
@@ -255,7 +255,7 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   const int32_t *g_nptr = c.nptr + it.nptr;
   const bool dyn = LEV && it.n_diodes > 0;
   const int nsw = DT > 0 ? it.n_diodes : 0;
-  const int ne = dyn ? g_nptr[v.n] : 0;
+  const int ne = SM && dyn && !c.csr_global ? g_nptr[v.n] : 0;
   const bool seeds = adjoint && (SM || !c.seeds_global);  // recorded columns' cotangents in LDS
   const RowProg gp = seeds ? it.ga : it.gf;
   // the closed form's values beyond what the LDS has room for stay in L2
@@ -323,8 +323,10 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
     if (dyn) {
       v.nptr.off = o.rf_nptr;
       v.nent.off = o.rf_nent;
-      copy_to<BS>(o.rf_nptr, g_nptr, v.n + 1);
-      copy_to<BS>(o.rf_nent, c.nent + it.nent, ne);
+      if (ne > 0) {
+        copy_to<BS>(o.rf_nptr, g_nptr, v.n + 1);
+        copy_to<BS>(o.rf_nent, c.nent + it.nent, ne);
+      }
       v.rf_rowptr.off = o.rf_rowptr;
       v.rf_flev.off = o.rf_flev;
       v.rf_fent_ptr.off = o.rf_fent;
@@ -335,8 +337,6 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
       copy_to_u16<BS>(o.rf_rows, c.symi + sd.flevrows, v.n);
     }
   } else {
-    v.nptr.p = g_nptr;
-    v.nent.p = c.nent + it.nent;
     v.fdesc.p = c.symd + sd.fdesc;
     v.bdesc.p = c.symd + sd.bdesc;
     v.fcol.p = c.symh + sd.fcol;
@@ -1643,6 +1643,9 @@ __device__ __forceinline__ void refactor_dynamic(const DevCtx &c, const ItemDesc
   double *sv = gcur + it.n_br + sd.nnz + n;
   double *di = sv + sd.nsv;
   const int32_t *g_rowptr = c.symi + sd.rowptr;
+  const int32_t *g_nptr = c.nptr + it.nptr;
+  const uint16_t *g_nent = c.nent + it.nent;
+  const bool csr = SM && !c.csr_global;
   const int32_t *bk = c.bk + it.br, *bm = c.bm + it.br, *gpos = c.bgpos + it.br;
   const int tid = lane_id();
 #pragma unroll
@@ -1659,9 +1662,9 @@ __device__ __forceinline__ void refactor_dynamic(const DevCtx &c, const ItemDesc
     }
     for (int q = q0; q < q1; ++q) Lr[q] = 0.0;
     double d = 0.0;
-    const int e1 = v.nptr[r + 1];
-    for (int e = v.nptr[r]; e < e1; ++e) {
-      const int ent = v.nent[e];
+    const int e1 = csr ? v.nptr[r + 1] : g_nptr[r + 1];
+    for (int e = csr ? v.nptr[r] : g_nptr[r]; e < e1; ++e) {
+      const int ent = csr ? v.nent[e] : g_nent[e];
       const int b = ent >> 1;
       const double gv = gcur[b];
       d = d + gv;

@@ -122,3 +122,19 @@ def test_staged_batch_that_fills_the_lds(torch_cuda, what):
     one.factor()
     ref = one.step(T).cpu().numpy()[0]
     assert np.max(np.abs(ref)) > 0 and np.array_equal(got, np.repeat(ref, n_col, axis=1))
+
+
+def test_diode_grid_stays_staged(torch_cuda, oracle_mod):
+    # 640 nodes with 20 diode bridges, refactorised by levels inside the loop:
+    # the factor and its structure stay in the LDS, where only the node CSR has
+    # no room beside them
+    from paper_1903_01081_amd.sim import Simulator
+    T = 60
+    nets, cfg = netgen.config1(seed=3, n_bus=200, n_steps=T, fault_step=30, rectifiers=20)
+    say("20 diode bridges, sparse solver")
+    sim = Simulator(nets, cfg["dt"], T, solver="sparse")
+    assert sim.info()["lds_staged"]
+    sim.factor()
+    got = sim.step(T).cpu().numpy()[0]
+    sim.sync()
+    assert rel(got, oracle_mod.run(nets[0], cfg["dt"], T)) < 1e-9
