@@ -654,12 +654,20 @@ static void build_comp(emt_ctx &c, const emt_net *nets) {
   c.comp_max_rank = P.max_rank;
 }
 
-// Thrown by upload_all where components with diodes or controlled switches,
-// whose terminals the analysis ordered last, are factorised by levels: the
-// build starts again without that order.
-struct SwitchesByLevels {};
+// What a build tries, and what upload_all throws where it finds that out to be
+// wrong: the build starts again with the plan thrown.
+struct BuildPlan {
+  // the terminals of diodes and controlled switches are ordered last (not
+  // where their components are factorised by levels after all)
+  bool switches_last = true;
+  // symbolic patterns whose closed form does not fit the LDS
+  std::vector<char> by_levels;
+};
+struct Replan {
+  BuildPlan plan;
+};
 
-static void upload_all(emt_ctx &c, const emt_net *nets) {
+static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
   using namespace emt;
   Analysis &A = c.A;
   const emt_sim &sim = c.sim;
@@ -851,6 +859,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       // last, would need the tail's inverse beside the matrix)
       may = d_min <= closed_tail_max(bs) && all_diode[q] && A.switches_last;
     }
+    if (q < plan.by_levels.size() && plan.by_levels[q]) continue;
     // level passes need less LDS
     if (!may || sym_fixed[q] > max_lds || 2 * (n + 1) > 65535) continue;
     const bool fixed = solver == EMT_SOLVER_DENSE || (forced_tail >= 0 && !sym_diode[q]);
@@ -873,7 +882,11 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
   // Components with switches that go by levels after all: their terminals
   // are not ordered last then.
   auto by_levels = [&]() {
-    if (A.switches_last) throw SwitchesByLevels{};
+    if (!A.switches_last) return;
+    Replan r{plan};
+    r.plan.switches_last = false;
+    r.plan.by_levels.clear();  // the patterns change with the order
+    throw r;
   };
   for (size_t q = 0; q < A.syms.size(); ++q)
     if (sym_diode[q] && !closed[q] && !sym_split[q] && solver == EMT_SOLVER_AUTO) by_levels();
@@ -1105,6 +1118,22 @@ static void upload_all(emt_ctx &c, const emt_net *nets) {
       lds_figures();
     }
     c.bpt_global = bpt;
+  }
+  // Padding for the kernels without staged factors may leave a closed form
+  // that sym_fixed let through without room for its two vectors and the
+  // injections: its component goes by levels, which need one.
+  if (!comp && (!c.sm_fwd || !c.sm_adj)) {
+    Replan r{plan};
+    r.plan.by_levels.resize(A.syms.size(), 0);
+    bool any = false;
+    for (int q = 0; q < NI; ++q) {
+      const int sym = A.items[q].sym;
+      if (c.is_split[q] || !closed[sym]) continue;
+      if (std::max(item_lds(q, false, false), K > 0 ? item_lds(q, false, true) : 0) <= (size_t)max_lds) continue;
+      r.plan.by_levels[sym] = 1;
+      any = true;
+    }
+    if (any) throw r;
   }
   // every step kernel runs exactly bs * ks.bpt branch slots per item
   for (const Item &it : A.items)
@@ -1862,18 +1891,20 @@ emt_status emt_build(const emt_net *nets, int32_t n_scen, const emt_sim *sim, em
     emt::Analysis A = emt::analyze(nets, n_scen, *sim);
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return set_error(EMT_EDEVICE, "no HIP device");
-    std::unique_ptr<emt_ctx> c(new emt_ctx);
-    auto upload = [&](emt::Analysis a) {
-      c->A = std::move(a);
+    std::unique_ptr<emt_ctx> c;
+    BuildPlan plan;
+    for (bool built = false; !built;) {
+      c.reset(new emt_ctx);
+      c->A = std::move(A);
       c->sim = *sim;
       hip_check(hipGetDevice(&c->device), "hipGetDevice");
-      upload_all(*c, nets);
-    };
-    try {
-      upload(std::move(A));
-    } catch (const SwitchesByLevels &) {
-      c.reset(new emt_ctx);
-      upload(emt::analyze(nets, n_scen, *sim, false));
+      try {
+        upload_all(*c, nets, plan);
+        built = true;
+      } catch (const Replan &r) {  // each names something that the plan before did not
+        plan = r.plan;
+        A = emt::analyze(nets, n_scen, *sim, plan.switches_last);
+      }
     }
     hip_check(emt::launch_companions(c->dc, c->ca, nullptr), "companions");
     hip_check(emt::launch_reset(c->dc, c->d_bitem, c->d_blocal, c->nbr_total, c->nodes_total, c->ring_doubles, nullptr), "reset");

@@ -85,6 +85,39 @@ def test_adjoint_of_large_components_with_every_node_recorded(torch_cuda, n, kw)
     assert np.all(np.isfinite(ref)) and np.max(np.abs(ref)) > 0 and rel(got, ref) < 1e-11
 
 
+def hub(n_leaf, n_chain, caps=0):
+    """A hub with a source, n_leaf leaves on resistors of 50 ohm and a chain of
+    n_chain nodes; the first `caps` leaves have a capacitor."""
+    br = [dict(k=0, m=-1, kind=SRC, R=1.0, L=1e-3, E=10.0, omega=W60, phase=0.0)]
+    br += [dict(k=j if j else 0, m=j + 1, kind=RES, R=5.0) for j in range(n_chain)]
+    br.append(dict(k=n_chain, m=-1, kind=CAP, C=1e-6))
+    a = 1 + n_chain
+    br += [dict(k=0, m=a + j, kind=RES, R=50.0) for j in range(n_leaf)]
+    br += [dict(k=a + j, m=-1, kind=CAP, C=1e-7) for j in range(caps)]
+    return a, br
+
+
+@pytest.mark.parametrize("n_leaf", [5500, 5869, 6100])
+def test_hub_with_a_chain_at_the_lds_limit(torch_cuda, oracle_mod, n_leaf):
+    # the chain makes level passes dear, so that the closed form is chosen; its
+    # vectors fit the LDS with 12 branch slots a lane, and from about 5870
+    # nodes on not with the 16 of the kernels without staged factors. Leaves
+    # without a capacitor follow the hub
+    from paper_1903_01081_amd.sim import Simulator
+    n_chain, dt, T = 30, 20e-6, 12
+    a, br = hub(n_leaf, n_chain)
+    net = netgen.circuit(a + n_leaf, br, rec_nodes=[0, n_chain, a, a + n_leaf - 1])
+    small = netgen.circuit(a, hub(0, n_chain)[1], rec_nodes=[0, n_chain])
+    say(f"hub with {n_leaf} leaves and a chain")
+    sim = Simulator([net], dt, T)
+    say(sim.info())
+    assert (sim.info()["sweep_levels"] <= 3) == (n_leaf < 5800)
+    sim.factor()
+    got = sim.step(T).cpu().numpy()[0]
+    ref = oracle_mod.run(small, dt, T)
+    assert rel(got, ref[:, [0, 1, 0, 0]]) < 1e-9
+
+
 def rectifier():
     """A half-wave rectifier: a source, a diode, an R-C load."""
     return [dict(k=0, m=-1, kind=SRC, R=0.5, L=1e-3, E=10.0, omega=W60, phase=-1.2),
