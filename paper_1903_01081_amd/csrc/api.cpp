@@ -839,7 +839,11 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
       may = true;
     } else {
       d = forced_tail >= 0 ? std::min({forced_tail, n, c.ks.dmax}) : choose_tail(A.syms[q], c.ks.dmax);
-      may = true;
+      // A caller who asks for no tail asks for triangular sweeps and no
+      // inverse: in a part that is tied to ground by 1e9 ohm alone they keep
+      // differences of voltages to 6e-13, the closed form of such a component
+      // (its whole inverse) to 6e-7. With a tail every cluster is tied to it.
+      may = forced_tail != 0;
     }
     plans[q] = plan_sweeps(A.syms[q], d);
     // diodes and controlled switches: their terminals, ordered last, must lie
