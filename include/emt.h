@@ -177,8 +177,9 @@ typedef struct {
 /* Simulation settings shared by all scenarios of a context.
  *   dt > 0, n_steps >= 1 (the horizon T).
  *   checkpoint_every K: 0 = no checkpoints (emt_adjoint unavailable); else
- *     the forward run stores the branch state every K steps and the adjoint
- *     recomputes each K-step segment from its checkpoint.
+ *     the forward run stores the branch state every K steps, and the adjoint
+ *     restores each K-step segment's branch currents from its checkpoint and
+ *     the stored node voltages, or runs its steps again (segment_rows).
  *   solver: how each connected component's G v = rhs is solved (Sec. III-A,
  *     fourth basic process). SPARSE: level-scheduled forward/backward sweeps
  *     over the LDL^T factor. DENSE: v = G^{-1} rhs with the component's whole
@@ -240,7 +241,15 @@ typedef struct {
  *     the workgroup (COMPENSATION: 64, 128, 192 or 256; 0 = the fewest
  *     that hold its branches at up to 8 per lane), and a workgroup of
  *     block_size x comp_items lanes (at most 1024, covering the
- *     component's nodes) applies Z to all of its components at once. */
+ *     component's nodes) applies Z to all of its components at once.
+ *   segment_rows: 1 = with checkpoints, keep the node voltages of one
+ *     checkpoint segment at a time (two with the pipelined adjoint), which
+ *     emt_adjoint recomputes; 0 = of every step of the horizon, 8 bytes per
+ *     node and source and step, where that is at most a sixteenth of the
+ *     device's memory and half of what is free at emt_build (else as 1, also
+ *     where the device turns out to have no room for them). Results are
+ *     bitwise the same either way; 1 bounds the memory by checkpoint_every,
+ *     0 saves emt_adjoint the second forward run. */
 typedef struct {
   double dt;
   int64_t n_steps;
@@ -254,6 +263,7 @@ typedef struct {
   int32_t split_device_scope;
   int32_t pack_nodes;
   int32_t comp_items;
+  int32_t segment_rows;
 } emt_sim;
 
 /* Sizes of a built context (emt_info) or of a host-only analysis. */

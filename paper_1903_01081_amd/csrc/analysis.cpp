@@ -442,6 +442,7 @@ Analysis analyze(const emt_net *nets, int n_scen, const emt_sim &sim, bool switc
   if (sim.dense_tail < -1) fail(EMT_EINVAL, "dense_tail must be >= -1");
   if (sim.sweep_from_global != 0 && sim.sweep_from_global != 1) fail(EMT_EINVAL, "sweep_from_global must be 0 or 1");
   if (sim.serial_adjoint != 0 && sim.serial_adjoint != 1) fail(EMT_EINVAL, "serial_adjoint must be 0 or 1");
+  if (sim.segment_rows != 0 && sim.segment_rows != 1) fail(EMT_EINVAL, "segment_rows must be 0 or 1");
   if (sim.split_device_scope != 0 && sim.split_device_scope != 1)
     fail(EMT_EINVAL, "split_device_scope must be 0 or 1");
   if (sim.pack_nodes < 0 || sim.pack_nodes > 32766) fail(EMT_EINVAL, "pack_nodes must be 0..32766");

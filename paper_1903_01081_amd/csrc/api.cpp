@@ -662,6 +662,8 @@ struct BuildPlan {
   bool switches_last = true;
   // symbolic patterns whose closed form does not fit the LDS
   std::vector<char> by_levels;
+  // the adjoint's trajectory rows of the whole horizon, where they fit
+  bool keep_rows = true;
 };
 struct Replan {
   BuildPlan plan;
@@ -959,12 +961,12 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
         rows[r].row = r;
         for (int e = it.nptr[r]; e < it.nptr[r + 1]; ++e) rows[r].e.push_back({it.nent[e], 0});
       }
-      auto program = [&](const std::vector<int> &k) {
+      auto program = [&](const std::vector<int> &k, const std::vector<int> *lg) {
         auto f = prog_ids.emplace(k, (int)gprogs.size());
-        if (f.second) gprogs.push_back(schedule_rows(rows, bs, it.n_br << 1, 0));
+        if (f.second) gprogs.push_back(schedule_rows(rows, bs, it.n_br << 1, 0, lg));
         return f.first->second;
       };
-      prog_f[q] = program(key);
+      prog_f[q] = program(key, nullptr);
       if (K <= 0) continue;
       prog_a[q] = prog_f[q];
       if (seeds_global) continue;
@@ -976,7 +978,9 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
         key.push_back(nodes[e]);
       }
       key.push_back(-1);
-      prog_a[q] = program(key);
+      // (a segment run again then rounds as the forward run did)
+      const std::vector<int> lg = gprogs[prog_f[q]].lg;
+      prog_a[q] = program(key, &lg);
     }
   };
   plan_gathers();
@@ -1148,15 +1152,18 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
   if (f_gl > (size_t)max_lds) throw Error{EMT_EINVAL, "a connected component needs more LDS than a workgroup has"};
   c.ks_adj_ok = a_gl <= (size_t)max_lds;
   // Trajectory rows (checkpoints): all T steps where they fit a sixteenth of
-  // the device's memory, else one segment's (two for the pipelined adjoint).
+  // the device's memory and half of what is free, else one segment's (two for
+  // the pipelined adjoint).
   bool vt_full = false;
   if (K > 0) {
     double per_step = 0.0;
     for (const Item &it : A.items) per_step += 8.0 * (it.n + it.n_src);
     size_t free_b = 0, total_b = 0;
     hip_check(hipMemGetInfo(&free_b, &total_b), "memory size");
-    vt_full = per_step * (double)T <= std::min((double)total_b / 16.0, (double)free_b / 2.0);
+    vt_full = plan.keep_rows && !sim.segment_rows &&
+              per_step * (double)T <= std::min((double)total_b / 16.0, (double)free_b / 2.0);
   }
+  c.dc.vt_full = vt_full ? 1 : 0;
   c.ks.gen = !vt_full || any_level;
   // Pipelined adjoint where both workgroups of every item fit on the device
   // at once (cooperative launch) and it was not turned off.
@@ -1621,7 +1628,6 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
   dc.ck_u = K > 0 ? c.alloc<double>(ck_off) : nullptr;
   dc.seg_i = K > 0 ? c.alloc<double>(seg_off) : nullptr;
   dc.vt = K > 0 ? c.alloc<double>(vt_off) : nullptr;
-  dc.vt_full = vt_full ? 1 : 0;
   if (c.adj_pipe) c.d_pipe = c.alloc<int32_t>(2 * (size_t)NI);
   dc.sw_tab = sw_tab.empty() ? nullptr : c.upload(sw_tab);
   dc.line_tab = line_tab.empty() ? nullptr : c.upload(line_tab);
@@ -1907,8 +1913,13 @@ emt_status emt_build(const emt_net *nets, int32_t n_scen, const emt_sim *sim, em
         built = true;
       } catch (const Replan &r) {  // each names something that the plan before did not
         plan = r.plan;
-        A = emt::analyze(nets, n_scen, *sim, plan.switches_last);
+      } catch (const emt::Error &e) {
+        // no room beside the rows of the whole horizon: one segment's
+        if (e.status != EMT_ENOMEM || !c->dc.vt_full) throw;
+        (void)hipGetLastError();
+        plan.keep_rows = false;
       }
+      if (!built) A = emt::analyze(nets, n_scen, *sim, plan.switches_last);
     }
     hip_check(emt::launch_companions(c->dc, c->ca, nullptr), "companions");
     hip_check(emt::launch_reset(c->dc, c->d_bitem, c->d_blocal, c->nbr_total, c->nodes_total, c->ring_doubles, nullptr), "reset");

@@ -21,13 +21,14 @@ struct Batch {
 };
 
 // Batches of rows when a lane takes at most `most` entries (long rows take
-// more once 2^kMaxLg lanes share them).
-std::vector<Batch> make_batches(const std::vector<RowSum> &rows, int most) {
+// more once 2^kMaxLg lanes share them), or of rows whose lanes are given.
+std::vector<Batch> make_batches(const std::vector<RowSum> &rows, int most, const std::vector<int> *lg_given,
+                                std::vector<int> &lg_of) {
   std::vector<std::pair<int, int>> order;  // (-lg, index): widest teams first, long rows first
-  std::vector<int> lg_of(rows.size());
+  lg_of.assign(rows.size(), 0);
   for (size_t i = 0; i < rows.size(); ++i) {
     const int cnt = (int)rows[i].e.size();
-    int lg = 0;
+    int lg = lg_given ? (*lg_given)[i] : 0;
     while (lg < kMaxLg && (cnt + (1 << lg) - 1) >> lg > most) ++lg;
     lg_of[i] = lg;
   }
@@ -71,15 +72,17 @@ int assign(const std::vector<Batch> &b, int waves, std::vector<int> &wave_of) {
 
 }  // namespace
 
-RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_code, int pad_src) {
+RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_code, int pad_src,
+                         const std::vector<int> *lg) {
   const int waves = lanes / kWave;
   std::vector<Batch> best;
-  std::vector<int> best_wave;
+  std::vector<int> best_wave, best_lg;
   int64_t best_cost = INT64_MAX;
   if (!rows.empty())
     for (int q : {1, 2, 3, 4, 6, 8, 16}) {
-      std::vector<Batch> b = make_batches(rows, q * kQuad);
-      std::vector<int> w;
+      if (lg && q != 16) continue;
+      std::vector<int> w, l;
+      std::vector<Batch> b = make_batches(rows, q * kQuad, lg, l);
       // the slowest wave, and (LDS traffic) all quads
       int64_t quads = 0;
       for (const Batch &x : b) quads += x.quads;
@@ -88,12 +91,14 @@ RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_cod
         best_cost = cost;
         best = std::move(b);
         best_wave = std::move(w);
+        best_lg = std::move(l);
       }
     }
   for (const RowSum &r : rows)
     if ((int)r.e.size() > kMaxRowEntries)
       throw Error{EMT_EINVAL, "a row of a component's sums has more than " + std::to_string(kMaxRowEntries) + " entries"};
   RowProgram p;
+  p.lg = std::move(best_lg);
   p.meta.assign(waves + 1, 0);
   std::vector<int32_t> words;
   for (int w = 0; w < waves; ++w) {

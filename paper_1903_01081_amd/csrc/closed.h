@@ -32,6 +32,7 @@ struct RowProgram {
   int batches = 0, quads = 0;
   std::vector<int32_t> meta, src;
   std::vector<uint16_t> code, row;
+  std::vector<int> lg;  // log2 of the lanes that share each row given
 };
 
 struct RowSum {
@@ -45,8 +46,11 @@ struct RowSum {
 // where a node is recorded in more columns than that.
 constexpr int kMaxRowEntries = 255 * 4 * 16;
 
-// Throws Error (EMT_EINVAL) on a longer row.
-RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_code, int pad_src);
+// Throws Error (EMT_EINVAL) on a longer row. lg: the lanes of each row as in
+// another program whose rows begin with the same entries, so that these meet
+// in the same order and entries of value zero after them change no sum.
+RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_code, int pad_src,
+                         const std::vector<int> *lg = nullptr);
 
 // Sizes of the closed form at one cut.
 struct ClosedSize {
