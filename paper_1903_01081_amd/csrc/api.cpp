@@ -177,6 +177,15 @@ double closed_cost(const emt::ClosedSize &z, int d, int n, int bs, double room) 
   return tail + (d < n ? 300 : 0) + (d > 0 && d < n ? 300 : 0) + entries / 256.0 * 36 + 40 * rounds +
          (bytes > room ? 300 + (bytes - std::max(0.0, room)) / 32 : 0);
 }
+// Rough cycles of factorising anew after a switch changes its state: the
+// tail's pivots, one barrier and a lane's share of the tail each (124 pivots
+// at 256 lanes 1000 cycles each, 192 at 512 lanes 1800), or the levels of the
+// whole elimination tree, two barriers each (22 levels: 38 us).
+double tail_factor_cost(int d, int bs) {
+  const double rows = std::ceil(tail_capacity(bs, d) / (bs / 16.0)), cols = tail_capacity(bs, d) / 32.0;
+  return d * (350.0 + 10.0 * std::max(1.0, bs / 256.0) * rows * cols * 2.0);
+}
+double levels_factor_cost(int levels) { return 4100.0 * levels; }
 double levels_cost(const emt::SweepPlan &P) { return 700.0 * (P.nfpass() + P.nbpass()) + (P.d > 0 ? 600 : 0); }
 
 }  // namespace
@@ -787,12 +796,14 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
     if (c.is_split[q]) sym_split[A.items[q].sym] = 1;
   // items with diodes refactorise inside the time loop: sweeps only (the
   // dense tail's inverse would have to be recomputed there too)
-  std::vector<char> sym_diode(A.syms.size(), 0), item_diode(NI, 0);
+  std::vector<char> sym_diode(A.syms.size(), 0), item_diode(NI, 0), any_diode_in(A.syms.size(), 0);
   for (int q = 0; q < NI; ++q) {
     const Item &it = A.items[q];
     for (int b : it.br)
       if (b >= 0 && (nets[it.scen].kind[b] == EMT_DIODE || nets[it.scen].kind[b] == EMT_CSWITCH))
         sym_diode[it.sym] = item_diode[q] = 1;
+    for (int b : it.br)
+      if (b >= 0 && nets[it.scen].kind[b] == EMT_DIODE) any_diode_in[it.sym] = 1;
   }
   // Entries of G in each symbolic pattern (those of its first item: items
   // share a pattern only with the same edges).
@@ -870,12 +881,20 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
     if (!may || sym_fixed[q] > max_lds || 2 * (n + 1) > 65535) continue;
     const bool fixed = solver == EMT_SOLVER_DENSE || (forced_tail >= 0 && !sym_diode[q]);
     const std::vector<ClosedSize> z = closed_sizes(A.syms[q], fixed ? d : closed_tail_max(bs));
-    double best = levels_cost(plans[q]);
+    // Changes of state per step: a diode that ends an inductor's current
+    // chatters, and bridges change in most steps (124 nodes with two bridges:
+    // 51 us a step by levels, 53 with the cut of cheapest solve, the whole
+    // component, 8 with ten nodes). Hysteresis keeps controlled switches
+    // apart; their cut is the cheapest solve's, since a smaller tail leaves
+    // larger clusters to emt_factor (a short run of choppers took 343 us for
+    // 254).
+    const double changes = any_diode_in[q] ? 1.0 : 0.0;
+    double best = levels_cost(plans[q]) + changes * levels_factor_cost(A.syms[q].levels_f());
     const double room = max_lds - sym_lds[q] - 16.0 * (n + 1) - 8.0 * bs;
     int best_d = -1;
     for (int e = fixed ? d : d_min; e < (int)z.size(); ++e) {
       if (2 + z[e].q + z[e].nn > kClosedValues) continue;
-      const double cost = closed_cost(z[e], e, n, bs, room);
+      const double cost = closed_cost(z[e], e, n, bs, room) + changes * tail_factor_cost(e, bs);
       if (cost < best) {
         best = cost;
         best_d = e;

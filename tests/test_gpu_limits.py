@@ -199,3 +199,18 @@ def test_no_tail_keeps_differences_of_a_floating_part(torch_cuda, oracle_mod, n)
     got = sim.step(T).cpu().numpy()[0]
     ref = oracle_mod.run(net, 20e-6, T)
     assert rel(got[:, 2:] - got[:, 2:3], ref[:, 2:] - ref[:, 2:3]) < 1e-10
+
+
+@pytest.mark.parametrize("n_bus,device", [(40, dict(rectifiers=2)), (30, dict(rectifiers=1)), (60, dict(rectifiers=4))])
+def test_cut_of_components_with_diode_bridges(torch_cuda, oracle_mod, n_bus, device):
+    # the tail is factorised anew in most steps: it is not the whole component
+    from paper_1903_01081_amd.sim import Simulator
+    T = 400
+    nets, cfg = netgen.config1(seed=3, n_bus=n_bus, n_steps=T, fault_step=200, **device)
+    say(f"{n_bus} buses, {device}")
+    sim = Simulator(nets, cfg["dt"], T)
+    assert sim.info()["sweep_levels"] <= 3 and 0 < sim.info()["max_tail"] <= 64
+    sim.factor()
+    got = sim.step(T).cpu().numpy()[0]
+    sim.sync()
+    assert rel(got, oracle_mod.run(nets[0], cfg["dt"], T)) < 1e-9
