@@ -250,7 +250,7 @@ __device__ __forceinline__ void fma_rows8(double &acc, double x, const double (&
 #define EMT_FMA(U, Z) "v_fmac_f64_dpp %0, %1, %" #Z " row_newbcast:" #U " row_mask:0xf bank_mask:0xf\n\t"
   asm("s_nop 1\n\t" EMT_FMA(0, 2) EMT_FMA(1, 3) EMT_FMA(2, 4) EMT_FMA(3, 5) EMT_FMA(4, 6) EMT_FMA(5, 7)
           EMT_FMA(6, 8) EMT_FMA(7, 9)
-      : "+v"(acc)
+      : "+&v"(acc)
       : "v"(x), "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]), "v"(z[4]), "v"(z[5]), "v"(z[6]), "v"(z[7]));
 #undef EMT_FMA
 }
