@@ -182,6 +182,21 @@ struct View {
   Lds<int32_t> swflag;
 };
 
+// 16-byte blocks into LDS, block i from at(i), U of a lane's loads in flight
+// (loads past the end fetch the last block).
+template <int BS, int U, class F>
+__device__ __forceinline__ void copy_blocks(uint32_t off, int cnt, F &&at) {
+  uint4 *dst = reinterpret_cast<uint4 *>(emt_lds + off);
+  for (int q = (int)threadIdx.x; q < cnt; q += U * BS) {
+    uint4 r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = *at(q + u * BS < cnt ? q + u * BS : cnt - 1);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (q + u * BS < cnt) dst[q + u * BS] = r[u];
+  }
+}
+
 template <int BS, class T>
 __device__ __forceinline__ void copy_to(uint32_t off, const T *src, int cnt) {
   T *dst = reinterpret_cast<T *>(emt_lds + off);
@@ -576,15 +591,21 @@ __device__ __forceinline__ int factor_tail(Tail<BS, DT> &T, int d, double *line,
 }
 
 // Factor values and the tail inverse of topology t (values and 1/D in LDS
-// under SM, the lane's share of W in VGPRs).
-template <int BS, int DT, bool SM>
+// under SM, the lane's share of W in VGPRs). U: the closed form's values are
+// staged U blocks of a lane at a time.
+template <int BS, int DT, bool SM, int U = 1>
 __device__ __forceinline__ void select_factor(const DevCtx &c, const ItemDesc &it, View<SM> &v, int t,
                                               Tail<BS, DT> &T) {
   const double *sv = c.svals + it.sv + (int64_t)t * v.nsv;
   const double *di = c.dinv + it.dfac + (int64_t)t * v.n;
   v.svg = sv;
   if constexpr (SM) {
-    copy_to<BS>(v.sv_s.off, sv, v.closed ? 2 * v.lim : v.nsv);
+    if constexpr (U > 1) {
+      const uint4 *blocks = reinterpret_cast<const uint4 *>(sv);
+      copy_blocks<BS, U>(v.sv_s.off, v.lim, [&](int i) { return blocks + i; });
+    } else {
+      copy_to<BS>(v.sv_s.off, sv, v.closed ? 2 * v.lim : v.nsv);
+    }
     if (!v.closed) copy_to<BS>(v.dinv_s.off, di, v.ns);
   } else {
     v.sv.p = sv;
@@ -1726,6 +1747,14 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
                                                 double *rec) {
   constexpr bool kLevels = KIND == STEP_FULL || KIND == STEP_LEVELS;
   // line ends or coupled members
+  // A launch of a few steps is mostly staging. Where a lane carries several
+  // branches the factor's values are many for the lanes that stage them, and
+  // one load after another was a trip to memory each: one step a call on 40
+  // buses (64 lanes) 15.5 -> 13.4 us, on 400 (512 lanes) 14.3 -> 13.4; long
+  // launches of 20 to 1000 buses stay within 0.5 % or gain. With fewer branches a lane, or with
+  // lines, groups or switches, the values are few or the longer code costs the
+  // loop registers (lines at 64 lanes 3.03 -> 3.12 us a step).
+  constexpr int kBlocks = KIND == STEP_PLAIN && BPT >= 4 ? 4 : 1;
   constexpr bool kPass = KIND == STEP_LINES || KIND == STEP_GROUPS || KIND == STEP_FULL;
   const ItemDesc it = c.items[order[blockIdx.x]];
   View<SM> v = make_view<BS, SM, kLevels, KIND == STEP_SWITCH ? DT : 0>(c, it, false);
@@ -1758,7 +1787,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     for (int k = 0; k < 2 * Tail<BS, DT>::R * Tail<BS, DT>::Q; ++k) w.w[k] = 0.0;
     refactor_dynamic<BS, BPT, SM>(c, it, v, L);
   } else {
-    select_factor<BS, DT, SM>(c, it, v, t, w);
+    select_factor<BS, DT, SM, kBlocks>(c, it, v, t, w);
   }
   double dv[(Tail<BS, DT>::R + 3) / 4];
   SwitchLane sl;
@@ -1919,7 +1948,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
     if (sw) {
       ++t;
       next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
-      if (!diodes) select_factor<BS, DT, SM>(c, it, v, t, w);
+      if (!diodes) select_factor<BS, DT, SM, kBlocks>(c, it, v, t, w);
       fresh = switches;
     }
     special = special_step();
