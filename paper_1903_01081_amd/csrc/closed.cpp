@@ -16,41 +16,27 @@ constexpr int kWave = 64, kQuad = 4, kMaxLg = 4;
 int batch_cost(int quads, int lg) { return 60 + 40 * quads + 25 * lg; }
 
 struct Batch {
-  int lg = 0, quads = 0, cost = 0;
-  std::vector<int> rows;
+  int lg, quads, cost;
+  int first, count;  // rows, in the order below
 };
 
-// Batches of rows when a lane takes at most `most` entries (long rows take
-// more once 2^kMaxLg lanes share them), or of rows whose lanes are given.
-std::vector<Batch> make_batches(const std::vector<RowSum> &rows, int most, const std::vector<int> *lg_given,
-                                std::vector<int> &lg_of) {
-  std::vector<std::pair<int, int>> order;  // (-lg, index): widest teams first, long rows first
-  lg_of.assign(rows.size(), 0);
-  for (size_t i = 0; i < rows.size(); ++i) {
-    const int cnt = (int)rows[i].e.size();
-    int lg = lg_given ? (*lg_given)[i] : 0;
-    while (lg < kMaxLg && (cnt + (1 << lg) - 1) >> lg > most) ++lg;
-    lg_of[i] = lg;
-  }
-  std::vector<int> idx(rows.size());
-  std::iota(idx.begin(), idx.end(), 0);
-  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
-    if (lg_of[a] != lg_of[b]) return lg_of[a] > lg_of[b];
-    return rows[a].e.size() > rows[b].e.size();
-  });
-  std::vector<Batch> out;
-  for (int i : idx) {
-    if (out.empty() || out.back().lg != lg_of[i] || (int)out.back().rows.size() == (kWave >> lg_of[i])) {
-      out.emplace_back();
-      out.back().lg = lg_of[i];
+// Batches of rows, longest first within a lane count, when a lane takes at
+// most `most` entries (long rows take more once 2^kMaxLg lanes share them).
+// `order` holds the rows by lane count, then length, the longest first; lg_of
+// their lane counts.
+void make_batches(const std::vector<RowSum> &rows, const std::vector<int> &order, const std::vector<int> &lg_of,
+                  std::vector<Batch> &out) {
+  out.clear();
+  for (size_t k = 0; k < order.size(); ++k) {
+    const int i = order[k], lg = lg_of[i];
+    if (!out.empty() && out.back().lg == lg && out.back().count < (kWave >> lg)) {
+      out.back().count++;
+      continue;
     }
-    Batch &b = out.back();
-    const int per_lane = ((int)rows[i].e.size() + (1 << b.lg) - 1) >> b.lg;
-    b.quads = std::max(b.quads, std::max(1, (per_lane + kQuad - 1) / kQuad));
-    b.rows.push_back(i);
+    const int per_lane = ((int)rows[i].e.size() + (1 << lg) - 1) >> lg;
+    const int quads = std::max(1, (per_lane + kQuad - 1) / kQuad);
+    out.push_back({lg, quads, batch_cost(quads, lg), (int)k, 1});
   }
-  for (Batch &b : out) b.cost = batch_cost(b.quads, b.lg);
-  return out;
 }
 
 // Batches to waves, dearest first onto the least loaded wave; returns the
@@ -75,23 +61,40 @@ int assign(const std::vector<Batch> &b, int waves, std::vector<int> &wave_of) {
 RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_code, int pad_src,
                          const std::vector<int> *lg) {
   const int waves = lanes / kWave;
-  std::vector<Batch> best;
-  std::vector<int> best_wave, best_lg;
+  std::vector<Batch> best, b;
+  std::vector<int> best_wave, best_lg, w, lg_of(rows.size());
   int64_t best_cost = INT64_MAX;
+  // a row's lanes grow with its length, so one order serves every choice of
+  // `most`; given lane counts come first
+  std::vector<int> order(rows.size());
+  std::iota(order.begin(), order.end(), 0);
+  auto lanes_of = [&](int most) {
+    for (size_t i = 0; i < rows.size(); ++i) {
+      const int cnt = (int)rows[i].e.size();
+      int l = lg ? (*lg)[i] : 0;
+      while (l < kMaxLg && (cnt + (1 << l) - 1) >> l > most) ++l;
+      lg_of[i] = l;
+    }
+  };
+  if (lg) lanes_of(16 * kQuad);
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+    if (lg && lg_of[x] != lg_of[y]) return lg_of[x] > lg_of[y];
+    return rows[x].e.size() > rows[y].e.size();
+  });
   if (!rows.empty())
     for (int q : {1, 2, 3, 4, 6, 8, 16}) {
       if (lg && q != 16) continue;
-      std::vector<int> w, l;
-      std::vector<Batch> b = make_batches(rows, q * kQuad, lg, l);
+      if (!lg) lanes_of(q * kQuad);
+      make_batches(rows, order, lg_of, b);
       // the slowest wave, and (LDS traffic) all quads
       int64_t quads = 0;
       for (const Batch &x : b) quads += x.quads;
       const int64_t cost = assign(b, waves, w) + 8 * quads;
       if (cost < best_cost) {
         best_cost = cost;
-        best = std::move(b);
-        best_wave = std::move(w);
-        best_lg = std::move(l);
+        best.swap(b);
+        best_wave.swap(w);
+        best_lg = lg_of;
       }
     }
   for (const RowSum &r : rows)
@@ -113,10 +116,10 @@ RowProgram schedule_rows(const std::vector<RowSum> &rows, int lanes, int pad_cod
       p.row.resize(p.row.size() + kWave, 0xFFFF);
       const size_t r0 = p.row.size() - kWave;
       const int g = 1 << b.lg;
-      for (size_t k = 0; k < b.rows.size(); ++k) {
-        const RowSum &r = rows[b.rows[k]];
+      for (int k = 0; k < b.count; ++k) {
+        const RowSum &r = rows[order[b.first + k]];
         for (size_t e = 0; e < r.e.size(); ++e) {
-          const int lane = (int)k * g + (int)(e % g), slot = (int)(e / g);
+          const int lane = k * g + (int)(e % g), slot = (int)(e / g);
           const int quad = slot / kQuad, s = slot % kQuad;
           p.code[c0 + ((size_t)quad * kWave + lane) * kQuad + s] = (uint16_t)r.e[e].first;
           p.src[c0 + (size_t)quad * kWave * kQuad + (size_t)(s / 2) * kWave * 2 + lane * 2 + (s & 1)] = r.e[e].second;
