@@ -26,9 +26,9 @@
  * dropped), u is the voltage across a branch's passive part, i flows k -> m.
  * The initial state is v = 0, i = 0, u = A^T v - e(0). Switching events
  * apply at a step index: the new topology produces v at that step. The
- * conductance matrix is factorised once per topology (LDL^T on a symbolic
- * pattern shared by all topologies and by isomorphic scenarios); no
- * factorisation happens inside the time loop.
+ * conductance matrix is factorised once per topology (on a symbolic pattern
+ * shared by all topologies and by isomorphic scenarios), before the time
+ * loop; only diodes and controlled switches (below) factorise inside it.
  *
  * Conventions: FP64 values, int32 indices, node ids 0..n_nodes-1, ground -1,
  * row-major arrays. Host arrays passed to a call are borrowed for that call
@@ -105,8 +105,11 @@ typedef enum {
  *              whose current is negative blocks from the next step on and a
  *              blocking one whose voltage v_k - v_m is positive conducts
  *              from the next step on, the conductance matrix being
- *              refactorised inside the time loop (one-workgroup solvers,
- *              sweeps without a dense tail). Diodes take no events; a batch
+ *              refactorised inside the time loop (one-workgroup solvers:
+ *              AUTO keeps the switches' terminals in the dense tail, whose
+ *              factor alone changes then, or, where that does not fit or the
+ *              batch has lines or coupled groups as well, and with SPARSE,
+ *              factorises the component by levels). Diodes take no events; a batch
  *              with diodes runs forward only (EMT_EINVAL with checkpoints,
  *              the dense solver or emt_steady_state). The plain trapezoidal
  *              rule rings when a diode interrupts an inductor's current, so
@@ -124,7 +127,7 @@ typedef enum {
  *              (the one-step delay breaks the algebraic loop between the
  *              controller and the network it measures); in_service0 is its
  *              state before step 1. Like diodes: refactorised inside the
- *              loop, no events, forward only, sweep solvers.
+ *              loop, no events, forward only, solvers AUTO and SPARSE.
  *   E, omega, phase  source EMF E cos(omega t + phase); read for EMT_SRC only.
  *   line       pi-section line index l of the branch, or -1. Line parameters
  *              theta[3l + {0,1,2}] = (R_l, L_l, C_l) are the series R and L
@@ -188,9 +191,12 @@ typedef struct {
  *     split by columns over ceil(n/split_cols) workgroups that exchange
  *     partial voltages every step (all must be resident at once: EMT_EINVAL
  *     from emt_build otherwise; forward only: EMT_EINVAL with
- *     checkpoint_every > 0). AUTO: sweeps over the leading rows of the
- *     elimination order and the dense inverse of its trailing block, cut
- *     where a cost model finds fewest dependent phases.
+ *     checkpoint_every > 0). AUTO: the elimination order is cut where a
+ *     cost model finds the cheapest solve; its trailing block (the dense
+ *     tail) is solved by its inverse, and the leading nodes, which it parts
+ *     into small clusters, in closed form around it (two sets of independent
+ *     row sums), or by level-scheduled sweeps where that would be too dense
+ *     or would not fit a workgroup.
  *     COMPENSATION (Sec. III-B's many scenarios of one network, with Sec.
  *     III-A's factorisation done once for all of them; the compensation
  *     itself is not in the paper): the first scenario's components, in
@@ -217,12 +223,14 @@ typedef struct {
  *   split_cols: inverse columns per workgroup of a split component (16 or
  *     32; 0 = 32 where the lane state fits, else 16).
  *   dense_tail: AUTO solver only, the dense tail size in nodes (capped by
- *     the block size's limit); -1 = the cost model.
- *   sweep_from_global: 1 = the sweep data (factor values, row descriptors,
- *     node CSR) stay in global memory even where LDS would hold them.
- *   serial_adjoint: 1 = emt_adjoint recomputes and reverses each checkpoint
+ *     the block size's limit); 0 = level-scheduled sweeps without an inverse;
+ *     -1 = the cost model. Components with diodes or controlled switches keep
+ *     the model's.
+ *   sweep_from_global: 1 = the solve's data (factor values, row programs or
+ *     descriptors) stay in global memory even where LDS would hold them.
+ *   serial_adjoint: 1 = emt_adjoint restores and reverses each checkpoint
  *     segment in turn with one workgroup per item; 0 = where both fit on the
- *     device at once, a second workgroup per item recomputes segment s-1
+ *     device at once, a second workgroup per item restores segment s-1
  *     while the first reverses segment s (twice the segment buffer).
  *   split_device_scope: 1 = the workgroups of a split component always
  *     exchange their partial voltages through device-coherent memory; 0 =
@@ -282,7 +290,8 @@ typedef struct {
   int64_t device_bytes;  /* device memory owned by the context */
   int32_t dense_items;   /* items solved entirely by their dense tail inverse */
   int32_t block_size;    /* threads per work item in the step kernels */
-  int32_t sweep_levels;  /* barrier-separated solve phases per step (max over items) */
+  int32_t sweep_levels;  /* barrier-separated solve phases per step (max over items;
+                            at most 3 where every item is solved in closed form) */
   int32_t max_tail;      /* largest dense tail (nodes) */
   int32_t lds_bytes;     /* LDS per workgroup of the forward step kernel */
   int32_t lds_limit;     /* LDS per workgroup the device allows */
@@ -290,7 +299,7 @@ typedef struct {
   int32_t lanes_per_block; /* branches per lane */
   int32_t split_tiles;   /* workgroups of the split dense components (0 if none) */
   int32_t split_cols;    /* inverse columns per split workgroup (16 or 32; 0 if none) */
-  int32_t adjoint_pipelined; /* 1 if emt_adjoint overlaps each segment's recompute with
+  int32_t adjoint_pipelined; /* 1 if emt_adjoint overlaps restoring each segment with
                                 the previous segment's reversal (two workgroups per item) */
   int32_t split_local;   /* split components whose last launch exchanged through one XCD's L2
                             (0 before the first step; synchronises the device) */
@@ -338,7 +347,7 @@ emt_status emt_set_params(emt_ctx *ctx, const double *theta_dev, void *stream);
  * conductance matrix), done here once per topology that the switching
  * events produce, before the time loop.
  * Numerically factorise G of every topology of every scenario (LDL^T on the
- * shared symbolic pattern; with the COMPENSATION solver also each base's
+ * shared symbolic pattern, or the closed form's blocks; with the COMPENSATION solver also each base's
  * dense inverse and every scenario's K per topology). Starts a run (clears
  * the device error flag) and synchronises `stream` to check the pivots:
  * EMT_ESINGULAR if any pivot is non-positive or not finite (or a K does not
@@ -448,11 +457,12 @@ emt_status emt_steady_state(emt_ctx *ctx, void *stream);
  * transposed solves through the factors of emt_factor.
  * Reverse-time adjoint (vector-Jacobian product) of the whole recorded
  * waveform: given dJ_drec_dev [S][T][R] returns grad_dev [S][P] = dJ/dtheta
- * (entries past a scenario's n_params are set to 0). Recomputes each
- * checkpoint segment, then runs transposed solves through the same factors
- * backwards in time; where both fit on the device at once, a second
- * workgroup per component recomputes segment s-1 while segment s is
- * reversed (emt_info.adjoint_pipelined; a give-up of those workgroups is
+ * (entries past a scenario's n_params are set to 0). Restores each
+ * checkpoint segment (from the node voltages that the forward run kept, or by
+ * running its steps again: emt_sim.segment_rows), then runs transposed solves
+ * through the same factors backwards in time; where both fit on the device at
+ * once, a second workgroup per component restores segment s-1 while segment s
+ * is reversed (emt_info.adjoint_pipelined; a give-up of those workgroups is
  * reported by emt_sync as EMT_EDEVICE; while `stream` is being captured
  * into a HIP graph the one-workgroup kernel runs instead). Stream-ordered;
  * bitwise the same gradient either way. dJ_drec_dev may be

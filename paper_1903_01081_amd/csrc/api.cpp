@@ -815,12 +815,13 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
       if (p >= 0) g.push_back(p);
     g.insert(g.end(), it.mpos.begin(), it.mpos.end());
   }
-  // Closed form or level passes. The closed form where its row programs are
-  // estimated cheaper than the level passes (a tail that cuts the rest into
-  // small clusters; a pass costs about 700 cycles whatever it holds, a quad
-  // of a row program about 10 per wave). Level passes stay for solver
-  // SPARSE, for items refactorised inside the loop and for factors whose
-  // closed form would be too dense.
+  // Closed form or level passes. The closed form where its solve (closed_cost)
+  // is estimated cheaper than the level passes (levels_cost): a tail that cuts
+  // the rest into small clusters. Level passes stay for solver SPARSE and a
+  // forced tail of no nodes, for components whose closed form would be too
+  // dense or too large for the LDS, and for components with diodes or
+  // controlled switches beside others that only the general kernel runs
+  // (else these keep the tail's matrix in closed form: closed = 2).
   std::vector<char> closed(A.syms.size(), 0);
   std::vector<double> sym_lds(A.syms.size(), 0.0);  // injections and their sums' codes
   // what the closed form keeps in LDS whatever is staged there (step_lds),
@@ -1105,8 +1106,10 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
     }
   }
   // LDS a workgroup may take: all of a compute unit's, or half where the
-  // batch has more items than the device has compute units (two workgroups
-  // share one then; a 502-item batch at 107 KB each ran in two rounds).
+  // batch has more items than the device has compute units (two workgroups of
+  // the forward kernel share one then; a 502-item batch at 107 KB each ran in
+  // two rounds). The adjoint's kernels run one workgroup a unit at 256 lanes
+  // and more for their registers, and take the same half.
   int n_cu_lds = 0, n_one = 0;
   hip_check(hipDeviceGetAttribute(&n_cu_lds, hipDeviceAttributeMultiprocessorCount, c.device), "CU count");
   for (int q = 0; q < NI; ++q) n_one += c.is_split[q] ? 0 : 1;
@@ -1314,7 +1317,6 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
       d.ncl = (int32_t)C.cluster.size() / 2;
       d.n_n = C.n_n;
       d.n_q = C.n_q;
-      d.ngrp = (int32_t)C.n_ptr.size() - 1;
       d.nq_off = (int32_t)C.q_off.size() / 2;
       d.ns_off = (int32_t)C.s_off.size() / 2;
       d.ns_key = (int32_t)C.s_key.size();

@@ -59,7 +59,7 @@ struct SymDesc {
   // programs, 256 per quad, forward then backward): the programs, and for
   // the numeric kernel the plan's lists (closed.h) in symi
   RowProg fwd, bwd;
-  int32_t ncl, n_n, n_q, ngrp, nq_off, ns_off, ns_key, padc;
+  int32_t ncl, n_n, n_q, nq_off, ns_off, ns_key;
   int64_t cluster, q_diag, q_off, n_ptr, n_adj, n_grp, n_col, s_off, s_key, s_ptr, s_term;
   int64_t vsrc;  // [nsv] value index of every program value
 };

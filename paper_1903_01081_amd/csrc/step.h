@@ -14,17 +14,24 @@
 //                 the branch injection J = g e - h into LDS;
 //   gather        every node sums its incident branch ends' J in a fixed
 //                 (CSR) order — a deterministic segmented sum, no atomics;
+// and the solve, in closed form (closed.h) where that is planned,
+//   forward       c = r_D + N r_S, the dense tail's right-hand side;
+//   tail          x_D = W c, W held in VGPRs;
+//   backward      x_S = Q r_S + N^T x_D,
+// each a set of independent rows, or by level passes:
 //   forward       L y = rhs over the leading part of the elimination order,
-//                 one pass per level (level 0 needs none), then the dense
-//                 tail's reduced right-hand side c = rhs_D - L_DS y_S;
-//   tail          x_D = W c, W = (L_DD D_D L_DD^T)^{-1} held in VGPRs;
+//                 one pass per level (level 0 needs none), then the tail's
+//                 reduced right-hand side c = rhs_D - L_DS y_S;
+//   tail          the same;
 //   backward      x = D^{-1} y - L^T x, one pass per level.
-// In a sweep pass each row is shared by 2^k <= 16 adjacent lanes (k per
+// In a level pass each row is shared by 2^k <= 16 adjacent lanes (k per
 // pass, so that a few long rows at the top of the tree use many lanes and
 // many short rows one lane each); the lanes' partial sums meet in a fixed
 // scan of DPP row shifts, so every run rounds identically.
-// All factors of every topology are computed before the loop (k_factor,
-// k_tail); a switching event swaps coefficients and factor pointers.
+// All factors of every topology are computed before the loop (k_factor and
+// k_tail, or k_closed); a switching event swaps coefficients and factor
+// pointers. Components with diodes or controlled switches factor the tail
+// (closed form) or the whole component (level passes) anew inside the loop.
 //
 // Compiled with -ffp-contract=off so that identical formulas round
 // identically in every code path (forward, checkpoint recompute, reload).
@@ -1467,9 +1474,9 @@ __device__ __forceinline__ void switch_step(const DevCtx &c, const ItemDesc &it,
   }
 }
 
-// The tail's factor of a closed-form item with switches: their conductances stamped on the
-// tail's matrix S (k_closed left a copy per topology in the item's scratch),
-// inverted in the lanes' registers. The clusters' parts Q and N do not see
+// The tail's factor of a closed-form item with switches: their conductances
+// stamped on the tail's matrix S (k_closed left a copy per topology in the
+// item's scratch), factorised in the lanes' registers (factor_tail). The clusters' parts Q and N do not see
 // them. One barrier per pivot of the tail, about 450 cycles each, against two
 // barriers of about 2 us per level of the whole elimination tree (and no
 // dense tail for the steps in between) when the component was factorised
@@ -2348,10 +2355,13 @@ __device__ __forceinline__ void store_branch_adjoints(const DevCtx &c, const Ite
 }
 
 // Serial adjoint: one workgroup per item rebuilds (or recomputes) and
-// reverses each segment in turn, last segment first. With 256 lanes the register budget
-// is held to two waves per SIMD (two workgroups per compute unit), so a
-// batch of many components runs in fewer rounds than at the one wave per
-// SIMD that its largest branch-slot counts would otherwise take. GEN: the
+// reverses each segment in turn, last segment first. The registers are those
+// of one wave per SIMD (one workgroup of 256 lanes per compute unit): the
+// reversal carries the voltages and three accumulators of every slot from step
+// to step, 364 registers at 8 slots. Held to two waves it spills 168 of them
+// (324 B a lane), and though a batch of more items than compute units then
+// runs in fewer rounds it takes longer: 502 items 11.0 against 8.4 ms, 768
+// items 19.6 against 10.2. GEN: the
 // batch has level passes or no whole trajectory (the kernels without carry
 // none of their code and registers).
 template <int BS, int BPT, int DT, bool SM, bool GEN>
