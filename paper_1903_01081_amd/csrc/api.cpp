@@ -1074,8 +1074,10 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
       const Item &it = A.items[q];
       f_sm = std::max(f_sm, item_lds(q, true, false));
       f_gl = std::max(f_gl, item_lds(q, false, false));
-      a_sm = std::max(a_sm, item_lds(q, true, true));
-      a_gl = std::max(a_gl, item_lds(q, false, true));
+      if (K > 0) {  // else there is no adjoint whose size could matter
+        a_sm = std::max(a_sm, item_lds(q, true, true));
+        a_gl = std::max(a_gl, item_lds(q, false, true));
+      }
       if (!closed[it.sym] && plans[it.sym].nsv() > 65535)
         throw Error{EMT_EINVAL, "a connected component's factor is too large"};
     }

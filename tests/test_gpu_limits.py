@@ -214,3 +214,17 @@ def test_cut_of_components_with_diode_bridges(torch_cuda, oracle_mod, n_bus, dev
     got = sim.step(T).cpu().numpy()[0]
     sim.sync()
     assert rel(got, oracle_mod.run(nets[0], cfg["dt"], T)) < 1e-9
+
+
+def test_forward_only_batch_is_staged_by_its_own_size(torch_cuda, oracle_mod):
+    # 1000-node components, every node recorded, by level passes: the forward
+    # kernel's arrays fit the LDS, an adjoint's would not, and without
+    # checkpoints there is none
+    from paper_1903_01081_amd.sim import Simulator
+    T = 40
+    net = netgen.small_grid(1, 1000, fault_step=20)
+    say("1000 buses, all recorded, level passes around a 128-node tail")
+    sim = Simulator([net], 20e-6, T, block_size=512, dense_tail=128)
+    assert sim.info()["lds_staged"]
+    sim.factor()
+    assert rel(sim.step(T).cpu().numpy()[0], oracle_mod.run(net, 20e-6, T)) < 1e-9
