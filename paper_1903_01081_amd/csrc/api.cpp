@@ -917,12 +917,13 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
   for (size_t q = 0; q < A.syms.size(); ++q)
     if (sym_diode[q] && !closed[q] && !sym_split[q] && solver == EMT_SOLVER_AUTO) by_levels();
   // the forward kernel's kind
-  bool any_line = false, any_group = false, any_level = false, any_switch = false;
+  bool any_line = false, any_group = false, any_level = false, any_closed = false, any_switch = false;
   for (const Item &it : A.items) {
     if (c.is_split[&it - &A.items[0]]) continue;
     any_line = any_line || !it.line_bk.empty();
     any_group = any_group || !it.grp_b.empty();
     any_level = any_level || !closed[it.sym];
+    any_closed = any_closed || closed[it.sym];
     any_switch = any_switch || closed[it.sym] == 2;
   }
   if (any_switch && (any_line || any_group || any_level)) {
@@ -938,12 +939,12 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
     any_switch = false;
   }
   const bool any_diode = std::count(item_diode.begin(), item_diode.end(), 1) > 0;
-  c.ks.kind = any_level && !any_line && !any_group && !any_diode ? STEP_LEVELS
-              : any_level || (any_line && any_group)             ? STEP_FULL
-              : any_line                                         ? STEP_LINES
-              : any_group                                        ? STEP_GROUPS
-              : any_switch                                       ? STEP_SWITCH
-                                                                 : STEP_PLAIN;
+  c.ks.kind = any_level && !any_closed && !any_line && !any_group && !any_diode ? STEP_LEVELS
+              : any_level || (any_line && any_group)                            ? STEP_FULL
+              : any_line                                                        ? STEP_LINES
+              : any_group                                                       ? STEP_GROUPS
+              : any_switch                                                      ? STEP_SWITCH
+                                                                                : STEP_PLAIN;
   std::vector<ClosedPlan> cplans(A.syms.size());
   auto plan_closed_of = [&](size_t q) {
     if (closed[q]) cplans[q] = plan_closed(A.syms[q], gpos[q], plans[q].d, bs);

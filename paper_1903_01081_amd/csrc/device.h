@@ -178,7 +178,7 @@ enum StepKind : int {
   STEP_GROUPS = 2,  // coupled three-phase groups
   STEP_FULL = 3,    // several of these, or level passes with one (in-loop LDL^T of diodes and controlled switches)
   STEP_SWITCH = 4,  // diodes or controlled switches, closed form
-  STEP_LEVELS = 5,  // level passes
+  STEP_LEVELS = 5,  // level passes, every component
 };
 
 // One diode or controlled switch of a closed-form item: its local branch, its

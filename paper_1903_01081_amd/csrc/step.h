@@ -49,6 +49,9 @@ namespace step {
 
 constexpr int64_t kNever = INT64_MAX;
 
+// How the components of a kernel's batch are solved.
+enum : int { CLOSED = 0, LEVELS = 1, BOTH = 2 };
+
 __device__ __forceinline__ double gamma_of(uint32_t pk, double g) {
   const uint32_t c = pk >> 30;
   return c == GAMMA_PLUS_G ? g : (c == GAMMA_MINUS_G ? -g : 0.0);
@@ -255,10 +258,12 @@ __device__ __forceinline__ void load_rows(const DevCtx &c, const RowProg &p, uin
 }
 
 // The LDS layout is step_lds() (device.h), which the host sizes launches by.
-// LEV: the batch may hold components solved by level passes (the kernels
-// without them carry none of their scalars: those of both together spill).
+// LEV: how the batch's components are solved: CLOSED form, LEVEL passes or some
+// each (the kernels of one kind carry no scalars of the other: those of both
+// together spill, and level passes alone take a quarter of the registers less,
+// which is twice the workgroups of a batch at once at 256 lanes).
 // DT > 0: its items may have diodes or controlled switches in closed form.
-template <int BS, bool SM, bool LEV, int DT = 0>
+template <int BS, bool SM, int LEV, int DT = 0>
 __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &it, bool adjoint) {
   const SymDesc sd = c.syms[it.sym];
   View<SM> v;
@@ -270,12 +275,12 @@ __device__ __forceinline__ View<SM> make_view(const DevCtx &c, const ItemDesc &i
   v.nsrc = it.n_src;
   v.nsv = sd.nsv;
   v.nrec = it.n_rec;
-  v.closed = LEV ? sd.closed : 1;
+  v.closed = LEV == LEVELS ? 0 : (LEV == CLOSED ? 1 : sd.closed);
   v.nfpass = sd.nfpass;
   v.nbpass = sd.nbpass;
   v.fvals = sd.fwd.nq * 256;
   const int32_t *g_nptr = c.nptr + it.nptr;
-  const bool dyn = LEV && it.n_diodes > 0;
+  const bool dyn = LEV == BOTH && it.n_diodes > 0;
   const int nsw = DT > 0 ? it.n_diodes : 0;
   const int ne = SM && dyn && !c.csr_global ? g_nptr[v.n] : 0;
   const bool seeds = adjoint && (SM || !c.seeds_global);  // recorded columns' cotangents in LDS
@@ -894,10 +899,10 @@ __device__ __forceinline__ void tail_solve_factored(const View<SM> &v, const Tai
 // The solve after the gather: closed form (c = r_D + N r_S, x_D = W c,
 // x_S = Q r_S + N^T x_D; a component that is all tail gathers straight into
 // c), or the level passes around the tail.
-template <int BS, int DT, bool SM, bool LEV, bool SW = false>
+template <int BS, int DT, bool SM, int LEV, bool SW = false>
 __device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail<BS, DT> &T, const double *dv = nullptr,
                                                    bool factored = false) {
-  if (!LEV || v.closed) {
+  if (LEV != LEVELS && (LEV == CLOSED || v.closed)) {
     if (v.d > 0) {
       if (v.ns > 0) {
         value_rows<SM>(v, v.fwd, 0, [&](int row, double s) { v.cD[row] = s; });
@@ -916,7 +921,8 @@ __device__ __forceinline__ void solve_after_gather(const View<SM> &v, const Tail
   }
   // from LDS the table's entries go to scalar registers; a uniform load from
   // memory the compiler moves there itself where it pays (1000 buses, solver
-  // sparse: 269 us a step with every entry moved, 263 without)
+  // sparse: 269 us a step with every entry moved, 263 without, in a kernel that
+  // carried the closed form's code as well; 244 in the present one)
   auto pass = [](const Ref<int32_t, SM> &p, int i) {
     if constexpr (SM)
       return __builtin_amdgcn_readfirstlane(p[i]);
@@ -1752,7 +1758,7 @@ __device__ __forceinline__ void refactor_dynamic(const DevCtx &c, const ItemDesc
 template <int BS, int BPT, int DT, bool SM, int KIND>
 __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, int64_t n0, int64_t nsteps,
                                                 double *rec) {
-  constexpr bool kLevels = KIND == STEP_FULL || KIND == STEP_LEVELS;
+  constexpr int kSolve = KIND == STEP_FULL ? BOTH : (KIND == STEP_LEVELS ? LEVELS : CLOSED);
   // line ends or coupled members
   // A launch of a few steps is mostly staging. Where a lane carries several
   // branches the factor's values are many for the lanes that stage them, and
@@ -1764,7 +1770,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   constexpr int kBlocks = KIND == STEP_PLAIN && BPT >= 4 ? 4 : 1;
   constexpr bool kPass = KIND == STEP_LINES || KIND == STEP_GROUPS || KIND == STEP_FULL;
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, kLevels, KIND == STEP_SWITCH ? DT : 0>(c, it, false);
+  View<SM> v = make_view<BS, SM, kSolve, KIND == STEP_SWITCH ? DT : 0>(c, it, false);
   const int64_t *topo = c.topo + it.topo;
   int t = topo_of(topo, it.n_topo, n0 + 1);
   int64_t next = (t + 1 < it.n_topo) ? topo[t + 1] : kNever;
@@ -1851,7 +1857,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
   // the adjoint's trajectory rows (batches with checkpoints have no lines,
   // groups or diodes)
   double *rows = nullptr;
-  if ((KIND == STEP_PLAIN || kLevels) && c.vt_full) rows = c.vt + it.vt + n0 * (int64_t)(v.n + v.nsrc);
+  if ((KIND == STEP_PLAIN || kSolve != CLOSED) && c.vt_full) rows = c.vt + it.vt + n0 * (int64_t)(v.n + v.nsrc);
   for (int64_t n = n0 + 1; n <= n_end; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     if (lines) lines_ahead<BS, NL>(it, ln, n);
@@ -1872,7 +1878,7 @@ __global__ __launch_bounds__(BS) void k_forward(DevCtx c, const int32_t *order, 
         fresh = false;
       }
     }
-    solve_after_gather<BS, DT, SM, kLevels, KIND == STEP_SWITCH>(v, w, dv, switches);
+    solve_after_gather<BS, DT, SM, kSolve, KIND == STEP_SWITCH>(v, w, dv, switches);
     if (switches) {
       if ((int)threadIdx.x < it.n_diodes) switch_step<SM>(c, it, v, sl, (int)threadIdx.x, n);
       for (int q = (int)threadIdx.x + BS; q < it.n_diodes; q += BS) {
@@ -2071,7 +2077,7 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
   for (int64_t n = lo + 1; n <= hi; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     gather_all<BS, SM>(v);
-    solve_after_gather<BS, DT, SM, true>(v, w);
+    solve_after_gather<BS, DT, SM, BOTH>(v, w);
     double *st_i = seg_i + (n - lo - 1) * (int64_t)nbr;
     store_row<BS, BPT, SM>(v, L, rows + (n - lo - 1) * (int64_t)(v.n + v.nsrc));
     if (n < hi && n + 1 != next) {
@@ -2276,7 +2282,7 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
     const double seed0 = from_ck ? 0.0 : load_seed<SM>(c, it, v, dJ, n - 1);
     gather_all<BS, SM>(v);
     if (!SM && c.seeds_global) add_seeds<BS, SM>(c, it, v, dJ, n);
-    solve_after_gather<BS, DT, SM, GEN>(v, w);
+    solve_after_gather<BS, DT, SM, GEN ? BOTH : CLOSED>(v, w);
     if (!from_ck && n - 1 >= first && t_nx == t) {
       // no checkpoint and no topology change on either side: the update and
       // the next step's injections slot by slot (out of service: hbar = 0,
@@ -2368,7 +2374,7 @@ template <int BS, int BPT, int DT, bool SM, bool GEN>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1))) void k_adjoint(
     DevCtx c, const int32_t *order, const double *dJ) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, GEN>(c, it, true);
+  View<SM> v = make_view<BS, SM, GEN ? BOTH : CLOSED>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   double *seg_i = c.seg_i + it.seg;
   Lane<BPT> L;
@@ -2450,7 +2456,7 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
   const bool recompute = (int)blockIdx.x >= n_items;
   const int q = order[recompute ? blockIdx.x - n_items : blockIdx.x];
   const ItemDesc it = c.items[q];
-  View<SM> v = make_view<BS, SM, GEN>(c, it, true);
+  View<SM> v = make_view<BS, SM, GEN ? BOTH : CLOSED>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   const int64_t steps = c.K < c.T ? c.K : c.T;
   const int64_t seg_len = steps * (int64_t)v.nbr, row_len = v.n + v.nsrc;
