@@ -228,3 +228,25 @@ def test_forward_only_batch_is_staged_by_its_own_size(torch_cuda, oracle_mod):
     assert sim.info()["lds_staged"]
     sim.factor()
     assert rel(sim.step(T).cpu().numpy()[0], oracle_mod.run(net, 20e-6, T)) < 1e-9
+
+
+@pytest.mark.parametrize("what,closed", [
+    ("9 buses", True), ("100 buses", True), ("400 buses", True), ("sparse", False), ("no tail", False),
+    ("coupled", True), ("lines", True), ("choppers", True), ("bridges", True), ("1200 buses", False),
+])
+def test_routes(torch_cuda, what, closed):
+    # at most three solve phases in closed form, one per level otherwise
+    from paper_1903_01081_amd.sim import Simulator
+    kw = dict(sparse=dict(solver="sparse")).get(what, dict(dense_tail=0) if what == "no tail" else {})
+    if what in ("choppers", "bridges"):
+        net = netgen.config1(seed=3, n_bus=100, n_steps=10, fault_step=5,
+                             **{dict(choppers="choppers", bridges="rectifiers")[what]: 4})[0][0]
+    elif what == "coupled":
+        net = netgen.small_grid(1, 100, coupled=True)
+    elif what == "lines":
+        net = netgen.small_grid(1, 300, travelling_wave_dt=20e-6)
+    else:
+        net = netgen.small_grid(1, int(what.split()[0]) if what[0].isdigit() else 60)
+    say(f"route of {what}")
+    sim = Simulator([net], 20e-6, 10, **kw)
+    assert (sim.info()["sweep_levels"] <= 3) == closed
