@@ -23,8 +23,8 @@ SOURCES = [
     ("api.cpp", "api", []),
     ("aux.hip", "aux", []),
     *(("step.hip", f"step{bs}{part.lower()}{kind}", [f"-DEMT_BS={bs}", f"-DEMT_PART_{part}", f"-DEMT_KIND={kind}"])
-      for bs in (512, 256, 64) for part, kind in (("FWD", 3), ("FWD", 5), ("ADJ", 1), ("PIPE", 1), ("ADJ", 0),
-                                              ("PIPE", 0), ("FWD", 1), ("FWD", 2), ("FWD", 4), ("FWD", 0))),
+      for bs in (512, 256, 64) for part, kind in (("FWD", 3), ("FWD", 5), ("ADJ", 1), ("PIPE", 1), ("ADJ", 0), ("ADJ", 2),
+                                              ("PIPE", 0), ("PIPE", 2), ("FWD", 1), ("FWD", 2), ("FWD", 4), ("FWD", 0))),
     ("closed.cpp", "closed_plan", []),
     ("closed.hip", "closed", []),
     ("split.hip", "split", []),

@@ -145,12 +145,10 @@ int tail_max(int bs) { return bs >= 512 ? 128 : (bs >= 256 ? 64 : 32); }
 // Largest dense tail of the closed form: the kernels' largest capacities.
 int closed_tail_max(int bs) { return bs >= 512 ? 192 : (bs >= 256 ? 128 : 64); }
 
-// The launcher for a block size and an adjoint's GEN.
+// The launcher for a block size and an AdjointKind.
 template <class F>
-F by_size(int bs, bool gen, F f64, F g64, F f256, F g256, F f512, F g512) {
-  if (bs == 64) return gen ? g64 : f64;
-  if (bs == 256) return gen ? g256 : f256;
-  return gen ? g512 : f512;
+F by_size(int bs, int kind, const F (&f64)[3], const F (&f256)[3], const F (&f512)[3]) {
+  return (bs == 64 ? f64 : (bs == 256 ? f256 : f512))[kind];
 }
 
 // Capacity (KernelShape::dt) that holds a tail of d nodes; 0 = none.
@@ -1189,7 +1187,7 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
               per_step * (double)T <= std::min((double)total_b / 16.0, (double)free_b / 2.0);
   }
   c.dc.vt_full = vt_full ? 1 : 0;
-  c.ks.gen = !vt_full || any_level;
+  c.ks.gen = any_level && !any_closed ? ADJ_LEVELS : (any_level || !vt_full ? ADJ_GENERAL : ADJ_PLAIN);
   // Pipelined adjoint where both workgroups of every item fit on the device
   // at once (cooperative launch) and it was not turned off.
   c.adj_pipe = false;
@@ -1199,9 +1197,12 @@ static void upload_all(emt_ctx &c, const emt_net *nets, const BuildPlan &plan) {
     if (!ks.sm) ks.bpt = c.bpt_global;
     int per_cu = 0, n_cu = 0, n_fwd = 0;
     for (int q = 0; q < NI; ++q) n_fwd += c.is_split[q] ? 0 : 1;
-    hipError_t e = by_size(bs, ks.gen, adjoint_pipe_blocks_per_cu<64, false>, adjoint_pipe_blocks_per_cu<64, true>,
-                           adjoint_pipe_blocks_per_cu<256, false>, adjoint_pipe_blocks_per_cu<256, true>,
-                           adjoint_pipe_blocks_per_cu<512, false>, adjoint_pipe_blocks_per_cu<512, true>)(ks, &per_cu);
+    hipError_t e = by_size(
+        bs, ks.gen,
+        {adjoint_pipe_blocks_per_cu<64, 0>, adjoint_pipe_blocks_per_cu<64, 1>, adjoint_pipe_blocks_per_cu<64, 2>},
+        {adjoint_pipe_blocks_per_cu<256, 0>, adjoint_pipe_blocks_per_cu<256, 1>, adjoint_pipe_blocks_per_cu<256, 2>},
+        {adjoint_pipe_blocks_per_cu<512, 0>, adjoint_pipe_blocks_per_cu<512, 1>, adjoint_pipe_blocks_per_cu<512, 2>})(
+        ks, &per_cu);
     hip_check(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c.device), "CU count");
     c.adj_pipe = e == hipSuccess && (int64_t)per_cu * n_cu >= 2 * (int64_t)n_fwd;
   }
@@ -1895,9 +1896,12 @@ static hipError_t launch_adjoint(emt_ctx &c, const double *dJ, hipStream_t st) {
   emt::KernelShape ks = c.ks;
   ks.sm = c.sm_adj;
   if (!ks.sm) ks.bpt = c.bpt_global;
-  return by_size(ks.bs, ks.gen, emt::launch_adjoint<64, false>, emt::launch_adjoint<64, true>,
-                 emt::launch_adjoint<256, false>, emt::launch_adjoint<256, true>, emt::launch_adjoint<512, false>,
-                 emt::launch_adjoint<512, true>)(c.dc, ks, c.d_order, c.n_fwd, dJ, st);
+  return by_size(
+      ks.bs, ks.gen,
+      {emt::launch_adjoint<64, 0>, emt::launch_adjoint<64, 1>, emt::launch_adjoint<64, 2>},
+      {emt::launch_adjoint<256, 0>, emt::launch_adjoint<256, 1>, emt::launch_adjoint<256, 2>},
+      {emt::launch_adjoint<512, 0>, emt::launch_adjoint<512, 1>, emt::launch_adjoint<512, 2>})(c.dc, ks, c.d_order,
+                                                                                          c.n_fwd, dJ, st);
 }
 
 extern "C" {
@@ -2256,9 +2260,11 @@ emt_status emt_adjoint(emt_ctx *ctx, const double *dJ_drec_dev, double *grad_dev
       hip_check(emt::launch_fill_i32(ctx->d_pipe, 2 * (int64_t)ctx->A.items.size(), 0, st), "pipe counters");
       hip_check(emt::launch_fill_i32(ctx->dc.flags + 2, 1, 0, st), "pipe error flag");
       const int n = ctx->n_fwd;
-      hip_check(by_size(ks.bs, ks.gen, emt::launch_adjoint_pipe<64, false>, emt::launch_adjoint_pipe<64, true>,
-                        emt::launch_adjoint_pipe<256, false>, emt::launch_adjoint_pipe<256, true>,
-                        emt::launch_adjoint_pipe<512, false>, emt::launch_adjoint_pipe<512, true>)(
+      hip_check(by_size(
+                    ks.bs, ks.gen,
+                    {emt::launch_adjoint_pipe<64, 0>, emt::launch_adjoint_pipe<64, 1>, emt::launch_adjoint_pipe<64, 2>},
+                    {emt::launch_adjoint_pipe<256, 0>, emt::launch_adjoint_pipe<256, 1>, emt::launch_adjoint_pipe<256, 2>},
+                    {emt::launch_adjoint_pipe<512, 0>, emt::launch_adjoint_pipe<512, 1>, emt::launch_adjoint_pipe<512, 2>})(
                     ctx->dc, ks, ctx->d_order, n, dJ_drec_dev, ctx->d_pipe, st),
                 "adjoint");
       ctx->adjoint_pending = true;

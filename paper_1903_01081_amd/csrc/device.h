@@ -180,6 +180,13 @@ enum StepKind : int {
   STEP_SWITCH = 4,  // diodes or controlled switches, closed form
   STEP_LEVELS = 5,  // level passes, every component
 };
+// The same of the adjoint's kernels (batches without lines, groups and
+// switches).
+enum AdjointKind : int {
+  ADJ_PLAIN = 0,    // closed form, trajectory rows of the whole horizon kept
+  ADJ_GENERAL = 1,  // any solve, segments run again where the rows are not kept
+  ADJ_LEVELS = 2,   // level passes, every component; rows kept or not
+};
 
 // One diode or controlled switch of a closed-form item: its local branch, its
 // terminals and a controlled switch's measured nodes (local; the ground is the

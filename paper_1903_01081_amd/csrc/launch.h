@@ -21,7 +21,7 @@ struct KernelShape {
   size_t lds_fwd = 0, lds_adj = 0;
   int dmax = 0;    // largest dense tail this block size supports
   int kind = 0;    // StepKind
-  bool gen = false;  // adjoint: level passes or no whole trajectory
+  int gen = 0;     // AdjointKind
 };
 
 struct CompanionArgs {
@@ -36,14 +36,14 @@ template <int BS, int KIND>
 hipError_t launch_forward(const DevCtx &, const KernelShape &, const int32_t *, int, int64_t, int64_t, double *,
                           hipStream_t);
 // Serial adjoint, pipelined adjoint (two workgroups per item, cooperative
-// launch) and the latter's resident workgroups per compute unit; GEN: the
-// batch has level passes or keeps no whole trajectory.
-template <int BS, bool GEN>
+// launch) and the latter's resident workgroups per compute unit; GEN: an
+// AdjointKind.
+template <int BS, int GEN>
 hipError_t launch_adjoint(const DevCtx &, const KernelShape &, const int32_t *, int, const double *, hipStream_t);
-template <int BS, bool GEN>
+template <int BS, int GEN>
 hipError_t launch_adjoint_pipe(const DevCtx &, const KernelShape &, const int32_t *, int, const double *, int32_t *,
                                hipStream_t);
-template <int BS, bool GEN>
+template <int BS, int GEN>
 hipError_t adjoint_pipe_blocks_per_cu(const KernelShape &, int *);
 
 hipError_t launch_factor(const DevCtx &c, const int32_t *pairs, int n_pairs, int max_tail, hipStream_t st);

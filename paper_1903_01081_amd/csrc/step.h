@@ -51,6 +51,7 @@ constexpr int64_t kNever = INT64_MAX;
 
 // How the components of a kernel's batch are solved.
 enum : int { CLOSED = 0, LEVELS = 1, BOTH = 2 };
+constexpr int adjoint_solve(int gen) { return gen == ADJ_PLAIN ? CLOSED : (gen == ADJ_LEVELS ? LEVELS : BOTH); }
 
 __device__ __forceinline__ double gamma_of(uint32_t pk, double g) {
   const uint32_t c = pk >> 30;
@@ -2057,7 +2058,7 @@ __device__ __forceinline__ double load_seed(const DevCtx &c, const ItemDesc &it,
 
 // Runs steps lo+1..hi of segment s again from its checkpoint. Afterwards L's
 // coefficients and the factors are those of step hi.
-template <int BS, int BPT, int DT, bool SM>
+template <int BS, int BPT, int DT, bool SM, int LEV>
 __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v, Lane<BPT> &L,
                                                   Tail<BS, DT> &w, int64_t s, double *seg_i, double *rows) {
   const int64_t *topo = c.topo + it.topo;
@@ -2077,7 +2078,7 @@ __device__ __forceinline__ void recompute_segment(const DevCtx &c, const ItemDes
   for (int64_t n = lo + 1; n <= hi; ++n) {
     emf_advance<BPT, SM>(c, v, L, n + 1, false);
     gather_all<BS, SM>(v);
-    solve_after_gather<BS, DT, SM, BOTH>(v, w);
+    solve_after_gather<BS, DT, SM, LEV>(v, w);
     double *st_i = seg_i + (n - lo - 1) * (int64_t)nbr;
     store_row<BS, BPT, SM>(v, L, rows + (n - lo - 1) * (int64_t)(v.n + v.nsrc));
     if (n < hi && n + 1 != next) {
@@ -2196,7 +2197,7 @@ __device__ __forceinline__ void rebuild_segment(const DevCtx &c, const ItemDesc 
 // hb_nx holds hbar of step hi+1 (0 past the horizon); on exit hb_nx holds
 // hbar of step lo+1, and the gradient accumulators have taken the segment's
 // terms.
-template <int BS, int BPT, int DT, bool SM, bool GEN>
+template <int BS, int BPT, int DT, bool SM, int GEN>
 __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc &it, View<SM> &v, Lane<BPT> &L,
                                                 Tail<BS, DT> &w, int64_t s, int t, const double *seg_i,
                                                 const double *rows, double (&hb_nx)[BPT], double (&gb)[BPT],
@@ -2282,7 +2283,7 @@ __device__ __forceinline__ void reverse_segment(const DevCtx &c, const ItemDesc 
     const double seed0 = from_ck ? 0.0 : load_seed<SM>(c, it, v, dJ, n - 1);
     gather_all<BS, SM>(v);
     if (!SM && c.seeds_global) add_seeds<BS, SM>(c, it, v, dJ, n);
-    solve_after_gather<BS, DT, SM, GEN ? BOTH : CLOSED>(v, w);
+    solve_after_gather<BS, DT, SM, adjoint_solve(GEN)>(v, w);
     if (!from_ck && n - 1 >= first && t_nx == t) {
       // no checkpoint and no topology change on either side: the update and
       // the next step's injections slot by slot (out of service: hbar = 0,
@@ -2367,14 +2368,14 @@ __device__ __forceinline__ void store_branch_adjoints(const DevCtx &c, const Ite
 // to step, 364 registers at 8 slots. Held to two waves it spills 168 of them
 // (324 B a lane), and though a batch of more items than compute units then
 // runs in fewer rounds it takes longer: 502 items 11.0 against 8.4 ms, 768
-// items 19.6 against 10.2. GEN: the
-// batch has level passes or no whole trajectory (the kernels without carry
-// none of their code and registers).
-template <int BS, int BPT, int DT, bool SM, bool GEN>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1))) void k_adjoint(
+// items 19.6 against 10.2. Level passes alone (ADJ_LEVELS) need fewer and gain
+// from two: 300 items of 150 nodes 34.2 against 58.3 us a step. GEN: an
+// AdjointKind.
+template <int BS, int BPT, int DT, bool SM, int GEN>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 && GEN == ADJ_LEVELS ? 2 : 1))) void k_adjoint(
     DevCtx c, const int32_t *order, const double *dJ) {
   const ItemDesc it = c.items[order[blockIdx.x]];
-  View<SM> v = make_view<BS, SM, GEN ? BOTH : CLOSED>(c, it, true);
+  View<SM> v = make_view<BS, SM, adjoint_solve(GEN)>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   double *seg_i = c.seg_i + it.seg;
   Lane<BPT> L;
@@ -2389,7 +2390,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1))) void k_
     const int64_t hi = (s * c.K + c.K < c.T) ? s * c.K + c.K : c.T;
     const int t = topo_of(c.topo + it.topo, it.n_topo, hi);
     double *rows = c.vt + it.vt;
-    if (!GEN || c.vt_full) {
+    if (GEN == ADJ_PLAIN || c.vt_full) {
       rows += s * c.K * (int64_t)(v.n + v.nsrc);
       rebuild_segment<BS, BPT, SM>(c, it, v, L, s, seg_i, rows);
       if (t != t_w) {
@@ -2397,7 +2398,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(1))) void k_
         t_w = t;
       }
     } else {
-      recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, s, seg_i, rows);
+      recompute_segment<BS, BPT, DT, SM, adjoint_solve(GEN)>(c, it, v, L, w, s, seg_i, rows);
     }
     __syncthreads();
     reverse_segment<BS, BPT, DT, SM, GEN>(c, it, v, L, w, s, t, seg_i, rows, hb_nx, gb, bb, cb, dJ);
@@ -2450,19 +2451,19 @@ __device__ __forceinline__ void publish_flag(int32_t *flag, int32_t value) {
 // recompute of segment s-1 overlaps the reversal of segment s. Per item,
 // pipe[2q] counts recomputed segments and pipe[2q+1] reversed ones; the
 // recompute of the k-th segment waits until the (k-2)-th is reversed.
-template <int BS, int BPT, int DT, bool SM, bool GEN>
+template <int BS, int BPT, int DT, bool SM, int GEN>
 __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *order, int n_items,
                                                      const double *dJ, int32_t *pipe) {
   const bool recompute = (int)blockIdx.x >= n_items;
   const int q = order[recompute ? blockIdx.x - n_items : blockIdx.x];
   const ItemDesc it = c.items[q];
-  View<SM> v = make_view<BS, SM, GEN ? BOTH : CLOSED>(c, it, true);
+  View<SM> v = make_view<BS, SM, adjoint_solve(GEN)>(c, it, true);
   const int64_t nseg = (c.T + c.K - 1) / c.K;
   const int64_t steps = c.K < c.T ? c.K : c.T;
   const int64_t seg_len = steps * (int64_t)v.nbr, row_len = v.n + v.nsrc;
   // the rows of the k-th segment handled
   auto rows_of = [&](int64_t k) {
-    return c.vt + it.vt + (!GEN || c.vt_full ? (nseg - 1 - k) * c.K : (k & 1) * steps) * row_len;
+    return c.vt + it.vt + (GEN == ADJ_PLAIN || c.vt_full ? (nseg - 1 - k) * c.K : (k & 1) * steps) * row_len;
   };
   int32_t *ready = pipe + 2 * q, *done = pipe + 2 * q + 1;
   Lane<BPT> L;
@@ -2472,10 +2473,10 @@ __global__ __launch_bounds__(BS) void k_adjoint_pipe(DevCtx c, const int32_t *or
     for (int64_t k = 0; k < nseg; ++k) {
       if (k >= 2 && !wait_flag(done, (int32_t)(k - 1), c.flags + 2, v.flag)) return;
       const int64_t o = it.seg + (k & 1) * seg_len;
-      if (!GEN || c.vt_full)
+      if (GEN == ADJ_PLAIN || c.vt_full)
         rebuild_segment<BS, BPT, SM>(c, it, v, L, nseg - 1 - k, c.seg_i + o, rows_of(k));
       else
-        recompute_segment<BS, BPT, DT, SM>(c, it, v, L, w, nseg - 1 - k, c.seg_i + o, rows_of(k));
+        recompute_segment<BS, BPT, DT, SM, adjoint_solve(GEN)>(c, it, v, L, w, nseg - 1 - k, c.seg_i + o, rows_of(k));
       publish_flag(ready, (int32_t)(k + 1));
     }
     return;

@@ -1,6 +1,6 @@
 // Instantiations of the step kernels for one workgroup size (EMT_BS, set by
 // the build: 64, 256 or 512) and one kind of kernel (EMT_PART_*: FWD with
-// EMT_KIND, a StepKind; ADJ and PIPE with EMT_KIND 0 or 1 = GEN), so that they
+// EMT_KIND, a StepKind; ADJ and PIPE with EMT_KIND, an AdjointKind), so that they
 // compile in parallel.
 #include <hip/hip_runtime.h>
 
@@ -12,6 +12,8 @@
 #endif
 
 namespace emt {
+
+static_assert(STEP_LEVELS == 5 && ADJ_LEVELS == 2, "EMT_LEVELS below");
 
 namespace {
 
@@ -31,7 +33,7 @@ hipError_t fwd(const DevCtx &c, const int32_t *order, int n_items, int64_t n0, i
 template <int BPT, int DT, bool SM>
 hipError_t adj(const DevCtx &c, const int32_t *order, int n_items, const double *dJ, size_t lds,
                hipStream_t st) {
-  auto k = step::k_adjoint<EMT_BS, BPT, DT, SM, EMT_KIND != 0>;
+  auto k = step::k_adjoint<EMT_BS, BPT, DT, SM, EMT_KIND>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -43,7 +45,7 @@ hipError_t adj(const DevCtx &c, const int32_t *order, int n_items, const double 
 template <int BPT, int DT, bool SM>
 hipError_t adj_pipe(const DevCtx &c, const int32_t *order, int n_items, const double *dJ, int32_t *pipe,
                     size_t lds, hipStream_t st) {
-  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM, EMT_KIND != 0>;
+  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM, EMT_KIND>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -59,7 +61,7 @@ hipError_t adj_pipe(const DevCtx &c, const int32_t *order, int n_items, const do
 
 template <int BPT, int DT, bool SM>
 hipError_t adj_pipe_occupancy(size_t lds, int *blocks) {
-  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM, EMT_KIND != 0>;
+  auto k = step::k_adjoint_pipe<EMT_BS, BPT, DT, SM, EMT_KIND>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -74,10 +76,22 @@ hipError_t adj_pipe_occupancy(size_t lds, int *blocks) {
 #define EMT_SHAPES_W(X, D) \
   X(1, D, true) X(2, D, true) X(4, D, true) X(6, D, true) X(8, D, true) X(12, D, true) X(16, D, true) \
   X(4, D, false) X(8, D, false) X(16, D, false)
-#if EMT_BS >= 512
+// Tails of level passes are smaller than those of the closed form.
+#if defined(EMT_PART_FWD)
+#define EMT_LEVELS (EMT_KIND == 5)
+#else
+#define EMT_LEVELS (EMT_KIND == 2)
+#endif
+#if EMT_BS >= 512 && EMT_LEVELS
+#define EMT_SHAPES(X) EMT_SHAPES_W(X, 64) EMT_SHAPES_W(X, 128)
+#elif EMT_BS >= 512
 #define EMT_SHAPES(X) EMT_SHAPES_W(X, 64) EMT_SHAPES_W(X, 128) EMT_SHAPES_W(X, 192)
+#elif EMT_BS >= 256 && EMT_LEVELS
+#define EMT_SHAPES(X) EMT_SHAPES_W(X, 64)
 #elif EMT_BS >= 256
 #define EMT_SHAPES(X) EMT_SHAPES_W(X, 64) EMT_SHAPES_W(X, 128)
+#elif EMT_LEVELS
+#define EMT_SHAPES(X) EMT_SHAPES_W(X, 32)
 #else
 #define EMT_SHAPES(X) EMT_SHAPES_W(X, 32) EMT_SHAPES_W(X, 64)
 #endif
@@ -97,7 +111,7 @@ hipError_t launch_forward<EMT_BS, EMT_KIND>(const DevCtx &c, const KernelShape &
 
 #ifdef EMT_PART_ADJ
 template <>
-hipError_t launch_adjoint<EMT_BS, EMT_KIND != 0>(const DevCtx &c, const KernelShape &ks, const int32_t *order,
+hipError_t launch_adjoint<EMT_BS, EMT_KIND>(const DevCtx &c, const KernelShape &ks, const int32_t *order,
                                               int n_items, const double *dJ, hipStream_t st) {
 #define EMT_CASE(BPT, DT, SM) \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj<BPT, DT, SM>(c, order, n_items, dJ, ks.lds_adj, st);
@@ -110,7 +124,7 @@ hipError_t launch_adjoint<EMT_BS, EMT_KIND != 0>(const DevCtx &c, const KernelSh
 
 #ifdef EMT_PART_PIPE
 template <>
-hipError_t launch_adjoint_pipe<EMT_BS, EMT_KIND != 0>(const DevCtx &c, const KernelShape &ks, const int32_t *order,
+hipError_t launch_adjoint_pipe<EMT_BS, EMT_KIND>(const DevCtx &c, const KernelShape &ks, const int32_t *order,
                                                    int n_items, const double *dJ, int32_t *pipe, hipStream_t st) {
 #define EMT_CASE(BPT, DT, SM) \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj_pipe<BPT, DT, SM>(c, order, n_items, dJ, pipe, ks.lds_adj, st);
@@ -120,7 +134,7 @@ hipError_t launch_adjoint_pipe<EMT_BS, EMT_KIND != 0>(const DevCtx &c, const Ker
 }
 
 template <>
-hipError_t adjoint_pipe_blocks_per_cu<EMT_BS, EMT_KIND != 0>(const KernelShape &ks, int *blocks) {
+hipError_t adjoint_pipe_blocks_per_cu<EMT_BS, EMT_KIND>(const KernelShape &ks, int *blocks) {
 #define EMT_CASE(BPT, DT, SM) \
   if (ks.bpt == BPT && ks.dt == DT && ks.sm == SM) return adj_pipe_occupancy<BPT, DT, SM>(ks.lds_adj, blocks);
   EMT_SHAPES(EMT_CASE)
